@@ -302,3 +302,160 @@ def tolerance(case):
     if case["kind"] == "attention":
         return {"rel": 4e-3, "max": 4e-2}
     return {"rel": 3e-2 if case["shape"] == "8b-shape" else 1.5e-2, "max": 0.24, "differ": 0.0}
+
+
+# ---------------------------------------------------------------- the same in 64 bits
+def _rows(kind, k, bl, L):
+    """(position, causal keys seen, mask block or -1) of every row of one sequence, and how many of them are causal."""
+    if kind == "step":
+        rows = [(L + i, i + 1, -1) for i in range(k)] + [(L + 1 + j + s, j + 1, j) for j in range(k) for s in range(k)]
+        return rows, k
+    if kind == "ar":
+        return [(L, 1, -1)], 1
+    rows = [(i, i + 1, -1) for i in range(L)]
+    if kind == "prefill":
+        rows += [(L + s, L, 0) for s in range(k)]
+    elif bl:
+        rows += [(i, i // bl * bl, i // bl) for i in range(L)]
+    return rows, L
+
+
+def _seen(rows, nc, cached):
+    """[rows, cached + rows]: which keys a row attends to."""
+    vis = torch.tensor([r[1] for r in rows], device=DEV).view(-1, 1)
+    blk = torch.tensor([r[2] for r in rows], device=DEV)
+    i = torch.arange(len(rows), device=DEV)
+    new = ((i < nc) & (i.view(1, -1) < vis)) | ((blk >= 0) & (blk == blk.view(-1, 1)))
+    return torch.cat([torch.ones(len(rows), cached, dtype=torch.bool, device=DEV), new], 1)
+
+
+def _attend(q, k, v, seen):
+    """q [R, heads, hd], k and v [T, kv heads, hd], one kv head's group of query heads at a time."""
+    R, nq, hd = q.shape
+    out = torch.empty_like(q)
+    group = nq // k.shape[1]
+    for h in range(k.shape[1]):
+        for i in range(h * group, (h + 1) * group):
+            s = (q[:, i] @ k[:, h].t().contiguous()) / math.sqrt(hd)
+            out[:, i] = s.masked_fill(~seen, -math.inf).softmax(-1) @ v[:, h].contiguous()
+    return out
+
+
+def _norm(x, gain, eps):
+    return x / torch.sqrt((x * x).mean(-1, keepdim=True) + eps) * gain.double()
+
+
+def _rotate(x, pos, base):
+    half = x.shape[-1] // 2
+    inv = base ** (-torch.arange(half, dtype=torch.float64, device=DEV) * 2 / x.shape[-1])
+    ang = pos.double().view(-1, 1, 1) * inv
+    a, b = x[..., :half], x[..., half:]
+    return torch.cat([a * ang.cos() - b * ang.sin(), b * ang.cos() + a * ang.sin()], -1)
+
+
+def _paged(kp, vp, table, L, hd):
+    """K and V [L, kv heads, hd] of one sequence out of one layer's pages."""
+    pos = torch.arange(L, device=DEV)
+    page, slot = table[pos // T.PAGE].long(), pos % T.PAGE
+    return (kp.view(kp.shape[0], kp.shape[1], T.PAGE, hd)[page, :, slot],
+            vp.view(vp.shape[0], vp.shape[1], hd, T.PAGE)[page, :, :, slot])
+
+
+def _place(kp, vp, table, L, k, v):
+    pos = torch.arange(L, L + k.shape[0], device=DEV)
+    page, slot, hd = table[pos // T.PAGE].long(), pos % T.PAGE, k.shape[-1]
+    kp.view(kp.shape[0], kp.shape[1], T.PAGE, hd)[page, :, slot] = k
+    vp.view(vp.shape[0], vp.shape[1], hd, T.PAGE)[page, :, :, slot] = v
+
+
+def exact(case, seed):
+    """What `run` returns, by the plain definition in 64 bits on the card (tokens and lengths: no such value)."""
+    sh = TI.SHAPES[case["shape"]]
+    kind, B, k, bl, lens = case["kind"], case["batch"], case["k"], case["block_len"], _lengths(case)
+    hd = sh.head_dim
+    if kind == "attention":
+        st = _prepare_attention(case, sh, lens, seed, {})
+        kp, vp, out = st["k_pages"][0].double(), st["v_pages"][0].double(), torch.empty_like(st["q"], dtype=torch.float64)
+        for b, L in enumerate(lens):
+            rows, nc = _rows("step", k, 0, L)
+            kc, vc = _paged(kp, vp, st["table"][b], L, hd)
+            kn, vn = st["k_new"][b].double(), st["v_new"][b].double()
+            out[b] = _attend(st["q"][b].double(), torch.cat([kc, kn]), torch.cat([vc, vn]), _seen(rows, nc, L))
+            _place(kp, vp, st["table"][b], L, kn[:nc], vn[:nc])
+        return {"out": out, "k_pages": kp[None], "v_pages": vp[None]}
+    new = {"step": k, "ar": 1, "prefill": k, "score": 0}[kind]
+    pps = (max(lens) + new + T.PAGE + T.PAGE - 1) // T.PAGE
+    size = (B * pps, sh.n_kv_heads, T.PAGE * hd)
+    if sh.n_layers * math.prod(size) > 1 << 30:
+        return None                                   # minutes and tens of gigabytes
+    dtype = torch.bfloat16 if case["dtype"] == "bf16" else torch.float32
+    w = _weights(sh, seed, dtype)
+    table = TI.shuffled_page_table(B * pps, B * pps, seed).view(B, pps).to(DEV)
+    cached = lens if kind in ("step", "ar") else [0] * B
+    if kind == "step":
+        toks = _drafts(sh, B, k, seed + 9)
+    elif kind == "ar":
+        toks = _drafts(sh, B, 1, seed + 9)
+    else:
+        toks = _text(sh, B, max(lens), seed + 5)
+    g = _gen(seed + 7)
+    xs, plan = [], []
+    for b, L in enumerate(lens):
+        rows, nc = _rows(kind, k, bl, L)
+        ids = torch.cat([toks[b, :nc].long(), torch.full((len(rows) - nc,), sh.mask_token_id, device=DEV)])
+        xs.append(w["embed"][ids].double())
+        plan.append((nc, torch.tensor([r[0] for r in rows], device=DEV), _seen(rows, nc, cached[b])))
+    k_pages, v_pages = [], []
+    for lw in w["layers"]:
+        m = {n: t.double() for n, t in lw.items()}
+        kp, vp = torch.zeros(size, dtype=dtype, device=DEV), torch.zeros(size, dtype=dtype, device=DEV)
+        if kind in ("step", "ar"):
+            kp.normal_(0.0, 1.0, generator=g)
+            vp.normal_(0.0, 1.0, generator=g)
+        kp, vp = kp.double(), vp.double()
+        for b, (nc, pos, seen) in enumerate(plan):
+            x, L = xs[b], cached[b]
+            h = _norm(x, m["attn_norm"], sh.rms_eps)
+            q = _rotate((h @ m["wq"].t()).view(len(x), -1, hd), pos, sh.rope_base)
+            kn = _rotate((h @ m["wk"].t()).view(len(x), -1, hd), pos, sh.rope_base)
+            vn = (h @ m["wv"].t()).view(len(x), -1, hd)
+            kc, vc = _paged(kp, vp, table[b], L, hd)
+            x = x + _attend(q, torch.cat([kc, kn]), torch.cat([vc, vn]), seen).reshape(len(x), -1) @ m["wo"].t()
+            h = _norm(x, m["ffn_norm"], sh.rms_eps)
+            xs[b] = x + (torch.nn.functional.silu(h @ m["w_gate"].t()) * (h @ m["w_up"].t())) @ m["w_down"].t()
+            _place(kp, vp, table[b], L, kn[:nc], vn[:nc])
+        k_pages.append(kp)
+        v_pages.append(vp)
+    got = {"k_pages": torch.stack(k_pages), "v_pages": torch.stack(v_pages)}
+    del k_pages, v_pages, m, lw
+    w["layers"].clear()
+    scored = kind == "score"
+    if not (scored or case["logits"]):
+        names = {"step": ("accepted_len", "accepted", "next_drafts", "prefix_len", "logits"),
+                 "ar": ("token", "prefix_len", "logits"), "prefill": ("first_drafts", "logits", "prefix_len")}[kind]
+        return {**{n: None for n in names}, **got}
+    head = w["lm_head"].double()
+
+    def logits(x):
+        return _norm(x, w["final_norm"], sh.rms_eps) @ head.t()
+
+    if scored:
+        ar = torch.zeros(B, max(lens), dtype=torch.float64, device=DEV)
+        diff = torch.zeros_like(ar) if bl else None
+        for b, L in enumerate(lens):
+            ids = toks[b, :L].long()
+            for c in range(0, L, 512):
+                e = min(c + 512, L - 1)
+                if e > c:
+                    ar[b, c:e] = logits(xs[b][c:e]).log_softmax(-1).gather(1, ids[c + 1:e + 1, None])[:, 0]
+                if bl:
+                    e = min(c + 512, L)
+                    diff[b, c:e] = logits(xs[b][L + c:L + e]).log_softmax(-1).gather(1, ids[c:e, None])[:, 0]
+        return {"ar": ar, "diff": diff, "loss": None, **got}
+    if kind == "prefill":
+        return {"first_drafts": None, "logits": torch.stack([logits(x[L - 1:]) for x, L in zip(xs, lens)]),
+                "prefix_len": None, **got}
+    lg = torch.stack([logits(x) for x in xs])
+    if kind == "ar":
+        return {"token": None, "prefix_len": None, "logits": lg[:, 0], **got}
+    return {"accepted_len": None, "accepted": None, "next_drafts": None, "prefix_len": None, "logits": lg, **got}
