@@ -29,38 +29,13 @@
 // (row, key) predicate and a per-(query tile, key pair) skip when nothing is visible.
 #include <type_traits>
 
+#include "lds_dma.h"
 #include "tidar_internal.h"
 
 namespace {
 
 constexpr int HD = 128;
 constexpr int TILE = 32 * HD;           // bf16 elements of one K tile (32 keys) and of one V^T tile
-
-// 16 bytes per lane straight from a raw buffer into LDS at lds_addr + 16 * lane (the tile's wave-uniform base goes
-// through M0).  Written as inline assembly so that only the explicit vmcnt waits of the kernel order these loads
-// against the LDS reads: issued through the compiler's builtin, every LDS read waits for *all* loads in flight,
-// which is exactly the prefetch this is meant to keep running.
-typedef int int4v __attribute__((ext_vector_type(4)));
-__device__ inline int4v raw_desc(const void *base, size_t bytes) {
-    const unsigned long long p = (unsigned long long)base;
-    return (int4v){(int)(p & 0xffffffffull), (int)((p >> 32) & 0xffffull),
-                   (int)(bytes > 0x7fffffe0ull ? 0x7fffffe0ull : bytes), 0x00020000};
-}
-// (M0 is a reserved register that the compiler sets itself right before each of its own uses; this kernel has none.)
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ inline void dma16(unsigned lds_addr, int voff, int4v desc, int soff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff)
-                 : "memory", "m0");
-}
-#pragma clang diagnostic pop
-__device__ inline void lds_barrier() {       // workgroup barrier for LDS traffic only: global loads stay in flight
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
 
 struct AttnArgs {
     const bf16_t *q;

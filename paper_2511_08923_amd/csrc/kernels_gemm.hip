@@ -18,9 +18,8 @@
 //     16x16x32: measured 2.2 vs 1.2 PFLOP/s), A staged through LDS once per workgroup and prefetched into
 //     registers ahead of the MFMAs; 4 waves either as a 2 x 2 grid over 128 columns (two row halves x two
 //     64-column groups: launches without a row split), or side by side, every wave over all row tiles of the pass
-//     (no weight fragment is then loaded by two waves): over 256 columns with two column tiles per wave for
-//     single-split grids that are resident all at once and for the many-row class, over 128 columns with one
-//     column tile per wave for the two-pass launches of 33-480 rows (no padded tile slots; twice the LDS fragment
+//     (no weight fragment is then loaded by two waves): eight waves over 256 columns for single-split grids, four over
+//     128 columns for the two-pass launches of 33-480 rows, one column tile per wave (no padded tile slots; twice the LDS fragment
 //     reads per MFMA, which the LDS has room for).  The weight fragment is the MFMA's first operand, so the
 //     accumulators hold the output transposed (lane = row): every epilogue starts from that.
 //   * split-K over blockIdx.y works in units of 512 k, row passes over blockIdx.z; up to 480 rows the split count
@@ -33,63 +32,9 @@
 // 16x16x32: A lane l = row l%16, k slots 8*(l/16)..+7; B lane l = column l%16, same k slots; D lane l register i
 // = row 4*(l/16)+i, column l%16.   32x32x16: A lane l = row l%32, k slots 8*(l/32)..+7; B lane l = column l%32;
 // D lane l register i = row 8*(i/4) + 4*(l/32) + i%4, column l%32.
-#include "tidar_internal.h"
+#include "gemm_device.h"
 
 namespace {
-
-constexpr int SPLIT_UNIT = 512;           // k elements
-constexpr int OOB = 0x7ffffff0;           // byte offset beyond any buffer: the load returns zeros
-
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, size_t bytes) {
-    // raw buffer (stride 0), 32-bit data format; num_records in bytes
-    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)(bytes > 0x7fffffe0ull ? 0x7fffffe0ull : bytes),
-                                             0x00020000);
-}
-__device__ inline bf16x8 buf_load(__amdgpu_buffer_rsrc_t r, int byte_off) {
-    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 0));
-}
-
-struct SplitRange {
-    int q0, q1;   // k steps [q0, q1)
-};
-__device__ inline SplitRange split_range(int K, int splits, int split) {
-    const int units = (K + SPLIT_UNIT - 1) / SPLIT_UNIT;
-    const int per = (units + splits - 1) / splits;
-    SplitRange r;
-    r.q0 = split * per * (SPLIT_UNIT / 32);
-    r.q1 = min(K >> 5, (split + 1) * per * (SPLIT_UNIT / 32));
-    return r;
-}
-
-// What the fused vocabulary reduction does with output row `row`: perturb its values before the maximum is formed
-// (key, inv_t when noisy) and/or also write its logits to the compact buffer (sel >= 0: row index there).
-struct RowChoice {
-    bool noisy;
-    uint64_t key;
-    float inv_t;
-    int sel;
-};
-__device__ inline RowChoice row_choice(const ChooseArgs &ch, int row, int M) {
-    RowChoice rc;
-    rc.noisy = false;
-    rc.key = 0;
-    rc.inv_t = 1.f;
-    rc.sel = -1;
-    if (ch.n_choose <= 0 || row >= M) return rc;
-    const int b = row / ch.Rh, o = row - b * ch.Rh;
-    if (o < ch.n_choose) {
-        if (ch.sample) {
-            rc.noisy = true;                // causal rows are label shifted: they predict the position after theirs
-            rc.key = noise_key(ch.seed, ch.seq_base + b, ch.pos_rows[(size_t)b * ch.pos_stride + ch.pos_row0 + o] + 1);
-            rc.inv_t = ch.inv_t;
-        }
-        if (ch.sel_logits) rc.sel = b * 2 * ch.n_choose + o;
-    } else if (ch.sel_logits) {
-        const int m = o - ch.n_choose;
-        if (m % ch.mix_stride == 0 && m / ch.mix_stride < ch.n_choose) rc.sel = b * 2 * ch.n_choose + ch.n_choose + m / ch.mix_stride;
-    }
-    return rc;
-}
 
 template <int MTW, int NT>
 __device__ inline void store_tiles(const f32x4 (&acc)[MTW][NT], float *out, int split, int M, int N, int tile0,
@@ -483,8 +428,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
     static_assert(NT == 2 || (NT == 1 && WIDE), "one column tile per wave only with the waves side by side");
     static_assert(NW == 4 || (NW == 8 && WIDE && NT == 1), "eight waves only side by side with one column tile each");
     constexpr int THREADS = 64 * NW;
-    constexpr bool BIG = WIDE && MTA >= 6 && NT == 2;   // the many-row variants: registers go to the accumulators
-    constexpr int PFK = BIG ? KS : 2 * KS;       // weight ring depth in k steps: one chunk or two
+    constexpr int PFK = 2 * KS;                  // weight ring depth in k steps: two chunks
     constexpr int CTL = WIDE ? MTA : (MTA == 5) ? 9 : 2 * MTA;
     // Many row passes: the (pass, column block) plane is cut into super-tiles of swz_p x swz_c workgroups, each
     // handed whole to one XCD (workgroup i of a launch runs on XCD i % 8), passes fastest: the workgroups that
@@ -536,22 +480,17 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
     const int wv = __builtin_amdgcn_readfirstlane(wave);
     const int a_chunk_step = KS * m_tiles * 1024;
     const int lane16 = lane * 16;
-    // HALF (the many-row variants, which have no registers to spare): half as many staging registers, each
-    // carrying two pieces per chunk; a piece is then in flight for half a chunk instead of a whole one.
-    constexpr bool HALF = BIG;
-    constexpr int SR = HALF ? STAGE / 2 : STAGE;
-    static_assert(!HALF || (STAGE % 2 == 0 && 4 * STAGE <= FR), "two events per staging register and chunk");
-    bf16x8 stage[SR];
-    auto load_a1 = [&](int s, int c) {          // piece s of chunk c -> staging register s % SR
+    bf16x8 stage[STAGE];
+    auto load_a1 = [&](int s, int c) {          // piece s of chunk c -> staging register s
         const int i = wv + NW * s;
         const int ks = i / CTL, ct = i % CTL;
         const bool ok = i < CTL * KS && ct < ct_here && c < c1;
-        stage[s % SR] = __builtin_bit_cast(
+        stage[s] = __builtin_bit_cast(
             bf16x8, __builtin_amdgcn_raw_buffer_load_b128(ra, ok ? lane16 : OOB,
                                                           (ks * m_tiles + mt_base + ct) * 1024 + c * a_chunk_step, 0));
     };
     auto store_a1 = [&](int s, int buf) {
-        if (STAGE * THREADS == PIECES || tid + s * THREADS < PIECES) lds[buf * PIECES + tid + s * THREADS] = stage[s % SR];
+        if (STAGE * THREADS == PIECES || tid + s * THREADS < PIECES) lds[buf * PIECES + tid + s * THREADS] = stage[s];
     };
 
     f32x16 acc[MTA][NT];
@@ -566,30 +505,21 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
     // The loads of the ring's second half and of the second chunk's A are issued in the order the loop issues
     // them, so that the in-flight counts the compiler derives at the loop entry equal those of the back edge.
 #pragma unroll
-    for (int s = 0; s < SR; ++s) load_a1(s, c0);
+    for (int s = 0; s < STAGE; ++s) load_a1(s, c0);
 #pragma unroll
     for (int s = 0; s < KS; ++s)
 #pragma unroll
         for (int j = 0; j < NT; ++j) wbuf[s][j] = ld_w(j, q0 + s);
 #pragma unroll
-    for (int s = 0; s < SR; ++s) store_a1(s, 0);
-    if (HALF) {
+    for (int s = 0; s < STAGE; ++s) store_a1(s, 0);
 #pragma unroll
-        for (int s = SR; s < STAGE; ++s) load_a1(s, c0);
+    for (int f = 0; f < FR; ++f) {
+        if (f % MTA == MTA - 1) {
 #pragma unroll
-        for (int s = SR; s < STAGE; ++s) store_a1(s, 0);
-#pragma unroll
-        for (int s = 0; s < SR; ++s) load_a1(s, c0 + 1);
-    } else {
-#pragma unroll
-        for (int f = 0; f < FR; ++f) {
-            if (f % MTA == MTA - 1) {
-#pragma unroll
-                for (int j = 0; j < NT; ++j) wbuf[KS + f / MTA][j] = ld_w(j, q0 + KS + f / MTA);
-            }
-            if ((f & 1) && (f >> 1) < STAGE) load_a1(f >> 1, c0 + 1);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int j = 0; j < NT; ++j) wbuf[KS + f / MTA][j] = ld_w(j, q0 + KS + f / MTA);
         }
+        if ((f & 1) && (f >> 1) < STAGE) load_a1(f >> 1, c0 + 1);
+        __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
 
@@ -623,16 +553,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
                 // the next chunk's A goes to the other LDS buffer one piece at a time between the MFMAs (a
                 // burst of stores would sit in front of the fragment reads in the in-order LDS queue), and
                 // the freed staging register at once takes the piece of the chunk after that
-                if (HALF) {
-                    // event e stores piece e of the next chunk and reloads its register with the piece that is
-                    // stored half a chunk later: e + STAGE/2 of the next chunk, or e - STAGE/2 of the one after
-                    if ((f & 3) == 1 && (f >> 2) < STAGE) {
-                        const int e = f >> 2;
-                        store_a1(e, buf ^ 1);
-                        if (e < SR) load_a1(e + SR, c + 1);
-                        else load_a1(e - SR, c + 2);
-                    }
-                } else if ((f & 1) && (f >> 1) < STAGE) {
+                if ((f & 1) && (f >> 1) < STAGE) {
                     store_a1(f >> 1, buf ^ 1);
                     load_a1(f >> 1, c + 2);
                 }
@@ -642,167 +563,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
         }
     }
 
-    // ---- epilogue.  The weight fragment is the MFMA's first operand, so the accumulator holds the output tile
-    // transposed: lane l owns activation row l%32 of the row tile, and its register e is column
-    // 8*(e/4) + 4*(l/32) + e%4 of the 32-column tile: four consecutive registers are four consecutive columns of
-    // one row.
-    const int lq = lane & 31, lh = lane >> 5;
-    if (epi == GEMM_EPI_SWIGLU) {
-        // columns 0-15 of a tile are gate, 16-31 up, of the same 16 features (tile T = features 16T..16T+15 =
-        // exactly one k step of the next GEMM's A-fragment layout), so gate and up of a feature sit in the same
-        // lane, 8 registers apart: h = silu(gate) * up needs no shuffle.  A lane then holds features 4*(l/32)+0..3
-        // and 8+4*(l/32)+0..3 of its row; the fragment wants 8*(l/32)+0..7.  One half-wave swap fixes that: the
-        // upper lanes hand their features 4-7 to the lower lanes and take the lower lanes' 8-11.
-        bf16_t *ho = reinterpret_cast<bf16_t *>(out);
-        typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-        for (int mt = 0; mt < MTA; ++mt) {
-            const int tile_r = mh * MTA + mt;
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                unsigned pk[4];
-#pragma unroll
-                for (int i = 0; i < 8; i += 2) {
-                    float h2[2];
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        const float g = acc[mt][j][i + t], u = acc[mt][j][i + t + 8];
-                        h2[t] = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
-                    }
-                    bf16x2 b;
-                    b[0] = (bf16_t)h2[0];
-                    b[1] = (bf16_t)h2[1];
-                    pk[i >> 1] = __builtin_bit_cast(unsigned, b);
-                }
-                // pk[0..1]: features 4*lh + 0..3; pk[2..3]: features 8 + 4*lh + 0..3
-                const auto s0 = __builtin_amdgcn_permlane32_swap(pk[0], pk[2], false, false);
-                const auto s1 = __builtin_amdgcn_permlane32_swap(pk[1], pk[3], false, false);
-                typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-                const u32x4 piece = {s0[0], s1[0], s0[1], s1[1]};
-                if (tile_r < ct_here && tile0 + j < t32)
-                    *(u32x4 *)(ho + (((size_t)(tile0 + j) * m_tiles + mt_base + tile_r) * 64 + lane) * 8) = piece;
-            }
-        }
-        return;
-    }
-    if (epi == GEMM_EPI_ARGMAX) {
-        // a lane walks its 16 columns of each of the wave's tiles in rising order (strict > keeps the lowest column
-        // of a tie), then the two half-waves, which hold the same rows, are folded.  A column group is 64 columns:
-        // the wave's two tiles, or (NT = 1) the tiles of two neighbouring waves, folded through LDS.
-        const int G = (t32 + 1) >> 1;
-        float *pmax = out;
-        int *pidx = (int *)(out + (size_t)G * M);
-        float bests[MTA];
-        int bis[MTA];
-#pragma unroll
-        for (int mt = 0; mt < MTA; ++mt) {
-            const int tile_r = mh * MTA + mt;
-            float best = -INFINITY;
-            int bi = tile0 * 32 + 4 * lh;
-            bests[mt] = best;
-            bis[mt] = bi;
-            if (tile_r >= ct_here) continue;      // wave-uniform
-            const RowChoice rc = row_choice(ch, (mt_base + tile_r) * 32 + lq, M);
-            if (__any(rc.noisy || rc.sel >= 0)) {     // a tile that holds rows a token is taken from (wave-uniform)
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int col = (tile0 + j) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
-                        float v = acc[mt][j][e];
-                        if (rc.sel >= 0 && col < N) ch.sel_logits[(size_t)rc.sel * N + col] = v;
-                        if (rc.noisy) v = perturbed_logit(v, rc.inv_t, rc.key, (uint32_t)col);
-                        if (col < N && v > best) {
-                            best = v;
-                            bi = col;
-                        }
-                    }
-            } else {
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int col = (tile0 + j) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
-                        const float v = acc[mt][j][e];
-                        if (col < N && v > best) {
-                            best = v;
-                            bi = col;
-                        }
-                    }
-            }
-            const float ob = __shfl_xor(best, 32);
-            const int oi = __shfl_xor(bi, 32);
-            if (ob > best || (ob == best && oi < bi)) {
-                best = ob;
-                bi = oi;
-            }
-            bests[mt] = best;
-            bis[mt] = bi;
-        }
-        if constexpr (NT == 1) {
-            // the odd wave of a pair hands its result to the even one (the staging buffers are free by now)
-            float *rb = reinterpret_cast<float *>(gemm_smem);
-            int *ri = reinterpret_cast<int *>(gemm_smem) + NW * MTA * 32;
-            if (lh == 0) {
-#pragma unroll
-                for (int mt = 0; mt < MTA; ++mt) {
-                    rb[(wave * MTA + mt) * 32 + lq] = bests[mt];
-                    ri[(wave * MTA + mt) * 32 + lq] = bis[mt];
-                }
-            }
-            __syncthreads();
-            if (wave & 1) return;
-#pragma unroll
-            for (int mt = 0; mt < MTA; ++mt) {
-                const float ob = rb[((wave + 1) * MTA + mt) * 32 + lq];
-                const int oi = ri[((wave + 1) * MTA + mt) * 32 + lq];
-                if (ob > bests[mt] || (ob == bests[mt] && oi < bis[mt])) {
-                    bests[mt] = ob;
-                    bis[mt] = oi;
-                }
-            }
-        }
-#pragma unroll
-        for (int mt = 0; mt < MTA; ++mt) {
-            const int tile_r = mh * MTA + mt;
-            const int row = (mt_base + tile_r) * 32 + lq;
-            if (tile_r < ct_here && lh == 0 && row < M && tile0 < t32) {
-                pmax[(size_t)(tile0 >> 1) * M + row] = bests[mt];
-                pidx[(size_t)(tile0 >> 1) * M + row] = bis[mt];
-            }
-        }
-        return;
-    }
-    // Partial sums and logits: a lane's four consecutive columns are 16 bytes, but neighbouring lanes are
-    // neighbouring rows, 128 bytes apart in the tiled layout.  Each tile is therefore turned through a per-wave
-    // LDS patch (16-byte writes, 16-byte reads; the staging buffers are free after the last barrier) so that eight
-    // lanes together store one whole row of the tile (128 bytes) and a store instruction covers 1 KiB in one run.
-    float *scr = reinterpret_cast<float *>(gemm_smem) + wave * (32 * 36);
-    float *o = out + (size_t)blockIdx.y * pt_split_stride(M, N);
-#pragma unroll
-    for (int mt = 0; mt < MTA; ++mt) {
-        const int tile_r = mh * MTA + mt;
-        if (tile_r >= ct_here) continue;          // also drops the repeated tile (wave-uniform)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                *(f32x4 *)(scr + lq * 36 + 8 * g + 4 * lh) = (f32x4){acc[mt][j][4 * g], acc[mt][j][4 * g + 1],
-                                                                     acc[mt][j][4 * g + 2], acc[mt][j][4 * g + 3]};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int idx = lane + 64 * i;
-                const int r = idx >> 3, c4 = idx & 7;
-                const f32x4 v = *(const f32x4 *)(scr + r * 36 + 4 * c4);
-                const int row = (mt_base + tile_r) * 32 + r;
-                const int col = (tile0 + j) * 32 + 4 * c4;
-                if (row < M && col < N) {
-                    const size_t oi = (epi == GEMM_EPI_ROWMAJOR) ? (size_t)row * N + col : pt_index(col, row, M);
-                    *(f32x4 *)(o + oi) = v;
-                }
-            }
-        }
-    }
+    large_epilogue<MTA, NT, NW>(acc, out, gemm_smem, epi, blockIdx.y, M, N, mt_base, ct_here, tile0, mh, wave, lane, ch);
 }
 
 template <int MT, int PFK>
@@ -866,6 +627,7 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
     p.wide = 0;
     p.nw = 4;
     p.swz = 0;
+    p.rows = 0;
     const int wgs = (N + 127) / 128;
     const int units = (K + SPLIT_UNIT - 1) / SPLIT_UNIT;
     auto fit = [&](int want) {                   // clamp to the units there are and drop empty trailing splits
@@ -934,36 +696,44 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
             ctl = 5;
             p.swz = 4;
         }
-        // 512 rows and more: the launch is bound by the compute units' L1 bandwidth, not by HBM (every workgroup
-        // pulls its A rows and W columns through it), so the workgroup tile is made as square as the register
-        // file allows: up to 256 rows x 256 columns, eight row tiles per wave.  Measured at 4096 rows of the 8B shape:
-        // 0.65-0.95 PFLOP/s with 288 x 128 tiles, 0.88-1.28 with these.  Grids of many rounds (the LM head) are
-        // also dealt to the XCDs in 4 x 4 super-tiles (+20 %; on grids of a few rounds the uneven deal costs more
-        // than the sharing gains).
-        if (t >= 16) {
-            p.wide = 1;
-            p.nt = 2;
-            const int passes = (t + 7) / 8;
-            p.mt = ctl = (t + passes - 1) / passes;      // 6, 7 or 8 row tiles per pass: the passes come out even
-            p.swz = (N + 255) / 256 >= 256 ? 4 : 0;
-            // With this many rows the row passes fill the chip by themselves, and a split costs M x N floats
-            // written and read again (570 MB per launch at 8704 rows and N = 4096, four splits).  The count, never
-            // above the (N, K) rule's, minimises an estimate in microseconds: rounds of 256 workgroups x (a
-            // workgroup's share of K at the measured 22 ns per k of a 256 x 256 tile + 8 of prologue and
-            // epilogue) + the partial sums through the fabric at 6 TB/s out and 4 TB/s back in.  It is a function
-            // of the pass count (rows / 256, rounded up) alone, so within this class a row's sum is grouped the
-            // same way for every row count with the same number of passes.
-            const int base = ((N + 255) / 256) * passes, s_max = splits;
-            double best = 0.0;
+        if (t >= 16) {                               // kernels_gemm_rows.hip
+            // The number of row passes (of five to nine row tiles, equal to within one) and of splits that minimise an
+            // estimate in microseconds: rounds of 256 workgroups x (K share x the measured time per k of a pass of h
+            // row tiles and 256 columns, 7.5 + 1.6 h ns, plus 6 + h of prologue and epilogue), plus the partial sums
+            // through the fabric at 6 TB/s out and 4 TB/s back in.  (Predicted / measured: 2048 x 24576 x 4096 292 /
+            // 340, 2176 x 4096 x 12288 178 / 165, 1000 x 24576 x 4096 179 / 181, 600 x 24576 x 4096 149 / 146.)
+            // The split count, never above the (N, K) rule's, is taken for whole 256-row multiples: within this
+            // class a row's sum is grouped the same way for every row count of the same multiple.
+            p.rows = 1;
+            const int cols = (N + 255) / 256, s_max = splits;
+            auto best_passes = [&](int tiles, int sc, double *cost) {
+                int best = 0;
+                for (int n = (tiles + 8) / 9; n <= tiles / 5; ++n) {      // no pass higher than nine, none below five
+                    const int h = (tiles + n - 1) / n;
+                    const int rounds = (n * cols * sc + 255) / 256;
+                    const double c = rounds * ((0.0075 + 0.0016 * h) * K / sc + 6.0 + h);
+                    if (best == 0 || c < *cost) {
+                        best = n;
+                        *cost = c;
+                    }
+                }
+                return best;
+            };
+            const int t8 = (t + 7) / 8 * 8;
+            double best = 0.0, cost = 0.0;
             for (int c = 1; c <= s_max; ++c) {
                 const int sc = fit(c);
-                const int rounds = (base * sc + 255) / 256;
-                const double cost = rounds * (0.022 * K / sc + 8.0) + sc * (256.0 * passes) * N * 1.67e-6;
+                (void)best_passes(t8, sc, &cost);
+                cost += sc * (32.0 * t8) * N * 1.67e-6;
                 if (c == 1 || cost < best) {
                     best = cost;
                     splits = sc;
                 }
             }
+            p.m_chunks = best_passes(t, splits, &cost);
+            p.mt = (t + p.m_chunks - 1) / p.m_chunks;
+            p.splits = splits;
+            return p;
         }
         p.m_chunks = (t + ctl - 1) / ctl;
     }
@@ -975,7 +745,9 @@ void launch_gemm_bf16(const bf16_t *a, const bf16_t *w, float *out, int M, int N
                       int out_row_major, hipStream_t st, const ChooseArgs *choose) {
     ChooseArgs ch = {};
     if (choose && out_row_major == GEMM_EPI_ARGMAX) ch = *choose;
-    if (M <= 32) {
+    if (p.rows) {
+        launch_gemm_bf16_rows(a, w, out, M, N, K, p, out_row_major, st, ch);
+    } else if (M <= 32) {
         if (p.mt == 1) launch_small<1, 16>(a, w, out, M, N, K, p, out_row_major, st, ch);
         else launch_small<2, 8>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1 && p.nw == 8) {     // eight waves side by side, one column tile each
@@ -996,14 +768,6 @@ void launch_gemm_bf16(const bf16_t *a, const bf16_t *w, float *out, int M, int N
         launch_large<7, true, 1>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1) {
         launch_large<8, true, 1>(a, w, out, M, N, K, p, out_row_major, st, ch);
-    } else if (p.wide && p.mt == 8) {
-        launch_large<8, true>(a, w, out, M, N, K, p, out_row_major, st, ch);
-    } else if (p.wide && p.mt == 7) {
-        launch_large<7, true>(a, w, out, M, N, K, p, out_row_major, st, ch);
-    } else if (p.wide && p.mt == 6) {
-        launch_large<6, true>(a, w, out, M, N, K, p, out_row_major, st, ch);
-    } else if (p.wide) {
-        launch_large<5, true>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.mt == 1) {
         launch_large<1, false>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.mt == 2) {

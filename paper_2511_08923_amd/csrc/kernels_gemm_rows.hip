@@ -1,0 +1,310 @@
+// bf16 GEMM of many rows (large batches, prefill and scoring passes): out = A[M][K] x W[N][K]^T, fp32 accumulation,
+// same operand layouts, epilogues and split-K rule as kernels_gemm.hip.
+//
+// Here every weight byte is used hundreds of times and the matrix cores decide - or rather the power they take: with
+// all of them busy the clock settles far below its limit (the same launch on zeros is a quarter faster), so a
+// variant that spends less energy per product is faster even where it issues no faster.  Hence 16x16x32 MFMAs, and
+// as few LDS reads per MFMA as the registers allow: a workgroup of four waves, one per SIMD, owns up to nine row
+// tiles x 8 column tiles of 32, a wave one half of every row tile x 4 column tiles (up to 288 accumulator registers,
+// 17 fragment reads per 72 MFMAs).
+// Both operands go from memory straight into LDS (buffer_load ... lds): they are stored as 32x32x16 register images,
+// and a 16x16x32 fragment is four contiguous 256-byte runs of two of those, so every read is conflict-free.
+// LDS holds four chunks of K = 32; a chunk's loads are issued more than three chunks (3000 cycles) before they are
+// needed.  With one wave per SIMD nothing else covers a stall, so everything is spread between the MFMAs: fragments
+// of the next chunk and the loads of the chunk after the next three go out a few at a time behind each row of eight
+// MFMAs, and after the one barrier of a chunk there are always fragments in registers to go on with.
+// The row passes of a launch are equally high, or differ by one row tile (the plan picks their number).
+#include <type_traits>
+
+#include "gemm_device.h"
+#include "lds_dma.h"
+
+namespace {
+
+constexpr int BUFS = 4;                           // chunks in LDS
+
+// out^T tiles: lane l holds activation row l % 16 and weight columns 4 * (l / 16) .. +3 of each 16 x 16 tile.
+// Two neighbouring column tiles make the 128 bytes a row has in a 32-column tile of the output; half of the lanes
+// trade one tile's values so that eight lanes store one whole row.
+template <bool ROWMAJOR>
+__device__ inline void store_pair(const f32x4 &t0, const f32x4 &t1, float *__restrict__ o, int row0, int col0, int M, int N,
+                                  int lane) {
+    const int n = lane & 15, g = lane >> 4;
+    const bool low = n < 8;
+    f32x4 first, second;                          // rows row0 + n % 8 and row0 + 8 + n % 8
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float give = low ? t1[e] : t0[e];
+        const float got = __builtin_bit_cast(
+            float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, give), 0x128, 0xf, 0xf, true));   // row_ror:8
+        first[e] = low ? t0[e] : got;
+        second[e] = low ? got : t1[e];
+    }
+    const int col = col0 + (low ? 0 : 16) + 4 * g;
+    if (col >= N) return;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int row = row0 + 8 * h + (n & 7);
+        if (row < M) *(f32x4 *)(o + (ROWMAJOR ? (size_t)row * N + col : pt_index(col, row, M))) = h ? second : first;
+    }
+}
+
+// RT: row tiles of the higher passes; the first n_tall of the n_pass passes have RT row tiles, the others RT - 1.
+template <int RT, int EPI>
+__global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__restrict__ a, const bf16_t *__restrict__ w,
+                                                             float *__restrict__ out, int M, int N, int K, int splits,
+                                                             int n_pass, int n_tall, int n_colblk, ChooseArgs ch) {
+    constexpr int CT = 8;                              // 16-column tiles of a wave
+    constexpr int LOADS = RT > 8 ? RT : 8;             // loads per wave and chunk
+    constexpr int CHUNK = 4 * LOADS * 1024;            // A [k step][row tile], then W [k step][column tile], 1 KiB each
+    extern __shared__ __attribute__((aligned(16))) unsigned char rows_smem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int mh = wave >> 1, ng = wave & 1;
+    const int t32 = (N + 31) >> 5, m_tiles = (M + 31) >> 5;
+
+    // Workgroup i of a launch runs on XCD i % 8.  Each XCD takes one contiguous eighth of the (row pass, column block)
+    // plane, four column blocks wide and passes downwards, so that what is resident on it together shares A rows
+    // and W columns through its L2.
+    int bx, bz;
+    {
+        const int n_wg = n_pass * n_colblk, q = n_wg >> 3, r = n_wg & 7, x = blockIdx.x & 7;
+        const int i = x * q + min(x, r) + (blockIdx.x >> 3), band = 4 * n_pass;
+        const int g = i / band, o = i - g * band, wd = min(4, n_colblk - 4 * g);
+        bz = o / wd;
+        bx = 4 * g + o - bz * wd;
+    }
+    const int mt_base = bz * (RT - 1) + min(bz, n_tall), ct_here = bz < n_tall ? RT : RT - 1;
+    const SplitRange sr = split_range(K, splits, blockIdx.y);
+    const int n_chunks = max(sr.q1 - sr.q0, 0);                 // one chunk = 32 k
+
+    // loads: waves 0 and 1 bring the W tiles of the chunk's two k steps, waves 2 and 3 the A tiles
+    const bool ld_w = wave < 2;
+    const int ld_tiles = ld_w ? t32 : m_tiles, ld_t0 = ld_w ? bx * 8 : mt_base;
+    const int ld_here = ld_w ? min(8, t32 - bx * 8) : ct_here;
+    const int4v ld_desc = raw_desc(ld_w ? w : a, (size_t)(K >> 4) * ld_tiles * 1024);
+    const unsigned ld_dst = lds_address(rows_smem) + ((ld_w ? 2 : 0) + (wave & 1)) * LOADS * 1024;
+    const int ld_src = ((sr.q0 * 2 + (wave & 1)) * ld_tiles + ld_t0) * 1024, ld_step = 2 * ld_tiles * 1024;
+    int ld_off[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) ld_off[i] = i < ld_here ? lane * 16 : OOB;
+    // Tiles that do not exist and chunks past the last are asked for too, out of bounds: no traffic, and the number
+    // of loads in flight is the same for every wave and chunk
+    auto load = [&](int c, int i) __attribute__((always_inline)) {
+        dma16(ld_dst + (c & (BUFS - 1)) * CHUNK + i * 1024, c < n_chunks ? ld_off[i] : OOB, ld_desc,
+              c < n_chunks ? ld_src + c * ld_step + i * 1024 : 0);
+    };
+    // Workgroup barrier for LDS traffic only (loads stay in flight).  The wait is the builtin, not inline assembly: the
+    // compiler then knows that no LDS read is outstanding and counts exactly which of the next ones an MFMA needs.
+    auto barrier = [&]() __attribute__((always_inline)) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    // The wave's row tile i (16 rows) is half mh of the pass's 32-row tile i.
+    f32x4 acc[RT][CT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    bf16x8 af[2][RT], wf[2][CT];
+    // lane (n, g) of a 16x16x32 fragment takes k slots 8g .. 8g+7 of row n: stored k step g/2, stored lane (g%2)*32 + n
+    const unsigned char *frag0 = rows_smem + (lane >> 5) * LOADS * 1024 + ((lane >> 4) & 1) * 512 + (lane & 15) * 16;
+    auto read = [&](int s, int c, int f) __attribute__((always_inline)) {      // W fragments first: all of them are
+        const unsigned char *b = frag0 + (c & (BUFS - 1)) * CHUNK;             // needed before the second A fragment
+        if (f < CT) wf[s][f] = *(const bf16x8 *)(b + (2 * LOADS + ng * 4 + (f >> 1)) * 1024 + (f & 1) * 256);
+        else af[s][f - CT] = *(const bf16x8 *)(b + (f - CT) * 1024 + mh * 256);
+    };
+
+#pragma unroll
+    for (int c = 0; c < BUFS; ++c)
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) load(c, i);
+    wait_loads<(BUFS - 1) * LOADS>();
+    barrier();
+    // the k loop over RA row tiles
+    auto k_loop = [&](auto ra_tag) __attribute__((always_inline)) {
+        constexpr int RA = decltype(ra_tag)::value, READS = CT + RA;
+        auto row = [&](int s, int i) __attribute__((always_inline)) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < CT; ++j) {
+                // The ninth row's accumulators do not fit the 256 AGPRs any more; left to the compiler, which wants
+                // all of them there, they are copied in and out around every use.  (Nothing reads these results
+                // before the wait behind the loop.)
+                if (i == 8)
+                    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[i][j]) : "v"(wf[s][j]), "v"(af[s][i]));
+                else
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][j], af[s][i], acc[i][j], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto chunk = [&](int s, int c) __attribute__((always_inline)) {
+            row(s, 0);
+            wait_loads<(BUFS - 2) * LOADS>();
+            barrier();                       // chunk c+1 has landed for everyone, chunk c has been read by everyone
+#pragma unroll
+            for (int i = 1; i < RA; ++i) {
+#pragma unroll
+                for (int f = READS * (i - 1) / (RA - 1); f < READS * i / (RA - 1); ++f) read(s ^ 1, c + 1, f);
+#pragma unroll
+                for (int l = LOADS * (i - 1) / (RA - 1); l < LOADS * i / (RA - 1); ++l) load(c + BUFS, l);
+                row(s, i);
+            }
+        };
+#pragma unroll
+        for (int f = 0; f < READS; ++f) read(0, 0, f);
+        // two chunks at a time (the fragment sets alternate); an odd one at the end runs with a chunk of zeros, so
+        // that the loop stays one piece of code and the accumulators stay where they are
+        for (int c = 0, end = n_chunks & ~1;; end += 2) {
+            for (; c < end; c += 2) {
+                chunk(0, c);
+                chunk(1, c + 1);
+            }
+            if (end >= n_chunks) break;
+            bf16x8 *z = reinterpret_cast<bf16x8 *>(rows_smem + (n_chunks & (BUFS - 1)) * CHUNK);
+#pragma unroll
+            for (int i = 0; i < CHUNK / 4096; ++i) z[threadIdx.x + 256 * i] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
+        }
+    };
+    if (ct_here == RT) k_loop(std::integral_constant<int, RT>());
+    else k_loop(std::integral_constant<int, RT - 1>());
+    wait_loads<0>();
+    barrier();
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");     // the compiler does not see the ninth row's MFMAs finish
+
+    // ---- epilogue
+    const int n = lane & 15, g = lane >> 4;
+    const int col_w = bx * 256 + ng * 128;                       // the wave's first column
+    auto row_of = [&](int i) { return (mt_base + i) * 32 + mh * 16; };
+    auto exists = [&](int i) { return i < RT - 1 || ct_here == RT; };
+    if constexpr (EPI == GEMM_EPI_SWIGLU) {
+        // tile 2j: gate, tile 2j + 1: up, of the same 16 features; a lane's four are half of a 16-byte piece of the
+        // next GEMM's A fragment
+        typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+        bf16_t *ho = reinterpret_cast<bf16_t *>(out);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            if (!exists(i)) continue;
+#pragma unroll
+            for (int j = 0; j < CT; j += 2) {
+                const int tile = (col_w >> 5) + (j >> 1);
+                bf16x4 h;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float gt = acc[i][j][e], u = acc[i][j + 1][e];
+                    h[e] = (bf16_t)(gt * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gt)) * u);
+                }
+                if (tile < t32)
+                    *(bf16x4 *)(ho + (((size_t)tile * m_tiles + (row_of(i) >> 5)) * 64 + (g >> 1) * 32 + mh * 16 + n) * 8 +
+                                (g & 1) * 4) = h;
+            }
+        }
+    } else if constexpr (EPI == GEMM_EPI_ARGMAX) {
+        // per row and 64 columns (four column tiles): a lane walks its columns in rising order (strict > keeps the
+        // lowest column of a tie), then the four lanes of a row are folded
+        const int G = (t32 + 1) >> 1;
+        float *pmax = out;
+        int *pidx = (int *)(out + (size_t)G * M);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            if (!exists(i)) continue;
+            const int row = row_of(i) + n;
+            float best[2] = {-INFINITY, -INFINITY};
+            int bi[2] = {col_w + 4 * g, col_w + 64 + 4 * g};
+            const RowChoice rc = row_choice(ch, row, M);
+            if (__any(rc.noisy || rc.sel >= 0)) {            // wave-uniform: rows a token is taken from.  Few of them:
+                // a loop over values the lane parks in LDS (the staging buffers are free) instead of unrolled code
+                f32x4 *park = reinterpret_cast<f32x4 *>(rows_smem) + threadIdx.x;
+#pragma unroll
+                for (int j = 0; j < CT; ++j) park[256 * j] = acc[i][j];
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll 1
+                    for (int t = 0; t < 16; ++t) {
+                        const int col = col_w + 64 * p + 16 * (t >> 2) + 4 * g + (t & 3);
+                        float v = reinterpret_cast<const float *>(park + 256 * (4 * p + (t >> 2)))[t & 3];
+                        if (rc.sel >= 0 && col < N) ch.sel_logits[(size_t)rc.sel * N + col] = v;
+                        if (rc.noisy) v = perturbed_logit(v, rc.inv_t, rc.key, (uint32_t)col);
+                        if (col < N && v > best[p]) {
+                            best[p] = v;
+                            bi[p] = col;
+                        }
+                    }
+            } else {
+#pragma unroll
+                for (int j = 0; j < CT; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int col = col_w + 16 * j + 4 * g + e;
+                        if (col < N && acc[i][j][e] > best[j >> 2]) {
+                            best[j >> 2] = acc[i][j][e];
+                            bi[j >> 2] = col;
+                        }
+                    }
+            }
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+#pragma unroll
+                for (int o = 16; o < 64; o <<= 1) {
+                    const float ob = __shfl_xor(best[p], o);
+                    const int oi = __shfl_xor(bi[p], o);
+                    if (ob > best[p] || (ob == best[p] && oi < bi[p])) {
+                        best[p] = ob;
+                        bi[p] = oi;
+                    }
+                }
+                if (g == 0 && row < M && col_w + 64 * p < 32 * t32) {
+                    pmax[(size_t)((col_w >> 6) + p) * M + row] = best[p];
+                    pidx[(size_t)((col_w >> 6) + p) * M + row] = bi[p];
+                }
+            }
+        }
+    } else {
+        float *o = out + (size_t)blockIdx.y * pt_split_stride(M, N);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            if (!exists(i)) continue;
+#pragma unroll
+            for (int j = 0; j < CT; j += 2)
+                store_pair<EPI == GEMM_EPI_ROWMAJOR>(acc[i][j], acc[i][j + 1], o, row_of(i), col_w + 16 * j, M, N, lane);
+        }
+    }
+}
+
+template <int RT, int EPI>
+void launch_rows(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, hipStream_t st,
+                 const ChooseArgs &ch) {
+    constexpr int SMEM = BUFS * 4 * (RT > 8 ? RT : 8) * 1024;
+    const int n_colblk = (N + 255) / 256, n_tall = (M + 31) / 32 - p.m_chunks * (RT - 1);
+    static bool attr_set[64] = {};           // LDS above 64 KiB has to be granted per kernel and device
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    if (dev < 0 || dev >= 64 || !attr_set[dev]) {
+        (void)hipFuncSetAttribute((const void *)gemm_bf16_rows_kernel<RT, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  SMEM);
+        if (dev >= 0 && dev < 64) attr_set[dev] = true;
+    }
+    gemm_bf16_rows_kernel<RT, EPI><<<dim3(p.m_chunks * n_colblk, p.splits), 256, SMEM, st>>>(
+        a, w, out, M, N, K, p.splits, p.m_chunks, n_tall, n_colblk, ch);
+}
+
+template <int EPI>
+void launch_rows_epi(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, hipStream_t st,
+                     const ChooseArgs &ch) {
+    if (p.mt == 9) launch_rows<9, EPI>(a, w, out, M, N, K, p, st, ch);
+    else if (p.mt == 8) launch_rows<8, EPI>(a, w, out, M, N, K, p, st, ch);
+    else if (p.mt == 7) launch_rows<7, EPI>(a, w, out, M, N, K, p, st, ch);
+    else launch_rows<6, EPI>(a, w, out, M, N, K, p, st, ch);
+}
+
+}  // namespace
+
+void launch_gemm_bf16_rows(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi,
+                           hipStream_t st, const ChooseArgs &ch) {
+    if (epi == GEMM_EPI_SWIGLU) launch_rows_epi<GEMM_EPI_SWIGLU>(a, w, out, M, N, K, p, st, ch);
+    else if (epi == GEMM_EPI_ARGMAX) launch_rows_epi<GEMM_EPI_ARGMAX>(a, w, out, M, N, K, p, st, ch);
+    else if (epi == GEMM_EPI_ROWMAJOR) launch_rows_epi<GEMM_EPI_ROWMAJOR>(a, w, out, M, N, K, p, st, ch);
+    else launch_rows_epi<GEMM_EPI_TILED>(a, w, out, M, N, K, p, st, ch);
+}
