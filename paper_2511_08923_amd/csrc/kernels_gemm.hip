@@ -628,6 +628,7 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
     p.nw = 4;
     p.swz = 0;
     p.rows = 0;
+    p.mid = 0;
     const int wgs = (N + 127) / 128;
     const int units = (K + SPLIT_UNIT - 1) / SPLIT_UNIT;
     auto fit = [&](int want) {                   // clamp to the units there are and drop empty trailing splits
@@ -649,6 +650,40 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
         // whatever the batch size.
         if (!force_single_split) splits = fit(128 / wgs);
         const int t = (M + 31) / 32;             // 32-row tiles
+        if (t < 16 && !force_single_split) {
+            // kernels_gemm_mid.hip: the waves of a workgroup split K.  It takes the products whose two row passes
+            // below would fill less than half of the compute units (the small model's QKV and O: 272 x 1536 x 1536 12.2
+            // -> 8.6 us in 3 splits either way; where they fill more it gains nothing alone and loses 10 % inside a
+            // step, where the activations come from other XCDs), and the wide single-split ones up to five row
+            // tiles (72 x 24576 x 4096 45.2 -> 40.8, 160 rows 56.7 -> 51.8; 272 rows 68.2 -> 81.5), or whose passes as
+            // eight-wave workgroups are not resident at once (420 rows 137 -> 122).
+            const bool single = splits == 1 && wgs >= 128;
+            if (single ? t <= 5 || (t > 7 && (N + 255) / 256 * ((t + 4) / 5) > 256) : wgs * splits <= 64) {
+                // Per workgroup: its fragments at the 27 B per clock that a compute unit takes in from afar, or the
+                // matrix cores' rate, plus 4 us of launch, ring fill and reduction; a split also costs the partial
+                // sums at 6 TB/s out and 4 TB/s back in.  The split count is the best at nine row tiles in two passes,
+                // a function of (N, K) alone (a row's sum is grouped the same way whatever the row count); the number
+                // of passes follows the rows.
+                p.mid = 1;
+                p.nt = single ? 3 : 2;
+                const int t32 = (N + 31) / 32, most = p.nt == 2 ? 8 : 5;      // row tiles whose accumulators fit the AGPRs
+                auto cost = [&](int tiles, int sc, int passes) {
+                    const int rt = (tiles + passes - 1) / passes;
+                    const int rounds = ((t32 + p.nt - 1) / p.nt * sc * passes + 255) / 256;
+                    const double load = (rt + p.nt) * 1024 / 27.0, mfma = rt * p.nt * 8 / 0.9;
+                    return rounds * (K / 16.0 / sc * (load > mfma ? load : mfma) / 2100.0 + 4.0) +
+                           sc * tiles * 32.0 * N * 1.67e-6;
+                };
+                p.splits = 1;
+                for (int c = 2; !single && c <= units && c <= 8; ++c)
+                    if (cost(9, fit(c), 2) < cost(9, p.splits, 2)) p.splits = fit(c);
+                p.m_chunks = (t + most - 1) / most;
+                for (int n = p.m_chunks + 1; n <= t; ++n)
+                    if (cost(t, p.splits, n) < cost(t, p.splits, p.m_chunks)) p.m_chunks = n;
+                p.mt = (t + p.m_chunks - 1) / p.m_chunks;
+                return p;
+            }
+        }
         const bool row_split = !force_single_split && wgs * splits <= 128;
         const int per_pass = row_split ? (t + 1) / 2 : t;
         p.mt = per_pass <= 2 ? 1 : per_pass <= 4 ? 2 : per_pass <= 6 ? 3 : 5;      // per wave (wide kernel)
@@ -708,7 +743,7 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
             const int cols = (N + 255) / 256, s_max = splits;
             auto best_passes = [&](int tiles, int sc, double *cost) {
                 int best = 0;
-                for (int n = (tiles + 8) / 9; n <= tiles / 5; ++n) {      // no pass higher than nine, none below five
+                for (int n = (tiles + 8) / 9; n <= tiles / 5 && n <= (tiles + 8) / 9 + 4; ++n) {      // no pass higher than nine, none below five
                     const int h = (tiles + n - 1) / n;
                     const int rounds = (n * cols * sc + 255) / 256;
                     const double c = rounds * ((0.0075 + 0.0016 * h) * K / sc + 6.0 + h);
@@ -723,6 +758,7 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
             double best = 0.0, cost = 0.0;
             for (int c = 1; c <= s_max; ++c) {
                 const int sc = fit(c);
+                if (c > 1 && sc == fit(c - 1)) continue;
                 (void)best_passes(t8, sc, &cost);
                 cost += sc * (32.0 * t8) * N * 1.67e-6;
                 if (c == 1 || cost < best) {
@@ -747,6 +783,8 @@ void launch_gemm_bf16(const bf16_t *a, const bf16_t *w, float *out, int M, int N
     if (choose && out_row_major == GEMM_EPI_ARGMAX) ch = *choose;
     if (p.rows) {
         launch_gemm_bf16_rows(a, w, out, M, N, K, p, out_row_major, st, ch);
+    } else if (p.mid) {
+        launch_gemm_bf16_mid(a, w, out, M, N, K, p, out_row_major, st);
     } else if (M <= 32) {
         if (p.mt == 1) launch_small<1, 16>(a, w, out, M, N, K, p, out_row_major, st, ch);
         else launch_small<2, 8>(a, w, out, M, N, K, p, out_row_major, st, ch);

@@ -165,6 +165,7 @@ struct GemmPlan {
     int wide;      // the waves side by side, each over all row tiles of the pass (instead of 2 x 2 waves)
     int nw;        // waves per workgroup: 4, or 8 (side by side, one column tile each: two waves per SIMD)
     int rows;      // the many-row kernel (kernels_gemm_rows.hip): m_chunks passes of mt or mt - 1 row tiles of 32
+    int mid;       // kernels_gemm_mid.hip: m_chunks passes of mt or mt - 1 row tiles of 32, nt column tiles of 32
     int swz;       // > 0: (row pass, column block) plane dealt to the XCDs in super-tiles of swz x swz workgroups
 };
 
@@ -196,6 +197,8 @@ void launch_gemm_bf16(const bf16_t *a, const bf16_t *w_packed, float *out, int M
                       int epi, hipStream_t st, const ChooseArgs *choose = nullptr);
 void launch_gemm_bf16_rows(const bf16_t *a, const bf16_t *w_packed, float *out, int M, int N, int K, const GemmPlan &p,
                            int epi, hipStream_t st, const ChooseArgs &ch);
+void launch_gemm_bf16_mid(const bf16_t *a, const bf16_t *w_packed, float *out, int M, int N, int K, const GemmPlan &p,
+                          int epi, hipStream_t st);
 void launch_gemm_f32(const float *a, const float *w, float *out, int M, int N, int K, int out_row_major,
                      hipStream_t st);
 
