@@ -67,7 +67,8 @@ __host__ __device__ inline size_t af_index(int row, int k, ActLayout a) {
         return ((((size_t)(k >> 4) * a.tiles + (row >> 5)) * 64) + ((k >> 3) & 1) * 32 + (row & 31)) * 8 + (k & 7);
     return ((((size_t)(k >> 5) * a.tiles + (row >> 4)) * 64) + ((k >> 3) & 3) * 16 + (row & 15)) * 8 + (k & 7);
 }
-__host__ __device__ inline size_t af_elems(int rows, int K) { return (size_t)((rows + 31) / 32) * 32 * K; }
+// (the narrow form is laid out in whole k steps of 32, the wide one in steps of 16: a ragged K takes a whole step)
+__host__ __device__ inline size_t af_elems(int rows, int K) { return (size_t)((rows + 31) / 32) * 32 * ((K + 31) / 32 * 32); }
 // Layout of every GEMM output except the logits: [split][32-column tile][row][32] fp32.  A row's share of a tile
 // is one 128-byte cache line, so a consumer that owns a row never fetches a line it shares with another row's
 // consumer (with 16-column tiles every line was fetched twice, by two different XCDs).  N is padded to whole

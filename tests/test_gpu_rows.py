@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import tidar_inputs as TI
-from test_gpu_ops import _gemm
+from test_gpu_ops import _attention_case, _gemm
 
 pytestmark = pytest.mark.gpu
 
@@ -68,3 +68,28 @@ def test_many_row_step_fused_vocabulary_reduction_equals_logits_path(T, sample, 
                                    (480, 528, 288), (97, 16400, 160), (160, 24576, 608), (420, 24576, 96), (470, 24560, 512)])
 def test_k_split_gemm_matches_fp64_matmul(T, M, N, K):
     test_many_row_gemm_matches_fp64_matmul(T, M, N, K)
+
+
+# fp32: one element of everything, K that is no multiple of 32 or of 128, ragged rows (the narrow and the wide activation
+# layout), more 16 x 16 tiles than the one-tile form takes
+@pytest.mark.parametrize("M,N,K", [(1, 16, 8), (17, 48, 24), (20, 384, 128), (33, 80, 200), (272, 1040, 152)])
+def test_fp32_gemm_matches_fp64_matmul(T, M, N, K):
+    ctx = T.tidar_create(T.make_config(TI.TINY, T.TIDAR_F32, max_k=4, max_batch=1))
+    a, w = TI.make_normal((M, K), seed=M + K).cuda(), TI.make_normal((N, K), seed=N + K, std=0.02).cuda()
+    packed = torch.zeros(T.tidar_packed_weight_bytes(T.TIDAR_F32, N, K) // 4, device="cuda")
+    T.tidar_pack_weight(T.TIDAR_F32, w, packed, N)
+    out = torch.full((M, N), float("nan"), device="cuda")
+    ws = torch.empty(T.tidar_gemm_workspace_bytes(T.TIDAR_F32, M, N, K), dtype=torch.uint8, device="cuda")
+    T.tidar_gemm(ctx, a, packed, out, M, N, K, ws)
+    err = (out.double() - a.double() @ w.double().T).abs().max()
+    T.tidar_destroy(ctx)
+    assert float(err) < K * 2.0 ** -24 * 0.02 * 16       # K roundings of sums that stay below 16 products of 0.02
+
+
+# fp32 attention: head dimensions on both sides of 32 and 64 and one whose rows are no 16-byte pieces, several groups of
+# four units per wave, several mask tiles
+@pytest.mark.parametrize("hd,k,L", [(32, 4, 300), (64, 8, 70), (128, 16, 40), (128, 3, 270), (30, 5, 33), (96, 2, 0)])
+def test_fp32_attention_head_dims(T, hd, k, L):
+    sh = TI.ModelShape("t", 1, 128, 8, 8 if hd % 4 else 4, hd, 512, 512, False)
+    for got, want in _attention_case(T, sh, 2, [L, max(L - 17, 0)], k, k, k, 1, seed=hd + L, dtype_id=T.TIDAR_F32):
+        assert torch.allclose(got, want, atol=2e-5), float((got - want).abs().max())
