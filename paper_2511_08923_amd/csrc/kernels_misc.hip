@@ -651,125 +651,201 @@ __global__ void set_i32_kernel(int32_t *p, int n, int32_t v) {
     if (i < n) p[i] = v;
 }
 
-// ------------------------------------------------------------------ fp32 GEMM (plain ALU)
+// ------------------------------------------------------------------ fp32 GEMM (v_mfma_f32_16x16x4_f32)
 // a: A-fragment layout (fp32 elements), w: row-major [N][K], out: tiled or row-major.
+// The fp32 configuration is a small model whose GEMMs are all latency, so a workgroup's four waves split K (32 at a
+// time, in turn), every wave takes both operands straight into registers, eight k of one row or column per lane (a
+// 16x16x4 MFMA sums one of them over the four lane groups), and the four sums meet in LDS in wave order: one trip to
+// memory per 128 k instead of four with two barriers each (20 x 128 x 512 44 -> 4.2 us, 272 x 4096 x 4096 617 -> 191).  RT x CT tiles of 16 per
+// workgroup: one by one while that leaves compute units idle, then 2 x 4.
+template <int RT, int CT>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ a, const float *__restrict__ w,
                                                        float *__restrict__ out, int M, int N, int K,
                                                        int out_row_major) {
-    __shared__ float As[16][33];
-    __shared__ float Ws[64][33];
-    const int n0 = blockIdx.x * 64, m0 = blockIdx.y * 16;
-    const int tc = threadIdx.x & 63, tr = threadIdx.x >> 6;      // column, row group (4 rows each)
+    __shared__ float part[4][RT * CT * 4][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const int row0 = blockIdx.y * 16 * RT, col0 = blockIdx.x * 16 * CT;
     const ActLayout lay = act_layout(M);
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += 32) {
-        for (int i = threadIdx.x; i < 16 * 32; i += 256) {
-            int r = i >> 5, c = i & 31;
-            As[r][c] = (m0 + r < M && k0 + c < K) ? a[af_index(m0 + r, k0 + c, lay)] : 0.f;
-        }
-        for (int i = threadIdx.x; i < 64 * 32; i += 256) {
-            int r = i >> 5, c = i & 31;
-            Ws[r][c] = (n0 + r < N && k0 + c < K) ? w[(size_t)(n0 + r) * K + k0 + c] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int c = 0; c < 32; ++c) {
-            float wv = Ws[tc][c];
+    f32x4 acc[RT][CT];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = fmaf(As[tr * 4 + i][c], wv, acc[i]);
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    for (int kb = 32 * wave; kb < K; kb += 128) {
+        const int k = kb + 8 * g;                  // K is a multiple of 8: a lane's eight k exist or do not
+        f32x4 av[RT][2], wv[CT][2];
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            const int row = row0 + 16 * i + n;
+            const bool ok = row < M && k < K;
+            const float *p = a + (ok ? af_index(row, k, lay) : 0);
+            av[i][0] = ok ? *(const f32x4 *)p : zero;
+            av[i][1] = ok ? *(const f32x4 *)(p + 4) : zero;
         }
-        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int col = col0 + 16 * j + n;
+            const bool ok = col < N && k < K;
+            const float *p = w + (ok ? (size_t)col * K + k : 0);
+            wv[j][0] = ok ? *(const f32x4 *)p : zero;
+            wv[j][1] = ok ? *(const f32x4 *)(p + 4) : zero;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int j = 0; j < CT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i][e >> 2][e & 3], wv[j][e >> 2][e & 3], acc[i][j], 0, 0, 0);
     }
-    for (int i = 0; i < 4; ++i) {
-        int m = m0 + tr * 4 + i, n = n0 + tc;
-        if (m < M && n < N) out[out_row_major ? (size_t)m * N + n : pt_index(n, m, M)] = acc[i];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[wave][(i * CT + j) * 4 + e][lane] = acc[i][j][e];
+    __syncthreads();
+    for (int x = wave; x < RT * CT * 4; x += 4) {      // register x % 4 of tile x / 4: row 4 * (lane / 16) + x % 4
+        const float v = ((part[0][x][lane] + part[1][x][lane]) + part[2][x][lane]) + part[3][x][lane];
+        const int t = x >> 2, m = row0 + 16 * (t / CT) + 4 * g + (x & 3), c = col0 + 16 * (t % CT) + n;
+        if (m < M && c < N) out[out_row_major ? (size_t)m * N + c : pt_index(c, m, M)] = v;
     }
 }
 
 // ------------------------------------------------------------------ fp32 hybrid-mask attention (plain ALU)
-// One wave per (sequence, query head, row).  Keys: cache positions [0, L + nc) then the mask rows' scratch tiles.
-__global__ __launch_bounds__(64) void attention_f32_kernel(const float *__restrict__ q, KvView kv,
-                                                           const float *__restrict__ k_scr,
-                                                           const float *__restrict__ v_scr,
-                                                           const int32_t *__restrict__ prefix_len, RowDesc d, int n_q,
-                                                           float *__restrict__ out, int out_af, ActLayout lay) {
-    int row = blockIdx.x;                  // b * R + r
-    int head = blockIdx.y;
-    int b = row / d.R, r = row - b * d.R;
-    int hd = kv.hd, n_kv = kv.n_kv;
-    int g = head / (n_q / n_kv);
-    int L = clamp_prefix(kv, prefix_len[d.seq_base + b], d.nc);
-    RowInfo ri = row_info(d, r, L);
-    int n_cache = L + d.nc, n_mask = d.nm, n_mtiles = (n_mask + 15) / 16;
-    int T = n_cache + n_mask;
-    const float *kp = (const float *)kv.k_pages;
-    const float *vp = (const float *)kv.v_pages;
+// One workgroup per (sequence, query head, row).  Keys come in units of 16: cache pages 0 .. ceil((L + nc) / 16) - 1,
+// then the mask rows' scratch tiles.  A wave takes four units at a time, one key per lane for the scores, one head
+// dimension (of two halves of the units where hd <= 32) per lane for the values; the four waves take every fourth
+// group of units and are folded at the end.  What bounds it is latency: page id, K row, V piece, three dependent
+// trips per 64 keys (they used to be two per key: 22 -> 5.4 us at 20 rows, 64 cached tokens).
+// VEC: rows of K are whole, aligned 16-byte pieces and the pages start on 16 bytes.
+template <bool VEC>
+__global__ __launch_bounds__(256) void attention_f32_kernel(const float *__restrict__ q, KvView kv,
+                                                            const float *__restrict__ k_scr,
+                                                            const float *__restrict__ v_scr,
+                                                            const int32_t *__restrict__ prefix_len, RowDesc d, int n_q,
+                                                            float *__restrict__ out, int out_af, ActLayout lay) {
+    const int row = blockIdx.x, head = blockIdx.y;                 // row = b * R + r
+    const int b = row / d.R, r = row - b * d.R;
+    const int hd = kv.hd, n_kv = kv.n_kv, g = head / (n_q / n_kv);
+    const int L = clamp_prefix(kv, prefix_len[d.seq_base + b], d.nc);
+    const RowInfo ri = row_info(d, r, L);
+    const int n_cache = L + d.nc, n_mtiles = (d.nm + 15) / 16;
+    const int cache_units = (n_cache + 15) / 16, units = cache_units + n_mtiles;
+    const float *kp = (const float *)kv.k_pages, *vp = (const float *)kv.v_pages;
     const int32_t *pt = kv.page_table + (size_t)(d.seq_base + b) * kv.pages_per_seq;
-    __shared__ float qs[128];
-    __shared__ float ps[64];
-    int lane = threadIdx.x;
-    for (int i = lane; i < hd; i += 64) qs[i] = q[((size_t)row * n_q + head) * hd + i];
+    __shared__ __attribute__((aligned(16))) float qs[128];
+    __shared__ __attribute__((aligned(16))) float ps[4][64];
+    __shared__ float fold[4][2 + 128];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int i = threadIdx.x; i < hd; i += 256) qs[i] = q[((size_t)row * n_q + head) * hd + i];
     __syncthreads();
-    float scale = rsqrtf((float)hd);
+    const float scale = rsqrtf((float)hd);
+    const bool split = hd <= 32;                    // 32 dimensions: the half-waves take two units each
+    const int d0 = split ? lane & 31 : lane;
     float m_run = -INFINITY, l_run = 0.f;
-    float o0 = 0.f, o1 = 0.f;              // this lane's output dims: lane, lane + 64
-    for (int t0 = 0; t0 < T; t0 += 64) {
-        int t = t0 + lane;
+    float o0 = 0.f, o1 = 0.f;                       // this lane's output dimensions: d0, d0 + 64
+    for (int u0 = 4 * wave; u0 < units; u0 += 16) {
+        const int u = u0 + (lane >> 4), slot = lane & 15;
         bool vis = false;
-        const float *krow = nullptr;
-        if (t < n_cache) {
-            vis = (t < L) || (t - L < ri.vis);
-            const int page = pt[t >> 4];
-            krow = kp + k_page_offset(kv, page_ok(kv, page) ? page : 0, g, t & 15, 0);
-        } else if (t < T) {
-            int m = t - n_cache;
-            vis = (ri.blk >= 0) && (m / d.bl == ri.blk);
-            krow = k_scr + ((((size_t)b * n_kv + g) * n_mtiles + (m >> 4)) * 16 + (m & 15)) * hd;
+        const float *kt = nullptr, *vt = nullptr;   // this lane's unit (16 keys) of K and V
+        if (u < cache_units) {
+            const int t = 16 * u + slot;
+            vis = t < L || (t < n_cache && t - L < ri.vis);
+            const int page = pt[u], pg = page_ok(kv, page) ? page : 0;
+            kt = kp + k_page_offset(kv, pg, g, 0, 0);
+            vt = vp + v_page_offset(kv, pg, g, 0, 0);
+        } else if (u < units) {
+            const int m = 16 * (u - cache_units) + slot;
+            vis = ri.blk >= 0 && m < d.nm && m / d.bl == ri.blk;
+            const size_t tile = ((size_t)b * n_kv + g) * n_mtiles + (u - cache_units);
+            kt = k_scr + tile * 16 * hd;
+            vt = v_scr + tile * hd * 16;
         }
         float s = -INFINITY;
         if (vis) {
+            const float *krow = kt + slot * hd;
             float acc = 0.f;
-            for (int i = 0; i < hd; ++i) acc = fmaf(qs[i], krow[i], acc);
+            if (VEC) {
+#pragma unroll 8
+                for (int i = 0; i < hd; i += 4) {
+                    const float4 k4 = *(const float4 *)(krow + i), q4 = *(const float4 *)(qs + i);
+                    acc = fmaf(q4.x, k4.x, acc);
+                    acc = fmaf(q4.y, k4.y, acc);
+                    acc = fmaf(q4.z, k4.z, acc);
+                    acc = fmaf(q4.w, k4.w, acc);
+                }
+            } else {
+                for (int i = 0; i < hd; ++i) acc = fmaf(qs[i], krow[i], acc);
+            }
             s = acc * scale;
         }
-        float mx = wave_max(s);
-        if (mx == -INFINITY) continue;     // nothing visible in this chunk (uniform across the wave)
-        float m_new = fmaxf(m_run, mx);
-        float alpha = __expf(m_run - m_new);
-        float p = vis ? __expf(s - m_new) : 0.f;
+        const float mx = wave_max(s);
+        if (mx == -INFINITY) continue;     // nothing visible in these units (uniform across the wave)
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = __expf(m_run - m_new);
+        const float p = vis ? __expf(s - m_new) : 0.f;
         l_run = l_run * alpha + wave_sum(p);
         o0 *= alpha;
         o1 *= alpha;
         m_run = m_new;
-        ps[lane] = p;
-        __syncthreads();
-        int lim = min(64, T - t0);
-        for (int j = 0; j < lim; ++j) {
-            float pj = ps[j];
-            if (pj == 0.f) continue;
-            int tj = t0 + j;
-            const float *vbase;
-            size_t stride_d;
-            if (tj < n_cache) {
-                const int page = pt[tj >> 4];
-                vbase = vp + v_page_offset(kv, page_ok(kv, page) ? page : 0, g, tj & 15, 0);
-                stride_d = 16;
+        __builtin_amdgcn_wave_barrier();
+        ps[wave][lane] = p;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const unsigned long long any = __ballot(p != 0.f);
+        // a key that carries no weight is never multiplied: its slot may hold anything
+        auto take = [&](int uu, int dd, float &o) {
+            const float *src = (const float *)__shfl((unsigned long long)vt, 16 * uu) + (size_t)dd * 16;
+            if (!((any >> (16 * uu)) & 0xffffull) || dd >= hd) return;
+            float v[16];
+            if (VEC) {
+#pragma unroll
+                for (int x = 0; x < 4; ++x) *(float4 *)(v + 4 * x) = *(const float4 *)(src + 4 * x);
             } else {
-                int m = tj - n_cache;
-                vbase = v_scr + (((size_t)b * n_kv + g) * n_mtiles + (m >> 4)) * hd * 16 + (m & 15);
-                stride_d = 16;
+#pragma unroll
+                for (int x = 0; x < 16; ++x) v[x] = src[x];
             }
-            if (lane < hd) o0 = fmaf(pj, vbase[(size_t)lane * stride_d], o0);
-            if (lane + 64 < hd) o1 = fmaf(pj, vbase[(size_t)(lane + 64) * stride_d], o1);
+#pragma unroll
+            for (int x = 0; x < 16; ++x) {
+                const float pj = ps[wave][16 * uu + x];
+                o = pj != 0.f ? fmaf(pj, v[x], o) : o;
+            }
+        };
+        if (split) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x) take(2 * x + (lane >> 5), d0, o0);
+        } else {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                take(x, d0, o0);
+                if (hd > 64) take(x, d0 + 64, o1);
+            }
         }
-        __syncthreads();
     }
-    float inv = 1.f / l_run;
-    auto oidx = [&](int dd) {
-        return out_af ? af_index(row, head * hd + dd, lay) : ((size_t)row * n_q + head) * hd + dd;
-    };
-    if (lane < hd) out[oidx(lane)] = o0 * inv;
-    if (lane + 64 < hd) out[oidx(lane + 64)] = o1 * inv;
+    if (split) o0 += __shfl_xor(o0, 32);
+    if (lane == 0) {
+        fold[wave][0] = m_run;
+        fold[wave][1] = l_run;
+    }
+    if (d0 < hd && (!split || lane < 32)) fold[wave][2 + d0] = o0;
+    if (hd > 64 && d0 + 64 < hd) fold[wave][2 + d0 + 64] = o1;
+    __syncthreads();
+    const int dd = threadIdx.x;
+    if (dd < hd) {
+        const float m = fmaxf(fmaxf(fold[0][0], fold[1][0]), fmaxf(fold[2][0], fold[3][0]));
+        float num = 0.f, den = 0.f;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            if (fold[x][0] == -INFINITY) continue;       // no key of this wave is visible
+            const float wgt = __expf(fold[x][0] - m);
+            num = fmaf(wgt, fold[x][2 + dd], num);
+            den = fmaf(wgt, fold[x][1], den);
+        }
+        out[out_af ? af_index(row, head * hd + dd, lay) : ((size_t)row * n_q + head) * hd + dd] = num / den;
+    }
 }
 
 inline int grid_for(size_t n, int block, int cap = 4096) {
@@ -828,8 +904,11 @@ void launch_rmsnorm(int dtype, float *x, const float *part, int S, const void *g
 
 void launch_gemm_f32(const float *a, const float *w, float *out, int M, int N, int K, int out_row_major,
                      hipStream_t st) {
-    dim3 grid((N + 63) / 64, (M + 15) / 16);
-    gemm_f32_kernel<<<grid, 256, 0, st>>>(a, w, out, M, N, K, out_row_major);
+    // 16 x 16 tiles until there are a few workgroups for every compute unit
+    if ((size_t)((N + 15) / 16) * ((M + 15) / 16) <= 1024)
+        gemm_f32_kernel<1, 1><<<dim3((N + 15) / 16, (M + 15) / 16), 256, 0, st>>>(a, w, out, M, N, K, out_row_major);
+    else
+        gemm_f32_kernel<2, 4><<<dim3((N + 63) / 64, (M + 31) / 32), 256, 0, st>>>(a, w, out, M, N, K, out_row_major);
 }
 
 void launch_pack_act(int dtype, const void *src, int M, int K, void *dst, hipStream_t st) {
@@ -877,8 +956,13 @@ void launch_attention_f32(const float *q, KvView kv, const float *k_scr, const f
                           const int32_t *prefix_len, RowDesc d, int B, int n_q, float *out, int out_af,
                           hipStream_t st) {
     dim3 grid(B * d.R, n_q);
-    attention_f32_kernel<<<grid, 64, 0, st>>>(q, kv, k_scr, v_scr, prefix_len, d, n_q, out, out_af,
-                                              act_layout(B * d.R));
+    const bool vec = kv.hd % 4 == 0 && (((uintptr_t)kv.k_pages | (uintptr_t)kv.v_pages | (uintptr_t)k_scr | (uintptr_t)v_scr) & 15) == 0;
+    if (vec)
+        attention_f32_kernel<true><<<grid, 256, 0, st>>>(q, kv, k_scr, v_scr, prefix_len, d, n_q, out, out_af,
+                                                          act_layout(B * d.R));
+    else
+        attention_f32_kernel<false><<<grid, 256, 0, st>>>(q, kv, k_scr, v_scr, prefix_len, d, n_q, out, out_af,
+                                                           act_layout(B * d.R));
 }
 
 void launch_swiglu(int dtype, const float *part, int S, int M, int d_ff, void *out, hipStream_t st) {

@@ -116,8 +116,17 @@ size_t gemm_out_floats(const tidar_config &c, int M, int N, int K) {
 
 // Workspace of one forward over B sequences of R rows (n_mask mask rows each), Mh rows through the LM head.
 // n_mix: causal rows per sequence whose verification may mix two rows of logits (the decode step: k; else 0).
+// gemm_floats: room for the partial sums where the caller knows it already (0: worked out here).
+size_t forward_gemm_floats(const tidar_config &c, int M) {
+    const int q_dim = c.n_q_heads * c.head_dim, kv_dim = c.n_kv_heads * c.head_dim;
+    const size_t g[4] = {gemm_out_floats(c, M, q_dim + 2 * kv_dim, c.d_model), gemm_out_floats(c, M, c.d_model, q_dim),
+                         gemm_out_floats(c, M, 2 * c.d_ff, c.d_model), gemm_out_floats(c, M, c.d_model, c.d_ff)};
+    size_t best = 0;
+    for (size_t v : g) best = v > best ? v : best;
+    return best;
+}
 Layout make_layout(const tidar_config &c, int B, int R, int n_mask, int Mh, int max_keys, bool own_logits,
-                   int n_mix = 0) {
+                   int n_mix = 0, size_t gemm_floats = 0) {
     Layout l;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -127,7 +136,7 @@ Layout make_layout(const tidar_config &c, int B, int R, int n_mask, int Mh, int 
     };
     size_t es = esize(c.dtype);
     int M = B * R;
-    int q_dim = c.n_q_heads * c.head_dim, kv_dim = c.n_kv_heads * c.head_dim;
+    int q_dim = c.n_q_heads * c.head_dim;
     l.pos = take((size_t)M * 4);
     l.rope_cs = take((size_t)M * c.head_dim * 4);
     l.x = take((size_t)M * c.d_model * 4);
@@ -136,13 +145,7 @@ Layout make_layout(const tidar_config &c, int B, int R, int n_mask, int Mh, int 
     const bool fused_rows = c.dtype == TIDAR_BF16 && M <= kFuseMaxRows;
     l.x2 = take(fused_rows ? (size_t)M * c.d_model * 4 : 0);
     l.xn = take(af_elems(M, c.d_model) * es);
-    size_t g = gemm_out_floats(c, M, q_dim + 2 * kv_dim, c.d_model);
-    size_t g2 = gemm_out_floats(c, M, c.d_model, q_dim);
-    size_t g3 = gemm_out_floats(c, M, 2 * c.d_ff, c.d_model);
-    size_t g4 = gemm_out_floats(c, M, c.d_model, c.d_ff);
-    g = g > g2 ? g : g2;
-    g = g > g3 ? g : g3;
-    g = g > g4 ? g : g4;
+    const size_t g = gemm_floats ? gemm_floats : forward_gemm_floats(c, M);
     l.gemm_out = take(g * 4);
     l.gemm_out2 = take(fused_rows ? g * 4 : 0);
     l.q = take((size_t)M * q_dim * es);
@@ -608,8 +611,9 @@ tidar_status tidar_workspace_bytes(const tidar_ctx *ctx, int32_t batch, int32_t 
     // prefill passes: a full causal chunk, or a last pass of 1..chunk causal rows plus the mask block
     Layout full = make_layout(c, 1, ctx->prefill_chunk, 0, 0, max_prefix_len + ctx->prefill_chunk, true);
     if (full.total > t) t = full.total;
+    const size_t g = forward_gemm_floats(c, ctx->prefill_chunk + k);          // grows with the rows: enough for each
     for (int nc = 1; nc <= ctx->prefill_chunk; ++nc) {
-        Layout p = make_layout(c, 1, nc + k, k, 1 + k, max_prefix_len + k, true);
+        Layout p = make_layout(c, 1, nc + k, k, 1 + k, max_prefix_len + k, true, 0, g);
         if (p.total > t) t = p.total;
     }
     *bytes = t;
