@@ -640,8 +640,9 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
     if (M <= 32) {
         p.mt = M <= 16 ? 1 : 2;                  // 16-row tiles per wave (narrow kernel)
         p.m_chunks = 1;
-        // nearest count that brings the grid to about one wave of CUs
-        if (!force_single_split && wgs < 224) splits = fit((256 + wgs / 2) / wgs);
+        // nearest count that brings the grid to about one wave of CUs; from half of that on a single split, which saves
+        // the partial sums and, for gate/up, the SwiGLU launch (1.5B shape, 6 rows: 17.1 + 4.0 us in two splits)
+        if (!force_single_split && wgs < 128) splits = fit((256 + wgs / 2) / wgs);
     } else {
         // Partial sums are the expensive part of a split (each one is M x N floats written and read again), so
         // the column blocks are split over K only until about half the CUs are busy; the rest of the chip is
