@@ -367,8 +367,11 @@ __global__ void swiglu_kernel(const float *__restrict__ part, int S, size_t spli
 }
 
 // ------------------------------------------------------------------ vocabulary argmax / Gumbel-max
-// One block per (sequence, row o < n_rows) over materialised logits with Rh rows per sequence.
-__global__ void argmax_rows_kernel(const float *__restrict__ logits, int Rh, int n_rows, int vocab, int n_choose,
+// One block per (sequence, row o < n_rows) over materialised logits with Rh rows per sequence.  With few rows it is a
+// chain of trips to memory, with many a stream: U pieces of W columns per thread are on their way at a time (one
+// column at a time: 20 rows of 151 936 72 us, 272 rows 93 us; now 24 and 58).  W = 4: 16-byte aligned rows.
+template <int W>
+__global__ __launch_bounds__(1024) void argmax_rows_kernel(const float *__restrict__ logits, int Rh, int n_rows, int vocab, int n_choose,
                                    const int32_t *__restrict__ pos_rows, int pos_stride, int pos_row0, int seq_base,
                                    int sample, float temperature, uint64_t seed, float beta, int mix_base,
                                    int mix_stride, int32_t *__restrict__ y, int y_stride) {
@@ -388,11 +391,28 @@ __global__ void argmax_rows_kernel(const float *__restrict__ logits, int Rh, int
     }
     float best = -INFINITY;
     int best_i = 0x7fffffff;
-    for (int v = threadIdx.x; v < vocab; v += blockDim.x) {
-        float val = lg[v];
-        if (mix) val = beta * val + (1.f - beta) * mix[v];
+    constexpr int U = 8;
+    typedef float vec __attribute__((ext_vector_type(W)));
+    auto take = [&](float val, float other, int v) {
+        if (mix) val = beta * val + (1.f - beta) * other;
         if (noisy) val = perturbed_logit(val, inv_t, key, (uint32_t)v);
         if (val > best || (val == best && v < best_i)) { best = val; best_i = v; }
+    };
+    for (int v0 = W * threadIdx.x; v0 < vocab; v0 += U * W * blockDim.x) {      // vocab is a multiple of W
+        vec x[U], m[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int v = min(v0 + u * W * (int)blockDim.x, vocab - W);             // clamped: always a real address
+            x[u] = *(const vec *)(lg + v);
+            if (mix) m[u] = *(const vec *)(mix + v);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int v = v0 + u * W * (int)blockDim.x;
+            if (v >= vocab) break;
+#pragma unroll
+            for (int e = 0; e < W; ++e) take(x[u][e], mix ? m[u][e] : 0.f, v + e);
+        }
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -985,9 +1005,14 @@ void launch_argmax_rows(const float *logits, int B, int Rh, int n_rows, int voca
                         const int32_t *pos_rows, int pos_stride, int pos_row0, int seq_base, int sample,
                         float temperature, uint64_t seed, float beta, int mix_base, int mix_stride, int32_t *y,
                         int y_stride, hipStream_t st) {
-    argmax_rows_kernel<<<B * n_rows, 1024, 0, st>>>(logits, Rh, n_rows, vocab, n_choose, pos_rows, pos_stride, pos_row0,
-                                                    seq_base, sample, temperature, seed, beta, mix_base, mix_stride, y,
-                                                    y_stride);
+    if (((uintptr_t)logits & 15) == 0 && vocab % 4 == 0)
+        argmax_rows_kernel<4><<<B * n_rows, 1024, 0, st>>>(logits, Rh, n_rows, vocab, n_choose, pos_rows, pos_stride, pos_row0,
+                                                       seq_base, sample, temperature, seed, beta, mix_base, mix_stride,
+                                                       y, y_stride);
+    else
+        argmax_rows_kernel<1><<<B * n_rows, 1024, 0, st>>>(logits, Rh, n_rows, vocab, n_choose, pos_rows, pos_stride, pos_row0,
+                                                       seq_base, sample, temperature, seed, beta, mix_base, mix_stride,
+                                                       y, y_stride);
 }
 
 void launch_score_rows(const float *logits, int rows, int vocab, const int32_t *text, int len, int c0, int nc,
