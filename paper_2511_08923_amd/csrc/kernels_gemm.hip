@@ -651,13 +651,15 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
         // whatever the batch size.
         if (!force_single_split) splits = fit(128 / wgs);
         const int t = (M + 31) / 32;             // 32-row tiles
-        if (t < 16 && !force_single_split) {
+        if (!force_single_split && (t < 16 || (t < 28 && wgs * splits <= 40))) {
             // kernels_gemm_mid.hip: the waves of a workgroup split K.  It takes the products whose two row passes
             // below would fill less than half of the compute units (the small model's QKV and O: 272 x 1536 x 1536 12.2
             // -> 8.6 us in 3 splits either way; where they fill more it gains nothing alone and loses 10 % inside a
             // step, where the activations come from other XCDs), and the wide single-split ones up to five row
             // tiles (72 x 24576 x 4096 45.2 -> 40.8, 160 rows 56.7 -> 51.8; 272 rows 68.2 -> 81.5), or whose passes as
-            // eight-wave workgroups are not resident at once (420 rows 137 -> 122).
+            // eight-wave workgroups are not resident at once (420 rows 137 -> 122).  The narrowest keep it beyond 480 rows
+            // (1536 x 1536 at 544 / 700 / 816 rows: 20.3 / 19.5 / 19.4 us in the many-row kernel, 13.6 / 15.4 / 17.1
+            // here; at N = 2048 20.6 / 20.2 / 20.2 and 19.2 / 22.3 / 19.6, so the line lies between).
             const bool single = splits == 1 && wgs >= 128;
             if (single ? t <= 5 || (t > 7 && (N + 255) / 256 * ((t + 4) / 5) > 256) : wgs * splits <= 64) {
                 // Per workgroup: its fragments at the 27 B per clock that a compute unit takes in from afar, or the

@@ -65,7 +65,8 @@ def test_many_row_step_fused_vocabulary_reduction_equals_logits_path(T, sample, 
 # two of the four waves have none), a share of K that is no multiple of the ring, ragged N; wide single-split products
 # up to five row tiles and beyond the eight-wave form
 @pytest.mark.parametrize("M,N,K", [(33, 48, 32), (100, 784, 608), (272, 1536, 1536), (300, 1040, 96), (470, 2048, 1536),
-                                   (480, 528, 288), (97, 16400, 160), (160, 24576, 608), (420, 24576, 96), (470, 24560, 512)])
+                                   (480, 528, 288), (97, 16400, 160), (160, 24576, 608), (420, 24576, 96), (470, 24560, 512),
+                                   (864, 1536, 1536)])
 def test_k_split_gemm_matches_fp64_matmul(T, M, N, K):
     test_many_row_gemm_matches_fp64_matmul(T, M, N, K)
 
