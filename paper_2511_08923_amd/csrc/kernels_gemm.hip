@@ -1,6 +1,7 @@
 // Skinny bf16 GEMM of the decode step: out = A[M][K] (bf16) x W[N][K]^T (bf16), fp32 accumulation.
 //
-// M is the step's row count (1 .. 272 at batch 1; more rows run as row passes), N and K are model dimensions: every weight byte is used once
+// M is the step's row count (1 .. 272 at batch 1; more rows run as row passes, 481 and more in kernels_gemm_rows.hip,
+// some shapes of 33 .. 480 in kernels_gemm_mid.hip), N and K are model dimensions: every weight byte is used once
 // per step, so the kernel is a weight streamer with MFMA attached.
 //   * W lives in HBM as the register image of the 32x32x16 MFMA B operand
 //     ([k step of 16][32-column tile][lane][8]); a wave's load of one fragment is one fully coalesced 1 KiB read
@@ -14,8 +15,8 @@
 //     has no branches, and the compiler can keep exact in-flight counts (vmcnt(n), not vmcnt(0)) on the ring;
 //     sched_barrier pins each reload right behind the MFMAs that free its slot.
 //   * M <= 32: 16x16x32 MFMA (fewer pad rows), no LDS, no barriers; a wave streams its 32 columns and the A
-//     fragments through two register rings.  M > 32: 32x32x16 MFMA (on gfx950 it issues at twice the rate of
-//     16x16x32: measured 2.2 vs 1.2 PFLOP/s), A staged through LDS once per workgroup and prefetched into
+//     fragments through two register rings.  M > 32: 32x32x16 MFMA (half the operand reads of 16x16x32 per
+//     product; a bare loop with few accumulators measured 2.2 vs 1.2 PFLOP/s), A staged through LDS once per workgroup and prefetched into
 //     registers ahead of the MFMAs; 4 waves either as a 2 x 2 grid over 128 columns (two row halves x two
 //     64-column groups: launches without a row split), or side by side, every wave over all row tiles of the pass
 //     (no weight fragment is then loaded by two waves): eight waves over 256 columns for single-split grids, four over
