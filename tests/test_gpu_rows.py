@@ -94,3 +94,27 @@ def test_fp32_attention_head_dims(T, hd, k, L):
     sh = TI.ModelShape("t", 1, 128, 8, 8 if hd % 4 else 4, hd, 512, 512, False)
     for got, want in _attention_case(T, sh, 2, [L, max(L - 17, 0)], k, k, k, 1, seed=hd + L, dtype_id=T.TIDAR_F32):
         assert torch.allclose(got, want, atol=2e-5), float((got - want).abs().max())
+
+
+@pytest.mark.parametrize("B", [5, 40])
+def test_one_token_step_of_more_than_four_sequences(T, B):
+    """The attention workgroups rotate the new rows at any batch: logits and the new K/V rows against the same sequence
+    stepped alone (B = 40: more than 32 rows, the other GEMM class in front)."""
+    sh = TI.SMALL_GQA
+    w = TI.make_weights(sh, seed=5, dtype=torch.bfloat16)
+    lens = [15 + 3 * (b % 13) for b in range(B)]           # page boundaries among them
+    prompt = TI.make_prompt(sh, max(lens), seed=8, batch=B)
+    tok = TI.make_drafts(sh, 1, seed=9, batch=B).view(B).cuda()
+    many = T.Engine(sh, w, dtype=T.TIDAR_BF16, max_k=1, max_batch=B, max_seq_len=96)
+    many.prefill(prompt, 1, prompt_len=lens)
+    _, lg = many.ar_step(tok, hint=max(lens), want_logits=True)
+    for b in (0, B // 2, B - 1):
+        one = T.Engine(sh, w, dtype=T.TIDAR_BF16, max_k=1, max_batch=1, max_seq_len=96)
+        one.prefill(prompt[b:b + 1, :lens[b]], 1)
+        _, want = one.ar_step(tok[b:b + 1].contiguous(), hint=lens[b], want_logits=True)
+        assert float((lg[b] - want[0]).abs().max()) < 2e-2          # the bf16 tolerance of the small models
+        for layer in range(sh.n_layers):
+            for got, ref in zip(many.read_cache(layer, b, lens[b] + 1), one.read_cache(layer, 0, lens[b] + 1)):
+                assert torch.allclose(got.float(), ref.float(), atol=2e-2, rtol=2e-2)
+        one.close()
+    many.close()
