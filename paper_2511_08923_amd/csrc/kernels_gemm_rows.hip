@@ -14,6 +14,9 @@
 // of the next chunk and the loads of the chunk after the next three go out a few at a time behind each row of eight
 // MFMAs, and after the one barrier of a chunk there are always fragments in registers to go on with.
 // The row passes of a launch are equally high, or differ by one row tile (the plan picks their number).
+// Measured against four waves of 256 x 64 with 32x32x16 MFMAs, weights in a register ring: 2176 x 24576 x 4096 440 -> 339
+// us (1.29 PFLOP/s), 2176 x 4096 x 12288 220 -> 165, 4000 x 17920 x 1536 248 -> 203; 23 instead of 25 ns per k of a
+// 256 x 256 tile with every compute unit busy, 18 on zeros.
 #include <type_traits>
 
 #include "gemm_device.h"
