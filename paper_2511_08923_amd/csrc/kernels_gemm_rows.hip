@@ -134,8 +134,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
 #pragma unroll
             for (int j = 0; j < CT; ++j) {
                 // The ninth row's accumulators do not fit the 256 AGPRs any more; left to the compiler, which wants
-                // all of them there, they are copied in and out around every use.  (Nothing reads these results
-                // before the wait behind the loop.)
+                // all of them there, they are copied in and out around every use.  (The wait that their reader needs
+                // stands behind the loop and names them.)
                 if (i == 8)
                     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[i][j]) : "v"(wf[s][j]), "v"(af[s][i]));
                 else
@@ -170,12 +170,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
 #pragma unroll
             for (int i = 0; i < CHUNK / 4096; ++i) z[threadIdx.x + 256 * i] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
         }
+        // The compiler does not see the ninth row's MFMAs finish: the wait (32 states; the longest MFMA asks for
+        // fewer than 20 before its result is read) takes their results in and hands them on, so no use comes before it
+        if constexpr (RA == 9)
+            asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc[8][0]), "+v"(acc[8][1]), "+v"(acc[8][2]), "+v"(acc[8][3]),
+                         "+v"(acc[8][4]), "+v"(acc[8][5]), "+v"(acc[8][6]), "+v"(acc[8][7]));
     };
     if (ct_here == RT) k_loop(std::integral_constant<int, RT>());
     else k_loop(std::integral_constant<int, RT - 1>());
     wait_loads<0>();
     barrier();
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");     // the compiler does not see the ninth row's MFMAs finish
 
     // ---- epilogue
     const int n = lane & 15, g = lane >> 4;
