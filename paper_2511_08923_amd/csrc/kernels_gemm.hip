@@ -1,7 +1,7 @@
 // Skinny bf16 GEMM of the decode step: out = A[M][K] (bf16) x W[N][K]^T (bf16), fp32 accumulation.
 //
 // M is the step's row count (1 .. 272 at batch 1; more rows run as row passes, 481 and more in kernels_gemm_rows.hip,
-// some shapes of 33 .. 480 in kernels_gemm_mid.hip), N and K are model dimensions: every weight byte is used once
+// the narrower products of 33 .. 480 - the narrowest to 768 - in kernels_gemm_mid.hip), N and K are model dimensions: every weight byte is used once
 // per step, so the kernel is a weight streamer with MFMA attached.
 //   * W lives in HBM as the register image of the 32x32x16 MFMA B operand
 //     ([k step of 16][32-column tile][lane][8]); a wave's load of one fragment is one fully coalesced 1 KiB read
@@ -24,8 +24,9 @@
 //     reads per MFMA, which the LDS has room for).  The weight fragment is the MFMA's first operand, so the
 //     accumulators hold the output transposed (lane = row): every epilogue starts from that.
 //   * split-K over blockIdx.y works in units of 512 k, row passes over blockIdx.z; up to 480 rows the split count
-//     depends on (N, K) and the kernel class (M <= 32 or not) only, so the partial-sum grouping of a row does not
-//     depend on how many rows travel with it (from 481 rows on it also follows the number of 256-row passes).  Splits fill about half the CUs, two row passes the other half: a split
+//     and the kernel family depend on (N, K) and the row class (M <= 32 or not) only, so the partial-sum grouping of a
+//     row does not depend on how many rows travel with it (from 481 rows on both also follow the number of 256-row
+//     multiples).  Splits fill about half the CUs, two row passes the other half: a split
 //     costs an M x N partial sum written and read again, a row pass only a second read of W from L2.
 //   * output: [split][32-column tile][row][32] fp32 partial sums (summed in fixed order by the consumer), or
 //     row-major logits, or - fused epilogues - bf16 SwiGLU products in the next GEMM's A-fragment layout, or
@@ -652,41 +653,37 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
         // whatever the batch size.
         if (!force_single_split) splits = fit(128 / wgs);
         const int t = (M + 31) / 32;             // 32-row tiles
-        if (!force_single_split && (t < 16 || (t < 28 && wgs * splits <= 40))) {
+        if (!force_single_split && (t < 16 ? wgs * splits <= 64 : t <= 24 && wgs * splits <= 40)) {
             // kernels_gemm_mid.hip: the waves of a workgroup split K.  It takes the products whose two row passes
             // below would fill less than half of the compute units (the small model's QKV and O: 272 x 1536 x 1536 12.2
             // -> 8.6 us in 3 splits either way; where they fill more it gains nothing alone and loses 10 % inside a
-            // step, where the activations come from other XCDs), and the wide single-split ones up to five row
-            // tiles (72 x 24576 x 4096 45.2 -> 40.8, 160 rows 56.7 -> 51.8; 272 rows 68.2 -> 81.5), or whose passes as
-            // eight-wave workgroups are not resident at once (420 rows 137 -> 122).  The narrowest keep it beyond 480 rows
-            // (1536 x 1536 at 544 / 700 / 816 rows: 20.3 / 19.5 / 19.4 us in the many-row kernel, 13.6 / 15.4 / 17.1
-            // here; at N = 2048 20.6 / 20.2 / 20.2 and 19.2 / 22.3 / 19.6, so the line lies between).
-            const bool single = splits == 1 && wgs >= 128;
-            if (single ? t <= 5 || (t > 7 && (N + 255) / 256 * ((t + 4) / 5) > 256) : wgs * splits <= 64) {
-                // Per workgroup: its fragments at the 27 B per clock that a compute unit takes in from afar, or the
-                // matrix cores' rate, plus 4 us of launch, ring fill and reduction; a split also costs the partial
-                // sums at 6 TB/s out and 4 TB/s back in.  The split count is the best at nine row tiles in two passes,
-                // a function of (N, K) alone (a row's sum is grouped the same way whatever the row count); the number
-                // of passes follows the rows.
-                p.mid = 1;
-                p.nt = single ? 3 : 2;
-                const int t32 = (N + 31) / 32, most = p.nt == 2 ? 8 : 5;      // row tiles whose accumulators fit the AGPRs
-                auto cost = [&](int tiles, int sc, int passes) {
-                    const int rt = (tiles + passes - 1) / passes;
-                    const int rounds = ((t32 + p.nt - 1) / p.nt * sc * passes + 255) / 256;
-                    const double load = (rt + p.nt) * 1024 / 27.0, mfma = rt * p.nt * 8 / 0.9;
-                    return rounds * (K / 16.0 / sc * (load > mfma ? load : mfma) / 2100.0 + 4.0) +
-                           sc * tiles * 32.0 * N * 1.67e-6;
-                };
-                p.splits = 1;
-                for (int c = 2; !single && c <= units && c <= 8; ++c)
-                    if (cost(9, fit(c), 2) < cost(9, p.splits, 2)) p.splits = fit(c);
-                p.m_chunks = (t + most - 1) / most;
-                for (int n = p.m_chunks + 1; n <= t; ++n)
-                    if (cost(t, p.splits, n) < cost(t, p.splits, p.m_chunks)) p.m_chunks = n;
-                p.mt = (t + p.m_chunks - 1) / p.m_chunks;
-                return p;
-            }
+            // step, where the activations come from other XCDs).  The narrowest keep it up to 768 rows (1536 x 1536 at
+            // 544 / 700 rows: 20.3 / 19.5 us in the many-row kernel, 13.6 / 15.4 here; at N = 2048 20.6 / 20.2 and 19.2 /
+            // 22.3, so the line lies between).  The row limits are class borders (480 rows, a 256-row multiple):
+            // the four waves sum K in four interleaved shares, so inside a class the choice has to be one of (N, K)
+            // alone.  (It is also faster for wide single-split products of up to five row tiles, 72 x 24576 x 4096
+            // 45.2 -> 40.8 us, but not at nine, 68.2 -> 81.5: those stay below whatever the row count.)
+            // Per workgroup: its fragments at the 27 B per clock that a compute unit takes in from afar, or the
+            // matrix cores' rate, plus 4 us of launch, ring fill and reduction; a split also costs the partial
+            // sums at 6 TB/s out and 4 TB/s back in.  The split count is the best at nine row tiles in two passes,
+            // a function of (N, K) alone; the number of passes follows the rows.
+            p.mid = 1;
+            const int t32 = (N + 31) / 32;
+            auto cost = [&](int tiles, int sc, int passes) {
+                const int rt = (tiles + passes - 1) / passes;
+                const int rounds = ((t32 + 1) / 2 * sc * passes + 255) / 256;
+                const double load = (rt + 2) * 1024 / 27.0, mfma = rt * 2 * 8 / 0.9;
+                return rounds * (K / 16.0 / sc * (load > mfma ? load : mfma) / 2100.0 + 4.0) +
+                       sc * tiles * 32.0 * N * 1.67e-6;
+            };
+            p.splits = 1;
+            for (int c = 2; c <= units && c <= 8; ++c)
+                if (cost(9, fit(c), 2) < cost(9, p.splits, 2)) p.splits = fit(c);
+            p.m_chunks = (t + 7) / 8;                // eight row tiles: the accumulators that fit the AGPRs
+            for (int n = p.m_chunks + 1; n <= t; ++n)
+                if (cost(t, p.splits, n) < cost(t, p.splits, p.m_chunks)) p.m_chunks = n;
+            p.mt = (t + p.m_chunks - 1) / p.m_chunks;
+            return p;
         }
         const bool row_split = !force_single_split && wgs * splits <= 128;
         const int per_pass = row_split ? (t + 1) / 2 : t;

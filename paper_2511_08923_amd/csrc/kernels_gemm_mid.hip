@@ -1,5 +1,5 @@
-// bf16 GEMM of 33 to 480 rows (the decode step's projections): out = A[M][K] x W[N][K]^T, fp32 accumulation, same
-// operand layouts as kernels_gemm.hip.
+// bf16 GEMM of the narrower products of 33 to 480 rows (the narrowest: to 768): out = A[M][K] x W[N][K]^T, fp32
+// accumulation, same operand layouts as kernels_gemm.hip.
 //
 // A workgroup has no barrier and no LDS in its loop: its four waves, one per SIMD, split K between them (k steps in
 // turn) and each accumulates the whole tile of RT x CT 32 x 32 blocks, taking both operands from memory straight into
@@ -7,8 +7,8 @@
 // wave waits for another; the four sums meet in LDS at the end, in wave order, where the epilogue reads them in the
 // order it stores them.  What bounds it is the time a compute unit's loads are under way: about 57 GB/s per unit with
 // weights from HBM (the same loop on weights that stay in L2 takes 60 instead of 81 us at 272 x 24576 x 4096, on
-// activations that stay in L1 no less), so it serves the products that leave compute units idle otherwise or need
-// only one row pass; the accumulators, held four times, leave no registers for a deeper ring.
+// activations that stay in L1 no less), so it serves the products that leave compute units idle otherwise;
+// the accumulators, held four times, leave no registers for a deeper ring.
 #include <type_traits>
 
 #include "gemm_device.h"
@@ -157,33 +157,22 @@ void launch_mid(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int 
 
 // ring depth in k steps: as many registers as the accumulators leave, four or eight (the waves' shares of K are usually
 // multiples of eight steps)
-template <int CT, int EPI, int MOST>
+template <int EPI>
 void launch_mid_rows(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, hipStream_t st) {
-    if (p.mt == 1) launch_mid<1, CT, 8, EPI>(a, w, out, M, N, K, p, st);
-    else if (p.mt == 2) launch_mid<2, CT, 8, EPI>(a, w, out, M, N, K, p, st);
-    else if (p.mt == 3) launch_mid<3, CT, 8, EPI>(a, w, out, M, N, K, p, st);
-    else if (p.mt == 4) launch_mid<4, CT, CT == 2 ? 8 : 4, EPI>(a, w, out, M, N, K, p, st);
-    else if (p.mt == 5) launch_mid<5, CT, CT == 2 ? 8 : 4, EPI>(a, w, out, M, N, K, p, st);
-    else if constexpr (MOST > 5) {
-        if (p.mt == 6) launch_mid<6, CT, 4, EPI>(a, w, out, M, N, K, p, st);
-        else if constexpr (MOST > 6) {
-            if (p.mt == 7) launch_mid<7, CT, 4, EPI>(a, w, out, M, N, K, p, st);
-            else launch_mid<8, CT, 4, EPI>(a, w, out, M, N, K, p, st);
-        }
-    }
+    if (p.mt == 1) launch_mid<1, 2, 8, EPI>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 2) launch_mid<2, 2, 8, EPI>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 3) launch_mid<3, 2, 8, EPI>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 4) launch_mid<4, 2, 8, EPI>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 5) launch_mid<5, 2, 8, EPI>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 6) launch_mid<6, 2, 4, EPI>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 7) launch_mid<7, 2, 4, EPI>(a, w, out, M, N, K, p, st);
+    else launch_mid<8, 2, 4, EPI>(a, w, out, M, N, K, p, st);
 }
 
 }  // namespace
 
 void launch_gemm_bf16_mid(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi,
                           hipStream_t st) {
-    if (epi == GEMM_EPI_SWIGLU && p.nt == 3) {
-        launch_mid_rows<3, GEMM_EPI_SWIGLU, 5>(a, w, out, M, N, K, p, st);
-    } else if (epi == GEMM_EPI_SWIGLU) {
-        launch_mid_rows<2, GEMM_EPI_SWIGLU, 8>(a, w, out, M, N, K, p, st);
-    } else if (p.nt == 3) {
-        launch_mid_rows<3, GEMM_EPI_TILED, 5>(a, w, out, M, N, K, p, st);
-    } else {
-        launch_mid_rows<2, GEMM_EPI_TILED, 8>(a, w, out, M, N, K, p, st);
-    }
+    if (epi == GEMM_EPI_SWIGLU) launch_mid_rows<GEMM_EPI_SWIGLU>(a, w, out, M, N, K, p, st);
+    else launch_mid_rows<GEMM_EPI_TILED>(a, w, out, M, N, K, p, st);
 }

@@ -98,7 +98,7 @@ struct Layout {
 
 size_t gemm_out_floats(const tidar_config &c, int M, int N, int K) {
     if (c.dtype != TIDAR_BF16) return pt_split_stride(M, N);
-    // the split count depends on the row-tile class of M (and, from 481 rows on, on the number of 256-row passes);
+    // the split count depends on the row-tile class of M (and, from 481 rows on, on the number of 256-row multiples);
     // taking the maximum over the class boundaries below M keeps the size monotone in M and large enough for
     // every call with fewer rows (the passes of a prefill differ in length)
     size_t best = 0;
@@ -108,8 +108,8 @@ size_t gemm_out_floats(const tidar_config &c, int M, int N, int K) {
         size_t v = (size_t)p.splits * pt_split_stride(m, N);
         if (v > best) best = v;
     };
-    const int bounds[7] = {16, 32, 80, 144, 480, 864, M};
-    for (int i = 0; i < 7; ++i) consider(bounds[i]);
+    const int bounds[6] = {16, 32, 80, 144, 480, M};
+    for (int i = 0; i < 6; ++i) consider(bounds[i]);
     for (int m = 512; m < M; m += 256) consider(m);      // the largest row count of each pass count
     return best;
 }

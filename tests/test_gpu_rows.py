@@ -71,6 +71,22 @@ def test_k_split_gemm_matches_fp64_matmul(T, M, N, K):
     test_many_row_gemm_matches_fp64_matmul(T, M, N, K)
 
 
+# one (N, K) of each kernel family; row counts on both sides of every tile and pass arrangement of a class
+@pytest.mark.parametrize("N,K,rows", [(16400, 608, (33, 72, 160, 161, 224, 272, 420, 480)),
+                                      (784, 1056, (33, 97, 160, 161, 272, 350, 480)), (4096, 1056, (40, 160, 272, 480)),
+                                      (784, 1056, (513, 640, 768)), (784, 1056, (769, 865, 1024)),
+                                      (16400, 608, (545, 768)), (4096, 1056, (800, 1024))])
+def test_a_rows_sum_does_not_follow_the_row_count(T, N, K, rows):
+    """Bit for bit: what else is in flight (batch, k) must not move a row's result inside a row class."""
+    ctx = T.tidar_create(T.make_config(TI.SHAPE_8B.with_layers(1), T.TIDAR_BF16, max_k=16, max_batch=4))
+    a = TI.make_normal((rows[-1], K), seed=K, dtype=torch.bfloat16)
+    w = TI.make_normal((N, K), seed=N, dtype=torch.bfloat16, std=0.02)
+    most = _gemm(T, ctx, a, w)
+    for M in rows[:-1]:
+        assert torch.equal(_gemm(T, ctx, a[:M].contiguous(), w), most[:M]), (M, N, K)
+    T.tidar_destroy(ctx)
+
+
 # fp32: one element of everything, K that is no multiple of 32 or of 128, ragged rows (the narrow and the wide activation
 # layout), more 16 x 16 tiles than the one-tile form takes
 @pytest.mark.parametrize("M,N,K", [(1, 16, 8), (17, 48, 24), (20, 384, 128), (33, 80, 200), (272, 1040, 152)])
