@@ -725,11 +725,13 @@ tidar_status tidar_score_workspace_bytes(const tidar_ctx *ctx, int32_t max_len, 
     if (!ctx || !bytes || max_len < 1 || block_len < 0 || block_len > TIDAR_MAX_K) return TIDAR_EINVAL;
     const tidar_config &c = ctx->cfg;
     const int chunk = score_chunk(ctx, block_len);
+    const int most = chunk < max_len ? chunk : max_len;
+    const size_t g = forward_gemm_floats(c, score_desc(most, block_len, 0).R);      // grows with the rows: enough for each
     size_t t = 0;
     // the workspace grows with the key bound for a given pass shape, and no pass ends beyond max_len
-    for (int nc = 1; nc <= chunk && nc <= max_len; ++nc) {
+    for (int nc = 1; nc <= most; ++nc) {
         RowDesc d = score_desc(nc, block_len, 0);
-        Layout l = make_layout(c, 1, d.R, d.nm, d.R, max_len + d.nm, true);
+        Layout l = make_layout(c, 1, d.R, d.nm, d.R, max_len + d.nm, true, 0, g);
         if (l.total > t) t = l.total;
     }
     *bytes = score_header_bytes(c) + t;

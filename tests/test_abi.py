@@ -2,6 +2,7 @@
 import ctypes as C
 import os
 import re
+import time
 
 import pytest
 
@@ -62,6 +63,29 @@ def test_workspace_bytes_monotone_and_validated(T):
     for args in [(0, 16, 10), (5, 16, 10), (1, 17, 10), (1, 0, 10), (1, 4, -1)]:
         with pytest.raises(T.TidarError):
             T.tidar_workspace_bytes(ctx, *args)
+    T.tidar_destroy(ctx)
+
+
+@pytest.mark.parametrize("shape", [TI.SHAPE_1P5B, TI.SHAPE_8B])
+def test_score_workspace_is_planned_once_per_call_not_once_per_length(T, shape):
+    """A scoring program asks for the size in front of every call, with the GPU idle meanwhile.  It has to cost about what
+    tidar_workspace_bytes costs, which also walks every pass length but plans the GEMMs of the largest only (planned
+    per length it is 30 to 60 times that).  The size must cover every shorter text."""
+    ctx = T.tidar_create(T.make_config(shape, T.TIDAR_BF16, max_k=16, max_batch=1))
+
+    def fastest(f):
+        best = float("inf")
+        for _ in range(10):
+            t = time.perf_counter()
+            f()
+            best = min(best, time.perf_counter() - t)
+        return best
+
+    step = fastest(lambda: T.tidar_workspace_bytes(ctx, 1, 16, 2000))
+    for bl in (0, 16):
+        assert fastest(lambda: T.tidar_score_workspace_bytes(ctx, 2000, bl)) < 6 * step
+        sizes = [T.tidar_score_workspace_bytes(ctx, n, bl) for n in [*range(1, 2000, 61), 2048, 2049, 3000, 5000]]
+        assert sizes == sorted(sizes)
     T.tidar_destroy(ctx)
 
 
