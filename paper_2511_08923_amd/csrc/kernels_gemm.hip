@@ -97,7 +97,8 @@ __device__ inline void store_tiles(const f32x4 (&acc)[MTW][NT], float *out, int 
                 for (int i = 0; i < 4; ++i) {
                     const int row = (mt0 + mt) * 16 + (lane >> 4) * 4 + i;
                     const float g = acc[mt][0][i], u = acc[mt][1][i];
-                    const float h = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
+                    // a division, as in swiglu_kernel: v_rcp_f32 flushes silu below g = -87.3 and is an ulp off above
+                    const float h = g / (1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
                     if (row < M) ho[af_index(row, (tile0 >> 1) * 16 + (lane & 15), lay)] = (bf16_t)h;
                 }
         }

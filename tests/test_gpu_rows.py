@@ -134,3 +134,29 @@ def test_one_token_step_of_more_than_four_sequences(T, B):
                 assert torch.allclose(got.float(), ref.float(), atol=2e-2, rtol=2e-2)
         one.close()
     many.close()
+
+
+@pytest.mark.parametrize("B", [3, 5, 20])
+def test_swiglu_of_up_to_32_rows_divides(T, B):
+    """silu(-88) is an ordinary fp32 number (-5.3e-37), but 1 / (1 + e^88) is below the smallest normal one, which an
+    approximate reciprocal flushes to zero: the product with an `up` of 2^110 tells which was used.  Three rows: the
+    GEMM that folds the norm in; five and twenty: one and two row tiles of the narrow one.  128 column blocks, one split."""
+    sh = TI.ModelShape("t", 1, 256, 2, 1, 128, 8192, 512, False)
+    w = TI.make_weights(sh, seed=3, dtype=torch.bfloat16)
+    w["embed"] = torch.ones(sh.vocab, sh.d_model, dtype=torch.bfloat16)
+    lw, f = w["layers"][0], torch.arange(sh.d_ff)
+    for name in ("wo", "w_gate", "w_up", "w_down"):
+        lw[name] = torch.zeros_like(lw[name])
+    lw["w_gate"][f, f % sh.d_model] = -88.0
+    lw["w_up"][f, f % sh.d_model] = 2.0 ** 110
+    d = torch.arange(sh.d_model // 2)
+    lw["w_down"][d, d] = 1024.0
+    h = torch.tensor(-88.0 / (1.0 + math.exp(88.0)) * 2.0 ** 110).to(torch.bfloat16).double()      # -7e-4
+    x = torch.ones(sh.d_model, dtype=torch.float64)
+    x[d] += 1024.0 * h                                                                             # 0.29
+    want = (x / x.pow(2).mean().sqrt()) @ w["lm_head"].double().T
+    eng = T.Engine(sh, w, dtype=T.TIDAR_BF16, max_k=1, max_batch=B, max_seq_len=32)
+    _, lg = eng.ar_step(torch.zeros(B, dtype=torch.int32, device="cuda"), hint=0, want_logits=True)
+    err = float((lg.cpu().double() - want).abs().max())
+    eng.close()
+    assert err < 256 * 1.4 * 2.0 ** -9 * 0.02            # 256 products of |x| <= 1.4, rounded to 8 bits, and |w| ~ 0.02
