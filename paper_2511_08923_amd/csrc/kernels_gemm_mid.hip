@@ -18,7 +18,7 @@ namespace {
 constexpr int PIECE = 528;                        // 16-byte pieces of 32 rows, padded: reads of a row's 8 pieces are conflict-free
 constexpr int phase_of(int tiles) { return tiles < 8 ? tiles : 8; }      // tiles reduced at a time: 4 waves x 4.1 KiB each
 
-template <int RT, int CT, int D, int EPI>
+template <int RT, int CT, int D, bool SWIGLU>
 __global__ __launch_bounds__(256) void gemm_bf16_mid_kernel(const bf16_t *__restrict__ a, const bf16_t *__restrict__ w,
                                                             float *__restrict__ out, int M, int N, int K, int splits,
                                                             int n_pass, int n_tall) {
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_mid_kernel(const bf16_t *__rest
                 for (int x = 1; x < 4; ++x) v += *(const f32x4 *)(s + x * (PHASE * 8 * PIECE));
                 return v;
             };
-            if constexpr (EPI == GEMM_EPI_SWIGLU) {
+            if constexpr (SWIGLU) {
                 // columns 0-15 gate, 16-31 up of the same 16 features: lane (half, row) makes features 8 * half .. +7 of
                 // its row, its 16 bytes of the next GEMM's A fragment
                 bf16x8 h;
@@ -131,15 +131,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_mid_kernel(const bf16_t *__rest
                     const int r = (lane >> 3) + 8 * x, c4 = lane & 7;
                     const int row = (mt_base + i) * 32 + r, col = (tile0 + j) * 32 + 4 * c4;
                     const f32x4 v = piece(c4, r);
-                    if (row < M && col < N)
-                        *(f32x4 *)(o + (EPI == GEMM_EPI_ROWMAJOR ? (size_t)row * N + col : pt_index(col, row, M))) = v;
+                    if (row < M && col < N) *(f32x4 *)(o + pt_index(col, row, M)) = v;
                 }
             }
         }
     }
 }
 
-template <int RT, int CT, int D, int EPI>
+template <int RT, int CT, int D, bool SWIGLU>
 void launch_mid(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, hipStream_t st) {
     constexpr int REDUCE_LDS = 4 * phase_of(RT * CT) * 8 * PIECE;
     const int units = ((N + 31) / 32 + CT - 1) / CT * p.splits, n_tall = (M + 31) / 32 - p.m_chunks * (RT - 1);
@@ -147,32 +146,33 @@ void launch_mid(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int 
     int dev = 0;
     (void)hipGetDevice(&dev);
     if (dev < 0 || dev >= 64 || !attr_set[dev]) {
-        (void)hipFuncSetAttribute((const void *)gemm_bf16_mid_kernel<RT, CT, D, EPI>,
+        (void)hipFuncSetAttribute((const void *)gemm_bf16_mid_kernel<RT, CT, D, SWIGLU>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, REDUCE_LDS);
         if (dev >= 0 && dev < 64) attr_set[dev] = true;
     }
-    gemm_bf16_mid_kernel<RT, CT, D, EPI><<<dim3((units + 7) / 8 * 8 * p.m_chunks), 256, REDUCE_LDS, st>>>(
+    gemm_bf16_mid_kernel<RT, CT, D, SWIGLU><<<dim3((units + 7) / 8 * 8 * p.m_chunks), 256, REDUCE_LDS, st>>>(
         a, w, out, M, N, K, p.splits, p.m_chunks, n_tall);
 }
 
 // ring depth in k steps: as many registers as the accumulators leave, four or eight (the waves' shares of K are usually
 // multiples of eight steps)
-template <int EPI>
+template <bool SWIGLU>
 void launch_mid_rows(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, hipStream_t st) {
-    if (p.mt == 1) launch_mid<1, 2, 8, EPI>(a, w, out, M, N, K, p, st);
-    else if (p.mt == 2) launch_mid<2, 2, 8, EPI>(a, w, out, M, N, K, p, st);
-    else if (p.mt == 3) launch_mid<3, 2, 8, EPI>(a, w, out, M, N, K, p, st);
-    else if (p.mt == 4) launch_mid<4, 2, 8, EPI>(a, w, out, M, N, K, p, st);
-    else if (p.mt == 5) launch_mid<5, 2, 8, EPI>(a, w, out, M, N, K, p, st);
-    else if (p.mt == 6) launch_mid<6, 2, 4, EPI>(a, w, out, M, N, K, p, st);
-    else if (p.mt == 7) launch_mid<7, 2, 4, EPI>(a, w, out, M, N, K, p, st);
-    else launch_mid<8, 2, 4, EPI>(a, w, out, M, N, K, p, st);
+    if (p.mt == 1) launch_mid<1, 2, 8, SWIGLU>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 2) launch_mid<2, 2, 8, SWIGLU>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 3) launch_mid<3, 2, 8, SWIGLU>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 4) launch_mid<4, 2, 8, SWIGLU>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 5) launch_mid<5, 2, 8, SWIGLU>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 6) launch_mid<6, 2, 4, SWIGLU>(a, w, out, M, N, K, p, st);
+    else if (p.mt == 7) launch_mid<7, 2, 4, SWIGLU>(a, w, out, M, N, K, p, st);
+    else launch_mid<8, 2, 4, SWIGLU>(a, w, out, M, N, K, p, st);
 }
 
 }  // namespace
 
-void launch_gemm_bf16_mid(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi,
+// Partial sums in the tiled layout, or (one split) SwiGLU of the interleaved gate/up matrix.
+void launch_gemm_bf16_mid(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, bool swiglu,
                           hipStream_t st) {
-    if (epi == GEMM_EPI_SWIGLU) launch_mid_rows<GEMM_EPI_SWIGLU>(a, w, out, M, N, K, p, st);
-    else launch_mid_rows<GEMM_EPI_TILED>(a, w, out, M, N, K, p, st);
+    if (swiglu) launch_mid_rows<true>(a, w, out, M, N, K, p, st);
+    else launch_mid_rows<false>(a, w, out, M, N, K, p, st);
 }

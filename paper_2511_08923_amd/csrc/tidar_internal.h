@@ -158,15 +158,15 @@ enum KernelClass {
 };
 
 struct GemmPlan {
-    int mt;        // 16-row tiles per workgroup pass
-    int nt;        // 16-column tiles per wave
+    int mt;        // row tiles per wave: of 16 up to 32 rows (narrow kernel), of 32 beyond, there of the higher passes
+    int nt;        // column tiles per wave: two of 16 (narrow kernel), one or two of 32 (kernels_gemm.hip beyond 32 rows)
     int splits;    // split-K factor
     int bk;        // K elements staged per LDS chunk
     int m_chunks;  // passes over M (grid.z)
     int wide;      // the waves side by side, each over all row tiles of the pass (instead of 2 x 2 waves)
     int nw;        // waves per workgroup: 4, or 8 (side by side, one column tile each: two waves per SIMD)
     int rows;      // the many-row kernel (kernels_gemm_rows.hip): m_chunks passes of mt or mt - 1 row tiles of 32
-    int mid;       // kernels_gemm_mid.hip: m_chunks passes of mt or mt - 1 row tiles of 32, nt column tiles of 32
+    int mid;       // kernels_gemm_mid.hip: m_chunks passes of mt or mt - 1 row tiles of 32
     int swz;       // > 0: (row pass, column block) plane dealt to the XCDs in super-tiles of swz x swz workgroups
 };
 
@@ -199,7 +199,7 @@ void launch_gemm_bf16(const bf16_t *a, const bf16_t *w_packed, float *out, int M
 void launch_gemm_bf16_rows(const bf16_t *a, const bf16_t *w_packed, float *out, int M, int N, int K, const GemmPlan &p,
                            int epi, hipStream_t st, const ChooseArgs &ch);
 void launch_gemm_bf16_mid(const bf16_t *a, const bf16_t *w_packed, float *out, int M, int N, int K, const GemmPlan &p,
-                          int epi, hipStream_t st);
+                          bool swiglu, hipStream_t st);
 void launch_gemm_f32(const float *a, const float *w, float *out, int M, int N, int K, int out_row_major,
                      hipStream_t st);
 
