@@ -30,6 +30,36 @@ def products():
     return sorted(out)
 
 
+# Sizes of the GPU tests, (M, N, K), by the kernel they are there for.
+# kernels_gemm_rows: two passes of 8+8, 9+8 and 9+9 row tiles with one, two, three and five chunks of K (fewer than the four
+# LDS buffers, odd counts; an odd 32-column tile, ragged column blocks and rows), passes that differ by one tile, all
+# passes of five, split K, more workgroups than compute units
+MANY_ROWS = [(481, 24560, 32), (513, 24560, 64), (545, 24592, 96), (576, 24560, 160), (600, 5392, 160), (640, 5136, 96),
+             (650, 5136, 608), (864, 5168, 1056), (864, 1536, 1536), (1665, 8208, 288), (2305, 256, 4096)]
+# kernels_gemm_mid: one to eight row tiles per pass with unequal passes, one k step per wave and fewer (K = 32: two of the
+# four waves have none), a share of K that is no multiple of the ring, ragged N, the row counts beyond 480
+K_SPLIT = [(33, 48, 32), (100, 784, 608), (272, 1536, 1536), (300, 1040, 96), (470, 2048, 1536), (480, 528, 288), (481, 272, 32),
+           (513, 784, 96), (545, 528, 64), (576, 1040, 1056), (608, 4112, 160), (650, 304, 608), (768, 1552, 288),
+           (160, 1536, 1536), (420, 5136, 288), (369, 2064, 1056)]
+# kernels_gemm, two row passes of four waves side by side: 1+1, 2+1, 2+2, 3+2, 4+3, 6+5, 7+6 and 8+7 row tiles, ragged N and K
+TWO_PASS = [(33, 2064, 2080), (65, 4096, 2048), (100, 2064, 2080), (160, 4096, 1056), (200, 4096, 2048), (350, 2064, 2080),
+            (416, 2064, 2080), (470, 2064, 2080)]
+# kernels_gemm, one split of many column blocks: 2 x 2 waves, one pass of six tiles, 256-column workgroups of eight waves
+WIDE = [(97, 16400, 160), (160, 24576, 608), (170, 16400, 96), (300, 16400, 160), (420, 24576, 96), (470, 24560, 512)]
+
+
+@pytest.mark.parametrize("sizes,kernel", [(MANY_ROWS, "rows"), (K_SPLIT, "mid"), (TWO_PASS, "two pass"), (WIDE, "wide")])
+def test_sizes_of_the_gpu_tests_reach_the_kernel_they_are_for(sizes, kernel):
+    plan, heights = planner(), set()
+    for M, N, K in sizes:
+        p = plan(M, N, K, False)
+        reached = "rows" if p.rows else "mid" if p.mid else "two pass" if p.wide and p.nw == 4 and p.m_chunks == 2 else "wide"
+        assert reached == kernel, (M, N, K, reached)
+        assert kernel != "wide" or (p.splits == 1 and N >= 128 * 128), (M, N, K)
+        heights.add(p.mt)
+    assert heights >= {"rows": {5, 6, 7, 8, 9}, "mid": set(range(1, 9)), "two pass": {1, 2, 3, 4, 6, 7, 8}, "wide": {2, 3, 5, 6}}[kernel]
+
+
 @pytest.mark.parametrize("N,K", products())
 def test_grouping_of_a_sum_does_not_follow_the_row_count(N, K):
     """33-480 rows: one kernel family (one chain of 32x32x16 MFMAs per split, or the K-splitting waves) and one split count

@@ -47,16 +47,14 @@ def _gemm(T, ctx, a, w):
                                    # row passes: 3 tiles as 2+1, 5 as 3+2, 7 as 4+3, 12 as 6+6; one tile (no row split)
                                    (65, 4096, 2048), (160, 1536, 1536), (200, 4096, 1024), (384, 2048, 4096),
                                    (40, 6144, 1024),
-                                   # two row passes with the waves side by side, one column tile each: passes of
-                                   # 1 (one real row in the second), 2, 6+5, 7+6 and 8+7 tiles, ragged N and K
+                                   # few workgroups, the waves split K: passes of one to three tiles, ragged N and K
                                    (33, 784, 608), (100, 1040, 1056), (350, 528, 288), (416, 784, 608),
                                    (470, 1040, 1056),
-                                   # 512 rows and more: 256 x 256 workgroup tiles (eight row tiles per wave, half-size
-                                   # staging ring), whole and ragged row passes, split K, ragged column block, an
-                                   # odd chunk count (K = 384), and a grid wide enough for the XCD super-tiles
+                                   # 512 rows and more (the narrow ones still split K between waves): whole and ragged
+                                   # row passes, split K, ragged column block, several rounds of workgroups
                                    (512, 1024, 1024), (1000, 4096, 4096), (1025, 784, 608), (2176, 1536, 12288),
                                    (600, 16400, 384), (777, 65536 + 48, 256),
-                                   # six row tiles per pass (17 tiles as 6+6+5, 18 as 6+6+6)
+                                   # 17 tiles of a narrow product, 18 as 6+6+6
                                    (544, 2048, 1024), (576, 6144, 512),
                                    # many rows: the split count follows the number of 256-row passes (3, 2 and 1
                                    # splits where up to 1024 rows take 4)

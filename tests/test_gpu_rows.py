@@ -1,10 +1,13 @@
-"""GPU parity of the many-row GEMM (481 rows and more): pass heights, remainders, and its epilogues against each other."""
+"""GPU parity of the GEMM beyond 32 rows, kernel by kernel (pass heights, remainders, epilogues against each other), and of
+what goes with it: fp32 GEMM and attention, the one-token step of many sequences."""
 import math
+from dataclasses import replace
 
 import pytest
 import torch
 
 import tidar_inputs as TI
+from test_gemm_plan import K_SPLIT, MANY_ROWS, TWO_PASS, WIDE
 from test_gpu_ops import _attention_case, _gemm
 
 pytestmark = pytest.mark.gpu
@@ -17,10 +20,7 @@ def T():
     return T
 
 
-# row tiles as 9+7 .. 9+9 (two passes), 5s and 6s, a last pass that is one tile lower; one chunk of K, an odd count;
-# a ragged column block, an odd 32-column tile, more workgroups than compute units
-@pytest.mark.parametrize("M,N,K", [(481, 272, 32), (513, 784, 96), (545, 528, 64), (576, 1040, 1056), (608, 4112, 160),
-                                   (650, 304, 608), (1665, 8208, 288), (2305, 256, 4096)])
+@pytest.mark.parametrize("M,N,K", MANY_ROWS)
 def test_many_row_gemm_matches_fp64_matmul(T, M, N, K):
     print(f"many-row gemm M={M} N={N} K={K}", flush=True)
     ctx = T.tidar_create(T.make_config(TI.SHAPE_8B.with_layers(1), T.TIDAR_BF16, max_k=16, max_batch=4))
@@ -34,12 +34,14 @@ def test_many_row_gemm_matches_fp64_matmul(T, M, N, K):
     assert float((got.double() - want).abs().max()) < 2e-4 * max(1.0, math.sqrt(K / 256))
 
 
+# the vocabulary GEMM in passes of 6+5.. row tiles (816 rows), of 9+8 (544) and of 8+8 (504), the last column block ragged
+@pytest.mark.parametrize("vocab,B,k", [(2048, 3, 16), (24560, 2, 16), (24560, 7, 8)])
 @pytest.mark.parametrize("sample,beta", [(False, 1.0), (True, 1.0), (True, 0.25)])
-def test_many_row_step_fused_vocabulary_reduction_equals_logits_path(T, sample, beta):
-    """Three sequences at k = 16 are 816 rows: without logits the LM head's epilogue reduces (and perturbs, or copies out
-    for the mix) them in place, with logits they are written and reduced by the row kernel.  Same accumulators, same
-    expressions: the tokens have to be the same."""
-    sh, B, k, P = TI.SMALL_GQA, 3, 16, 40
+def test_many_row_step_fused_vocabulary_reduction_equals_logits_path(T, sample, beta, vocab, B, k):
+    """From 481 rows on: without logits the LM head's epilogue reduces (and perturbs, or copies out for the mix) them in
+    place, with logits they are written and reduced by the row kernel.  Same accumulators, same expressions: the tokens
+    have to be the same."""
+    sh, P = replace(TI.SMALL_GQA, vocab=vocab), 40
     w = TI.make_weights(sh, seed=5, dtype=torch.bfloat16)
     eng = T.Engine(sh, w, dtype=T.TIDAR_BF16, max_k=k, max_batch=B, max_seq_len=160)
     mode = T.make_mode(sample=sample, temperature=1.0, seed=9, beta=beta)
@@ -61,13 +63,8 @@ def test_many_row_step_fused_vocabulary_reduction_equals_logits_path(T, sample, 
     eng.close()
 
 
-# kernels_gemm_mid: two to five and eight row tiles per pass with unequal passes, one k step per wave and fewer (K = 32:
-# two of the four waves have none), a share of K that is no multiple of the ring, ragged N; wide single-split products
-# up to five row tiles and beyond the eight-wave form
-@pytest.mark.parametrize("M,N,K", [(33, 48, 32), (100, 784, 608), (272, 1536, 1536), (300, 1040, 96), (470, 2048, 1536),
-                                   (480, 528, 288), (97, 16400, 160), (160, 24576, 608), (420, 24576, 96), (470, 24560, 512),
-                                   (864, 1536, 1536)])
-def test_k_split_gemm_matches_fp64_matmul(T, M, N, K):
+@pytest.mark.parametrize("M,N,K", K_SPLIT + TWO_PASS + WIDE)
+def test_gemm_of_33_to_768_rows_matches_fp64_matmul(T, M, N, K):
     test_many_row_gemm_matches_fp64_matmul(T, M, N, K)
 
 
