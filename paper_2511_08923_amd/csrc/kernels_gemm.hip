@@ -827,14 +827,19 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
         const int t = (M + 31) / 32;             // 32-row tiles
         if (!force_single_split && (t < 16 ? wgs * splits <= 64 : t <= 24 && wgs * splits <= 40)) {
             // kernels_gemm_mid.hip: the waves of a workgroup split K.  It takes the products whose two row passes
-            // below would fill less than half of the compute units (the small model's QKV and O: 272 x 1536 x 1536 12.2
-            // -> 8.6 us in 3 splits either way; where they fill more it gains nothing alone and loses 10 % inside a
-            // step, where the activations come from other XCDs).  The narrowest keep it up to 768 rows (1536 x 1536 at
-            // 544 / 700 rows: 20.3 / 19.5 us in the many-row kernel, 13.6 / 15.4 here; at N = 2048 20.6 / 20.2 and 19.2 /
-            // 22.3, so the line lies between).  The row limits are class borders (480 rows, a 256-row multiple):
-            // the four waves sum K in four interleaved shares, so inside a class the choice has to be one of (N, K)
-            // alone.  (It is also faster for wide single-split products of up to five row tiles, 72 x 24576 x 4096
-            // 45.2 -> 40.8 us, but not at nine, 68.2 -> 81.5: those stay below whatever the row count.)
+            // below would fill less than half of the compute units.  Measured at 132 / 272 / 430 rows, two passes -> this:
+            // with 24-36 column blocks x splits 7.5 / 11.5 / 15.7 -> 6.4 / 8.4 / 10.5 us (1024 x 2048, 4096 x 512; the small
+            // model's O, 1536 x 1536, in 3 splits either way 7.6 / 11.5 / 16.2 -> 6.6 / 8.8 / 12.8), with 48 (its QKV, 2048 x
+            // 1536; 1536 x 2048, 3072 x 1024) 8.0 / 12.3 / 17.2 -> 8.0 / 11.7 / 15.0, with 64 (2048 x 2048, 4096 x 1024) 8.6 /
+            // 13.7 / 18 -> 8.6 / 13.2 / 16.8; up to 100 rows within 5 % of each other.  Where two passes fill more it
+            // loses 10 % inside a step, where the activations come from other XCDs.
+            // The narrowest keep it up to 768 rows, many-row kernel -> this at 544 / 640 / 768 rows: with 36 (1536 x 1536)
+            // 21.0 / 18.9 / 20.3 -> 13.4 / 15.1 / 14.3, with 40 (2560 x 1024) 21.4 / 19.6 / 20.8 -> 13.8 / 15.9 / 17.6, with 48
+            // (2048 x 1536) 20.0 / 18.7 / 20.4 -> 18.5 / 19.1 / 20.7, with 64 (2048 x 2048) 20.3 / 19.0 / 20.7 -> 22.0 / 23.0 /
+            // 22.9.  The row limits are class borders (480 rows, a 256-row multiple): the four waves sum K in four
+            // interleaved shares, so inside a class the choice has to be one of (N, K) alone.  (It is also faster for
+            // wide single-split products of up to five row tiles, 72 x 24576 x 4096 45.2 -> 40.8 us, but not at nine,
+            // 68.2 -> 81.5: those stay below whatever the row count.)
             // Per workgroup: its fragments at the 27 B per clock that a compute unit takes in from afar, or the
             // matrix cores' rate, plus 4 us of launch, ring fill and reduction; a split also costs the partial
             // sums at 6 TB/s out and 4 TB/s back in.  The split count is the best at nine row tiles in two passes,
