@@ -868,6 +868,9 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
             // row tiles and 256 columns, 7.5 + 1.6 h ns, plus 6 + h of prologue and epilogue), plus the partial sums
             // through the fabric at 6 TB/s out and 4 TB/s back in.  (Predicted / measured: 2048 x 24576 x 4096 292 /
             // 340, 2176 x 4096 x 12288 178 / 165, 1000 x 24576 x 4096 179 / 181, 600 x 24576 x 4096 149 / 146.)
+            // The class begins where a layer as a whole gains over the register-ring kernel that served 512 rows and more
+            // before: 8B shape at 481 / 531 rows QKV 52.9 -> 46.7 / 41.2 -> 45.6 us, O 34.0 -> 29.6 / 27.9 -> 30.1, gate/up
+            // 100.6 -> 103.3 / 141.1 -> 106.7, down 76.2 -> 66.6 / 60.6 -> 63.3.
             // The split count, never above the (N, K) rule's, is taken for whole 256-row multiples: within this
             // class a row's sum is grouped the same way for every row count of the same multiple.
             p.rows = 1;

@@ -340,7 +340,7 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
             gemm(ctx, ws + l.xn, w->wqkv[layer], g_cur, M, q_dim + 2 * kv_dim, c.d_model, false, &S, st);
         }
         // The one-token step of any batch has no RoPE launch: its attention workgroups rotate the new row themselves
-        // (1.5B shape, 6 sequences: attention 9.2 -> 11.2 us, RoPE's 4.6 gone)
+        // (1.5B shape, 6 sequences: attention 9.2 -> 10.9 us, RoPE's 4.6 gone)
         AttnRope rope = {};
         if (c.dtype == TIDAR_BF16 && attention_rope_ok(d, c.n_q_heads / c.n_kv_heads, c.head_dim)) {
             rope.part = g_cur;
