@@ -678,6 +678,8 @@ __global__ void set_i32_kernel(int32_t *p, int n, int32_t v) {
 // 16x16x4 MFMA sums one of them over the four lane groups), and the four sums meet in LDS in wave order: one trip to
 // memory per 128 k instead of four with two barriers each (20 x 128 x 512 44 -> 4.2 us, 272 x 4096 x 4096 617 -> 191).  RT x CT tiles of 16 per
 // workgroup: one by one while that leaves compute units idle, then 2 x 4.
+// (A caller's fp32 buffers may start on any float; a 16-byte load takes any multiple of four bytes, the type says so.)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 template <int RT, int CT>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ a, const float *__restrict__ w,
                                                        float *__restrict__ out, int M, int N, int K,
@@ -701,16 +703,16 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
             const int row = row0 + 16 * i + n;
             const bool ok = row < M && k < K;
             const float *p = a + (ok ? af_index(row, k, lay) : 0);
-            av[i][0] = ok ? *(const f32x4 *)p : zero;
-            av[i][1] = ok ? *(const f32x4 *)(p + 4) : zero;
+            av[i][0] = ok ? *(const f32x4_any *)p : zero;
+            av[i][1] = ok ? *(const f32x4_any *)(p + 4) : zero;
         }
 #pragma unroll
         for (int j = 0; j < CT; ++j) {
             const int col = col0 + 16 * j + n;
             const bool ok = col < N && k < K;
             const float *p = w + (ok ? (size_t)col * K + k : 0);
-            wv[j][0] = ok ? *(const f32x4 *)p : zero;
-            wv[j][1] = ok ? *(const f32x4 *)(p + 4) : zero;
+            wv[j][0] = ok ? *(const f32x4_any *)p : zero;
+            wv[j][1] = ok ? *(const f32x4_any *)(p + 4) : zero;
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e)

@@ -100,6 +100,22 @@ def test_fp32_gemm_matches_fp64_matmul(T, M, N, K):
     assert float(err) < K * 2.0 ** -24 * 0.02 * 16       # K roundings of sums that stay below 16 products of 0.02
 
 
+def test_fp32_gemm_takes_buffers_at_any_float(T):
+    """Packed weights and workspace one float past a 16-byte boundary: the same sums bit for bit."""
+    M, N, K = 20, 80, 72
+    ctx = T.tidar_create(T.make_config(TI.TINY, T.TIDAR_F32, max_k=4, max_batch=1))
+    a, w = TI.make_normal((M, K), seed=1).cuda(), TI.make_normal((N, K), seed=2, std=0.02).cuda()
+    got = []
+    for off in (0, 1):
+        packed = torch.zeros(T.tidar_packed_weight_bytes(T.TIDAR_F32, N, K) // 4 + off, device="cuda")[off:]
+        T.tidar_pack_weight(T.TIDAR_F32, w, packed, N)
+        ws = torch.empty(T.tidar_gemm_workspace_bytes(T.TIDAR_F32, M, N, K) // 4 + off, device="cuda")[off:]
+        got.append(torch.full((M, N), float("nan"), device="cuda"))
+        T.tidar_gemm(ctx, a, packed, got[-1], M, N, K, ws)
+    T.tidar_destroy(ctx)
+    assert torch.equal(got[0], got[1]) and not torch.isnan(got[0]).any()
+
+
 # fp32 attention: head dimensions on both sides of 32 and 64 and one whose rows are no 16-byte pieces, several groups of
 # four units per wave, several mask tiles
 @pytest.mark.parametrize("hd,k,L", [(32, 4, 300), (64, 8, 70), (128, 16, 40), (128, 3, 270), (30, 5, 33), (96, 2, 0)])
