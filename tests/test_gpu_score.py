@@ -1,9 +1,12 @@
 """GPU parity of AR-mode scoring and of the training-layout forward (Section 4.2.2, Section 3.1) through the C ABI."""
+from dataclasses import replace
+
 import pytest
 import torch
 
 import tidar_inputs as TI
 from oracle import tidar_oracle as O
+from test_gemm_plan import planner
 
 pytestmark = pytest.mark.gpu
 
@@ -136,4 +139,22 @@ def test_small_bf16_scores_match_oracle(T, S, bl, chunk):
         want = float(-ar_o.mean())
     assert abs(float(loss[0]) - want) < 5e-3                   # a mean: the per-token errors average out
     assert float(ar_o.std()) > 0.05                            # the scores are not a constant
+    eng.close()
+
+
+@pytest.mark.parametrize("S,heights", [(150, (2, 2, 1)), (210, (2, 2, 2, 1)), (440, (4, 4, 3, 3)), (480, (4, 4, 4, 3)),
+                                       (600, (7, 6, 6))])
+def test_swiglu_epilogue_in_row_passes_of_several_heights(T, S, heights):
+    """Gate/up as one split: up to 480 rows (of 4096 columns) the K-splitting kernel's SwiGLU epilogue, then the many-row
+    kernel's, every pass higher than one row tile somewhere and the last ones lower."""
+    sh = replace(TI.SMALL_GQA, n_layers=1, d_ff=2048 if S <= 480 else 2592)
+    p = planner()(S, 2 * sh.d_ff, sh.d_model, False)
+    assert (bool(p.mid), p.splits, p.mt, p.m_chunks) == (S <= 480, 1, heights[0], len(heights))
+    assert sum(heights) == (S + 31) // 32
+    w = TI.make_weights(sh, seed=3, dtype=torch.bfloat16, std=0.05)
+    eng = T.Engine(sh, w, dtype=T.TIDAR_BF16, max_k=1, max_batch=1, max_seq_len=640)
+    text = TI.make_prompt(sh, S, seed=S)
+    ar, _, _ = eng.score(text)
+    want = O.OracleModel(sh, w, bf16_faithful=True).score([int(t) for t in text[0]])
+    assert float((ar[0, : S - 1].cpu().double() - want).abs().max()) < SCORE_TOL
     eng.close()
