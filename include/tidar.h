@@ -159,7 +159,8 @@ tidar_status tidar_workspace_bytes(const tidar_ctx *ctx, int32_t batch, int32_t 
  * Prefill (paper Section 3.2, Appendix B): encode each prompt causally, append
  * one bidirectional block of k mask tokens, fill the cache with the prompt's
  * K/V and return the first drafts.  Runs in causal chunks through the same
- * kernels as the step; untuned.
+ * kernels as the step; prompts that are no longer than a chunk go through one
+ * pass together as far as a chunk's rows and the workspace reach.
  *   prompt      dev int32 [batch][prompt_stride]
  *   prompt_len  host int32 [batch], each >= 1
  *   prefix_len  dev int32 [batch] out: set to prompt_len

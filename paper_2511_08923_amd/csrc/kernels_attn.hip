@@ -225,8 +225,8 @@ __device__ inline bool attn_block_fixed_ref(const bf16_t *k_lds, const bf16_t *v
 }
 
 // QT: 32-row query tiles per wave.
-template <int QT, bool PRIO, bool ROPE>
-__global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a) {
+template <int QT, bool PRIO, bool ROPE, class SG>
+__global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a, SG sg) {
     constexpr int NBUF = 3, K_TILE = TILE, V_TILE = TILE;
     __shared__ __attribute__((aligned(16))) bf16_t k_lds[NBUF][K_TILE];
     __shared__ __attribute__((aligned(16))) bf16_t v_lds[NBUF][V_TILE];
@@ -256,7 +256,13 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a) {
     const int g = grp % a.kv.n_kv;
     const int b = grp / a.kv.n_kv;
     const int split = blockIdx.y;
-    const RowDesc d = a.d;
+    int row_base;                                    // the sequence's first row of the forward
+    const RowDesc d = seq_desc(a.d, sg, b, &row_base);
+    const int F = a.group * d.R;                     // flattened query rows of this kv head
+    const int TQ = (F + 31) >> 5;
+    const int t0 = chunk * a.tiles_per_chunk;
+    if (kSegs<SG> && t0 >= TQ) return;                            // a shorter sequence than the longest (whole workgroup)
+    const int t1 = min(TQ, t0 + a.tiles_per_chunk);
     const int L = clamp_prefix(a.kv, a.prefix_len[d.seq_base + b], d.nc);   // never walks past the page table
     const int n_mask = d.nm;
     const int n_cache_units = (L + d.nc + 15) >> 4;
@@ -271,10 +277,6 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a) {
     const int per = a.per;
     const int it0 = min(n_it, split * per);
     const int it1 = (split == a.splits - 1) ? n_it : min(n_it, it0 + per);
-    const int F = a.group * d.R;                     // flattened query rows of this kv head
-    const int TQ = (F + 31) >> 5;
-    const int t0 = chunk * a.tiles_per_chunk;
-    const int t1 = min(TQ, t0 + a.tiles_per_chunk);
     // Key-pair iterations this workgroup can need at all: cache units up to the furthest key any of its rows
     // sees, then the mask units of its rows' own blocks.  (Rows of one query head only; a workgroup that straddles
     // two heads keeps the whole range.)  Inside a prefill or scoring pass most of the range falls away: causal
@@ -411,7 +413,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a) {
         r_blk[i] = ok ? ri.blk : -2;
         if (ok) vis_min = min(vis_min, ri.vis);
         const bf16_t *qp = ROPE ? q_lds + (ok ? f : 0) * HD + 8 * lh
-                                : a.q + (((size_t)b * d.R + r) * a.n_q + (g * a.group + hq)) * HD + 8 * lh;
+                                : a.q + ((size_t)(row_base + r) * a.n_q + (g * a.group + hq)) * HD + 8 * lh;
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
             bf16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -648,7 +650,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a) {
             if (f >= F) continue;
             const float inv = 1.f / l;
             const int hq = f / d.R, r = f - hq * d.R;
-            const int row = b * d.R + r, col0 = (g * a.group + hq) * HD + 4 * lh;
+            const int row = row_base + r, col0 = (g * a.group + hq) * HD + 4 * lh;
             typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt)
@@ -665,7 +667,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a) {
     }
 
     // ---- write this split's partial (unnormalised O, reference in log2 units, denominator)
-    const size_t pbase = (((size_t)b * a.kv.n_kv + g) * a.splits + split) * F;
+    const size_t pbase = (size_t)row_base * a.n_q * a.splits + ((size_t)g * a.splits + split) * F;
 #pragma unroll
     for (int i = 0; i < QT; ++i) {
         const int tile = t0 + wave + 4 * i;
@@ -695,22 +697,25 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a) {
 // split keeps an integral reference.  One wave per (row, head): lane = (8-value head-dim chunk, one of 4 split
 // lanes); the split lanes share the splits between them and are folded with two shuffles.  The 16-byte result
 // goes out row-major or in the A-fragment layout of the O projection's input.
+template <class SG>
 __global__ __launch_bounds__(64) void attn_combine_kernel(const float *__restrict__ opart,
                                                           const float *__restrict__ mpart,
-                                                          const float *__restrict__ lpart, int R, int n_q, int n_kv,
-                                                          int splits, bf16_t *__restrict__ out, int out_af,
+                                                          const float *__restrict__ lpart, RowDesc d, SG sg, int n_q,
+                                                          int n_kv, int splits, bf16_t *__restrict__ out, int out_af,
                                                           ActLayout lay) {
-    const int row = blockIdx.x;                 // b * R + r
+    const int row = blockIdx.x;
     const int head = blockIdx.y;
-    const int b = row / R, r = row - b * R;
+    const int b = seq_of_row(d, sg, row);
+    int row_base;
+    const int R = seq_desc(d, sg, b, &row_base).R, r = row - row_base;
     const int group = n_q / n_kv;
     const int F = group * R;
     const int g = head / group, hq = head - g * group;
     const int f = hq * R + r;
     const int lane = threadIdx.x, d0 = 8 * (lane & 15), sl = lane >> 4;
-    const size_t base = ((size_t)b * n_kv + g) * splits;
+    const size_t base = (size_t)row_base * n_q * splits + (size_t)g * splits * F + f;      // partial result of split 0
     // reference of the whole row: lane s reads split s's (there are at most 64 splits), then a wave-wide maximum
-    float mmax = lane < splits ? mpart[(base + lane) * F + f] : -INFINITY;
+    float mmax = lane < splits ? mpart[base + (size_t)lane * F] : -INFINITY;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) mmax = fmaxf(mmax, __shfl_xor(mmax, o));
     float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, den = 0.f;
@@ -722,7 +727,7 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(const float *__restric
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int sp = sp0 + 4 * j;
-            const size_t pi = (base + min(sp, splits - 1)) * F + f;
+            const size_t pi = base + (size_t)min(sp, splits - 1) * F;
             m[j] = mpart[pi];
             l[j] = lpart[pi];
             const float *op = opart + pi * HD + d0;
@@ -758,12 +763,18 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(const float *__restric
 
 }  // namespace
 
-AttnPlan plan_attention(int B, int n_kv, int group, int R, int nc, int max_keys) {
+AttnPlan plan_attention(int B, int n_kv, int group, const RowDesc &d, const Segs &sg, int max_keys) {
     AttnPlan p;
-    int TQ = (group * R + 31) / 32;           // 32-row query tiles per kv head
+    const int nc = d.nc;
+    int TQ = (group * d.R + 31) / 32;         // 32-row query tiles per kv head (of the longest sequence)
     p.tiles_per_chunk = TQ < 4 ? TQ : 4;      // four waves x one query tile each
     p.n_chunks = (TQ + p.tiles_per_chunk - 1) / p.tiles_per_chunk;
     int base = B * n_kv * p.n_chunks;
+    if (sg.n) {                               // sequences of different length: the workgroups that have rows
+        base = 0;
+        for (int b = 0; b < sg.n; ++b)
+            base += n_kv * (((group * (sg.row0[b + 1] - sg.row0[b]) + 31) / 32 + p.tiles_per_chunk - 1) / p.tiles_per_chunk);
+    }
     // the caller's bound is taken in steps of 256 keys: bounds that differ by less cut the keys alike, so results do
     // not change bit for bit because a caller's estimate of the final length moved a little
     max_keys = (max_keys + 255) & ~255;
@@ -808,20 +819,17 @@ bool attention_rope_ok(RowDesc d, int group, int hd) {
     return d.R == 1 && d.nc == 1 && d.nm == 0 && group >= 1 && group <= 32 && hd == HD;
 }
 
-size_t attn_partial_floats(int B, int n_kv, int group, int R, int hd, int splits) {
-    return (size_t)B * n_kv * splits * group * R * (hd + 2);
-}
-
 void launch_attention_bf16(const bf16_t *q, KvView kv, const bf16_t *k_scr, const bf16_t *v_scr,
-                           const int32_t *prefix_len, RowDesc d, int B, int n_q, const AttnPlan &p, float *part,
-                           bf16_t *out, int out_af, hipStream_t st, const AttnRope *rope) {
+                           const int32_t *prefix_len, const RowDesc &d, const Segs &sg, int B, int M, int n_q,
+                           const AttnPlan &p, float *part, bf16_t *out, int out_af, hipStream_t st,
+                           const AttnRope *rope) {
     AttnArgs a;
     a.rp = AttnRope{};
     const bool fused_rope = rope && rope->part && attention_rope_ok(d, n_q / kv.n_kv, kv.hd);
     if (fused_rope) a.rp = *rope;
     a.out = out;
     a.out_af = out_af;
-    a.lay = act_layout(B * d.R);
+    a.lay = act_layout(M);
     a.q = q;
     a.kv = kv;
     a.k_scr = k_scr;
@@ -835,8 +843,7 @@ void launch_attention_bf16(const bf16_t *q, KvView kv, const bf16_t *k_scr, cons
     a.splits = p.splits;
     a.per = p.per;
     a.scale_log2e = 1.4426950408889634f / sqrtf((float)kv.hd);
-    size_t F = (size_t)a.group * d.R;
-    size_t rows = (size_t)B * kv.n_kv * p.splits * F;
+    size_t rows = (size_t)M * n_q * p.splits;
     a.opart = part;
     a.mpart = part + rows * HD;
     a.lpart = a.mpart + rows;
@@ -844,16 +851,23 @@ void launch_attention_bf16(const bf16_t *q, KvView kv, const bf16_t *k_scr, cons
     a.xcd_q = a.n_groups % 8 == 0 ? 1 : (a.n_groups < 8 && 8 % a.n_groups == 0) ? 8 / a.n_groups : 0;
     dim3 grid(a.n_groups * p.n_chunks, p.splits);
     if (a.xcd_q > 1) grid.x = 8 * ((p.n_chunks + a.xcd_q - 1) / a.xcd_q);
-    if (fused_rope) attn_bf16_kernel<1, false, true><<<grid, 256, 0, st>>>(a);
-    else if (p.tiles_per_chunk == 4) attn_bf16_kernel<1, true, false><<<grid, 256, 0, st>>>(a);
-    else attn_bf16_kernel<1, false, false><<<grid, 256, 0, st>>>(a);
+    auto go = [&](auto kernel, auto segs) { kernel<<<grid, 256, 0, st>>>(a, segs); };
+    const NoSegs none;
+    if (fused_rope) go(attn_bf16_kernel<1, false, true, NoSegs>, none);
+    else if (sg.n && p.tiles_per_chunk == 4) go(attn_bf16_kernel<1, true, false, Segs>, sg);
+    else if (sg.n) go(attn_bf16_kernel<1, false, false, Segs>, sg);
+    else if (p.tiles_per_chunk == 4) go(attn_bf16_kernel<1, true, false, NoSegs>, none);
+    else go(attn_bf16_kernel<1, false, false, NoSegs>, none);
 }
 
-void launch_attention_combine(const float *part, int B, int R, int n_q, int n_kv, int hd, int splits, bf16_t *out,
-                              int out_af, hipStream_t st) {
+void launch_attention_combine(const float *part, const RowDesc &d, const Segs &sg, int M, int n_q, int n_kv, int hd,
+                              int splits, bf16_t *out, int out_af, hipStream_t st) {
     if (splits == 1) return;                  // the attention kernel has written the result itself
-    size_t F = (size_t)(n_q / n_kv) * R;
-    size_t rows = (size_t)B * n_kv * splits * F;
-    attn_combine_kernel<<<dim3(B * R, n_q), 64, 0, st>>>(part, part + rows * hd, part + rows * hd + rows, R, n_q, n_kv,
-                                                         splits, out, out_af, act_layout(B * R));
+    size_t rows = (size_t)M * n_q * splits;
+    auto go = [&](auto segs) {
+        attn_combine_kernel<<<dim3(M, n_q), 64, 0, st>>>(part, part + rows * hd, part + rows * hd + rows, d, segs, n_q, n_kv,
+                                                         splits, out, out_af, act_layout(M));
+    };
+    if (sg.n) go(sg);
+    else go(NoSegs());
 }

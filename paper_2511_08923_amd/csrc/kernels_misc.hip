@@ -65,20 +65,25 @@ __global__ void pack_f32_kernel(const float *__restrict__ src, int rows, int K, 
 }
 
 // ------------------------------------------------------------------ row assembly + embedding gather (+ RoPE table)
-template <typename T>
+template <typename T, class SG>
 __global__ void embed_rows_kernel(const T *__restrict__ embed, const int32_t *__restrict__ tokens, int tok_stride,
-                                  const int32_t *__restrict__ prefix_len, RowDesc d, int d_model, int mask_id,
-                                  int vocab, KvView kv, int hd, float rope_base, float *__restrict__ x,
-                                  int32_t *__restrict__ pos_out, float *__restrict__ rope_cs) {
-    int row = blockIdx.x;                 // b * R + r
-    int b = row / d.R;
-    int r = row - b * d.R;
+                                  const int32_t *__restrict__ prefix_len, RowDesc d_any, SG sg, int d_model,
+                                  int mask_id, int vocab, KvView kv, int hd, float rope_base, float *__restrict__ x,
+                                  int32_t *__restrict__ pos_out, int n_head, float *__restrict__ rope_cs) {
+    int row = blockIdx.x;
+    int b = seq_of_row(d_any, sg, row), row_base;
+    const RowDesc d = seq_desc(d_any, sg, b, &row_base);
+    int r = row - row_base;
     int L = clamp_prefix(kv, prefix_len[d.seq_base + b], d.nc);
     RowInfo ri = row_info(d, r, L);
     int tok = (r < d.nc) ? tokens[(size_t)b * tok_stride + r] : mask_id;
     if ((unsigned)tok >= (unsigned)vocab) tok = mask_id;      // an id outside the table is never dereferenced (the
                                                               // kernel that finishes the call reports it)
-    if (threadIdx.x == 0) pos_out[row] = ri.pos;
+    // sequences of different row counts: the n_head rows of each that go through the LM head, one after the other
+    if (threadIdx.x == 0) {
+        if (!kSegs<SG>) pos_out[row] = ri.pos;
+        else if (r >= d.R - n_head) pos_out[b * n_head + r - (d.R - n_head)] = ri.pos;
+    }
     const T *e = embed + (size_t)tok * d_model;
     float *xo = x + (size_t)row * d_model;
     for (int c = threadIdx.x; c < d_model; c += blockDim.x) xo[c] = to_f<T>(e[c]);
@@ -96,15 +101,15 @@ __global__ void embed_rows_kernel(const T *__restrict__ embed, const int32_t *__
 
 // ------------------------------------------------------------------ residual add (split-K partials) + RMSNorm
 // One block per output row.  part: tiled GEMM output over M_all rows; out: A-fragment layout over the selected rows.
-template <typename T>
+template <typename T, class SG>
 __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *__restrict__ x, const float *__restrict__ part, int S,
                                                       size_t split_stride, const T *__restrict__ gain, float eps,
-                                                      int R, int row0, int d_model, int M_all, T *__restrict__ out,
-                                                      ActLayout lay) {
-    const int Rh = R - row0;
-    const int b = blockIdx.x / Rh;
-    const int o = blockIdx.x - b * Rh;
-    const int row = b * R + row0 + o;
+                                                      int n_rows, int R, SG sg, int d_model, int M_all,
+                                                      T *__restrict__ out, ActLayout lay) {
+    const int b = blockIdx.x / n_rows;
+    const int o = blockIdx.x - b * n_rows;
+    int row = (b + 1) * R - n_rows + o;
+    if constexpr (kSegs<SG>) row = sg.row0[b + 1] - n_rows + o;
     float *xr = x + (size_t)row * d_model;
     float ss = 0.f;
     for (int c = 4 * threadIdx.x; c < d_model; c += 4 * blockDim.x) {
@@ -153,19 +158,19 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *__restrict__ x, co
 // qkv_part: tiled GEMM output, [S] x (q_dim + 2 kv_dim) columns.  Q rows -> q_out [M][q_dim];
 // K/V of causal rows -> cache at position L + r; K/V of mask rows -> scratch tiles
 // k_scr [B][n_kv][n_mtiles][16][hd], v_scr [B][n_kv][n_mtiles][hd][16].
-template <typename T>
+template <typename T, class SG>
 __global__ __launch_bounds__(256) void rope_kv_kernel(const float *__restrict__ part, int S, size_t split_stride,
                                                       const float *__restrict__ rope_cs,
-                                                      const int32_t *__restrict__ prefix_len, RowDesc d, int n_q,
-                                                      int M_all, KvView kv, T *__restrict__ q_out,
+                                                      const int32_t *__restrict__ prefix_len, RowDesc d_any, SG sg,
+                                                      int n_q, int M_all, KvView kv, T *__restrict__ q_out,
                                                       T *__restrict__ k_scr, T *__restrict__ v_scr) {
     const int hd = kv.hd, half = hd / 2, n_kv = kv.n_kv;
     const int q_dim = n_q * hd, kv_dim = n_kv * hd;
     if ((int)blockIdx.x >= M_all) {
         // item = (kv head, d, quarter of the tile's 16 keys): four keys gathered, 8 bytes (bf16) written; the four
         // quarters of a d are neighbouring lanes, so a wave still writes one contiguous run
-        const int n_ct = (d.nc + 15) / 16 + 1;           // cache pages the causal rows can touch
-        const int n_mtiles = (d.nm + 15) / 16;
+        const int n_ct = (d_any.nc + 15) / 16 + 1;       // cache pages the causal rows (of the longest sequence) can touch
+        const int n_mtiles = (d_any.nm + 15) / 16;
         const int items = n_kv * hd * 4;
         const int per_blk = gridDim.y * blockDim.x;
         const int parts = (items + per_blk - 1) / per_blk;
@@ -173,6 +178,8 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(const float *__restrict__ 
         const int part_i = vb % parts;
         vb /= parts;
         const int b = vb / (n_ct + n_mtiles), t = vb - b * (n_ct + n_mtiles);
+        int row_base;
+        const RowDesc d = seq_desc(d_any, sg, b, &row_base);
         const int idx = (part_i * gridDim.y + blockIdx.y) * blockDim.x + threadIdx.x;
         if (idx >= items) return;
         const int L_raw = prefix_len[d.seq_base + b];
@@ -217,7 +224,7 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(const float *__restrict__ 
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int s = min(max(s0 + e, lo), hi - 1);       // clamped: an existing row, value unused if outside
-            pp[e] = part + pt_index(q_dim + kv_dim + h * hd + dd, b * d.R + r0 + s, M_all);
+            pp[e] = part + pt_index(q_dim + kv_dim + h * hd + dd, row_base + r0 + s, M_all);
         }
 #pragma unroll 4
         for (int sp = 0; sp < S; ++sp) {
@@ -232,8 +239,10 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(const float *__restrict__ 
         return;
     }
     const int row = blockIdx.x;
-    const int b = row / d.R;
-    const int r = row - b * d.R;
+    const int b = seq_of_row(d_any, sg, row);
+    int row_base;
+    const RowDesc d = seq_desc(d_any, sg, b, &row_base);
+    const int r = row - row_base;
     const int per_head = half / 4;                   // groups of four rotation pairs
     const float *cs = rope_cs + (size_t)row * half * 2;
     auto val4 = [&](int col) {
@@ -571,11 +580,14 @@ __global__ __launch_bounds__(64) void finish_ar_kernel(const int32_t *__restrict
 // token id outside the vocabulary or met a page id outside the pool marks the sequence: prefix_len = -1, which
 // keeps every later pass from storing anything for it, and first_drafts = -1.
 __global__ __launch_bounds__(64) void finish_prefill_kernel(const int32_t *__restrict__ y,
-                                                            const int32_t *__restrict__ tokens, int k, int seq,
-                                                            int add_len, int last, int vocab, KvView kv,
-                                                            int32_t *__restrict__ prefix_len,
+                                                            const int32_t *__restrict__ tokens, int tok_stride, int k,
+                                                            int seq0, Segs sg, int add_len, int last, int vocab,
+                                                            KvView kv, int32_t *__restrict__ prefix_len,
                                                             int32_t *__restrict__ first_drafts) {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x, seq = seq0 + blockIdx.x;
+    y += (size_t)blockIdx.x * (1 + k);
+    tokens += (size_t)blockIdx.x * tok_stride;
+    if (sg.n) add_len = sg.row0[blockIdx.x + 1] - sg.row0[blockIdx.x] - k;
     const int L = prefix_len[seq];
     bool bad = !seq_fits(kv, L, add_len);
     if (!bad) {
@@ -743,14 +755,18 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
 // group of units and are folded at the end.  What bounds it is latency: page id, K row, V piece, three dependent
 // trips per 64 keys (they used to be two per key: 22 -> 5.4 us at 20 rows, 64 cached tokens).
 // VEC: rows of K are whole, aligned 16-byte pieces and the pages start on 16 bytes.
-template <bool VEC>
+template <bool VEC, class SG>
 __global__ __launch_bounds__(256) void attention_f32_kernel(const float *__restrict__ q, KvView kv,
                                                             const float *__restrict__ k_scr,
                                                             const float *__restrict__ v_scr,
-                                                            const int32_t *__restrict__ prefix_len, RowDesc d, int n_q,
-                                                            float *__restrict__ out, int out_af, ActLayout lay) {
-    const int row = blockIdx.x, head = blockIdx.y;                 // row = b * R + r
-    const int b = row / d.R, r = row - b * d.R;
+                                                            const int32_t *__restrict__ prefix_len, RowDesc d_any,
+                                                            SG sg, int n_q, float *__restrict__ out, int out_af,
+                                                            ActLayout lay) {
+    const int row = blockIdx.x, head = blockIdx.y;
+    const int b = seq_of_row(d_any, sg, row);
+    int row_base;
+    const RowDesc d = seq_desc(d_any, sg, b, &row_base);
+    const int r = row - row_base;
     const int hd = kv.hd, n_kv = kv.n_kv, g = head / (n_q / n_kv);
     const int L = clamp_prefix(kv, prefix_len[d.seq_base + b], d.nc);
     const RowInfo ri = row_info(d, r, L);
@@ -891,24 +907,25 @@ void launch_pack_weight(int dtype, const void *src, int rows, int cols, void *ds
 }
 
 void launch_embed_rows(int dtype, const void *embed, const int32_t *tokens, int tok_stride, const int32_t *prefix_len,
-                       RowDesc d, int B, int d_model, int mask_id, int vocab, KvView kv, float rope_base, float *x,
-                       int32_t *pos_out, float *rope_cs, hipStream_t st) {
-    int rows = B * d.R;
-    if (dtype == TIDAR_BF16)
-        embed_rows_kernel<bf16_t><<<rows, 256, 0, st>>>((const bf16_t *)embed, tokens, tok_stride, prefix_len, d,
-                                                         d_model, mask_id, vocab, kv, kv.hd, rope_base, x, pos_out,
-                                                         rope_cs);
-    else
-        embed_rows_kernel<float><<<rows, 256, 0, st>>>((const float *)embed, tokens, tok_stride, prefix_len, d,
-                                                        d_model, mask_id, vocab, kv, kv.hd, rope_base, x, pos_out,
-                                                        rope_cs);
+                       const RowDesc &d, const Segs &sg, int M, int d_model, int mask_id, int vocab, KvView kv,
+                       float rope_base, float *x, int32_t *pos_out, int n_head, float *rope_cs, hipStream_t st) {
+    auto go = [&](auto table, auto segs) {
+        embed_rows_kernel<<<M, 256, 0, st>>>(table, tokens, tok_stride, prefix_len, d, segs, d_model, mask_id, vocab, kv,
+                                             kv.hd, rope_base, x, pos_out, n_head, rope_cs);
+    };
+    auto typed = [&](auto table) {
+        if (sg.n) go(table, sg);
+        else go(table, NoSegs());
+    };
+    if (dtype == TIDAR_BF16) typed((const bf16_t *)embed);
+    else typed((const float *)embed);
 }
 
-void launch_rmsnorm(int dtype, float *x, const float *part, int S, const void *gain, float eps, int B, int R, int row0,
-                    int d_model, void *out, hipStream_t st) {
-    int rows = B * (R - row0), M_all = B * R;
+void launch_rmsnorm(int dtype, float *x, const float *part, int S, const void *gain, float eps, int B, int n_rows, int M,
+                    const Segs &sg, int d_model, void *out, hipStream_t st) {
+    int rows = B * n_rows, R = M / B;
     ActLayout mt_out = act_layout(rows);
-    size_t stride = pt_split_stride(M_all, d_model);
+    size_t stride = pt_split_stride(M, d_model);
     // a row is one workgroup's only work: with few rows the chip is empty anyway, so a row gets as many threads
     // as it has 4-column pieces (all of its loads in flight at once); with many rows the count measured no difference
     int threads = 256;
@@ -916,12 +933,15 @@ void launch_rmsnorm(int dtype, float *x, const float *part, int S, const void *g
         threads = ((d_model / 4 + 63) / 64) * 64;
         threads = threads > 1024 ? 1024 : threads < 64 ? 64 : threads;
     }
-    if (dtype == TIDAR_BF16)
-        rmsnorm_kernel<bf16_t><<<rows, threads, 0, st>>>(x, part, S, stride, (const bf16_t *)gain, eps, R, row0,
-                                                          d_model, M_all, (bf16_t *)out, mt_out);
-    else
-        rmsnorm_kernel<float><<<rows, threads, 0, st>>>(x, part, S, stride, (const float *)gain, eps, R, row0, d_model,
-                                                         M_all, (float *)out, mt_out);
+    auto go = [&](auto g, auto o, auto segs) {
+        rmsnorm_kernel<<<rows, threads, 0, st>>>(x, part, S, stride, g, eps, n_rows, R, segs, d_model, M, o, mt_out);
+    };
+    auto typed = [&](auto g, auto o) {
+        if (sg.n) go(g, o, sg);
+        else go(g, o, NoSegs());
+    };
+    if (dtype == TIDAR_BF16) typed((const bf16_t *)gain, (bf16_t *)out);
+    else typed((const float *)gain, (float *)out);
 }
 
 void launch_gemm_f32(const float *a, const float *w, float *out, int M, int N, int K, int out_row_major,
@@ -946,21 +966,26 @@ void launch_untile_sum(const float *part, int S, int M, int N, float *out, hipSt
     untile_sum_kernel<<<grid_for((size_t)M * N, 256, 8192), 256, 0, st>>>(part, S, M, N, out);
 }
 
-void launch_rope_kv(int dtype, const float *qkv_part, int S, const float *rope_cs, const int32_t *prefix_len, RowDesc d,
-                    int B, int n_q, KvView kv, void *q_out, void *k_scr, void *v_scr, hipStream_t st) {
-    int rows = B * d.R;
+void launch_rope_kv(int dtype, const float *qkv_part, int S, const float *rope_cs, const int32_t *prefix_len,
+                    const RowDesc &d, const Segs &sg, int B, int rows, int n_q, KvView kv, void *q_out, void *k_scr,
+                    void *v_scr, hipStream_t st) {
     size_t stride = pt_split_stride(rows, (n_q + 2 * kv.n_kv) * kv.hd);
     const int per_head = kv.hd / 8;                  // items (four rotation pairs) per head
     const int gy = (n_q * per_head + 255) / 256 + (kv.n_kv * per_head + 255) / 256;
     const int v_parts = (kv.n_kv * kv.hd * 4 + gy * 256 - 1) / (gy * 256);      // see the kernel's V-tile branch
     const int v_tiles = B * ((d.nc + 15) / 16 + 1 + (d.nm + 15) / 16);
     dim3 grid(rows + v_tiles * v_parts, gy);
-    if (dtype == TIDAR_BF16)
-        rope_kv_kernel<bf16_t><<<grid, 256, 0, st>>>(qkv_part, S, stride, rope_cs, prefix_len, d, n_q, rows, kv,
-                                                      (bf16_t *)q_out, (bf16_t *)k_scr, (bf16_t *)v_scr);
-    else
-        rope_kv_kernel<float><<<grid, 256, 0, st>>>(qkv_part, S, stride, rope_cs, prefix_len, d, n_q, rows, kv,
-                                                     (float *)q_out, (float *)k_scr, (float *)v_scr);
+    auto go = [&](auto q, auto segs) {
+        typedef decltype(q) out_t;
+        rope_kv_kernel<<<grid, 256, 0, st>>>(qkv_part, S, stride, rope_cs, prefix_len, d, segs, n_q, rows, kv, q, (out_t)k_scr,
+                                             (out_t)v_scr);
+    };
+    auto typed = [&](auto q) {
+        if (sg.n) go(q, sg);
+        else go(q, NoSegs());
+    };
+    if (dtype == TIDAR_BF16) typed((bf16_t *)q_out);
+    else typed((float *)q_out);
 }
 
 void launch_place_kv(int dtype, const void *k_new, const void *v_new, const int32_t *prefix_len, RowDesc d, int B,
@@ -975,16 +1000,17 @@ void launch_place_kv(int dtype, const void *k_new, const void *v_new, const int3
 }
 
 void launch_attention_f32(const float *q, KvView kv, const float *k_scr, const float *v_scr,
-                          const int32_t *prefix_len, RowDesc d, int B, int n_q, float *out, int out_af,
-                          hipStream_t st) {
-    dim3 grid(B * d.R, n_q);
+                          const int32_t *prefix_len, const RowDesc &d, const Segs &sg, int M, int n_q, float *out,
+                          int out_af, hipStream_t st) {
+    dim3 grid(M, n_q);
     const bool vec = kv.hd % 4 == 0 && (((uintptr_t)kv.k_pages | (uintptr_t)kv.v_pages | (uintptr_t)k_scr | (uintptr_t)v_scr) & 15) == 0;
-    if (vec)
-        attention_f32_kernel<true><<<grid, 256, 0, st>>>(q, kv, k_scr, v_scr, prefix_len, d, n_q, out, out_af,
-                                                          act_layout(B * d.R));
-    else
-        attention_f32_kernel<false><<<grid, 256, 0, st>>>(q, kv, k_scr, v_scr, prefix_len, d, n_q, out, out_af,
-                                                           act_layout(B * d.R));
+    auto go = [&](auto kernel, auto segs) {
+        kernel<<<grid, 256, 0, st>>>(q, kv, k_scr, v_scr, prefix_len, d, segs, n_q, out, out_af, act_layout(M));
+    };
+    if (vec && sg.n) go(attention_f32_kernel<true, Segs>, sg);
+    else if (vec) go(attention_f32_kernel<true, NoSegs>, NoSegs());
+    else if (sg.n) go(attention_f32_kernel<false, Segs>, sg);
+    else go(attention_f32_kernel<false, NoSegs>, NoSegs());
 }
 
 void launch_swiglu(int dtype, const float *part, int S, int M, int d_ff, void *out, hipStream_t st) {
@@ -1038,9 +1064,11 @@ void launch_finish_ar(const int32_t *y, const int32_t *token_in, int B, int voca
     finish_ar_kernel<<<(B + 63) / 64, 64, 0, st>>>(y, token_in, B, vocab, kv, prefix_len, token_out);
 }
 
-void launch_finish_prefill(const int32_t *y, const int32_t *tokens, int k, int seq, int add_len, int last, int vocab,
-                           KvView kv, int32_t *prefix_len, int32_t *first_drafts, hipStream_t st) {
-    finish_prefill_kernel<<<1, 64, 0, st>>>(y, tokens, k, seq, add_len, last, vocab, kv, prefix_len, first_drafts);
+void launch_finish_prefill(const int32_t *y, const int32_t *tokens, int tok_stride, int k, int seq, int B, const Segs &sg,
+                           int add_len, int last, int vocab, KvView kv, int32_t *prefix_len, int32_t *first_drafts,
+                           hipStream_t st) {
+    finish_prefill_kernel<<<B, 64, 0, st>>>(y, tokens, tok_stride, k, seq, sg, add_len, last, vocab, kv, prefix_len,
+                                            first_drafts);
 }
 
 void launch_set_i32(int32_t *p, int n, int32_t v, hipStream_t st) {

@@ -47,6 +47,41 @@ __host__ __device__ inline RowInfo row_info(const RowDesc &d, int r, int L) {
     return ri;
 }
 
+// Several sequences of different row counts in one forward (the last passes of several prompts, see tidar_prefill):
+// sequence b's rows are [row0[b], row0[b + 1]) of the forward's rows, all of them causal but the last nm, which are one
+// mask block behind them (RowDesc then holds the longest sequence).  n == 0: all sequences have the same rows, d.R each.
+constexpr int kMaxSegs = 32;
+struct Segs {
+    int n;
+    int row0[kMaxSegs + 1];
+};
+// (Kernels have the table's type as a template parameter: looked up at run time, the test for it and the trips to the
+// kernel arguments behind it made an attention launch of 42 us one longer.)
+struct NoSegs {};
+template <class S> constexpr bool kSegs = sizeof(S) == sizeof(Segs);
+template <class S>
+__device__ inline RowDesc seq_desc(const RowDesc &d, const S &s, int b, int *row_base) {
+    RowDesc e = d;
+    *row_base = b * d.R;
+    if constexpr (kSegs<S>) {
+        *row_base = s.row0[b];
+        e.R = s.row0[b + 1] - s.row0[b];
+        e.nc = e.R - e.nm;
+        e.cond0 = e.nc;
+    }
+    return e;
+}
+template <class S>
+__device__ inline int seq_of_row(const RowDesc &d, const S &s, int row) {
+    if constexpr (kSegs<S>) {
+        int b = 0;
+        while (b + 1 < s.n && row >= s.row0[b + 1]) ++b;
+        return b;
+    } else {
+        return row / d.R;
+    }
+}
+
 // Activation layout of every GEMM input: the register image of the MFMA A operand, so that the slice a
 // workgroup stages for a chunk of K is one contiguous block.  Two forms, chosen by the row count M:
 //   M <= 32 ("narrow", 16x16x32 MFMA): [k step of 32][16-row tile][lane][8], lane = (k/8 % 4) * 16 + row % 16
@@ -177,13 +212,13 @@ void launch_pack_weight(int dtype, const void *src, int rows, int cols, void *ds
                         int tile_stride, hipStream_t st);
 
 void launch_embed_rows(int dtype, const void *embed, const int32_t *tokens, int tok_stride, const int32_t *prefix_len,
-                       RowDesc d, int B, int d_model, int mask_id, int vocab, KvView kv, float rope_base,
-                       float *x, int32_t *pos_out, float *rope_cs, hipStream_t st);
+                       const RowDesc &d, const Segs &sg, int M, int d_model, int mask_id, int vocab, KvView kv,
+                       float rope_base, float *x, int32_t *pos_out, int n_head, float *rope_cs, hipStream_t st);
 
-// x[row] += sum_s part[s][row]; out[row'] = rmsnorm(x[row]) * gain for rows [row0, R) of each sequence.
-// part is in the tiled GEMM output layout over all B*R rows, out in the A-fragment layout over B*(R-row0) rows.
-void launch_rmsnorm(int dtype, float *x, const float *part, int S, const void *gain, float eps,
-                    int B, int R, int row0, int d_model, void *out, hipStream_t st);
+// x[row] += sum_s part[s][row]; out[row'] = rmsnorm(x[row]) * gain for the last n_rows rows of each of B sequences.
+// part is in the tiled GEMM output layout over all M rows, out in the A-fragment layout over the B * n_rows rows.
+void launch_rmsnorm(int dtype, float *x, const float *part, int S, const void *gain, float eps, int B, int n_rows, int M,
+                    const Segs &sg, int d_model, void *out, hipStream_t st);
 
 // Epilogue forms of the bf16 GEMM: tiled fp32 partial sums (default), plain row-major fp32 (the logits), or, for the
 // interleaved gate/up matrix with one split, SwiGLU applied in registers and h written as bf16 straight
@@ -236,7 +271,7 @@ void launch_pack_act(int dtype, const void *src, int M, int K, void *dst, hipStr
 void launch_untile_sum(const float *part, int S, int M, int N, float *out, hipStream_t st);
 
 void launch_rope_kv(int dtype, const float *qkv_part, int S, const float *rope_cs,
-                    const int32_t *prefix_len, RowDesc d, int B, int n_q, KvView kv,
+                    const int32_t *prefix_len, const RowDesc &d, const Segs &sg, int B, int M, int n_q, KvView kv,
                     void *q_out, void *k_scr, void *v_scr, hipStream_t st);
 
 void launch_place_kv(int dtype, const void *k_new, const void *v_new, const int32_t *prefix_len, RowDesc d, int B,
@@ -250,8 +285,8 @@ struct AttnPlan {
     int per;             // key-pair iterations per split, from the caller's bound on the key count (not from the
                          // sequence's current length): a key's split then depends on its position alone
 };
-AttnPlan plan_attention(int B, int n_kv, int group, int R, int nc, int max_keys);
-size_t attn_partial_floats(int B, int n_kv, int group, int R, int hd, int splits);
+AttnPlan plan_attention(int B, int n_kv, int group, const RowDesc &d, const Segs &sg, int max_keys);
+inline size_t attn_partial_floats(int M, int n_q, int hd, int splits) { return (size_t)M * n_q * splits * (hd + 2); }
 
 // The one-token step (R = 1, no mask rows) skips the RoPE launch: the attention workgroups take the new row's Q, K
 // and V straight from the QKV projection's split-K partial sums (tiled layout, S splits), rotate Q and K by the
@@ -270,15 +305,16 @@ struct AttnRope {
 // layout over B * R rows) and launch_attention_combine does nothing; with more it writes per-split partial
 // results to part, which launch_attention_combine folds into out.
 void launch_attention_bf16(const bf16_t *q, KvView kv, const bf16_t *k_scr, const bf16_t *v_scr,
-                           const int32_t *prefix_len, RowDesc d, int B, int n_q, const AttnPlan &p, float *part,
-                           bf16_t *out, int out_af, hipStream_t st, const AttnRope *rope = nullptr);
+                           const int32_t *prefix_len, const RowDesc &d, const Segs &sg, int B, int M, int n_q,
+                           const AttnPlan &p, float *part, bf16_t *out, int out_af, hipStream_t st,
+                           const AttnRope *rope = nullptr);
 // whether launch_attention_bf16 can take the new row from the partial sums for this row structure
 bool attention_rope_ok(RowDesc d, int group, int hd);
-void launch_attention_combine(const float *part, int B, int R, int n_q, int n_kv, int hd, int splits, bf16_t *out,
-                              int out_af, hipStream_t st);
+void launch_attention_combine(const float *part, const RowDesc &d, const Segs &sg, int M, int n_q, int n_kv, int hd,
+                              int splits, bf16_t *out, int out_af, hipStream_t st);
 void launch_attention_f32(const float *q, KvView kv, const float *k_scr, const float *v_scr,
-                          const int32_t *prefix_len, RowDesc d, int B, int n_q, float *out, int out_af,
-                          hipStream_t st);
+                          const int32_t *prefix_len, const RowDesc &d, const Segs &sg, int M, int n_q, float *out,
+                          int out_af, hipStream_t st);
 
 void launch_swiglu(int dtype, const float *part, int S, int M, int d_ff, void *out, hipStream_t st);
 
@@ -304,6 +340,8 @@ void launch_verify_step(const int32_t *y, const int32_t *drafts, int k, int B, i
                         hipStream_t st);
 void launch_finish_ar(const int32_t *y, const int32_t *token_in, int B, int vocab, KvView kv, int32_t *prefix_len,
                       int32_t *token_out, hipStream_t st);
-void launch_finish_prefill(const int32_t *y, const int32_t *tokens, int k, int seq, int add_len, int last, int vocab,
-                           KvView kv, int32_t *prefix_len, int32_t *first_drafts, hipStream_t st);
+// (B > 1: the whole prompts of sequences seq .. seq + B - 1, add_len rows of each from sg)
+void launch_finish_prefill(const int32_t *y, const int32_t *tokens, int tok_stride, int k, int seq, int B, const Segs &sg,
+                           int add_len, int last, int vocab, KvView kv, int32_t *prefix_len, int32_t *first_drafts,
+                           hipStream_t st);
 void launch_set_i32(int32_t *p, int n, int32_t v, hipStream_t st);

@@ -114,7 +114,10 @@ size_t gemm_out_floats(const tidar_config &c, int M, int N, int K) {
     return best;
 }
 
-// Workspace of one forward over B sequences of R rows (n_mask mask rows each), Mh rows through the LM head.
+const Segs kUniform = {};      // all sequences of a forward have the same rows
+int forward_row_count(int B, const RowDesc &d, const Segs &sg) { return sg.n ? sg.row0[sg.n] : B * d.R; }
+
+// Workspace of one forward over B sequences with the rows of d (or sg), Mh rows through the LM head.
 // n_mix: causal rows per sequence whose verification may mix two rows of logits (the decode step: k; else 0).
 // gemm_floats: room for the partial sums where the caller knows it already (0: worked out here).
 size_t forward_gemm_floats(const tidar_config &c, int M) {
@@ -125,9 +128,10 @@ size_t forward_gemm_floats(const tidar_config &c, int M) {
     for (size_t v : g) best = v > best ? v : best;
     return best;
 }
-Layout make_layout(const tidar_config &c, int B, int R, int n_mask, int Mh, int max_keys, bool own_logits,
+Layout make_layout(const tidar_config &c, int B, const RowDesc &d, const Segs &sg, int Mh, int max_keys, bool own_logits,
                    int n_mix = 0, size_t gemm_floats = 0) {
     Layout l;
+    const int n_mask = d.nm;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         size_t o = off;
@@ -135,7 +139,7 @@ Layout make_layout(const tidar_config &c, int B, int R, int n_mask, int Mh, int 
         return o;
     };
     size_t es = esize(c.dtype);
-    int M = B * R;
+    int M = forward_row_count(B, d, sg);
     int q_dim = c.n_q_heads * c.head_dim;
     l.pos = take((size_t)M * 4);
     l.rope_cs = take((size_t)M * c.head_dim * 4);
@@ -155,9 +159,9 @@ Layout make_layout(const tidar_config &c, int B, int R, int n_mask, int Mh, int 
     l.attn_splits = 1;
     size_t pf = 0;
     if (c.dtype == TIDAR_BF16) {
-        AttnPlan ap = plan_attention(B, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, R, R - n_mask, max_keys);
+        AttnPlan ap = plan_attention(B, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, d, sg, max_keys);
         l.attn_splits = ap.splits;
-        pf = attn_partial_floats(B, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, R, c.head_dim, ap.splits_bound);
+        pf = attn_partial_floats(M, c.n_q_heads, c.head_dim, ap.splits_bound);
     }
     l.attn_part = take(pf * 4);
     l.o = take(af_elems(M, q_dim) * es);
@@ -246,28 +250,29 @@ void gemm(tidar_ctx *ctx, const void *a, const void *w, float *out, int M, int N
 
 // Returns the number of key splits whose partial results wait in the workspace (1: o_out holds the result).  With
 // defer_combine the partial results are left for the consumer to fold.
-int attention(tidar_ctx *ctx, const Layout &l, char *ws, KvView kvv, const int32_t *prefix_len,
-              RowDesc d, int B, int max_keys, void *o_out, hipStream_t st, bool defer_combine = false,
+int attention(tidar_ctx *ctx, const Layout &l, char *ws, KvView kvv, const int32_t *prefix_len, const RowDesc &d,
+              const Segs &sg, int B, int max_keys, void *o_out, hipStream_t st, bool defer_combine = false,
               const AttnRope *rope = nullptr) {
     const tidar_config &c = ctx->cfg;
+    const int M = forward_row_count(B, d, sg);
     if (c.dtype == TIDAR_BF16) {
-        AttnPlan ap = plan_attention(B, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, d.R, d.nc, max_keys);
+        AttnPlan ap = plan_attention(B, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, d, sg, max_keys);
         {
             Prof p(ctx, KC_ATTN, st);
             launch_attention_bf16((const bf16_t *)(ws + l.q), kvv, (const bf16_t *)(ws + l.k_scr),
-                                  (const bf16_t *)(ws + l.v_scr), prefix_len, d, B, c.n_q_heads, ap,
+                                  (const bf16_t *)(ws + l.v_scr), prefix_len, d, sg, B, M, c.n_q_heads, ap,
                                   (float *)(ws + l.attn_part), (bf16_t *)o_out, 1, st, rope);
         }
         if (ap.splits > 1 && !defer_combine) {
             Prof p(ctx, KC_ATTN_COMBINE, st);
-            launch_attention_combine((const float *)(ws + l.attn_part), B, d.R, c.n_q_heads, c.n_kv_heads, c.head_dim,
+            launch_attention_combine((const float *)(ws + l.attn_part), d, sg, M, c.n_q_heads, c.n_kv_heads, c.head_dim,
                                      ap.splits, (bf16_t *)o_out, 1, st);
         }
         return ap.splits;
     }
     Prof p(ctx, KC_ATTN, st);
     launch_attention_f32((const float *)(ws + l.q), kvv, (const float *)(ws + l.k_scr),
-                         (const float *)(ws + l.v_scr), prefix_len, d, B, c.n_q_heads, (float *)o_out, 1, st);
+                         (const float *)(ws + l.v_scr), prefix_len, d, sg, M, c.n_q_heads, (float *)o_out, 1, st);
     return 1;
 }
 
@@ -278,22 +283,22 @@ struct ScorePass {
     float *ar_out, *diff_out;
 };
 
-// One forward over B sequences with row structure d.  head_row0 < 0: no LM head.  Otherwise rows
+// One forward over B sequences with row structure d (and sg).  head_row0 < 0: no LM head.  Otherwise rows
 // [head_row0, R) of every sequence go through the final norm, the LM head and the vocabulary reduction;
 // the chosen tokens land in ws + layout.y.
-void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *kv, int B, RowDesc d,
-                  const int32_t *tokens, int tok_stride, const int32_t *prefix_len, int max_keys, int head_row0,
+void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *kv, int B, const RowDesc &d,
+                  const Segs &sg, const int32_t *tokens, int tok_stride, const int32_t *prefix_len, int max_keys, int head_row0,
                   int n_choose, const tidar_mode *mode, int mix_base, int mix_stride, float *logits_dst,
                   const Layout &l, char *ws, hipStream_t st, const ScorePass *score = nullptr) {
     const tidar_config &c = ctx->cfg;
-    const int M = B * d.R;
+    const int M = forward_row_count(B, d, sg);
     const int q_dim = c.n_q_heads * c.head_dim, kv_dim = c.n_kv_heads * c.head_dim;
     float *x = (float *)(ws + l.x);
     float *gout = (float *)(ws + l.gemm_out);
     {
         Prof p(ctx, KC_EMBED, st);
-        launch_embed_rows(c.dtype, w->embed, tokens, tok_stride, prefix_len, d, B, c.d_model, c.mask_token_id,
-                          c.vocab, layer_view(c, kv, 0), c.rope_base, x, (int32_t *)(ws + l.pos),
+        launch_embed_rows(c.dtype, w->embed, tokens, tok_stride, prefix_len, d, sg, M, c.d_model, c.mask_token_id,
+                          c.vocab, layer_view(c, kv, 0), c.rope_base, x, (int32_t *)(ws + l.pos), d.R - head_row0,
                           (float *)(ws + l.rope_cs), st);
     }
     int S_prev = 0;   // split count of the partial sums still waiting to be added to the residual stream
@@ -334,7 +339,7 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
         } else {
             {
                 Prof p(ctx, KC_RMSNORM, st);
-                launch_rmsnorm(c.dtype, x, g_cur, S_prev, w->attn_norm[layer], c.rms_eps, B, d.R, 0, c.d_model,
+                launch_rmsnorm(c.dtype, x, g_cur, S_prev, w->attn_norm[layer], c.rms_eps, 1, M, M, kUniform, c.d_model,
                                ws + l.xn, st);
             }
             gemm(ctx, ws + l.xn, w->wqkv[layer], g_cur, M, q_dim + 2 * kv_dim, c.d_model, false, &S, st);
@@ -352,10 +357,10 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
             rope.kv_dim = kv_dim;
         } else {
             Prof p(ctx, KC_ROPE_KV, st);
-            launch_rope_kv(c.dtype, g_cur, S, (const float *)(ws + l.rope_cs), prefix_len, d, B, c.n_q_heads, kvv,
+            launch_rope_kv(c.dtype, g_cur, S, (const float *)(ws + l.rope_cs), prefix_len, d, sg, B, M, c.n_q_heads, kvv,
                            ws + l.q, ws + l.k_scr, ws + l.v_scr, st);
         }
-        const int a_splits = attention(ctx, l, ws, kvv, prefix_len, d, B, max_keys, ws + l.o, st, fuse,
+        const int a_splits = attention(ctx, l, ws, kvv, prefix_len, d, sg, B, max_keys, ws + l.o, st, fuse,
                                        rope.part ? &rope : nullptr);
         if (fuse && a_splits > 1) {
             Prof p(ctx, KC_GEMM, st);
@@ -385,8 +390,8 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
         } else {
             {
                 Prof p(ctx, KC_RMSNORM, st);
-                launch_rmsnorm(c.dtype, x, g_cur, S, w->ffn_norm[layer], c.rms_eps, B, d.R, 0, c.d_model, ws + l.xn,
-                               st);
+                launch_rmsnorm(c.dtype, x, g_cur, S, w->ffn_norm[layer], c.rms_eps, 1, M, M, kUniform, c.d_model,
+                               ws + l.xn, st);
             }
             if (c.dtype == TIDAR_BF16) {
                 GemmPlan gp = plan_gemm_bf16(M, 2 * c.d_ff, c.d_model, false);
@@ -412,8 +417,9 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
     const int Mh = B * Rh;
     {
         Prof p(ctx, KC_RMSNORM, st);
-        launch_rmsnorm(c.dtype, x, gout, S_prev, w->final_norm, c.rms_eps, B, d.R, head_row0, c.d_model, ws + l.xh, st);
+        launch_rmsnorm(c.dtype, x, gout, S_prev, w->final_norm, c.rms_eps, B, Rh, M, sg, c.d_model, ws + l.xh, st);
     }
+    const int pos_stride = sg.n ? Rh : d.R, pos_row0 = sg.n ? 0 : head_row0;      // see embed_rows_kernel
     float *logits = logits_dst ? logits_dst : (float *)(ws + l.logits);
     if (score) {               // one sequence; every row's label is scored, no token is chosen
         int S1 = 1;
@@ -436,8 +442,8 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
         ch.Rh = Rh;
         ch.n_choose = n_choose;
         ch.pos_rows = (const int32_t *)(ws + l.pos);
-        ch.pos_stride = d.R;
-        ch.pos_row0 = head_row0;
+        ch.pos_stride = pos_stride;
+        ch.pos_row0 = pos_row0;
         ch.seq_base = d.seq_base;
         ch.sample = mix ? 0 : mode->sample;          // mixed rows are perturbed after the mix, by argmax_rows
         ch.inv_t = 1.f / mode->temperature;
@@ -453,7 +459,7 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
         Prof p(ctx, KC_ARGMAX, st);
         launch_argmax_groups(logits, Mh, G, (int32_t *)(ws + l.y), st);
         if (mix)       // compact rows per sequence: causal row i at i, its partner at n_choose + i
-            launch_argmax_rows(ch.sel_logits, B, 2 * n_choose, n_choose, c.vocab, n_choose, ch.pos_rows, d.R, head_row0,
+            launch_argmax_rows(ch.sel_logits, B, 2 * n_choose, n_choose, c.vocab, n_choose, ch.pos_rows, pos_stride, pos_row0,
                                d.seq_base, mode->sample, mode->temperature, mode->seed, mode->beta, n_choose, 1,
                                (int32_t *)(ws + l.y), Rh, st);
         return;
@@ -462,7 +468,7 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
     gemm(ctx, ws + l.xh, w->lm_head, logits, Mh, c.vocab, c.d_model, true, &S, st);
     {
         Prof p(ctx, KC_ARGMAX, st);
-        launch_argmax_rows(logits, B, Rh, Rh, c.vocab, n_choose, (const int32_t *)(ws + l.pos), d.R, head_row0,
+        launch_argmax_rows(logits, B, Rh, Rh, c.vocab, n_choose, (const int32_t *)(ws + l.pos), pos_stride, pos_row0,
                            d.seq_base, mode->sample, mode->temperature, mode->seed, mode->beta, mix_base, mix_stride,
                            (int32_t *)(ws + l.y), Rh, st);
     }
@@ -527,6 +533,37 @@ int score_chunk(const tidar_ctx *ctx, int block_len) {
         if (chunk < block_len) chunk = block_len;
     }
     return chunk;
+}
+
+// How many of the n prompts from here on (sequence b0 first) go through one pass together, and that pass.  A pass streams
+// every weight once however many rows it has, and its launches hardly get longer before a few hundred rows: whole prompts
+// are taken together as long as they make no more rows than the longest pass of a single one (three prompts of 515, 430
+// and 344 tokens on the 1.5B shape: 11.5 ms one after the other, 6.6 together).  The attention grid is laid out for the
+// longest of them: those that would leave three quarters of it without rows are left to a pass of their own.  So is
+// everything a caller's workspace has no room for, and passes of so few rows that the chain of fused launches serves them.
+int prefill_together(const tidar_ctx *ctx, const int32_t *prompt_len, int n, int k, int b0, size_t ws_bytes, RowDesc *d,
+                     Segs *sg, Layout *l) {
+    int rows = 0, longest = 0, taken = 0;
+    sg->n = 0;
+    sg->row0[0] = 0;
+    while (taken < n && taken < kMaxSegs) {
+        const int P = prompt_len[taken], top = P > longest ? P : longest;
+        if (P > ctx->prefill_chunk || rows + P + k > ctx->prefill_chunk + k) break;
+        if ((int64_t)(taken + 1) * (top + k) > 4 * (int64_t)(rows + P + k)) break;
+        longest = top;
+        rows += P + k;
+        sg->row0[++taken] = rows;
+    }
+    for (; taken > 1; --taken) {
+        if (sg->row0[taken] <= kFuseMaxRows) return 1;
+        longest = 0;
+        for (int i = 0; i < taken; ++i) longest = prompt_len[i] > longest ? prompt_len[i] : longest;
+        sg->n = taken;
+        *d = prefill_desc(longest, k, true, b0);
+        *l = make_layout(ctx->cfg, taken, *d, *sg, taken * (1 + k), longest + k, true);
+        if (l->total <= ws_bytes) return taken;
+    }
+    return 1;
 }
 
 size_t score_header_bytes(const tidar_config &c) { return align_up((size_t)c.max_batch * 4); }
@@ -605,16 +642,17 @@ tidar_status tidar_workspace_bytes(const tidar_ctx *ctx, int32_t batch, int32_t 
     if (!ctx || !bytes) return TIDAR_EINVAL;
     const tidar_config &c = ctx->cfg;
     if (batch < 1 || batch > c.max_batch || k < 1 || k > c.max_k || max_prefix_len < 0) return TIDAR_EINVAL;
-    int R = k * (k + 1);
-    Layout a = make_layout(c, batch, R, k * k, batch * R, max_prefix_len + R, true, k);
-    Layout b = make_layout(c, batch, 1, 0, batch, max_prefix_len + 1, true);
+    const int R = k * (k + 1);
+    Layout a = make_layout(c, batch, step_desc(k), kUniform, batch * R, max_prefix_len + R, true, k);
+    Layout b = make_layout(c, batch, ar_desc(), kUniform, batch, max_prefix_len + 1, true);
     size_t t = a.total > b.total ? a.total : b.total;
     // prefill passes: a full causal chunk, or a last pass of 1..chunk causal rows plus the mask block
-    Layout full = make_layout(c, 1, ctx->prefill_chunk, 0, 0, max_prefix_len + ctx->prefill_chunk, true);
+    Layout full = make_layout(c, 1, prefill_desc(ctx->prefill_chunk, k, false, 0), kUniform, 0,
+                              max_prefix_len + ctx->prefill_chunk, true);
     if (full.total > t) t = full.total;
     const size_t g = forward_gemm_floats(c, ctx->prefill_chunk + k);          // grows with the rows: enough for each
     for (int nc = 1; nc <= ctx->prefill_chunk; ++nc) {
-        Layout p = make_layout(c, 1, nc + k, k, 1 + k, max_prefix_len + k, true, 0, g);
+        Layout p = make_layout(c, 1, prefill_desc(nc, k, true, 0), kUniform, 1 + k, max_prefix_len + k, true, 0, g);
         if (p.total > t) t = p.total;
     }
     *bytes = t;
@@ -632,11 +670,11 @@ tidar_status tidar_step(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_c
     if (batch < 1 || batch > c.max_batch || k < 1 || k > c.max_k || max_prefix_len_hint < 0) return TIDAR_EINVAL;
     if ((int64_t)max_prefix_len_hint + k > (int64_t)kv->pages_per_seq * TIDAR_PAGE_SIZE) return TIDAR_ECAPACITY;
     RowDesc d = step_desc(k);
-    Layout l = make_layout(c, batch, d.R, k * k, batch * d.R, max_prefix_len_hint + d.R, logits_out == nullptr, k);
+    Layout l = make_layout(c, batch, d, kUniform, batch * d.R, max_prefix_len_hint + d.R, logits_out == nullptr, k);
     if (l.total > ws_bytes) return TIDAR_ENOMEM;
     hipStream_t st = (hipStream_t)stream;
     // causal row i is label shifted and judges draft i+1; with beta != 1 it is mixed with slot 0 of block i
-    forward_rows(ctx, w, kv, batch, d, drafts, k, prefix_len, max_prefix_len_hint + d.R, 0, k, mode, k, k, logits_out,
+    forward_rows(ctx, w, kv, batch, d, kUniform, drafts, k, prefix_len, max_prefix_len_hint + d.R, 0, k, mode, k, k, logits_out,
                  l, (char *)ws, st);
     {
         Prof p(ctx, KC_VERIFY, st);
@@ -655,12 +693,12 @@ tidar_status tidar_ar_step(tidar_ctx *ctx, const tidar_weights *w, const tidar_k
     if (batch < 1 || batch > c.max_batch || max_prefix_len_hint < 0) return TIDAR_EINVAL;
     if ((int64_t)max_prefix_len_hint + 1 > (int64_t)kv->pages_per_seq * TIDAR_PAGE_SIZE) return TIDAR_ECAPACITY;
     RowDesc d = ar_desc();
-    Layout l = make_layout(c, batch, 1, 0, batch, max_prefix_len_hint + 1, logits_out == nullptr);
+    Layout l = make_layout(c, batch, d, kUniform, batch, max_prefix_len_hint + 1, logits_out == nullptr);
     if (l.total > ws_bytes) return TIDAR_ENOMEM;
     hipStream_t st = (hipStream_t)stream;
     tidar_mode m = *mode;
     m.beta = 1.f;                 // a one-token step has no diffusion row to mix with
-    forward_rows(ctx, w, kv, batch, d, token_in, 1, prefix_len, max_prefix_len_hint + 1, 0, 1, &m, 0, 0, logits_out,
+    forward_rows(ctx, w, kv, batch, d, kUniform, token_in, 1, prefix_len, max_prefix_len_hint + 1, 0, 1, &m, 0, 0, logits_out,
                  l, (char *)ws, st);
     {
         Prof p(ctx, KC_VERIFY, st);
@@ -690,8 +728,8 @@ tidar_status tidar_prefill(tidar_ctx *ctx, const tidar_weights *w, const tidar_k
         for (int c0 = 0; c0 < P; c0 += ctx->prefill_chunk) {
             const int nc = (P - c0 < ctx->prefill_chunk) ? P - c0 : ctx->prefill_chunk;
             const bool last = c0 + nc >= P;
-            Layout l = make_layout(c, 1, nc + (last ? k : 0), last ? k : 0, last ? 1 + k : 0,
-                                   c0 + nc + (last ? k : 0), true);
+            const RowDesc d = prefill_desc(nc, k, last, b);
+            Layout l = make_layout(c, 1, d, kUniform, last ? 1 + k : 0, c0 + d.R, true);
             if (l.total > ws_bytes) return TIDAR_ENOMEM;
         }
     }
@@ -699,24 +737,39 @@ tidar_status tidar_prefill(tidar_ctx *ctx, const tidar_weights *w, const tidar_k
     tidar_mode pm = *mode;
     pm.beta = 1.f;                // the first token comes from the causal logits alone
     launch_set_i32(prefix_len, batch, 0, st);
-    for (int b = 0; b < batch; ++b) {
+    for (int b = 0; b < batch;) {
+        RowDesc dm;
+        Segs sg;
+        Layout lm;
+        const int n = prefill_together(ctx, prompt_len + b, batch - b, k, b, ws_bytes, &dm, &sg, &lm);
+        if (n > 1) {
+            const int32_t *toks = prompt + (size_t)b * prompt_stride;
+            forward_rows(ctx, w, kv, n, dm, sg, toks, prompt_stride, prefix_len, dm.R, dm.nc - 1, 1, &pm, 1, 0,
+                         logits_out ? logits_out + (size_t)b * (1 + k) * c.vocab : nullptr, lm, (char *)ws, st);
+            Prof p(ctx, KC_VERIFY, st);
+            launch_finish_prefill((const int32_t *)((char *)ws + lm.y), toks, prompt_stride, k, b, n, sg, 0, 1, c.vocab,
+                                  layer_view(c, kv, 0), prefix_len, first_drafts, st);
+            b += n;
+            continue;
+        }
         const int P = prompt_len[b];
         for (int c0 = 0; c0 < P; c0 += ctx->prefill_chunk) {
             const int nc = (P - c0 < ctx->prefill_chunk) ? P - c0 : ctx->prefill_chunk;
             const bool last = c0 + nc >= P;
             RowDesc d = prefill_desc(nc, k, last, b);
-            Layout l = make_layout(c, 1, d.R, last ? k : 0, last ? 1 + k : 0, c0 + d.R, true);
+            Layout l = make_layout(c, 1, d, kUniform, last ? 1 + k : 0, c0 + d.R, true);
             float *lg = (last && logits_out) ? logits_out + (size_t)b * (1 + k) * c.vocab : nullptr;
             // the last pass sends the final prompt row and the k mask rows through the LM head
-            forward_rows(ctx, w, kv, 1, d, prompt + (size_t)b * prompt_stride + c0, prompt_stride, prefix_len,
+            forward_rows(ctx, w, kv, 1, d, kUniform, prompt + (size_t)b * prompt_stride + c0, prompt_stride, prefix_len,
                          c0 + d.R, last ? nc - 1 : -1, 1, &pm, 1, 0, lg, l, (char *)ws, st);
             {
                 Prof p(ctx, KC_VERIFY, st);
-                launch_finish_prefill((const int32_t *)((char *)ws + l.y), prompt + (size_t)b * prompt_stride + c0, k,
-                                      b, nc, last ? 1 : 0, c.vocab, layer_view(c, kv, 0), prefix_len, first_drafts,
-                                      st);
+                launch_finish_prefill((const int32_t *)((char *)ws + l.y), prompt + (size_t)b * prompt_stride + c0,
+                                      prompt_stride, k, b, 1, kUniform, nc, last ? 1 : 0, c.vocab, layer_view(c, kv, 0),
+                                      prefix_len, first_drafts, st);
             }
         }
+        ++b;
     }
     return TIDAR_OK;
 }
@@ -731,7 +784,7 @@ tidar_status tidar_score_workspace_bytes(const tidar_ctx *ctx, int32_t max_len, 
     // the workspace grows with the key bound for a given pass shape, and no pass ends beyond max_len
     for (int nc = 1; nc <= most; ++nc) {
         RowDesc d = score_desc(nc, block_len, 0);
-        Layout l = make_layout(c, 1, d.R, d.nm, d.R, max_len + d.nm, true, 0, g);
+        Layout l = make_layout(c, 1, d, kUniform, d.R, max_len + d.nm, true, 0, g);
         if (l.total > t) t = l.total;
     }
     *bytes = score_header_bytes(c) + t;
@@ -755,7 +808,7 @@ tidar_status tidar_score(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_
         if ((int64_t)len[b] > (int64_t)kv->pages_per_seq * TIDAR_PAGE_SIZE) return TIDAR_ECAPACITY;
         for (int c0 = 0; c0 < len[b]; c0 += chunk) {
             RowDesc d = score_desc(len[b] - c0 < chunk ? len[b] - c0 : chunk, block_len, b);
-            Layout l = make_layout(c, 1, d.R, d.nm, d.R, c0 + d.R, true);
+            Layout l = make_layout(c, 1, d, kUniform, d.R, c0 + d.R, true);
             if (hdr + l.total > ws_bytes) return TIDAR_ENOMEM;
         }
     }
@@ -771,7 +824,7 @@ tidar_status tidar_score(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_
         const int32_t *text = tokens + (size_t)b * stride;
         for (int c0 = 0; c0 < len[b]; c0 += chunk) {
             RowDesc d = score_desc(len[b] - c0 < chunk ? len[b] - c0 : chunk, block_len, b);
-            Layout l = make_layout(c, 1, d.R, d.nm, d.R, c0 + d.R, true);
+            Layout l = make_layout(c, 1, d, kUniform, d.R, c0 + d.R, true);
             launch_set_i32(cur + b, 1, c0, st);
             ScorePass sp;
             sp.text = text;
@@ -779,7 +832,7 @@ tidar_status tidar_score(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_
             sp.c0 = c0;
             sp.ar_out = ar_logprob + (size_t)b * stride;
             sp.diff_out = diff_logprob ? diff_logprob + (size_t)b * stride : nullptr;
-            forward_rows(ctx, w, kv, 1, d, text + c0, stride, cur, c0 + d.R, 0, 0, &gm, 0, 0, nullptr, l, wsb, st, &sp);
+            forward_rows(ctx, w, kv, 1, d, kUniform, text + c0, stride, cur, c0 + d.R, 0, 0, &gm, 0, 0, nullptr, l, wsb, st, &sp);
         }
         if (loss) {
             Prof p(ctx, KC_SCORE, st);
@@ -818,11 +871,9 @@ tidar_status tidar_hybrid_attention(tidar_ctx *ctx, const tidar_kv_cache *kv, in
     if (n_mt < 1) n_mt = 1;
     size_t scr = align_up((size_t)batch * c.n_kv_heads * n_mt * 16 * c.head_dim * es);
     int max_keys = max_prefix_len_hint + d.R;
-    AttnPlan ap = plan_attention(batch, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, d.R, d.nc, max_keys);
-    size_t pf = c.dtype == TIDAR_BF16
-                    ? attn_partial_floats(batch, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, d.R, c.head_dim,
-                                          ap.splits_bound)
-                    : 0;
+    const int M = batch * d.R;
+    AttnPlan ap = plan_attention(batch, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, d, kUniform, max_keys);
+    size_t pf = c.dtype == TIDAR_BF16 ? attn_partial_floats(M, c.n_q_heads, c.head_dim, ap.splits_bound) : 0;
     if (2 * scr + align_up(pf * 4) > ws_bytes) return TIDAR_ENOMEM;
     char *wsb = (char *)ws;
     hipStream_t st = (hipStream_t)stream;
@@ -835,17 +886,17 @@ tidar_status tidar_hybrid_attention(tidar_ctx *ctx, const tidar_kv_cache *kv, in
         {
             Prof p(ctx, KC_ATTN, st);
             launch_attention_bf16((const bf16_t *)q, kvv, (const bf16_t *)wsb,
-                                  (const bf16_t *)(wsb + scr), prefix_len, d, batch, c.n_q_heads, ap,
+                                  (const bf16_t *)(wsb + scr), prefix_len, d, kUniform, batch, M, c.n_q_heads, ap,
                                   (float *)(wsb + 2 * scr), (bf16_t *)out, 0, st);
         }
         if (ap.splits == 1) return TIDAR_OK;
         Prof p(ctx, KC_ATTN_COMBINE, st);
-        launch_attention_combine((const float *)(wsb + 2 * scr), batch, d.R, c.n_q_heads, c.n_kv_heads, c.head_dim,
+        launch_attention_combine((const float *)(wsb + 2 * scr), d, kUniform, M, c.n_q_heads, c.n_kv_heads, c.head_dim,
                                  ap.splits, (bf16_t *)out, 0, st);
     } else {
         Prof p(ctx, KC_ATTN, st);
         launch_attention_f32((const float *)q, kvv, (const float *)wsb, (const float *)(wsb + scr), prefix_len, d,
-                             batch, c.n_q_heads, (float *)out, 0, st);
+                             kUniform, M, c.n_q_heads, (float *)out, 0, st);
     }
     return TIDAR_OK;
 }
