@@ -104,7 +104,7 @@ def gemm_source_digest():
     describe this one."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("kernels_gemm.hip", "kernels_gemm_mid.hip", "kernels_gemm_rows.hip", "gemm_device.h", "lds_dma.h",
+    for name in ("kernels_gemm.hip", "kernels_gemm_mid.hip", "kernels_gemm_tall.hip", "kernels_gemm_rows.hip", "gemm_device.h", "lds_dma.h",
                  "tidar_internal.h"):
         with open(os.path.join(ROOT, "paper_2511_08923_amd", "csrc", name), "rb") as f:
             h.update(f.read())

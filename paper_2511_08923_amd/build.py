@@ -10,7 +10,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(os.path.dirname(PKG), "include")
 LIB = os.path.join(PKG, "libtidar.so")
-SOURCES = ["tidar_lib.hip", "kernels_misc.hip", "kernels_gemm.hip", "kernels_gemm_mid.hip", "kernels_gemm_rows.hip",
+SOURCES = ["tidar_lib.hip", "kernels_misc.hip", "kernels_gemm.hip", "kernels_gemm_mid.hip", "kernels_gemm_tall.hip",
+           "kernels_gemm_rows.hip",
            "kernels_attn.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE, "-I" + CSRC,

@@ -1,7 +1,8 @@
 // Skinny bf16 GEMM of the decode step: out = A[M][K] (bf16) x W[N][K]^T (bf16), fp32 accumulation.
 //
 // M is the step's row count (1 .. 272 at batch 1; more rows run as row passes, 481 and more in kernels_gemm_rows.hip,
-// the narrower products of 33 .. 480 - the narrowest to 768 - in kernels_gemm_mid.hip), N and K are model dimensions: every weight byte is used once
+// the narrower products of 33 .. 480 - the narrowest to 768 - in kernels_gemm_mid.hip, the widest and those of many short
+// shares of K up to 480 rows in kernels_gemm_tall.hip), N and K are model dimensions: every weight byte is used once
 // per step, so the kernel is a weight streamer with MFMA attached.
 //   * W lives in HBM as the register image of the 32x32x16 MFMA B operand
 //     ([k step of 16][32-column tile][lane][8]); a wave's load of one fragment is one fully coalesced 1 KiB read
@@ -416,177 +417,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_fused_kernel(FuseArgs f, 
     store_tiles<MT, NT>(acc, out, blockIdx.y, M, N, tile0, n_tiles, 0, lane, epi, none);
 }
 
-// Epilogue of a wave that holds MTA row tiles (from row tile mh * MTA of the workgroup's pass on) by NT column tiles
-// (from tile0 on).  NW waves per workgroup; ct_here: row tiles of the pass that exist; smem: at least NW * 32 * 36
-// floats nobody reads any more (with NT == 1 and GEMM_EPI_ARGMAX all waves of the workgroup have to come here).
-template <int MTA, int NT, int NW>
-__device__ inline void large_epilogue(const f32x16 (&acc)[MTA][NT], float *__restrict__ out, unsigned char *gemm_smem,
-                                      int epi, int split, int M, int N, int mt_base, int ct_here, int tile0, int mh,
-                                      int wave, int lane, const ChooseArgs &ch) {
-    const int t32 = (N + 31) >> 5, m_tiles = (M + 31) >> 5;
-    // The weight fragment is the MFMA's first operand, so the accumulator holds the output tile
-    // transposed: lane l owns activation row l%32 of the row tile, and its register e is column
-    // 8*(e/4) + 4*(l/32) + e%4 of the 32-column tile: four consecutive registers are four consecutive columns of
-    // one row.
-    const int lq = lane & 31, lh = lane >> 5;
-    if (epi == GEMM_EPI_SWIGLU) {
-        // columns 0-15 of a tile are gate, 16-31 up, of the same 16 features (tile T = features 16T..16T+15 =
-        // exactly one k step of the next GEMM's A-fragment layout), so gate and up of a feature sit in the same
-        // lane, 8 registers apart: h = silu(gate) * up needs no shuffle.  A lane then holds features 4*(l/32)+0..3
-        // and 8+4*(l/32)+0..3 of its row; the fragment wants 8*(l/32)+0..7.  One half-wave swap fixes that: the
-        // upper lanes hand their features 4-7 to the lower lanes and take the lower lanes' 8-11.
-        bf16_t *ho = reinterpret_cast<bf16_t *>(out);
-        typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-        for (int mt = 0; mt < MTA; ++mt) {
-            const int tile_r = mh * MTA + mt;
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                unsigned pk[4];
-#pragma unroll
-                for (int i = 0; i < 8; i += 2) {
-                    float h2[2];
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        const float g = acc[mt][j][i + t], u = acc[mt][j][i + t + 8];
-                        h2[t] = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
-                    }
-                    bf16x2 b;
-                    b[0] = (bf16_t)h2[0];
-                    b[1] = (bf16_t)h2[1];
-                    pk[i >> 1] = __builtin_bit_cast(unsigned, b);
-                }
-                // pk[0..1]: features 4*lh + 0..3; pk[2..3]: features 8 + 4*lh + 0..3
-                const auto s0 = __builtin_amdgcn_permlane32_swap(pk[0], pk[2], false, false);
-                const auto s1 = __builtin_amdgcn_permlane32_swap(pk[1], pk[3], false, false);
-                typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-                const u32x4 piece = {s0[0], s1[0], s0[1], s1[1]};
-                if (tile_r < ct_here && tile0 + j < t32)
-                    *(u32x4 *)(ho + (((size_t)(tile0 + j) * m_tiles + mt_base + tile_r) * 64 + lane) * 8) = piece;
-            }
-        }
-        return;
-    }
-    if (epi == GEMM_EPI_ARGMAX) {
-        // a lane walks its 16 columns of each of the wave's tiles in rising order (strict > keeps the lowest column
-        // of a tie), then the two half-waves, which hold the same rows, are folded.  A column group is 64 columns:
-        // the wave's two tiles, or (NT = 1) the tiles of two neighbouring waves, folded through LDS.
-        const int G = (t32 + 1) >> 1;
-        float *pmax = out;
-        int *pidx = (int *)(out + (size_t)G * M);
-        float bests[MTA];
-        int bis[MTA];
-#pragma unroll
-        for (int mt = 0; mt < MTA; ++mt) {
-            const int tile_r = mh * MTA + mt;
-            float best = -INFINITY;
-            int bi = tile0 * 32 + 4 * lh;
-            bests[mt] = best;
-            bis[mt] = bi;
-            if (tile_r >= ct_here) continue;      // wave-uniform
-            const RowChoice rc = row_choice(ch, (mt_base + tile_r) * 32 + lq, M);
-            if (__any(rc.noisy || rc.sel >= 0)) {     // a tile that holds rows a token is taken from (wave-uniform)
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int col = (tile0 + j) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
-                        float v = acc[mt][j][e];
-                        if (rc.sel >= 0 && col < N) ch.sel_logits[(size_t)rc.sel * N + col] = v;
-                        if (rc.noisy) v = perturbed_logit(v, rc.inv_t, rc.key, (uint32_t)col);
-                        if (col < N && v > best) {
-                            best = v;
-                            bi = col;
-                        }
-                    }
-            } else {
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int col = (tile0 + j) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
-                        const float v = acc[mt][j][e];
-                        if (col < N && v > best) {
-                            best = v;
-                            bi = col;
-                        }
-                    }
-            }
-            const float ob = __shfl_xor(best, 32);
-            const int oi = __shfl_xor(bi, 32);
-            if (ob > best || (ob == best && oi < bi)) {
-                best = ob;
-                bi = oi;
-            }
-            bests[mt] = best;
-            bis[mt] = bi;
-        }
-        if constexpr (NT == 1) {
-            // the odd wave of a pair hands its result to the even one (the staging buffers are free by now)
-            float *rb = reinterpret_cast<float *>(gemm_smem);
-            int *ri = reinterpret_cast<int *>(gemm_smem) + NW * MTA * 32;
-            if (lh == 0) {
-#pragma unroll
-                for (int mt = 0; mt < MTA; ++mt) {
-                    rb[(wave * MTA + mt) * 32 + lq] = bests[mt];
-                    ri[(wave * MTA + mt) * 32 + lq] = bis[mt];
-                }
-            }
-            __syncthreads();
-            if (wave & 1) return;
-#pragma unroll
-            for (int mt = 0; mt < MTA; ++mt) {
-                const float ob = rb[((wave + 1) * MTA + mt) * 32 + lq];
-                const int oi = ri[((wave + 1) * MTA + mt) * 32 + lq];
-                if (ob > bests[mt] || (ob == bests[mt] && oi < bis[mt])) {
-                    bests[mt] = ob;
-                    bis[mt] = oi;
-                }
-            }
-        }
-#pragma unroll
-        for (int mt = 0; mt < MTA; ++mt) {
-            const int tile_r = mh * MTA + mt;
-            const int row = (mt_base + tile_r) * 32 + lq;
-            if (tile_r < ct_here && lh == 0 && row < M && tile0 < t32) {
-                pmax[(size_t)(tile0 >> 1) * M + row] = bests[mt];
-                pidx[(size_t)(tile0 >> 1) * M + row] = bis[mt];
-            }
-        }
-        return;
-    }
-    // Partial sums and logits: a lane's four consecutive columns are 16 bytes, but neighbouring lanes are
-    // neighbouring rows, 128 bytes apart in the tiled layout.  Each tile is therefore turned through a per-wave
-    // LDS patch (16-byte writes, 16-byte reads; the staging buffers are free after the last barrier) so that eight
-    // lanes together store one whole row of the tile (128 bytes) and a store instruction covers 1 KiB in one run.
-    float *scr = reinterpret_cast<float *>(gemm_smem) + wave * (32 * 36);
-    float *o = out + (size_t)split * pt_split_stride(M, N);
-#pragma unroll
-    for (int mt = 0; mt < MTA; ++mt) {
-        const int tile_r = mh * MTA + mt;
-        if (tile_r >= ct_here) continue;          // also drops the repeated tile (wave-uniform)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                *(f32x4 *)(scr + lq * 36 + 8 * g + 4 * lh) = (f32x4){acc[mt][j][4 * g], acc[mt][j][4 * g + 1],
-                                                                     acc[mt][j][4 * g + 2], acc[mt][j][4 * g + 3]};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int idx = lane + 64 * i;
-                const int r = idx >> 3, c4 = idx & 7;
-                const f32x4 v = *(const f32x4 *)(scr + r * 36 + 4 * c4);
-                const int row = (mt_base + tile_r) * 32 + r;
-                const int col = (tile0 + j) * 32 + 4 * c4;
-                if (row < M && col < N) {
-                    const size_t oi = (epi == GEMM_EPI_ROWMAJOR) ? (size_t)row * N + col : pt_index(col, row, M);
-                    *(f32x4 *)(o + oi) = v;
-                }
-            }
-        }
-    }
-}
-
 // ------------------------------------------------------------------ 32 < M: 32x32x16 MFMA, A through LDS
 // MTA: 32-row tiles per wave.  2 x 2 waves (WIDE false): the workgroup pass covers CTL = 2*MTA row tiles (9 when
 // MTA is 5: the second row half then repeats a tile whose results are dropped) of 128 columns.  WIDE: four waves
@@ -737,7 +567,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
         }
     }
 
-    large_epilogue<MTA, NT, NW>(acc, out, gemm_smem, epi, blockIdx.y, M, N, mt_base, ct_here, tile0, mh, wave, lane, ch);
+    large_epilogue<MTA, NT, NW>(acc, out, gemm_smem, epi, blockIdx.y, M, N, mt_base, ct_here, tile0, mh * MTA, 1, wave, lane,
+                                ch);
 }
 
 template <int MT, int PFK>
@@ -906,6 +737,36 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
             return p;
         }
         const bool row_split = !force_single_split && wgs * splits <= 128;
+        const int t32 = (N + 31) / 32;
+        // kernels_gemm_tall.hip: all row tiles (up to twelve) in one workgroup, both operands by LDS-DMA.  Same MFMAs in the
+        // same order per output tile as the kernels below, bit for bit, so the choice may follow the row count.  It needs
+        // most of the compute units at one workgroup each and a share of K that is long against its ring fill:
+        //   * wide single splits, three column tiles per workgroup (gate/up): the weights are read once, by every unit.  Before
+        //     -> this at 40 / 72 / 132 / 216 / 272 rows: 24576 x 4096 38.8 -> 36.2, 45.5 -> 39.7, 56.0 -> 50.7, 57.8 -> 55.3,
+        //     66.3 -> 63.7 us; 17920 x 1536 17.3 -> 15.0, 20.6 -> 16.4, 25.2 -> 21.4, 26.0 -> 23.6, 29.0 -> 26.4 (ten row tiles
+        //     29.7 -> 32.9: to nine).  From eleven on only where 256-column workgroups do not fit one round any
+        //     more: 340 / 440 x 24576 x 4096 129.5 -> 76.6, 134.5 -> 97.9, but 440 x 17920 x 1536 32.8 -> 43.2.
+        //   * two column tiles where K is cut into many short shares (the small model's down): 72 / 272 / 310 x 1536 x 8960 13.5 ->
+        //     11.4, 20.8 -> 17.5, 21.3 -> 18.4; 272 x 1792 x 9216 22.4 -> 18.7.  With fewer splits only up to three row tiles
+        //     and from 2048 k on: 72 x 4096 x 12288 26.8 -> 25.9, 72 x 3072 x 8192 17.5 -> 16.4; 272 x 4096 x 4096 17.5 -> 18.0,
+        //     272 x 4096 x 12288 37 -> 40, 72 x 4096 x 2048 (512 k) 8.6 -> 9.0.
+        int ct = 0;
+        if (!force_single_split) {
+            const int share = splits == 1 ? K : (units + splits - 1) / splits * SPLIT_UNIT;
+            const int t_max = splits >= 5 && share <= 1024 ? 10 : splits > 1 && share >= 2048 ? 3 : 0;
+            if (row_split && t <= t_max) ct = 2;
+            if (splits == 1 && wgs > 128 && (t <= 9 || (N + 255) / 256 * ((t + 4) / 5) > 256)) ct = 3;
+            const int n = ct ? (t32 + ct - 1) / ct * splits : 0;
+            if (share < 1024 || n < 180 || n > 256) ct = 0;
+        }
+        if (ct) {
+            p.wide = 2;
+            p.nt = ct;
+            p.splits = splits;
+            p.m_chunks = (t + 11) / 12;
+            p.mt = (t + p.m_chunks - 1) / p.m_chunks;
+            return p;
+        }
         const int per_pass = row_split ? (t + 1) / 2 : t;
         p.mt = per_pass <= 2 ? 1 : per_pass <= 4 ? 2 : per_pass <= 6 ? 3 : 5;      // per wave (wide kernel)
         int ctl = p.mt == 5 ? 9 : 2 * p.mt;
@@ -962,7 +823,9 @@ void launch_gemm_bf16(const bf16_t *a, const bf16_t *w, float *out, int M, int N
                       int out_row_major, hipStream_t st, const ChooseArgs *choose) {
     ChooseArgs ch = {};
     if (choose && out_row_major == GEMM_EPI_ARGMAX) ch = *choose;
-    if (p.rows) {
+    if (p.wide == 2) {
+        launch_gemm_bf16_tall(a, w, out, M, N, K, p, out_row_major, st);
+    } else if (p.rows) {
         launch_gemm_bf16_rows(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.mid && (out_row_major == GEMM_EPI_TILED || out_row_major == GEMM_EPI_SWIGLU)) {
         launch_gemm_bf16_mid(a, w, out, M, N, K, p, out_row_major == GEMM_EPI_SWIGLU, st);

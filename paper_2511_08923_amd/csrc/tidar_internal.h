@@ -198,7 +198,8 @@ struct GemmPlan {
     int splits;    // split-K factor
     int bk;        // K elements staged per LDS chunk
     int m_chunks;  // passes over M (grid.z)
-    int wide;      // the waves side by side, each over all row tiles of the pass (instead of 2 x 2 waves)
+    int wide;      // 0: 2 x 2 waves, 1: the waves side by side, each over all row tiles of the pass, 2: the waves over the
+                   // rows, each over all nt column tiles of the workgroup (kernels_gemm_tall.hip)
     int nw;        // waves per workgroup: 4, or 8 (side by side, one column tile each: two waves per SIMD)
     int rows;      // the many-row kernel (kernels_gemm_rows.hip): m_chunks passes of mt or mt - 1 row tiles of 32
     int mid;       // kernels_gemm_mid.hip: m_chunks passes of mt or mt - 1 row tiles of 32
@@ -235,6 +236,8 @@ void launch_gemm_bf16_rows(const bf16_t *a, const bf16_t *w_packed, float *out, 
                            int epi, hipStream_t st, const ChooseArgs &ch);
 void launch_gemm_bf16_mid(const bf16_t *a, const bf16_t *w_packed, float *out, int M, int N, int K, const GemmPlan &p,
                           bool swiglu, hipStream_t st);
+void launch_gemm_bf16_tall(const bf16_t *a, const bf16_t *w_packed, float *out, int M, int N, int K, const GemmPlan &p,
+                           int epi, hipStream_t st);
 void launch_gemm_f32(const float *a, const float *w, float *out, int M, int N, int K, int out_row_major,
                      hipStream_t st);
 
