@@ -1,6 +1,8 @@
 // Small kernels of the decode step: weight packing, row assembly + embedding gather, RMSNorm with fused
 // residual/split-K reduction, RoPE + K/V placement, SwiGLU, vocabulary argmax / Gumbel-max, verify/accept.
 // Also the fp32-mode GEMM and attention (plain ALU kernels used by the fp32 configuration).
+#include <type_traits>
+
 #include "tidar_internal.h"
 
 namespace {
@@ -748,6 +750,154 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
     }
 }
 
+// The same GEMM with its producer and its consumer folded in, for the few-row forwards of small fp32 models, which are a chain of
+// launches that cost more than their work (two layers of d = 128, 20 rows: 24 launches 89 us, with these 14 and 58):
+//   * A = rmsnorm(x + the pending partial sums of the previous GEMM) * gain.  Every workgroup sums its 16 rows over all of
+//     K for their mean squares (in registers: KI pieces of 128 k) and the first column block of each row tile writes the
+//     updated residual stream to x_out, which must not be x;
+//   * FUSE_ROPE: CT tiles are one head; Q rotated to q_out, K rotated and V into the cache pages or the scratch tiles, as
+//     rope_kv_kernel stores them (a rotation pair is CT / 2 tiles apart, in the same lane and register);
+//   * FUSE_SWIGLU: gate and up tile of the same 16 features, h into the A-fragment layout of the down projection;
+//   * FUSE_LOGITS: row-major output of the rows a sequence sends through the head.
+template <int KI, int CT, int EPI, class SG>
+__global__ __launch_bounds__(256) void gemm_f32_fused_kernel(const float *__restrict__ x, const float *__restrict__ pend,
+                                                             const float *__restrict__ gain, float eps,
+                                                             float *__restrict__ x_out, const float *__restrict__ w,
+                                                             float *__restrict__ out, int M, int N, int K, int n_rows,
+                                                             int R, int M_all, RowDesc d_any, SG sg, RopeOut ro) {
+    __shared__ float part[4][CT * 4][64];
+    __shared__ float sums[4][16];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const int row0 = blockIdx.y * 16, col0 = blockIdx.x * 16 * CT;
+    // this lane's row of A: output row row0 + n, row src of the forward
+    const int o_row = min(row0 + n, M - 1);
+    int src = o_row;
+    if (EPI == FUSE_LOGITS) {
+        const int b = o_row / n_rows;
+        src = (b + 1) * R;
+        if constexpr (kSegs<SG>) src = sg.row0[b + 1];
+        src += o_row - (b + 1) * n_rows;
+    }
+    f32x4 av[KI][2], wv[CT][2];
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    auto load_w = [&](int k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int col = col0 + 16 * j + n;
+            const bool ok = col < N && k < K;
+            const float *p = w + (ok ? (size_t)col * K + k : 0);
+            wv[j][0] = ok ? *(const f32x4_any *)p : zero;
+            wv[j][1] = ok ? *(const f32x4_any *)(p + 4) : zero;
+        }
+    };
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < KI; ++i) {
+        const int k = 128 * i + 32 * wave + 8 * g;
+        av[i][0] = av[i][1] = zero;
+        if (k < K) {
+            const float *p = x + (size_t)src * K + k;
+            av[i][0] = *(const f32x4_any *)p;
+            av[i][1] = *(const f32x4_any *)(p + 4);
+            if (pend) {
+                const float *q = pend + pt_index(k, src, M_all);
+                av[i][0] += *(const f32x4_any *)q;
+                av[i][1] += *(const f32x4_any *)(q + 4);
+            }
+        }
+    }
+    load_w(32 * wave + 8 * g);
+#pragma unroll
+    for (int i = 0; i < KI; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss += av[i][e >> 2][e & 3] * av[i][e >> 2][e & 3];
+    ss += __shfl_xor(ss, 16);
+    ss += __shfl_xor(ss, 32);
+    if (g == 0) sums[wave][n] = ss;
+    __syncthreads();
+    const float rs = rsqrtf((((sums[0][n] + sums[1][n]) + sums[2][n]) + sums[3][n]) / (float)K + eps);
+    f32x4 acc[CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) acc[j] = zero;
+#pragma unroll
+    for (int i = 0; i < KI; ++i) {
+        const int k = 128 * i + 32 * wave + 8 * g;
+        if (128 * i + 32 * wave >= K) break;           // wave-uniform
+        if (i) load_w(k);
+        if (EPI != FUSE_LOGITS && blockIdx.x == 0 && row0 + n < M && k < K) {
+            *(f32x4_any *)(x_out + (size_t)src * K + k) = av[i][0];
+            *(f32x4_any *)(x_out + (size_t)src * K + k + 4) = av[i][1];
+        }
+        const float *gp = gain + (k < K ? k : 0);
+        const f32x4 g0 = *(const f32x4_any *)gp, g1 = *(const f32x4_any *)(gp + 4);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float a = av[i][e >> 2][e & 3] * rs * (e < 4 ? g0[e & 3] : g1[e & 3]);
+#pragma unroll
+            for (int j = 0; j < CT; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, wv[j][e >> 2][e & 3], acc[j], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < CT; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part[wave][j * 4 + e][lane] = acc[j][e];
+    __syncthreads();
+    auto sum4 = [&](int i) { return ((part[0][i][lane] + part[1][i][lane]) + part[2][i][lane]) + part[3][i][lane]; };
+    // register e of tile t: row 4 * (lane / 16) + e, column 16 t + lane % 16
+    if constexpr (EPI == FUSE_LOGITS) {
+        for (int i = wave; i < CT * 4; i += 4) {
+            const int m = row0 + 4 * g + (i & 3), c = col0 + 16 * (i >> 2) + n;
+            const float v = sum4(i);
+            if (m < M && c < N) out[(size_t)m * N + c] = v;
+        }
+    } else if constexpr (EPI == FUSE_SWIGLU) {
+        const ActLayout lay = act_layout(M);
+        const int m = row0 + 4 * g + wave, f = (col0 >> 1) + n;
+        const float gt = sum4(wave), up = sum4(4 + wave);
+        if (m < M) out[af_index(m, f, lay)] = gt / (1.f + __expf(-gt)) * up;
+    } else {
+        const KvView &kv = ro.kv;
+        const int hd = 16 * CT, half = hd / 2, head = blockIdx.x, n_q = ro.n_q;
+        const int n_mtiles = (d_any.nm + 15) / 16;
+#pragma unroll
+        for (int t = 0; t < CT / 2; ++t) {
+            const int m = row0 + 4 * g + wave, i = 16 * t + n;        // rotation pair (i, i + half) of row m
+            const float lo = sum4(4 * t + wave), hi = sum4(4 * (t + CT / 2) + wave);
+            if (m >= M) continue;
+            const float c = ro.rope_cs[((size_t)m * half + i) * 2], s = ro.rope_cs[((size_t)m * half + i) * 2 + 1];
+            const float r0 = lo * c - hi * s, r1 = hi * c + lo * s;
+            if (head < n_q) {
+                float *q = out + ((size_t)m * n_q + head) * hd + i;
+                q[0] = r0;
+                q[half] = r1;
+                continue;
+            }
+            const int b = seq_of_row(d_any, sg, m);
+            int row_base;
+            const RowDesc d = seq_desc(d_any, sg, b, &row_base);
+            const int r = m - row_base, h = head < n_q + kv.n_kv ? head - n_q : head - n_q - kv.n_kv;
+            const bool is_k = head < n_q + kv.n_kv;
+            float *dst;                          // of pair element i; the other one `half` rows or values on
+            if (r < d.nc) {
+                const int L_raw = ro.prefix_len[d.seq_base + b], L = clamp_prefix(kv, L_raw, d.nc), p = L + r;
+                if (!seq_fits(kv, L_raw, d.nc)) continue;
+                const int page = kv.page_table[(size_t)(d.seq_base + b) * kv.pages_per_seq + (p >> 4)];
+                if (!page_ok(kv, page)) continue;
+                dst = is_k ? (float *)kv.k_pages + k_page_offset(kv, page, h, p & 15, i)
+                           : (float *)kv.v_pages + v_page_offset(kv, page, h, p & 15, i);
+            } else {
+                const int mm = r - d.nc;
+                const size_t tile = ((size_t)b * kv.n_kv + h) * n_mtiles + (mm >> 4);
+                dst = is_k ? ro.k_scr + (tile * 16 + (mm & 15)) * hd + i : ro.v_scr + (tile * hd + i) * 16 + (mm & 15);
+            }
+            dst[0] = is_k ? r0 : lo;
+            dst[is_k ? half : half * 16] = is_k ? r1 : hi;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ fp32 hybrid-mask attention (plain ALU)
 // One workgroup per (sequence, query head, row).  Keys come in units of 16: cache pages 0 .. ceil((L + nc) / 16) - 1,
 // then the mask rows' scratch tiles.  A wave takes four units at a time, one key per lane for the scores, one head
@@ -951,6 +1101,36 @@ void launch_gemm_f32(const float *a, const float *w, float *out, int M, int N, i
         gemm_f32_kernel<1, 1><<<dim3((N + 15) / 16, (M + 15) / 16), 256, 0, st>>>(a, w, out, M, N, K, out_row_major);
     else
         gemm_f32_kernel<2, 4><<<dim3((N + 63) / 64, (M + 31) / 32), 256, 0, st>>>(a, w, out, M, N, K, out_row_major);
+}
+
+// Every workgroup makes its own norm, so the line lies where that costs what the launch saved.  Four layers, k(k+1) rows, before ->
+// with: d 128 / 20 and 240 rows 126 -> 91, 155 -> 113 us; d 256 / 20, 72 and 240 rows 148 -> 132, 162 -> 143, 214 -> 188;
+// d 512 / 20 and 240 rows 189 -> 189, 356 -> 419; d 1024 / 20 rows 335 -> 442.
+bool gemm_f32_fuse_ok(int M, int K, int hd) {
+    return M <= kFuseF32Rows && K <= kFuseF32K && (hd == 32 || hd == 64 || hd == 128);
+}
+
+void launch_gemm_f32_fused(int epi, const float *x, const float *pend, const float *gain, float eps, float *x_out,
+                           const float *w, float *out, int M, int N, int K, int n_rows, int R, int M_all, const RowDesc &d,
+                           const Segs &sg, const RopeOut &ro, hipStream_t st) {
+    auto go = [&](auto ki, auto ct, auto e, auto segs) {
+        constexpr int KI = decltype(ki)::value, CT = decltype(ct)::value, E = decltype(e)::value;
+        gemm_f32_fused_kernel<KI, CT, E><<<dim3((N + 16 * CT - 1) / (16 * CT), (M + 15) / 16), 256, 0, st>>>(
+            x, pend, gain, eps, x_out, w, out, M, N, K, n_rows, R, M_all, d, segs, ro);
+    };
+    auto by_segs = [&](auto ki, auto ct, auto e) {
+        if (sg.n) go(ki, ct, e, sg);
+        else go(ki, ct, e, NoSegs());
+    };
+    auto by_k = [&](auto ct, auto e) {
+        if (K <= 128) by_segs(std::integral_constant<int, 1>(), ct, e);
+        else by_segs(std::integral_constant<int, kFuseF32K / 128>(), ct, e);
+    };
+    if (epi == FUSE_SWIGLU) by_k(std::integral_constant<int, 2>(), std::integral_constant<int, FUSE_SWIGLU>());
+    else if (epi == FUSE_LOGITS) by_k(std::integral_constant<int, 1>(), std::integral_constant<int, FUSE_LOGITS>());
+    else if (ro.kv.hd == 32) by_k(std::integral_constant<int, 2>(), std::integral_constant<int, FUSE_ROPE>());
+    else if (ro.kv.hd == 64) by_k(std::integral_constant<int, 4>(), std::integral_constant<int, FUSE_ROPE>());
+    else by_k(std::integral_constant<int, 8>(), std::integral_constant<int, FUSE_ROPE>());
 }
 
 void launch_pack_act(int dtype, const void *src, int M, int K, void *dst, hipStream_t st) {

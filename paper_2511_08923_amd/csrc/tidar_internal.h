@@ -241,6 +241,24 @@ void launch_gemm_bf16_tall(const bf16_t *a, const bf16_t *w_packed, float *out, 
 void launch_gemm_f32(const float *a, const float *w, float *out, int M, int N, int K, int out_row_major,
                      hipStream_t st);
 
+// The fp32 GEMM with the RMSNorm in front and RoPE + K/V placement, SwiGLU or nothing behind it (kernels_misc.hip).
+// x_out: the updated residual stream, another buffer than x (FUSE_LOGITS: not written).  pend: tiled partial sums of the previous
+// GEMM over all M_all rows, or nullptr.  FUSE_LOGITS: output rows are the last n_rows of every sequence (of R rows or of sg).
+enum { FUSE_ROPE = 0, FUSE_SWIGLU = 1, FUSE_LOGITS = 2 };
+constexpr int kFuseF32Rows = 256;      // rows up to which it is used
+constexpr int kFuseF32K = 256;         // and the widest residual stream
+struct RopeOut {                       // FUSE_ROPE: where K and V go (Q: to out)
+    KvView kv;
+    const float *rope_cs;
+    const int32_t *prefix_len;
+    int n_q;
+    float *k_scr, *v_scr;
+};
+bool gemm_f32_fuse_ok(int M, int K, int hd);
+void launch_gemm_f32_fused(int epi, const float *x, const float *pend, const float *gain, float eps, float *x_out,
+                           const float *w, float *out, int M, int N, int K, int n_rows, int R, int M_all, const RowDesc &d,
+                           const Segs &sg, const RopeOut &ro, hipStream_t st);
+
 // The narrow GEMM (a handful of rows: the one-token step, very short blocks) with its producer folded in: instead
 // of reading a ready bf16 operand, every workgroup builds the rows it multiplies itself.
 //   GEMM_FUSE_NORM: A = rmsnorm(x_in + sum of the previous GEMM's split-K partial sums) * gain, rounded to bf16 (the

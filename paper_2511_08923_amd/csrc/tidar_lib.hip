@@ -147,7 +147,9 @@ Layout make_layout(const tidar_config &c, int B, const RowDesc &d, const Segs &s
     // the fused chain of a few-row forward (see forward_rows) alternates between two residual buffers and two
     // partial-sum areas: a GEMM that folds its producer in reads one pair while it writes the other
     const bool fused_rows = c.dtype == TIDAR_BF16 && M <= kFuseMaxRows;
-    l.x2 = take(fused_rows ? (size_t)M * c.d_model * 4 : 0);
+    // (the fp32 chain alternates too; its buffer stays as M grows beyond the fused rows, so that the size grows with M)
+    const int x2_rows = c.dtype == TIDAR_F32 ? (M < kFuseF32Rows ? M : kFuseF32Rows) : fused_rows ? M : 0;
+    l.x2 = take((size_t)x2_rows * c.d_model * 4);
     l.xn = take(af_elems(M, c.d_model) * es);
     const size_t g = gemm_floats ? gemm_floats : forward_gemm_floats(c, M);
     l.gemm_out = take(g * 4);
@@ -307,6 +309,8 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
     // the GEMMs that consume them (6 launches per layer instead of 9; 5 for the one-token step, see below).
     const bool fuse = c.dtype == TIDAR_BF16 && gemm_fuse_ok(M, q_dim + 2 * kv_dim, c.d_model) &&
                       gemm_fuse_ok(M, c.d_model, q_dim) && gemm_fuse_ok(M, 2 * c.d_ff, c.d_model);
+    // The same in fp32 (5 launches per layer instead of 9): norm and RoPE around QKV, norm and SwiGLU around gate/up
+    const bool fuse32 = c.dtype == TIDAR_F32 && gemm_f32_fuse_ok(M, c.d_model, c.head_dim);
     float *x_alt = (float *)(ws + l.x2);
     float *g_cur = gout, *g_alt = (float *)(ws + l.gemm_out2);      // g_cur: where the pending partial sums are
     auto fused_norm_gemm = [&](const void *gain, const void *wmat, int N, float *dst, int epi, int *S_out) {
@@ -327,9 +331,28 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
         x = x_alt;
         x_alt = t;
     };
+    auto fused_f32 = [&](int epi, const void *gain, const void *wmat, int rows, int N, float *dst, const KvView &kvv) {
+        Prof p(ctx, KC_GEMM, st);
+        const RopeOut ro = {kvv, (const float *)(ws + l.rope_cs), prefix_len, c.n_q_heads, (float *)(ws + l.k_scr),
+                            (float *)(ws + l.v_scr)};
+        launch_gemm_f32_fused(epi, x, S_prev ? g_cur : nullptr, (const float *)gain, c.rms_eps, x_alt, (const float *)wmat,
+                              dst, rows, N, c.d_model, rows / B, d.R, M, d, sg, ro, st);
+        if (epi == FUSE_LOGITS) return;
+        float *t = x;          // the residual stream now lives in the other buffer
+        x = x_alt;
+        x_alt = t;
+    };
     for (int layer = 0; layer < c.n_layers; ++layer) {
         KvView kvv = layer_view(c, kv, layer);
         int S = 1;
+        if (fuse32) {
+            fused_f32(FUSE_ROPE, w->attn_norm[layer], w->wqkv[layer], M, q_dim + 2 * kv_dim, (float *)(ws + l.q), kvv);
+            attention(ctx, l, ws, kvv, prefix_len, d, sg, B, max_keys, ws + l.o, st);
+            gemm(ctx, ws + l.o, w->wo[layer], g_cur, M, c.d_model, q_dim, false, &S_prev, st);
+            fused_f32(FUSE_SWIGLU, w->ffn_norm[layer], w->w_gate_up[layer], M, 2 * c.d_ff, (float *)(ws + l.h), kvv);
+            gemm(ctx, ws + l.h, w->w_down[layer], g_cur, M, c.d_model, c.d_ff, false, &S_prev, st);
+            continue;
+        }
         if (fuse) {
             // reads (x, g_cur), writes the other residual buffer and the other partial-sum area
             fused_norm_gemm(w->attn_norm[layer], w->wqkv[layer], q_dim + 2 * kv_dim, g_alt, GEMM_EPI_TILED, &S);
@@ -415,15 +438,22 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
     if (head_row0 < 0) return;
     const int Rh = d.R - head_row0;
     const int Mh = B * Rh;
-    {
+    // (a head of more than 1024 tiles of 16 runs in larger ones: d 128, 240 rows, 32768 tokens 211 us
+    // with it folded, 156 without)
+    const bool fuse_head = fuse32 && (size_t)((c.vocab + 15) / 16) * ((Mh + 15) / 16) <= 1024;
+    if (!fuse_head) {
         Prof p(ctx, KC_RMSNORM, st);
         launch_rmsnorm(c.dtype, x, gout, S_prev, w->final_norm, c.rms_eps, B, Rh, M, sg, c.d_model, ws + l.xh, st);
     }
     const int pos_stride = sg.n ? Rh : d.R, pos_row0 = sg.n ? 0 : head_row0;      // see embed_rows_kernel
     float *logits = logits_dst ? logits_dst : (float *)(ws + l.logits);
+    auto head_gemm = [&]() {
+        int S = 1;
+        if (fuse_head) fused_f32(FUSE_LOGITS, w->final_norm, w->lm_head, Mh, c.vocab, logits, KvView());
+        else gemm(ctx, ws + l.xh, w->lm_head, logits, Mh, c.vocab, c.d_model, true, &S, st);
+    };
     if (score) {               // one sequence; every row's label is scored, no token is chosen
-        int S1 = 1;
-        gemm(ctx, ws + l.xh, w->lm_head, logits, Mh, c.vocab, c.d_model, true, &S1, st);
+        head_gemm();
         Prof p(ctx, KC_SCORE, st);
         launch_score_rows(logits, Mh, c.vocab, score->text, score->len, score->c0, d.nc, score->ar_out,
                           score->diff_out, st);
@@ -464,8 +494,7 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
                                (int32_t *)(ws + l.y), Rh, st);
         return;
     }
-    int S = 1;
-    gemm(ctx, ws + l.xh, w->lm_head, logits, Mh, c.vocab, c.d_model, true, &S, st);
+    head_gemm();
     {
         Prof p(ctx, KC_ARGMAX, st);
         launch_argmax_rows(logits, B, Rh, Rh, c.vocab, n_choose, (const int32_t *)(ws + l.pos), pos_stride, pos_row0,
