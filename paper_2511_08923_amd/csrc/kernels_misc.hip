@@ -151,6 +151,80 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *__restrict__ x, co
     }
 }
 
+// The same for many rows (bf16): a wave per row, four consecutive rows per workgroup, and the two workgroups of eight rows on
+// one XCD (workgroup i of a launch runs on XCD i % 8).  With one workgroup per row a 128-byte line of the output holds
+// pieces of eight rows and is written by eight workgroups on eight XCDs, a part each, and the row is read again behind
+// a workgroup barrier; here a line stays in one L2, and the row in registers (JP pieces of 8 columns per lane: up to
+// 512 JP columns), with the loads of the residual stream and of the first split in flight together.  It is bound by memory
+// (2176 x 4096 in two splits: 160 MB).  One workgroup per row -> this: 2176 x 4096 47 -> 37 us, 2048 x 4096 39.5 -> 28.4,
+// 4000 x 1536 27.1 -> 20.5, 816 x 4096 20.6 -> 17.7, 544 x 4096 14.8 -> 14.1, 544 x 1536 7.3 -> 7.1; 272 x 4096 9.7 -> 12.3.
+template <int JP, class SG>
+__global__ __launch_bounds__(256) void rmsnorm_rows_kernel(float *__restrict__ x, const float *__restrict__ part, int S,
+                                                           size_t split_stride, const bf16_t *__restrict__ gain, float eps,
+                                                           int n_rows, int R, SG sg, int d_model, int M_all, int rows,
+                                                           bf16_t *__restrict__ out, ActLayout lay) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int eight = (blockIdx.x >> 4) * 8 + (blockIdx.x & 7), half = (blockIdx.x >> 3) & 1;
+    const int o_row = eight * 8 + half * 4 + wave;
+    if (o_row >= rows) return;                      // no barrier in this kernel
+    const int b = o_row / n_rows;
+    int row = (b + 1) * R - n_rows + (o_row - b * n_rows);
+    if constexpr (kSegs<SG>) row = sg.row0[b + 1] - n_rows + (o_row - b * n_rows);
+    float *xr = x + (size_t)row * d_model;
+    float4 v[JP][2], q[JP][2];
+    auto load = [&](int sp) __attribute__((always_inline)) {
+        const float *pp = part + (size_t)sp * split_stride;
+#pragma unroll
+        for (int j = 0; j < JP; ++j) {
+            const float *s = pp + pt_index(min(8 * (lane + 64 * j), d_model - 8), row, M_all);      // clamped: a real address
+            q[j][0] = *(const float4 *)s;
+            q[j][1] = *(const float4 *)(s + 4);
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < JP; ++j) {
+        const int k = min(8 * (lane + 64 * j), d_model - 8);
+        v[j][0] = *(const float4 *)(xr + k);
+        v[j][1] = *(const float4 *)(xr + k + 4);
+    }
+    if (S > 0) load(0);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int sp = 0; sp < S; ++sp) {                // in split order
+#pragma unroll
+        for (int j = 0; j < JP; ++j)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                v[j][h].x += q[j][h].x; v[j][h].y += q[j][h].y; v[j][h].z += q[j][h].z; v[j][h].w += q[j][h].w;
+            }
+        if (sp + 1 < S) load(sp + 1);
+    }
+    float ss = 0.f;
+#pragma unroll
+    for (int j = 0; j < JP; ++j) {
+        const int k = 8 * (lane + 64 * j);
+        if (k >= d_model) continue;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            ss += v[j][h].x * v[j][h].x + v[j][h].y * v[j][h].y + v[j][h].z * v[j][h].z + v[j][h].w * v[j][h].w;
+        if (S > 0) {
+            *(float4 *)(xr + k) = v[j][0];
+            *(float4 *)(xr + k + 4) = v[j][1];
+        }
+    }
+    const float rs = rsqrtf(wave_sum(ss) / (float)d_model + eps);
+#pragma unroll
+    for (int j = 0; j < JP; ++j) {
+        const int k = 8 * (lane + 64 * j);
+        if (k >= d_model) continue;
+        const bf16x8 g = *(const bf16x8 *)(gain + k);
+        const bf16x8 o = {(bf16_t)(v[j][0].x * rs * (float)g[0]), (bf16_t)(v[j][0].y * rs * (float)g[1]),
+                          (bf16_t)(v[j][0].z * rs * (float)g[2]), (bf16_t)(v[j][0].w * rs * (float)g[3]),
+                          (bf16_t)(v[j][1].x * rs * (float)g[4]), (bf16_t)(v[j][1].y * rs * (float)g[5]),
+                          (bf16_t)(v[j][1].z * rs * (float)g[6]), (bf16_t)(v[j][1].w * rs * (float)g[7])};
+        *(bf16x8 *)(out + af_index(o_row, k, lay)) = o;
+    }
+}
+
 // ------------------------------------------------------------------ RoPE + K/V placement
 // blockIdx.x < rows: one row, blockIdx.y = slice of the row's work (Q rotation, K rotation and placement).
 // blockIdx.x >= rows: one 16-key V tile of one sequence (a cache page the causal rows touch, or a scratch tile of
@@ -1076,6 +1150,22 @@ void launch_rmsnorm(int dtype, float *x, const float *part, int S, const void *g
     int rows = B * n_rows, R = M / B;
     ActLayout mt_out = act_layout(rows);
     size_t stride = pt_split_stride(M, d_model);
+    // from where it gains on (figures at the kernel), which is also where the GEMMs change class.  (Gains are loaded 16 bytes
+    // at a time there: a caller's gain on another boundary stays with the kernel below.)
+    if (dtype == TIDAR_BF16 && rows > 480 && d_model <= 4096 && ((uintptr_t)gain & 15) == 0) {
+        auto go = [&](auto jp, auto segs) {
+            rmsnorm_rows_kernel<decltype(jp)::value><<<(rows + 63) / 64 * 16, 256, 0, st>>>(
+                x, part, S, stride, (const bf16_t *)gain, eps, n_rows, R, segs, d_model, M, rows, (bf16_t *)out, mt_out);
+        };
+        auto typed = [&](auto jp) {
+            if (sg.n) go(jp, sg);
+            else go(jp, NoSegs());
+        };
+        if (d_model <= 1536) typed(std::integral_constant<int, 3>());
+        else if (d_model <= 2048) typed(std::integral_constant<int, 4>());
+        else typed(std::integral_constant<int, 8>());
+        return;
+    }
     // a row is one workgroup's only work: with few rows the chip is empty anyway, so a row gets as many threads
     // as it has 4-column pieces (all of its loads in flight at once); with many rows the count measured no difference
     int threads = 256;
