@@ -697,13 +697,17 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a, SG sg) {
 // split keeps an integral reference.  One wave per (row, head): lane = (8-value head-dim chunk, one of 4 split
 // lanes); the split lanes share the splits between them and are folded with two shuffles.  The 16-byte result
 // goes out row-major or in the A-fragment layout of the O projection's input.
-template <class SG>
+// It is bound by the partial results (2176 rows x 32 heads in 3 splits: 109 MB), so no lane asks for more splits than there
+// are (J: with four at any count 2176 rows took 45 us, 4000 rows x 12 heads in 2 splits 28.7; with J = 1 and the rows
+// of an output line on one XCD 37.3 and 19.7).
+template <int J, class SG>
 __global__ __launch_bounds__(64) void attn_combine_kernel(const float *__restrict__ opart,
                                                           const float *__restrict__ mpart,
                                                           const float *__restrict__ lpart, RowDesc d, SG sg, int n_q,
-                                                          int n_kv, int splits, bf16_t *__restrict__ out, int out_af,
+                                                          int n_kv, int splits, int M, bf16_t *__restrict__ out, int out_af,
                                                           ActLayout lay) {
-    const int row = blockIdx.x;
+    const int row = gridDim.x != M ? line_row(blockIdx.x) : blockIdx.x;
+    if (row >= M) return;
     const int head = blockIdx.y;
     const int b = seq_of_row(d, sg, row);
     int row_base;
@@ -719,13 +723,13 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(const float *__restric
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) mmax = fmaxf(mmax, __shfl_xor(mmax, o));
     float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, den = 0.f;
-    // four splits of this split lane at a time: all their loads are issued before the first is used (an absent
-    // split re-reads the last one and is given the weight of an empty split)
-    for (int sp0 = sl; sp0 < splits; sp0 += 16) {
-        float m[4], l[4];
-        float4 a[4], c[4];
+    // J splits of this split lane at a time: all their loads are issued before the first is used (an absent split re-reads
+    // the last one and is given the weight of an empty split)
+    for (int sp0 = sl; sp0 < splits; sp0 += 4 * J) {
+        float m[J], l[J];
+        float4 a[J], c[J];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < J; ++j) {
             const int sp = sp0 + 4 * j;
             const size_t pi = base + (size_t)min(sp, splits - 1) * F;
             m[j] = mpart[pi];
@@ -736,7 +740,7 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(const float *__restric
             if (sp >= splits) m[j] = -INFINITY;
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < J; ++j) {
             if (m[j] == -INFINITY) continue;
             const float wgt = exp2f(m[j] - mmax);
             num[0] += wgt * a[j].x; num[1] += wgt * a[j].y; num[2] += wgt * a[j].z; num[3] += wgt * a[j].w;
@@ -864,10 +868,18 @@ void launch_attention_combine(const float *part, const RowDesc &d, const Segs &s
                               int splits, bf16_t *out, int out_af, hipStream_t st) {
     if (splits == 1) return;                  // the attention kernel has written the result itself
     size_t rows = (size_t)M * n_q * splits;
-    auto go = [&](auto segs) {
-        attn_combine_kernel<<<dim3(M, n_q), 64, 0, st>>>(part, part + rows * hd, part + rows * hd + rows, d, segs, n_q, n_kv,
-                                                         splits, out, out_af, act_layout(M));
+    const ActLayout lay = act_layout(M);
+    // many rows: the workgroups of the rows that share the output's lines on one XCD
+    const int blocks = out_af && M > 480 ? line_rows(M) : M;
+    auto go = [&](auto j, auto segs) {
+        attn_combine_kernel<decltype(j)::value><<<dim3(blocks, n_q), 64, 0, st>>>(
+            part, part + rows * hd, part + rows * hd + rows, d, segs, n_q, n_kv, splits, M, out, out_af, lay);
     };
-    if (sg.n) go(sg);
-    else go(NoSegs());
+    auto by_splits = [&](auto segs) {
+        if (splits <= 4) go(std::integral_constant<int, 1>(), segs);
+        else if (splits <= 8) go(std::integral_constant<int, 2>(), segs);
+        else go(std::integral_constant<int, 4>(), segs);
+    };
+    if (sg.n) by_splits(sg);
+    else by_splits(NoSegs());
 }

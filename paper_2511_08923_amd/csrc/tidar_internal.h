@@ -102,6 +102,11 @@ __host__ __device__ inline size_t af_index(int row, int k, ActLayout a) {
         return ((((size_t)(k >> 4) * a.tiles + (row >> 5)) * 64) + ((k >> 3) & 1) * 32 + (row & 31)) * 8 + (k & 7);
     return ((((size_t)(k >> 5) * a.tiles + (row >> 4)) * 64) + ((k >> 3) & 3) * 16 + (row & 15)) * 8 + (k & 7);
 }
+// A 128-byte line of the wide form holds 16 bytes of each of eight rows.  Where a workgroup makes a row, the workgroups of
+// eight rows are kept on one XCD (workgroup i of a launch runs on XCD i % 8), whose L2 then puts the line together: workgroup i
+// takes row line_row(i), of line_rows(rows) workgroups in all, if there is such a row.
+__host__ __device__ inline int line_rows(int rows) { return (rows + 63) / 64 * 64; }
+__host__ __device__ inline int line_row(int i) { return ((i >> 6) * 8 + (i & 7)) * 8 + ((i >> 3) & 7); }
 // (the narrow form is laid out in whole k steps of 32, the wide one in steps of 16: a ragged K takes a whole step)
 __host__ __device__ inline size_t af_elems(int rows, int K) { return (size_t)((rows + 31) / 32) * 32 * ((K + 31) / 32 * 32); }
 // Layout of every GEMM output except the logits: [split][32-column tile][row][32] fp32.  A row's share of a tile
