@@ -6,8 +6,9 @@
 // per step, so the kernel is a weight streamer with MFMA attached.
 //   * W lives in HBM as the register image of the 32x32x16 MFMA B operand
 //     ([k step of 16][32-column tile][lane][8]); a wave's load of one fragment is one fully coalesced 1 KiB read
-//     that goes straight to VGPRs through a ring many k steps deep.  Weights never pass through LDS.  The k
-//     step is the outer index so that the workgroups, which all advance through K at the same pace, read one
+//     that goes straight to VGPRs through a ring many k steps deep (up to 32 rows: into an LDS ring that the
+//     workgroup's waves share).  The k step is the outer index so that the workgroups, which all advance through K at
+//     the same pace, read one
 //     contiguous front of the matrix.
 //   * A lives in memory as the register image of the MFMA A operand (see ActLayout): the slice a workgroup
 //     needs for a chunk of K is one contiguous block and its LDS image reads back conflict-free.
@@ -15,9 +16,9 @@
 //     offset, which the hardware answers with zeros and no memory traffic.  The steady-state loop therefore
 //     has no branches, and the compiler can keep exact in-flight counts (vmcnt(n), not vmcnt(0)) on the ring;
 //     sched_barrier pins each reload right behind the MFMAs that free its slot.
-//   * M <= 32: 16x16x32 MFMA (fewer pad rows), no LDS, no barriers; a wave streams its 32 columns and the A
-//     fragments through two register rings.  M > 32: 32x32x16 MFMA (half the operand reads of 16x16x32 per
-//     product; a bare loop with few accumulators measured 2.2 vs 1.2 PFLOP/s), A staged through LDS once per workgroup and prefetched into
+//   * M <= 32: 16x16x32 MFMA (fewer pad rows), both operands through LDS (gemm_bf16_few_kernel).  M > 32: 32x32x16 MFMA
+//     (half the operand reads of 16x16x32 per product; a bare loop with few accumulators measured 2.2 vs 1.2 PFLOP/s),
+//     A staged through LDS once per workgroup and prefetched into
 //     registers ahead of the MFMAs; 4 waves either as a 2 x 2 grid over 128 columns (two row halves x two
 //     64-column groups: launches without a row split), or side by side, every wave over all row tiles of the pass
 //     (no weight fragment is then loaded by two waves): eight waves over 256 columns for single-split grids, four over
@@ -36,6 +37,7 @@
 // = row 4*(l/16)+i, column l%16.   32x32x16: A lane l = row l%32, k slots 8*(l/32)..+7; B lane l = column l%32;
 // D lane l register i = row 8*(i/4) + 4*(l/32) + i%4, column l%32.
 #include "gemm_device.h"
+#include "lds_dma.h"
 
 namespace {
 
@@ -85,7 +87,7 @@ __device__ inline void store_tiles(const f32x4 (&acc)[MTW][NT], float *out, int 
         }
         return;
     }
-    if (out_row_major == GEMM_EPI_SWIGLU) {
+    if (NT == 2 && out_row_major == GEMM_EPI_SWIGLU) {
         // the wave's two 16-column tiles are gate and up of the same 16 features (tile0 is even): a lane holds both
         // values of (row, feature), so h = silu(gate) * up needs no data movement; it is stored as bf16 in the
         // A-fragment layout of the next GEMM
@@ -97,7 +99,7 @@ __device__ inline void store_tiles(const f32x4 (&acc)[MTW][NT], float *out, int 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int row = (mt0 + mt) * 16 + (lane >> 4) * 4 + i;
-                    const float g = acc[mt][0][i], u = acc[mt][1][i];
+                    const float g = acc[mt][0][i], u = acc[mt][NT - 1][i];
                     // a division, as in swiglu_kernel: v_rcp_f32 flushes silu below g = -87.3 and is an ulp off above
                     const float h = g / (1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
                     if (row < M) ho[af_index(row, (tile0 >> 1) * 16 + (lane & 15), lay)] = (bf16_t)h;
@@ -126,78 +128,10 @@ __device__ inline void store_tiles(const f32x4 (&acc)[MTW][NT], float *out, int 
     }
 }
 
-// ------------------------------------------------------------------ M <= 32: register rings only
-template <int MT, int PFK>
-__global__ __launch_bounds__(256) void gemm_bf16_small_kernel(const bf16_t *__restrict__ a,
-                                                              const bf16_t *__restrict__ w, float *__restrict__ out,
-                                                              int M, int N, int K, int splits, int out_row_major,
-                                                              ChooseArgs ch) {
-    constexpr int NT = 2;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n_tiles = N >> 4, m_tiles = (M + 15) >> 4;
-    const SplitRange sr = split_range(K, splits, blockIdx.y);
-    const int tile0 = (blockIdx.x * 4 + wave) * NT;
-    if (tile0 >= n_tiles) return;                              // no barriers in this kernel
-    const __amdgpu_buffer_rsrc_t ra = make_rsrc(a, (size_t)(K >> 5) * m_tiles * 1024);
-    const __amdgpu_buffer_rsrc_t rw = make_rsrc(w, (size_t)((N + 31) / 32) * 32 * K * 2);
-    // byte offsets at k step 0; one k step further is n_tiles (resp. m_tiles) KiB on
-    // W is stored for the 32x32x16 form; two of its k steps hold the 32 k of one 16x16x32 step.  Lane (n, g)
-    // of the B operand takes its 8 values from stored k step 2Q + g/2, stored lane (g%2)*32 + 16*half + n:
-    // k slot g then covers k = 32Q + 8g .. +7, the same slots the narrow A layout gives lane group g.
-    const int t32 = (N + 31) >> 5;
-    const int n = lane & 15, g = lane >> 4;
-    int w_off[NT], a_off[MT];
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-        w_off[j] = (tile0 + j < n_tiles)
-                       ? ((((g >> 1) * t32 + ((tile0 + j) >> 1)) * 64) + (g & 1) * 32 + ((tile0 + j) & 1) * 16 + n) * 16
-                       : OOB;
-#pragma unroll
-    for (int i = 0; i < MT; ++i) a_off[i] = (i < m_tiles) ? (i * 64 + lane) * 16 : OOB;
-    const int w_step = 2 * t32 * 1024, a_step = m_tiles * 1024;
-    auto ld_w = [&](int j, int q) {
-        return buf_load(rw, (q < sr.q1 && w_off[j] != OOB) ? w_off[j] + q * w_step : OOB);
-    };
-    auto ld_a = [&](int i, int q) {
-        return buf_load(ra, (q < sr.q1 && a_off[i] != OOB) ? a_off[i] + q * a_step : OOB);
-    };
-
-    f32x4 acc[MT][NT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    bf16x8 wbuf[PFK][NT], abuf[PFK][MT];
-#pragma unroll
-    for (int s = 0; s < PFK; ++s) {
-#pragma unroll
-        for (int j = 0; j < NT; ++j) wbuf[s][j] = ld_w(j, sr.q0 + s);
-#pragma unroll
-        for (int i = 0; i < MT; ++i) abuf[s][i] = ld_a(i, sr.q0 + s);
-    }
-    for (int qb = sr.q0; qb < sr.q1; qb += PFK) {
-#pragma unroll
-        for (int s = 0; s < PFK; ++s) {
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(abuf[s][i], wbuf[s][j], acc[i][j], 0, 0, 0);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) wbuf[s][j] = ld_w(j, qb + s + PFK);
-#pragma unroll
-            for (int i = 0; i < MT; ++i) abuf[s][i] = ld_a(i, qb + s + PFK);
-            // keep each slot's reload right behind its use: hoisting or sinking it shortens the ring
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-    store_tiles<MT, NT>(acc, out, blockIdx.y, M, N, tile0, n_tiles, 0, lane, out_row_major, ch);
-}
-
 // ------------------------------------------------------------------ M <= 4: the same, its producer folded in
 // The A operand is built by the workgroup itself (see FuseArgs) into LDS as plain bf16 rows of its share of K; a
-// lane's fragment is then one 16-byte LDS read (lanes of rows that do not exist take zeros).  W streams through the
-// same register ring, whose first loads are in flight while the prologue runs.
+// lane's fragment is then one 16-byte LDS read (lanes of rows that do not exist take zeros).  W streams through a register
+// ring, whose first loads are in flight while the prologue runs.
 template <int FUSE>
 __global__ __launch_bounds__(256) void gemm_bf16_small_fused_kernel(FuseArgs f, const bf16_t *__restrict__ w,
                                                                     float *__restrict__ out, int M, int N, int K,
@@ -417,6 +351,86 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_fused_kernel(FuseArgs f, 
     store_tiles<MT, NT>(acc, out, blockIdx.y, M, N, tile0, n_tiles, 0, lane, epi, none);
 }
 
+// ------------------------------------------------------------------ M <= 32: both operands through LDS
+// A workgroup's four waves share both operands through LDS, where they go straight from memory (buffer_load ... lds), a ring of
+// four chunks of 64 k (80 KB with CT = 4: two workgroups per compute unit, one fills its ring while the other ends).  MT row
+// tiles of 16 x CT column tiles of 32: with two row tiles a wave takes one of them and every other column tile, with one row tile
+// (CT = 4) a column tile or (CT = 2) half a column tile.  It is bound by the weight stream: 6 and 20 x 24576 x 4096 32.2 and 33.1 us
+// (6.1 TB/s; with every wave streaming its own columns and all of A through register rings 35.7 and 42.3), 6 x 2048 x 1536 5.9 ->
+// 4.3, 6 x 17920 x 1536 15.1 -> 13.1, 20 x 17920 x 1536 18.0 -> 14.2, 20 x 151936 x 4096 247 -> 226.  Eight chunks instead of
+// four 34.2 and 225 us (one workgroup per unit), three 36.3 and 229.
+constexpr int FEW_CHUNKS = 4;
+template <int MT, int CT>
+__global__ __launch_bounds__(256) void gemm_bf16_few_kernel(const bf16_t *__restrict__ a, const bf16_t *__restrict__ w,
+                                                            float *__restrict__ out, int M, int N, int K, int splits,
+                                                            int epi, ChooseArgs ch) {
+    constexpr int P = FEW_CHUNKS, LOADS = CT + 1;
+    constexpr int CHUNK = 4 * (CT + 1) * 1024;                      // W [k step of 16][column tile], then A [k step of 32][row tile]
+    constexpr int NJ = CT * MT / 4 > 0 ? CT * MT / 4 : 1;           // column tiles (CT = 2, MT = 1: halves) of a wave
+    constexpr int NH = CT * MT >= 4 ? 2 : 1;                        // halves of a column tile a wave takes
+    static_assert(P * LOADS < 64, "the loads in flight are counted in six bits");
+    extern __shared__ __attribute__((aligned(16))) unsigned char few_smem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int mh = MT == 2 ? wave & 1 : 0, ng = MT == 2 ? wave >> 1 : NH == 2 ? wave : wave >> 1, h0 = NH == 2 ? 0 : wave & 1;
+    constexpr int STEP = MT == 2 ? 2 : 4;
+    const int t32 = (N + 31) >> 5, tile0 = blockIdx.x * CT;
+    const SplitRange sr = split_range(K, splits, blockIdx.y);
+    const int n_steps = max(sr.q1 - sr.q0, 0), n_chunks = (n_steps + 1) >> 1;      // steps of 32 k
+    const int4v da = raw_desc(a, (size_t)(K >> 5) * MT * 1024), dw = raw_desc(w, (size_t)t32 * 32 * K * 2);
+    const unsigned dst0 = lds_address(few_smem);
+    // a wave brings one of a chunk's four k steps of W and one of its 2 MT fragments of A; what does not exist is asked for
+    // too, out of bounds: zeros, and the same number of loads in flight everywhere
+    auto issue = [&](int c, int buf) __attribute__((always_inline)) {
+        const bool ok = 2 * c + (wave >> 1) < n_steps, ok_a = MT == 2 ? ok : wave < 2 && 2 * c + wave < n_steps;
+        const unsigned dst = dst0 + buf * CHUNK;
+        dma16(dst + (4 * CT + wave) * 1024, ok_a ? lane * 16 : OOB, da, ok_a ? ((sr.q0 + 2 * c) * MT + wave) * 1024 : 0);
+        const int src = ((2 * sr.q0 + 4 * c + wave) * t32 + tile0) * 1024;
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+            dma16(dst + (wave * CT + j) * 1024, ok && tile0 + j < t32 ? lane * 16 : OOB, dw, ok ? src + j * 1024 : 0);
+    };
+    f32x4 acc[NJ][1][NH];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int h = 0; h < NH; ++h) acc[j][0][h] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const unsigned char *fw = few_smem + ((lane >> 5) * CT + ng) * 1024 + ((lane >> 4) & 1) * 512 + h0 * 256 + (lane & 15) * 16;
+    const unsigned char *fa = few_smem + (4 * CT + mh) * 1024 + lane * 16;
+#pragma unroll
+    for (int c = 0; c < P - 1; ++c) issue(c, c);
+    int buf = 0, far = P - 1;
+    for (int c = 0; c < n_chunks; ++c) {
+        wait_loads<(P - 2) * LOADS>();
+        lds_barrier();                   // chunk c has landed for everyone, chunk c-1 has been read by everyone
+        bf16x8 af[2], wf[2][NJ][NH];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            af[kk] = *(const bf16x8 *)(fa + buf * CHUNK + kk * MT * 1024);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+                    wf[kk][j][h] = *(const bf16x8 *)(fw + buf * CHUNK + (2 * kk * CT + STEP * j) * 1024 + h * 256);
+        }
+        issue(c + P - 1, far);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+                    acc[j][0][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[kk], wf[kk][j][h], acc[j][0][h], 0, 0, 0);
+        far = buf;
+        buf = buf + 1 == P ? 0 : buf + 1;
+    }
+    wait_loads<0>();                     // nothing may land in LDS that is another workgroup's by then
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int t = 2 * (tile0 + ng + STEP * j) + h0;
+        if (t < (N >> 4)) store_tiles<1, NH>(acc[j], out, blockIdx.y, M, N, t, N >> 4, mh, lane, epi, ch);
+    }
+}
+
 // ------------------------------------------------------------------ 32 < M: 32x32x16 MFMA, A through LDS
 // MTA: 32-row tiles per wave.  2 x 2 waves (WIDE false): the workgroup pass covers CTL = 2*MTA row tiles (9 when
 // MTA is 5: the second row half then repeats a tile whose results are dropped) of 128 columns.  WIDE: four waves
@@ -571,11 +585,19 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
                                 ch);
 }
 
-template <int MT, int PFK>
-void launch_small(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int row_major,
-                  hipStream_t st, const ChooseArgs &ch) {
-    dim3 grid((N + 127) / 128, p.splits, 1);
-    gemm_bf16_small_kernel<MT, PFK><<<grid, 256, 0, st>>>(a, w, out, M, N, K, p.splits, row_major, ch);
+template <int MT, int CT>
+void launch_few(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi, hipStream_t st,
+                const ChooseArgs &ch) {
+    constexpr int SMEM = FEW_CHUNKS * 4 * (CT + 1) * 1024;
+    static bool attr_set[64] = {};           // LDS above 64 KiB has to be granted per kernel and device
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    if (dev < 0 || dev >= 64 || !attr_set[dev]) {
+        (void)hipFuncSetAttribute((const void *)gemm_bf16_few_kernel<MT, CT>, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+        if (dev >= 0 && dev < 64) attr_set[dev] = true;
+    }
+    gemm_bf16_few_kernel<MT, CT><<<dim3(((N + 31) / 32 + CT - 1) / CT, p.splits), 256, SMEM, st>>>(a, w, out, M, N, K,
+                                                                                                 p.splits, epi, ch);
 }
 
 template <int MTA, bool WIDE, int NT = 2, int NW = 4>
@@ -832,8 +854,14 @@ void launch_gemm_bf16(const bf16_t *a, const bf16_t *w, float *out, int M, int N
     } else if (p.mid) {        // no vocabulary epilogue there: those take a single split
         launch_gemm_bf16(a, w, out, M, N, K, plan_gemm_bf16(M, N, K, true), out_row_major, st, choose);
     } else if (M <= 32) {
-        if (p.mt == 1) launch_small<1, 16>(a, w, out, M, N, K, p, out_row_major, st, ch);
-        else launch_small<2, 8>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        // Two column tiles per workgroup where partial sums of a narrow product leave compute units idle otherwise, four where there
+        // are enough of them (and for the epilogues that need gate and up, or a column group, in one wave).  Four / two at 6 rows:
+        // 2048 x 1536 5.2 / 4.3 us, 1536 x 8960 7.9 / 7.2, 4096 x 12288 22.3 / 21.2, 4096 x 4096 9.4 / 9.3, 6144 x 4096 11.5 / 12.4.
+        const bool two = out_row_major == GEMM_EPI_TILED && N < 6144;
+        if (p.mt == 1 && two) launch_few<1, 2>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        else if (p.mt == 1) launch_few<1, 4>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        else if (two) launch_few<2, 2>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        else launch_few<2, 4>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1 && p.nw == 8) {     // eight waves side by side, one column tile each
         launch_large<5, true, 1, 8>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1 && p.mt == 1) {
