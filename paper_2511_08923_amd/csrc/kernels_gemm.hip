@@ -634,6 +634,16 @@ void launch_large(const bf16_t *a, const bf16_t *w, float *out, int M, int N, in
 
 }  // namespace
 
+// Clamps a split count to the units there are and drops empty trailing splits.
+static int fit_splits(int want, int units) {
+    want = want < 1 ? 1 : want > units ? units : want;
+    const int per = (units + want - 1) / want;
+    return (units + per - 1) / per;
+}
+
+// Products of up to 32 rows that run with two column tiles per workgroup (figures at the launch)
+static bool few_rows_two(int N) { return N < 6144; }
+
 bool gemm_fuse_ok(int M, int N, int K) { return M >= 1 && M <= kFuseMaxRows && K <= kFuseMaxK && K % 32 == 0 && N % 16 == 0; }
 
 void launch_gemm_bf16_fused(const FuseArgs &f, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p,
@@ -647,6 +657,15 @@ void launch_gemm_bf16_fused(const FuseArgs &f, const bf16_t *w, float *out, int 
         gemm_bf16_small_fused_kernel<GEMM_FUSE_COMBINE><<<grid, 256, smem, st>>>(f, w, out, M, N, K, p.splits, epi);
 }
 
+GemmPlan plan_gemm_bf16_fused(int M, int N, int K, bool force_single_split) {
+    GemmPlan p = plan_gemm_bf16(M, N, K, force_single_split);
+    if (!force_single_split) {          // column blocks of 128 whatever N: O of the 8B shape with half the splits 13.0 -> 15.0 us
+        const int wgs = (N + 127) / 128, units = (K + SPLIT_UNIT - 1) / SPLIT_UNIT;
+        p.splits = wgs < 128 ? fit_splits((256 + wgs / 2) / wgs, units) : 1;
+    }
+    return p;
+}
+
 GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
     GemmPlan p;
     p.nt = 2;
@@ -658,18 +677,17 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
     p.mid = 0;
     const int wgs = (N + 127) / 128;
     const int units = (K + SPLIT_UNIT - 1) / SPLIT_UNIT;
-    auto fit = [&](int want) {                   // clamp to the units there are and drop empty trailing splits
-        want = want < 1 ? 1 : want > units ? units : want;
-        int per = (units + want - 1) / want;
-        return (units + per - 1) / per;
-    };
+    auto fit = [&](int want) { return fit_splits(want, units); };
     int splits = 1;
     if (M <= 32) {
         p.mt = M <= 16 ? 1 : 2;                  // 16-row tiles per wave (narrow kernel)
         p.m_chunks = 1;
         // nearest count that brings the grid to about one wave of CUs; from half of that on a single split, which saves
         // the partial sums and, for gate/up, the SwiGLU launch (1.5B shape, 6 rows: 17.1 + 4.0 us in two splits)
-        if (!force_single_split && wgs < 128) splits = fit((256 + wgs / 2) / wgs);
+        // (narrow products run in column blocks of 64: as many splits as those need to fill the chip.  A split is a copy of the
+        // output that the next kernel reads, every workgroup of it where that folds the norm in)
+        const int blocks = few_rows_two(N) ? (N + 63) / 64 : wgs;
+        if (!force_single_split && wgs < 128) splits = fit((256 + blocks / 2) / blocks);
     } else {
         // Partial sums are the expensive part of a split (each one is M x N floats written and read again), so
         // the column blocks are split over K only until about half the CUs are busy; the rest of the chip is
@@ -857,7 +875,7 @@ void launch_gemm_bf16(const bf16_t *a, const bf16_t *w, float *out, int M, int N
         // Two column tiles per workgroup where partial sums of a narrow product leave compute units idle otherwise, four where there
         // are enough of them (and for the epilogues that need gate and up, or a column group, in one wave).  Four / two at 6 rows:
         // 2048 x 1536 5.2 / 4.3 us, 1536 x 8960 7.9 / 7.2, 4096 x 12288 22.3 / 21.2, 4096 x 4096 9.4 / 9.3, 6144 x 4096 11.5 / 12.4.
-        const bool two = out_row_major == GEMM_EPI_TILED && N < 6144;
+        const bool two = out_row_major == GEMM_EPI_TILED && few_rows_two(N);
         if (p.mt == 1 && two) launch_few<1, 2>(a, w, out, M, N, K, p, out_row_major, st, ch);
         else if (p.mt == 1) launch_few<1, 4>(a, w, out, M, N, K, p, out_row_major, st, ch);
         else if (two) launch_few<2, 2>(a, w, out, M, N, K, p, out_row_major, st, ch);

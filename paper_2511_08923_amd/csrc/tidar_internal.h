@@ -290,6 +290,7 @@ struct FuseArgs {
     int R, n_q, n_kv, a_splits;
 };
 bool gemm_fuse_ok(int M, int N, int K);
+GemmPlan plan_gemm_bf16_fused(int M, int N, int K, bool force_single_split);
 void launch_gemm_bf16_fused(const FuseArgs &f, const bf16_t *w_packed, float *out, int M, int N, int K,
                             const GemmPlan &p, int epi, hipStream_t st);
 // plain row-major [M][K] -> A-fragment layout, and tiled partial sums -> plain row-major [M][N]

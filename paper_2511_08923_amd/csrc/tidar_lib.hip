@@ -107,9 +107,12 @@ size_t gemm_out_floats(const tidar_config &c, int M, int N, int K) {
         GemmPlan p = plan_gemm_bf16(m, N, K, false);
         size_t v = (size_t)p.splits * pt_split_stride(m, N);
         if (v > best) best = v;
+        if (m > kFuseMaxRows) return;
+        v = (size_t)plan_gemm_bf16_fused(m, N, K, false).splits * pt_split_stride(m, N);
+        if (v > best) best = v;
     };
-    const int bounds[6] = {16, 32, 80, 144, 480, M};
-    for (int i = 0; i < 6; ++i) consider(bounds[i]);
+    const int bounds[7] = {kFuseMaxRows, 16, 32, 80, 144, 480, M};
+    for (int i = 0; i < 7; ++i) consider(bounds[i]);
     for (int m = 512; m < M; m += 256) consider(m);      // the largest row count of each pass count
     return best;
 }
@@ -315,7 +318,7 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
     float *g_cur = gout, *g_alt = (float *)(ws + l.gemm_out2);      // g_cur: where the pending partial sums are
     auto fused_norm_gemm = [&](const void *gain, const void *wmat, int N, float *dst, int epi, int *S_out) {
         Prof p(ctx, KC_GEMM, st);
-        GemmPlan gp = plan_gemm_bf16(M, N, c.d_model, epi == GEMM_EPI_SWIGLU);
+        GemmPlan gp = plan_gemm_bf16_fused(M, N, c.d_model, epi == GEMM_EPI_SWIGLU);
         FuseArgs f = {};
         f.kind = GEMM_FUSE_NORM;
         f.x_in = x;
@@ -387,7 +390,7 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
                                        rope.part ? &rope : nullptr);
         if (fuse && a_splits > 1) {
             Prof p(ctx, KC_GEMM, st);
-            GemmPlan gp = plan_gemm_bf16(M, c.d_model, q_dim, false);
+            GemmPlan gp = plan_gemm_bf16_fused(M, c.d_model, q_dim, false);
             const size_t rows = (size_t)B * c.n_kv_heads * a_splits * (c.n_q_heads / c.n_kv_heads) * d.R;
             FuseArgs f = {};
             f.kind = GEMM_FUSE_COMBINE;
