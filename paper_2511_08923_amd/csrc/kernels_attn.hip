@@ -27,6 +27,7 @@
 // Keys come in units of 16: cache pages 0 .. ceil((L+nc)/16)-1, then the mask rows' scratch tiles.  Pages that
 // lie wholly below L need no mask at all (every row sees the whole prefix); everything else goes through the
 // (row, key) predicate and a per-(query tile, key pair) skip when nothing is visible.
+#include <algorithm>
 #include <type_traits>
 
 #include "lds_dma.h"
@@ -54,6 +55,48 @@ struct AttnArgs {
     ActLayout lay;
     AttnRope rp;               // ROPE kernels only
 };
+
+// The order in which a launch's (query chunk, key split) items are dealt to its workgroups, split << 10 | chunk: see
+// make_order.  PlainOrder: by index.
+constexpr int kMaxOrder = 512;
+struct WorkOrder {
+    int n;
+    uint32_t item2[kMaxOrder / 2];        // two to a word: a dynamic index into the kernel arguments loads whole words
+};
+struct PlainOrder {};
+
+// Key-pair iterations a workgroup can need at all: cache units up to the furthest key any of its rows sees, then the
+// mask units of its rows' own blocks, [0, a1) and [b0, b1) with a1 <= b0.  (Rows of one query head only; a workgroup
+// that straddles two heads keeps the whole range.)  Inside a prefill or scoring pass most of the range falls away:
+// causal rows see neither the later rows of the pass nor any mask row, a mask block only the text before it and
+// itself.  Iterations are dropped whole, so the pairing of keys into iterations and splits is untouched.
+struct KeySpan {
+    int a1, b0, b1;
+};
+__host__ __device__ inline int imin(int x, int y) { return x < y ? x : y; }
+__host__ __device__ inline int imax(int x, int y) { return x > y ? x : y; }
+__host__ __device__ inline KeySpan key_span(const RowDesc &d, int L, int F, int t0, int t1) {
+    const int n_cache_units = (L + d.nc + 15) >> 4, n_it = (n_cache_units + ((d.nm + 15) >> 4) + 1) >> 1;
+    const int f_lo = t0 * 32, f_hi = imin(F, t1 * 32) - 1;
+    const int h_lo = f_lo / d.R, h_hi = f_hi / d.R;
+    if (h_lo != h_hi) return {n_it, n_it, n_it};
+    const int r_lo = f_lo - h_lo * d.R, r_hi = f_hi - h_lo * d.R;
+    int vis_max = imin(r_hi, d.nc - 1) + 1;                      // the causal rows among them
+    int um0 = 0, um1 = 0;                                        // mask units [um0, um1)
+    if (r_hi >= d.nc) {
+        const int j_lo = (imax(r_lo, d.nc) - d.nc) / d.bl, j_hi = (r_hi - d.nc) / d.bl;
+        if (r_lo >= d.nc) vis_max = 0;
+        vis_max = imax(vis_max, d.cond0 + j_hi * d.cstride);
+        um0 = (j_lo * d.bl) >> 4;
+        um1 = (imin((j_hi + 1) * d.bl, d.nm) + 15) >> 4;
+    }
+    KeySpan k;
+    const int uc1 = imin(n_cache_units, (L + imin(vis_max, d.nc) + 15) >> 4);
+    k.a1 = (uc1 + 1) >> 1;
+    k.b0 = imax(k.a1, (n_cache_units + um0) >> 1);
+    k.b1 = um1 > um0 ? imax(k.b0, (n_cache_units + um1 + 1) >> 1) : k.b0;
+    return k;
+}
 
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
@@ -225,8 +268,8 @@ __device__ inline bool attn_block_fixed_ref(const bf16_t *k_lds, const bf16_t *v
 }
 
 // QT: 32-row query tiles per wave.
-template <int QT, bool PRIO, bool ROPE, class SG>
-__global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a, SG sg) {
+template <int QT, bool PRIO, bool ROPE, class SG, class ORD>
+__global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a, SG sg, ORD ord) {
     constexpr int NBUF = 3, K_TILE = TILE, V_TILE = TILE;
     __shared__ __attribute__((aligned(16))) bf16_t k_lds[NBUF][K_TILE];
     __shared__ __attribute__((aligned(16))) bf16_t v_lds[NBUF][V_TILE];
@@ -239,8 +282,16 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a, SG sg) {
     // does not change that).  Where the (sequence, kv head) groups divide evenly over the XCDs, or the XCDs over
     // the groups, the query chunks of one group are dealt to one XCD (or to 8 / groups of them), whose L2 then
     // fetches that head's K and V once instead of once per XCD that happens to run one of its chunks.
-    int grp, chunk;
-    if (a.xcd_q == 0) {
+    int grp, chunk, split = blockIdx.y;
+    if constexpr (sizeof(ORD) == sizeof(WorkOrder)) {
+        const int xcd = blockIdx.x & 7;
+        const int i = (blockIdx.x >> 3) * a.xcd_q + xcd % a.xcd_q;
+        if (i >= ord.n) return;                      // padding of the last round (whole workgroup)
+        const unsigned item = (ord.item2[i >> 1] >> (16 * (i & 1))) & 0xffffu;
+        grp = xcd / a.xcd_q;
+        chunk = item & 1023;
+        split = item >> 10;
+    } else if (a.xcd_q == 0) {
         chunk = blockIdx.x % a.n_chunks;
         grp = blockIdx.x / a.n_chunks;
     } else if (a.n_groups >= 8) {
@@ -255,7 +306,6 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a, SG sg) {
     }
     const int g = grp % a.kv.n_kv;
     const int b = grp / a.kv.n_kv;
-    const int split = blockIdx.y;
     int row_base;                                    // the sequence's first row of the forward
     const RowDesc d = seq_desc(a.d, sg, b, &row_base);
     const int F = a.group * d.R;                     // flattened query rows of this kv head
@@ -277,37 +327,10 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a, SG sg) {
     const int per = a.per;
     const int it0 = min(n_it, split * per);
     const int it1 = (split == a.splits - 1) ? n_it : min(n_it, it0 + per);
-    // Key-pair iterations this workgroup can need at all: cache units up to the furthest key any of its rows
-    // sees, then the mask units of its rows' own blocks.  (Rows of one query head only; a workgroup that straddles
-    // two heads keeps the whole range.)  Inside a prefill or scoring pass most of the range falls away: causal
-    // rows see neither the later rows of the pass nor any mask row, a mask block only the text before it and
-    // itself.  Iterations are dropped whole, so the pairing of keys into iterations and splits is untouched.
-    int itA1 = n_it, itB0 = n_it, itB1 = n_it;       // [it0, itA1) and [itB0, itB1), itA1 <= itB0
-    {
-        const int f_lo = t0 * 32, f_hi = min(F, t1 * 32) - 1;
-        const int h_lo = f_lo / d.R, h_hi = f_hi / d.R;
-        if (h_lo == h_hi) {
-            const int r_lo = f_lo - h_lo * d.R, r_hi = f_hi - h_lo * d.R;
-            int vis_max = min(r_hi, d.nc - 1) + 1;                       // the causal rows among them
-            int um0 = 0, um1 = 0;                                        // mask units [um0, um1)
-            if (r_hi >= d.nc) {
-                const int j_lo = (max(r_lo, d.nc) - d.nc) / d.bl, j_hi = (r_hi - d.nc) / d.bl;
-                if (r_lo >= d.nc) vis_max = 0;
-                vis_max = max(vis_max, d.cond0 + j_hi * d.cstride);
-                um0 = (j_lo * d.bl) >> 4;
-                um1 = (min((j_hi + 1) * d.bl, n_mask) + 15) >> 4;
-            }
-            const int uc1 = min(n_cache_units, (L + min(vis_max, d.nc) + 15) >> 4);
-            itA1 = (uc1 + 1) >> 1;
-            itB0 = max(itA1, (n_cache_units + um0) >> 1);
-            itB1 = um1 > um0 ? max(itB0, (n_cache_units + um1 + 1) >> 1) : itB0;
-        } else {
-            itB0 = itB1 = n_it;
-        }
-    }
+    const KeySpan ks = key_span(d, L, F, t0, t1);
     // this split's share of the two ranges, walked as one sequence of nA + nB iterations
-    const int a0 = it0, a1 = max(a0, min(it1, itA1));
-    const int b0 = max(it0, itB0), b1 = max(b0, min(it1, itB1));
+    const int a0 = it0, a1 = max(a0, min(it1, ks.a1));
+    const int b0 = max(it0, ks.b0), b1 = max(b0, min(it1, ks.b1));
     const int nA = a1 - a0, n_seq = nA + (b1 - b0);
     auto seq_it = [&](int n) { return n < nA ? a0 + n : b0 + (n - nA); };
 
@@ -767,6 +790,48 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(const float *__restric
 
 }  // namespace
 
+// The order of a single sequence's causal pass (prefill, scoring; n_groups <= 8, so that a group has 8 / q XCDs to
+// itself).  Its workgroups walk key ranges of very different length, and all of them are resident from the start or
+// nearly so: two to a compute unit, the launch takes as long as the compute unit with the most to do (a workgroup left
+// alone on its SIMDs goes on at close to twice the speed).  The dispatcher deals the first 32 of an XCD's workgroups to
+// its 32 compute units and the next 32 to the same units in the same order, so by index a unit got the same rows of two
+// query heads, twice the longest range or twice the shortest.  Here the item in second place on a unit is the shorter
+// the longer the first one is; what is left after two rounds follows with the longest first.  8B prefill of 4096
+// tokens 60416 -> 59419 us, scoring of 2000 tokens (1.5B) 17434 -> 17216.
+static WorkOrder make_order(const RowDesc &d, int group, int n_chunks, int tiles_per_chunk, int splits, int per, int L,
+                            int q) {
+    struct Item {
+        int len;
+        uint16_t id;
+    } it[kMaxOrder];
+    const int F = group * d.R, TQ = (F + 31) >> 5;
+    int n = 0;
+    for (int c = 0; c < n_chunks; ++c) {
+        const KeySpan k = key_span(d, L, F, c * tiles_per_chunk, imin(TQ, (c + 1) * tiles_per_chunk));
+        for (int s = 0; s < splits; ++s) {
+            const int lo = s * per, hi = s == splits - 1 ? 1 << 30 : lo + per;
+            const int len = imax(0, imin(hi, k.a1) - lo) + imax(0, imin(hi, k.b1) - imax(lo, k.b0));
+            it[n++] = {len, (uint16_t)(s << 10 | c)};
+        }
+    }
+    std::stable_sort(it, it + n, [](const Item &x, const Item &y) { return x.len > y.len; });
+    WorkOrder o = {};
+    o.n = n;
+    for (int x = 0; x < q; ++x) {                    // XCD x of the group's takes every q-th item
+        const int m = (n - x + q - 1) / q;
+        const int second = imin(imax(m - 32, 0), 32);                  // compute units that get two
+        for (int p = 0; p < m; ++p) {
+            int rank = p;
+            if (p < second) rank = imin(m, 64) - 2 * second + p;       // the longer halves of the pairs
+            else if (p < 32) rank = p - second;                        // those that stay alone
+            else if (p < 64) rank = imin(m, 64) - 1 - (p - 32);        // the shorter halves
+            const int i = p * q + x;
+            o.item2[i >> 1] |= (uint32_t)it[rank * q + x].id << (16 * (i & 1));
+        }
+    }
+    return o;
+}
+
 AttnPlan plan_attention(int B, int n_kv, int group, const RowDesc &d, const Segs &sg, int max_keys) {
     AttnPlan p;
     const int nc = d.nc;
@@ -815,6 +880,7 @@ AttnPlan plan_attention(int B, int n_kv, int group, const RowDesc &d, const Segs
         }
     }
     p.splits = s < 1 ? 1 : s;
+    p.max_keys = max_keys;
     p.per = (iters + 1 + p.splits - 1) / p.splits;   // +1: the kernel counts cache and scratch units separately
     return p;
 }
@@ -855,13 +921,23 @@ void launch_attention_bf16(const bf16_t *q, KvView kv, const bf16_t *k_scr, cons
     a.xcd_q = a.n_groups % 8 == 0 ? 1 : (a.n_groups < 8 && 8 % a.n_groups == 0) ? 8 / a.n_groups : 0;
     dim3 grid(a.n_groups * p.n_chunks, p.splits);
     if (a.xcd_q > 1) grid.x = 8 * ((p.n_chunks + a.xcd_q - 1) / a.xcd_q);
-    auto go = [&](auto kernel, auto segs) { kernel<<<grid, 256, 0, st>>>(a, segs); };
+    const PlainOrder plain;
+    auto go = [&](auto kernel, auto segs) { kernel<<<grid, 256, 0, st>>>(a, segs, plain); };
     const NoSegs none;
-    if (fused_rope) go(attn_bf16_kernel<1, false, true, NoSegs>, none);
-    else if (sg.n && p.tiles_per_chunk == 4) go(attn_bf16_kernel<1, true, false, Segs>, sg);
-    else if (sg.n) go(attn_bf16_kernel<1, false, false, Segs>, sg);
-    else if (p.tiles_per_chunk == 4) go(attn_bf16_kernel<1, true, false, NoSegs>, none);
-    else go(attn_bf16_kernel<1, false, false, NoSegs>, none);
+    // more workgroups than compute units (otherwise each has one to itself in any order), rows of unequal key ranges
+    const int items = p.n_chunks * p.splits;
+    if (!sg.n && d.nc >= 64 && a.n_groups <= 8 && a.xcd_q && p.tiles_per_chunk == 4 && items <= kMaxOrder &&
+        p.n_chunks < 1024 && items * a.n_groups > 256) {
+        const dim3 line(8 * ((items + a.xcd_q - 1) / a.xcd_q));
+        attn_bf16_kernel<1, true, false, NoSegs, WorkOrder><<<line, 256, 0, st>>>(
+            a, none, make_order(d, a.group, p.n_chunks, p.tiles_per_chunk, p.splits, p.per, imax(0, p.max_keys - d.R), a.xcd_q));
+        return;
+    }
+    if (fused_rope) go(attn_bf16_kernel<1, false, true, NoSegs, PlainOrder>, none);
+    else if (sg.n && p.tiles_per_chunk == 4) go(attn_bf16_kernel<1, true, false, Segs, PlainOrder>, sg);
+    else if (sg.n) go(attn_bf16_kernel<1, false, false, Segs, PlainOrder>, sg);
+    else if (p.tiles_per_chunk == 4) go(attn_bf16_kernel<1, true, false, NoSegs, PlainOrder>, none);
+    else go(attn_bf16_kernel<1, false, false, NoSegs, PlainOrder>, none);
 }
 
 void launch_attention_combine(const float *part, const RowDesc &d, const Segs &sg, int M, int n_q, int n_kv, int hd,

@@ -309,6 +309,7 @@ struct AttnPlan {
     int splits_bound;    // the most splits any key bound can give this row structure (sizes the workspace)
     int n_chunks;        // q-tile chunks per kv head
     int tiles_per_chunk;
+    int max_keys;        // the caller's bound on the key count, in steps of 256
     int per;             // key-pair iterations per split, from the caller's bound on the key count (not from the
                          // sequence's current length): a key's split then depends on its position alone
 };
