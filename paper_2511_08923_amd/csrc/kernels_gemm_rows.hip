@@ -11,8 +11,10 @@
 // and a 16x16x32 fragment is four contiguous 256-byte runs of two of those, so every read is conflict-free.
 // LDS holds four chunks of K = 32; a chunk's loads are issued more than three chunks (3000 cycles) before they are
 // needed.  With one wave per SIMD nothing else covers a stall, so everything is spread between the MFMAs: fragments
-// of the next chunk and the loads of the chunk after the next three go out a few at a time behind each row of eight
-// MFMAs, and after the one barrier of a chunk there are always fragments in registers to go on with.
+// of the next chunk and the loads of the chunk after the next three go out one at a time, each behind an MFMA of its own
+// (an MFMA occupies the matrix core for 16 cycles, the three or four operations of a row in one lump take longer: 8B step of
+// 8 sequences 40855 -> 40188 us, scoring of 2000 tokens (1.5B) 17192 -> 16859), and after the one barrier of a chunk there
+// are always fragments in registers to go on with.
 // The row passes of a launch are equally high, or differ by one row tile (the plan picks their number).
 // Measured against four waves of 256 x 64 with 32x32x16 MFMAs, weights in a register ring: 2176 x 24576 x 4096 440 -> 339
 // us (1.29 PFLOP/s), 2176 x 4096 x 12288 220 -> 165, 4000 x 17920 x 1536 248 -> 203; 23 instead of 25 ns per k of a
@@ -129,7 +131,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
     // the k loop over RA row tiles
     auto k_loop = [&](auto ra_tag) __attribute__((always_inline)) {
         constexpr int RA = decltype(ra_tag)::value, READS = CT + RA;
-        auto row = [&](int s, int i) __attribute__((always_inline)) {
+        // a row of MFMAs with the n operations op(0 .. n-1) one by one between them
+        auto row = [&](int s, int i, int n, auto op) __attribute__((always_inline)) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < CT; ++j) {
@@ -140,20 +143,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
                     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[i][j]) : "v"(wf[s][j]), "v"(af[s][i]));
                 else
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][j], af[s][i], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = (n * j + CT - 1) / CT; k < (n * (j + 1) + CT - 1) / CT; ++k) op(k);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
         };
         auto chunk = [&](int s, int c) __attribute__((always_inline)) {
-            row(s, 0);
+            row(s, 0, 0, [](int) {});
             wait_loads<(BUFS - 2) * LOADS>();
             barrier();                       // chunk c+1 has landed for everyone, chunk c has been read by everyone
 #pragma unroll
             for (int i = 1; i < RA; ++i) {
-#pragma unroll
-                for (int f = READS * (i - 1) / (RA - 1); f < READS * i / (RA - 1); ++f) read(s ^ 1, c + 1, f);
-#pragma unroll
-                for (int l = LOADS * (i - 1) / (RA - 1); l < LOADS * i / (RA - 1); ++l) load(c + BUFS, l);
-                row(s, i);
+                const int f0 = READS * (i - 1) / (RA - 1), nf = READS * i / (RA - 1) - f0;
+                const int l0 = LOADS * (i - 1) / (RA - 1), nl = LOADS * i / (RA - 1) - l0;
+                row(s, i, nf + nl, [&](int k) __attribute__((always_inline)) {
+                    if (k < nf) read(s ^ 1, c + 1, f0 + k);
+                    else load(c + BUFS, l0 + k - nf);
+                });
             }
         };
 #pragma unroll
