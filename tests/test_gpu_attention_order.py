@@ -1,5 +1,6 @@
 """Causal passes of one sequence with more attention workgroups than compute units: their (query chunk, key split) items
-are dealt out by length, so every row has to come out once whatever the order, against dense attention in 64 bits."""
+are dealt out by length, so every row has to come out once whatever the order; and passes whose key splits are folded tile by
+tile.  Against dense attention in 64 bits."""
 import math
 
 import pytest
@@ -12,8 +13,11 @@ pytestmark = pytest.mark.gpu
 # shape, causal rows, mask rows, cached keys: 8 kv heads (one XCD each) with just more than 256 items, with 65 per XCD (a
 # third round, chunks that straddle two query heads), with a ragged last chunk behind a cached prefix; 2 kv heads (four
 # XCDs each) with key splits, padding on some of the XCDs, and mask rows
+# (the last three: few workgroups but many key splits, whose partial results lie as query tiles: a last tile of 4 rows, of 12, tiles
+# that straddle two heads, more than eight splits)
 CASES = [("8b-shape", 1030, 0, 0), ("8b-shape", 2048, 16, 0), ("8b-shape", 1333, 7, 1001), ("1.5b-shape", 700, 0, 0),
-         ("1.5b-shape", 1501, 16, 300), ("1.5b-shape", 2047, 0, 4000)]
+         ("1.5b-shape", 1501, 16, 300), ("1.5b-shape", 2047, 0, 4000), ("small-gqa", 50, 0, 3000),
+         ("small-gqa", 113, 5, 900), ("8b-shape", 25, 2, 2000)]
 
 
 @pytest.mark.parametrize("name,nc,nm,L", CASES)
