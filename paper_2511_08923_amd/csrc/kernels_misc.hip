@@ -103,18 +103,25 @@ __global__ void embed_rows_kernel(const T *__restrict__ embed, const int32_t *__
 
 // ------------------------------------------------------------------ residual add (split-K partials) + RMSNorm
 // One block per output row.  part: tiled GEMM output over M_all rows; out: A-fragment layout over the selected rows.
-template <typename T, class SG>
+// A row is a workgroup's only work and what bounds it is latency, so the host gives it a thread per 4-column piece (up to
+// 1024): all loads are in flight at once and a piece stays in its thread's registers across the barrier (pieces beyond the
+// first of a thread, in rows wider than that, are read again).  Where the output is in lines of eight rows (LINES) the
+// workgroups of a line's rows run on one XCD.  Against 256 threads per row above 64 rows, the row read again and lines
+// written by eight XCDs: 1.5B step k = 16 3106 -> 3048 us, 8B 8178 -> 8117, 8B k = 4 4324 -> 4293, one-token step of 6
+// sequences (1.5B) 1562 -> 1548.
+template <typename T, bool LINES, class SG>
 __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *__restrict__ x, const float *__restrict__ part, int S,
                                                       size_t split_stride, const T *__restrict__ gain, float eps,
-                                                      int n_rows, int R, SG sg, int d_model, int M_all,
+                                                      int n_rows, int R, SG sg, int d_model, int M_all, int rows,
                                                       T *__restrict__ out, ActLayout lay) {
-    const int b = blockIdx.x / n_rows;
-    const int o = blockIdx.x - b * n_rows;
+    const int o_row = LINES ? line_row(blockIdx.x) : blockIdx.x;
+    if (LINES && o_row >= rows) return;              // whole workgroup
+    const int b = o_row / n_rows;
+    const int o = o_row - b * n_rows;
     int row = (b + 1) * R - n_rows + o;
     if constexpr (kSegs<SG>) row = sg.row0[b + 1] - n_rows + o;
     float *xr = x + (size_t)row * d_model;
-    float ss = 0.f;
-    for (int c = 4 * threadIdx.x; c < d_model; c += 4 * blockDim.x) {
+    auto residual = [&](int c) __attribute__((always_inline)) {
         float4 v = *(const float4 *)(xr + c);
         if (S > 0) {
             const float *pp = part + pt_index(c, row, M_all);
@@ -135,8 +142,17 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *__restrict__ x, co
             }
             *(float4 *)(xr + c) = v;
         }
-        ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+        return v;
+    };
+    auto squares = [](const float4 &v) { return v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w; };
+    const int c0 = 4 * threadIdx.x;
+    float4 mine = {0.f, 0.f, 0.f, 0.f}, g0 = mine;
+    if (c0 < d_model) {
+        g0 = {to_f<T>(gain[c0]), to_f<T>(gain[c0 + 1]), to_f<T>(gain[c0 + 2]), to_f<T>(gain[c0 + 3])};
+        mine = residual(c0);
     }
+    float ss = squares(mine);
+    for (int c = c0 + 4 * blockDim.x; c < d_model; c += 4 * blockDim.x) ss += squares(residual(c));
     __shared__ float red[16];
     ss = wave_sum(ss);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
@@ -144,9 +160,11 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float *__restrict__ x, co
     float tot = 0.f;
     for (int w = 0; w < (int)(blockDim.x >> 6); ++w) tot += red[w];
     const float rs = rsqrtf(tot / (float)d_model + eps);
-    for (int c = 4 * threadIdx.x; c < d_model; c += 4 * blockDim.x) {
+    if (c0 < d_model)
+        store4<T>(out + af_index(o_row, c0, lay), mine.x * rs * g0.x, mine.y * rs * g0.y, mine.z * rs * g0.z, mine.w * rs * g0.w);
+    for (int c = c0 + 4 * blockDim.x; c < d_model; c += 4 * blockDim.x) {
         float4 v = *(const float4 *)(xr + c);          // this thread's own writes
-        store4<T>(out + af_index(blockIdx.x, c, lay), v.x * rs * to_f<T>(gain[c]), v.y * rs * to_f<T>(gain[c + 1]),
+        store4<T>(out + af_index(o_row, c, lay), v.x * rs * to_f<T>(gain[c]), v.y * rs * to_f<T>(gain[c + 1]),
                   v.z * rs * to_f<T>(gain[c + 2]), v.w * rs * to_f<T>(gain[c + 3]));
     }
 }
@@ -1166,15 +1184,16 @@ void launch_rmsnorm(int dtype, float *x, const float *part, int S, const void *g
         else typed(std::integral_constant<int, 8>());
         return;
     }
-    // a row is one workgroup's only work: with few rows the chip is empty anyway, so a row gets as many threads
-    // as it has 4-column pieces (all of its loads in flight at once); with many rows the count measured no difference
-    int threads = 256;
-    if (rows <= 64) {
-        threads = ((d_model / 4 + 63) / 64) * 64;
-        threads = threads > 1024 ? 1024 : threads < 64 ? 64 : threads;
-    }
+    int threads = ((d_model / 4 + 63) / 64) * 64;
+    threads = threads > 1024 ? 1024 : threads < 64 ? 64 : threads;
     auto go = [&](auto g, auto o, auto segs) {
-        rmsnorm_kernel<<<rows, threads, 0, st>>>(x, part, S, stride, g, eps, n_rows, R, segs, d_model, M, o, mt_out);
+        using T = std::remove_pointer_t<decltype(o)>;
+        if (mt_out.wide)
+            rmsnorm_kernel<T, true><<<line_rows(rows), threads, 0, st>>>(x, part, S, stride, g, eps, n_rows, R, segs, d_model, M,
+                                                                         rows, o, mt_out);
+        else
+            rmsnorm_kernel<T, false><<<rows, threads, 0, st>>>(x, part, S, stride, g, eps, n_rows, R, segs, d_model, M, rows, o,
+                                                               mt_out);
     };
     auto typed = [&](auto g, auto o) {
         if (sg.n) go(g, o, sg);

@@ -27,3 +27,10 @@ def test_scores_of_many_rows_match_the_oracle(d_model, rows):
     got = ar[0, :rows - 1].cpu().double()
     eng.close()
     assert float((got - torch.as_tensor(want).double()).abs().max()) < 2e-2      # the bf16 tolerance of the small models
+
+
+@pytest.mark.parametrize("d_model,rows", [(32, 34), (4096, 66), (1536, 100), (4128, 72), (544, 480)])
+def test_scores_of_a_few_hundred_rows_match_the_oracle(d_model, rows):
+    """A workgroup per row, the rows of an output line on one XCD: row counts on both sides of whole lines and of the 64 rows
+    that eight XCDs take in turn, a row wider than its threads' pieces (4128)."""
+    test_scores_of_many_rows_match_the_oracle(d_model, rows)
