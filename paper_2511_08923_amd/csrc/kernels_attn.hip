@@ -699,8 +699,8 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a, SG sg, OR
         l += __shfl_xor(l, 32);
         const int f = tile * 32 + lq;
         if (f < F) {
-            // PRIO (four query tiles to a workgroup and more rows than few): the tile as it lies in the registers, 16 bytes
-            // per row side by side, a store being one contiguous KiB; otherwise row by row
+            // PRIO (AttnPlan::tiled): the tile as it lies in the registers, 16 bytes per row side by side, a store being one
+            // contiguous KiB; otherwise row by row
             const int n_rows = min(32, F - 32 * tile);
             float *op = PRIO ? a.opart + (pbase + 32 * tile) * HD + 4 * (lh * n_rows + lq) : a.opart + (pbase + f) * HD + 4 * lh;
             const int piece = PRIO ? 8 * n_rows : 8;
@@ -792,13 +792,13 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(const float *__restric
     }
 }
 
-// The same for partial results that lie as query tiles (PRIO above).  A wave takes 16 head-dim values of the 32 rows of a
+// The same for partial results that lie as query tiles (AttnPlan::tiled).  A wave takes 16 head-dim values of the 32 rows of a
 // tile: lane = (row, half of each eight), so every load is one contiguous KiB, and so is the store to the A-fragment layout
 // where the rows do not straddle two of its row tiles.  The sums are grouped as above (four runs of every fourth split,
 // folded in pairs): the same bits.  With row-by-row partial results every store of the attention kernel was 64 pieces of 16
 // bytes in 32 lines: attention, its K/V placement and the combine at 8B heads, 272 rows and 4096 keys 46.3 -> 44.2 us,
 // 8B step k = 16 7726 -> 7620, 1.5B 3086 -> 3037.  Up to three tiles the waves per row stay: their rows are too few to
-// fill the chip by tiles, and the one-token step's reader takes them row by row.
+// fill the chip by tiles.
 template <class SG>
 __global__ __launch_bounds__(256) void attn_combine_tiles_kernel(const float *__restrict__ opart, const float *__restrict__ mpart,
                                                                  const float *__restrict__ lpart, RowDesc d, SG sg, int n_q,
@@ -927,6 +927,9 @@ AttnPlan plan_attention(int B, int n_kv, int group, const RowDesc &d, const Segs
     int TQ = (group * d.R + 31) / 32;         // 32-row query tiles per kv head (of the longest sequence)
     p.tiles_per_chunk = TQ < 4 ? TQ : 4;      // four waves x one query tile each
     p.n_chunks = (TQ + p.tiles_per_chunk - 1) / p.tiles_per_chunk;
+    // Four query tiles to a workgroup: partial results as tiles.  Not in a forward of so few rows that the O projection folds
+    // them itself (GEMM_FUSE_COMBINE), which takes them row by row: four rows of 25 and more heads on one K/V head.
+    p.tiled = p.tiles_per_chunk == 4 && (sg.n ? sg.row0[sg.n] : B * d.R) > kFuseMaxRows;
     int base = B * n_kv * p.n_chunks;
     if (sg.n) {                               // sequences of different length: the workgroups that have rows
         base = 0;
@@ -1015,7 +1018,7 @@ void launch_attention_bf16(const bf16_t *q, KvView kv, const bf16_t *k_scr, cons
     const NoSegs none;
     // more workgroups than compute units (otherwise each has one to itself in any order), rows of unequal key ranges
     const int items = p.n_chunks * p.splits;
-    if (!sg.n && d.nc >= 64 && a.n_groups <= 8 && a.xcd_q && p.tiles_per_chunk == 4 && items <= kMaxOrder &&
+    if (!sg.n && d.nc >= 64 && a.n_groups <= 8 && a.xcd_q && p.tiled && items <= kMaxOrder &&
         p.n_chunks < 1024 && items * a.n_groups > 256) {
         const dim3 line(8 * ((items + a.xcd_q - 1) / a.xcd_q));
         attn_bf16_kernel<1, true, false, NoSegs, WorkOrder><<<line, 256, 0, st>>>(
@@ -1023,19 +1026,20 @@ void launch_attention_bf16(const bf16_t *q, KvView kv, const bf16_t *k_scr, cons
         return;
     }
     if (fused_rope) go(attn_bf16_kernel<1, false, true, NoSegs, PlainOrder>, none);
-    else if (sg.n && p.tiles_per_chunk == 4) go(attn_bf16_kernel<1, true, false, Segs, PlainOrder>, sg);
+    else if (sg.n && p.tiled) go(attn_bf16_kernel<1, true, false, Segs, PlainOrder>, sg);
     else if (sg.n) go(attn_bf16_kernel<1, false, false, Segs, PlainOrder>, sg);
-    else if (p.tiles_per_chunk == 4) go(attn_bf16_kernel<1, true, false, NoSegs, PlainOrder>, none);
+    else if (p.tiled) go(attn_bf16_kernel<1, true, false, NoSegs, PlainOrder>, none);
     else go(attn_bf16_kernel<1, false, false, NoSegs, PlainOrder>, none);
 }
 
 void launch_attention_combine(const float *part, const RowDesc &d, const Segs &sg, int M, int n_q, int n_kv, int hd,
-                              int splits, bf16_t *out, int out_af, hipStream_t st) {
+                              const AttnPlan &p, bf16_t *out, int out_af, hipStream_t st) {
+    const int splits = p.splits;
     if (splits == 1) return;                  // the attention kernel has written the result itself
     size_t rows = (size_t)M * n_q * splits;
     const ActLayout lay = act_layout(M);
-    const int group = n_q / n_kv, tiles = (group * d.R + 31) / 32;
-    if (tiles >= 4) {                         // PRIO in launch_attention_bf16
+    if (p.tiled) {
+        const int tiles = (n_q / n_kv * d.R + 31) / 32;
         const int n_groups = (sg.n ? sg.n : M / d.R) * n_kv;
         auto by_tiles = [&](auto segs) {
             attn_combine_tiles_kernel<<<dim3(n_groups * tiles, 2), 256, 0, st>>>(

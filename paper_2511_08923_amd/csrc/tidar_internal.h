@@ -285,7 +285,7 @@ struct FuseArgs {
     size_t split_stride;
     const bf16_t *gain;
     float eps;
-    // GEMM_FUSE_COMBINE: partial results as the attention kernel lays them out
+    // GEMM_FUSE_COMBINE: partial results row by row, from a plan that is not AttnPlan::tiled
     const float *opart, *mpart, *lpart;
     int R, n_q, n_kv, a_splits;
 };
@@ -309,6 +309,7 @@ struct AttnPlan {
     int splits_bound;    // the most splits any key bound can give this row structure (sizes the workspace)
     int n_chunks;        // q-tile chunks per kv head
     int tiles_per_chunk;
+    bool tiled;          // the partial results of a split lie as whole query tiles (else row by row): every reader asks here
     int max_keys;        // the caller's bound on the key count, in steps of 256
     int per;             // key-pair iterations per split, from the caller's bound on the key count (not from the
                          // sequence's current length): a key's split then depends on its position alone
@@ -339,7 +340,7 @@ void launch_attention_bf16(const bf16_t *q, KvView kv, const bf16_t *k_scr, cons
 // whether launch_attention_bf16 can take the new row from the partial sums for this row structure
 bool attention_rope_ok(RowDesc d, int group, int hd);
 void launch_attention_combine(const float *part, const RowDesc &d, const Segs &sg, int M, int n_q, int n_kv, int hd,
-                              int splits, bf16_t *out, int out_af, hipStream_t st);
+                              const AttnPlan &p, bf16_t *out, int out_af, hipStream_t st);
 void launch_attention_f32(const float *q, KvView kv, const float *k_scr, const float *v_scr,
                           const int32_t *prefix_len, const RowDesc &d, const Segs &sg, int M, int n_q, float *out,
                           int out_af, hipStream_t st);

@@ -254,7 +254,7 @@ void gemm(tidar_ctx *ctx, const void *a, const void *w, float *out, int M, int N
 }
 
 // Returns the number of key splits whose partial results wait in the workspace (1: o_out holds the result).  With
-// defer_combine the partial results are left for the consumer to fold.
+// defer_combine partial results that lie row by row are left for the consumer to fold.
 int attention(tidar_ctx *ctx, const Layout &l, char *ws, KvView kvv, const int32_t *prefix_len, const RowDesc &d,
               const Segs &sg, int B, int max_keys, void *o_out, hipStream_t st, bool defer_combine = false,
               const AttnRope *rope = nullptr) {
@@ -268,12 +268,11 @@ int attention(tidar_ctx *ctx, const Layout &l, char *ws, KvView kvv, const int32
                                   (const bf16_t *)(ws + l.v_scr), prefix_len, d, sg, B, M, c.n_q_heads, ap,
                                   (float *)(ws + l.attn_part), (bf16_t *)o_out, 1, st, rope);
         }
-        if (ap.splits > 1 && !defer_combine) {
-            Prof p(ctx, KC_ATTN_COMBINE, st);
-            launch_attention_combine((const float *)(ws + l.attn_part), d, sg, M, c.n_q_heads, c.n_kv_heads, c.head_dim,
-                                     ap.splits, (bf16_t *)o_out, 1, st);
-        }
-        return ap.splits;
+        if (ap.splits == 1 || (defer_combine && !ap.tiled)) return ap.splits;
+        Prof p(ctx, KC_ATTN_COMBINE, st);
+        launch_attention_combine((const float *)(ws + l.attn_part), d, sg, M, c.n_q_heads, c.n_kv_heads, c.head_dim, ap,
+                                 (bf16_t *)o_out, 1, st);
+        return 1;
     }
     Prof p(ctx, KC_ATTN, st);
     launch_attention_f32((const float *)(ws + l.q), kvv, (const float *)(ws + l.k_scr),
@@ -388,7 +387,7 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
         }
         const int a_splits = attention(ctx, l, ws, kvv, prefix_len, d, sg, B, max_keys, ws + l.o, st, fuse,
                                        rope.part ? &rope : nullptr);
-        if (fuse && a_splits > 1) {
+        if (a_splits > 1) {
             Prof p(ctx, KC_GEMM, st);
             GemmPlan gp = plan_gemm_bf16_fused(M, c.d_model, q_dim, false);
             const size_t rows = (size_t)B * c.n_kv_heads * a_splits * (c.n_q_heads / c.n_kv_heads) * d.R;
@@ -924,7 +923,7 @@ tidar_status tidar_hybrid_attention(tidar_ctx *ctx, const tidar_kv_cache *kv, in
         if (ap.splits == 1) return TIDAR_OK;
         Prof p(ctx, KC_ATTN_COMBINE, st);
         launch_attention_combine((const float *)(wsb + 2 * scr), d, kUniform, M, c.n_q_heads, c.n_kv_heads, c.head_dim,
-                                 ap.splits, (bf16_t *)out, 0, st);
+                                 ap, (bf16_t *)out, 0, st);
     } else {
         Prof p(ctx, KC_ATTN, st);
         launch_attention_f32((const float *)q, kvv, (const float *)wsb, (const float *)(wsb + scr), prefix_len, d,
