@@ -5,7 +5,7 @@
 // into every workgroup.  What bounds it is how much a compute unit takes in: with weights from HBM among the loads about
 // 57 GB/s whatever the kernel (272 x 24576 x 4096: loads alone 57 us, MFMAs and LDS reads alone 48; activations alone 82
 // GB/s per unit, everything from L2 102), which is why a deeper ring or fewer LDS reads change nothing beyond this:
-//   * a workgroup owns all row tiles of the pass (up to twelve) and one to three column tiles, one workgroup per compute unit:
+//   * a workgroup owns all row tiles of the pass (up to twelve) and two or three column tiles, one workgroup per compute unit:
 //     no weight is read twice, all of them stream;
 //   * both operands go straight into LDS (buffer_load ... lds), PA chunks of 64 k of A and PW of W: the weights, which
 //     are longer on their way, are asked for up to seven chunks ahead, in front of the activations of nearer chunks;
@@ -159,9 +159,19 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
                 for (int m = 0; m < NM; ++m) {
                     if (q == 3 && m == B) sync();
                     __builtin_amdgcn_sched_barrier(0);
-                    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
-                                 : "+a"(acc[m / CT][m % CT])
-                                 : "v"(wf[s][m % CT]), "v"(af[s][m / CT]));
+                    // The compiler does not see the MFMAs finish, and where the loop ends it may copy their results at once, so
+                    // the last one of the last chunk brings the wait (32 states; it asks for 12 before its result is read) in
+                    // the same piece of assembly
+                    if (q == 3 && m == NM - 1)
+                        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0\n\t"
+                                     "s_cmp_lg_i32 %3, %4\n\ts_cbranch_scc1 .Lmore%=\n\ts_nop 15\n\ts_nop 15\n.Lmore%=:"
+                                     : "+a"(acc[m / CT][m % CT])
+                                     : "v"(wf[s][m % CT]), "v"(af[s][m / CT]), "s"(c + 1), "s"(n_chunks)
+                                     : "scc");
+                    else
+                        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
+                                     : "+a"(acc[m / CT][m % CT])
+                                     : "v"(wf[s][m % CT]), "v"(af[s][m / CT]));
                     __builtin_amdgcn_sched_barrier(0);
                     if (q != 3) ops(m, NM);
                     else if (m >= B) ops(m - B, NM - B);
@@ -174,11 +184,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
     const int mine = (ct_here - wave + 3) >> 2;              // row tiles of this wave: RW or one less
     if (mine == RW) k_loop(std::integral_constant<int, RW>());
     else k_loop(std::integral_constant<int, RW - 1>());
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-#pragma unroll
-    for (int i = 0; i < RW; ++i)
-#pragma unroll
-        for (int j = 0; j < CT; ++j) asm volatile("" : "+a"(acc[i][j]));
     wait_loads<0>();
     barrier();
     ChooseArgs none = {};
@@ -221,7 +226,6 @@ void launch_tall_rows(const bf16_t *a, const bf16_t *w, float *out, int M, int N
 
 void launch_gemm_bf16_tall(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi,
                            hipStream_t st) {
-    if (p.nt == 1) launch_tall_rows<1>(a, w, out, M, N, K, p, epi, st);
-    else if (p.nt == 2) launch_tall_rows<2>(a, w, out, M, N, K, p, epi, st);
+    if (p.nt == 2) launch_tall_rows<2>(a, w, out, M, N, K, p, epi, st);
     else launch_tall_rows<3>(a, w, out, M, N, K, p, epi, st);
 }
