@@ -56,14 +56,7 @@ struct AttnArgs {
     AttnRope rp;               // ROPE kernels only
 };
 
-// The order in which a launch's (query chunk, key split) items are dealt to its workgroups, split << 10 | chunk: see
-// make_order.  PlainOrder: by index.
-constexpr int kMaxOrder = 512;
-struct WorkOrder {
-    int n;
-    uint32_t item2[kMaxOrder / 2];        // two to a word: a dynamic index into the kernel arguments loads whole words
-};
-struct PlainOrder {};
+struct PlainOrder {};          // instead of a WorkOrder: by index
 
 // Key-pair iterations a workgroup can need at all: cache units up to the furthest key any of its rows sees, then the
 // mask units of its rows' own blocks, [0, a1) and [b0, b1) with a1 <= b0.  (Rows of one query head only; a workgroup
@@ -879,6 +872,12 @@ __global__ __launch_bounds__(256) void attn_combine_tiles_kernel(const float *__
 
 }  // namespace
 
+// XCDs that share the query chunks of one (sequence, kv head) group: 1 where the groups divide evenly over the XCDs, 8 / groups
+// where the XCDs divide over the groups, 0: workgroups by index.
+static int xcds_of_group(int n_groups) {
+    return n_groups % 8 == 0 ? 1 : (n_groups < 8 && 8 % n_groups == 0) ? 8 / n_groups : 0;
+}
+
 // The order of a single sequence's causal pass (prefill, scoring; n_groups <= 8, so that a group has 8 / q XCDs to
 // itself).  Its workgroups walk key ranges of very different length, and all of them are resident from the start or
 // nearly so: two to a compute unit, the launch takes as long as the compute unit with the most to do (a workgroup left
@@ -887,35 +886,38 @@ __global__ __launch_bounds__(256) void attn_combine_tiles_kernel(const float *__
 // query heads, twice the longest range or twice the shortest.  Here the item in second place on a unit is the shorter
 // the longer the first one is; what is left after two rounds follows with the longest first.  8B prefill of 4096
 // tokens 60416 -> 59419 us, scoring of 2000 tokens (1.5B) 17434 -> 17216.
-static WorkOrder make_order(const RowDesc &d, int group, int n_chunks, int tiles_per_chunk, int splits, int per, int L,
-                            int q) {
+WorkOrder attention_order(const AttnPlan &p, int B, int n_kv, int group, const RowDesc &d, const Segs &sg) {
+    WorkOrder o = {};
+    const int n = p.n_chunks * p.splits, n_groups = B * n_kv, q = xcds_of_group(n_groups);
+    // more workgroups than compute units (otherwise each has one to itself in any order), rows of unequal key ranges
+    if (sg.n || d.nc < 64 || n_groups > 8 || q == 0 || !p.tiled || n > kMaxOrder || p.n_chunks >= 1024 || n * n_groups <= 256)
+        return o;
     struct Item {
         int len;
         uint16_t id;
     } it[kMaxOrder];
-    const int F = group * d.R, TQ = (F + 31) >> 5;
-    int n = 0;
-    for (int c = 0; c < n_chunks; ++c) {
-        const KeySpan k = key_span(d, L, F, c * tiles_per_chunk, imin(TQ, (c + 1) * tiles_per_chunk));
-        for (int s = 0; s < splits; ++s) {
-            const int lo = s * per, hi = s == splits - 1 ? 1 << 30 : lo + per;
+    const int F = group * d.R, TQ = (F + 31) >> 5, L = imax(0, p.max_keys - d.R);
+    int i = 0;
+    for (int c = 0; c < p.n_chunks; ++c) {
+        const KeySpan k = key_span(d, L, F, c * p.tiles_per_chunk, imin(TQ, (c + 1) * p.tiles_per_chunk));
+        for (int s = 0; s < p.splits; ++s) {
+            const int lo = s * p.per, hi = s == p.splits - 1 ? 1 << 30 : lo + p.per;
             const int len = imax(0, imin(hi, k.a1) - lo) + imax(0, imin(hi, k.b1) - imax(lo, k.b0));
-            it[n++] = {len, (uint16_t)(s << 10 | c)};
+            it[i++] = {len, (uint16_t)(s << 10 | c)};
         }
     }
     std::stable_sort(it, it + n, [](const Item &x, const Item &y) { return x.len > y.len; });
-    WorkOrder o = {};
     o.n = n;
     for (int x = 0; x < q; ++x) {                    // XCD x of the group's takes every q-th item
         const int m = (n - x + q - 1) / q;
         const int second = imin(imax(m - 32, 0), 32);                  // compute units that get two
-        for (int p = 0; p < m; ++p) {
-            int rank = p;
-            if (p < second) rank = imin(m, 64) - 2 * second + p;       // the longer halves of the pairs
-            else if (p < 32) rank = p - second;                        // those that stay alone
-            else if (p < 64) rank = imin(m, 64) - 1 - (p - 32);        // the shorter halves
-            const int i = p * q + x;
-            o.item2[i >> 1] |= (uint32_t)it[rank * q + x].id << (16 * (i & 1));
+        for (int k = 0; k < m; ++k) {
+            int rank = k;
+            if (k < second) rank = imin(m, 64) - 2 * second + k;       // the longer halves of the pairs
+            else if (k < 32) rank = k - second;                        // those that stay alone
+            else if (k < 64) rank = imin(m, 64) - 1 - (k - 32);        // the shorter halves
+            const int at = k * q + x;
+            o.item2[at >> 1] |= (uint32_t)it[rank * q + x].id << (16 * (at & 1));
         }
     }
     return o;
@@ -983,8 +985,8 @@ bool attention_rope_ok(RowDesc d, int group, int hd) {
 
 void launch_attention_bf16(const bf16_t *q, KvView kv, const bf16_t *k_scr, const bf16_t *v_scr,
                            const int32_t *prefix_len, const RowDesc &d, const Segs &sg, int B, int M, int n_q,
-                           const AttnPlan &p, float *part, bf16_t *out, int out_af, hipStream_t st,
-                           const AttnRope *rope) {
+                           const AttnPlan &p, const WorkOrder &order, float *part, bf16_t *out, int out_af,
+                           hipStream_t st, const AttnRope *rope) {
     AttnArgs a;
     a.rp = AttnRope{};
     const bool fused_rope = rope && rope->part && attention_rope_ok(d, n_q / kv.n_kv, kv.hd);
@@ -1010,19 +1012,15 @@ void launch_attention_bf16(const bf16_t *q, KvView kv, const bf16_t *k_scr, cons
     a.mpart = part + rows * HD;
     a.lpart = a.mpart + rows;
     a.n_groups = B * kv.n_kv;
-    a.xcd_q = a.n_groups % 8 == 0 ? 1 : (a.n_groups < 8 && 8 % a.n_groups == 0) ? 8 / a.n_groups : 0;
+    a.xcd_q = xcds_of_group(a.n_groups);
     dim3 grid(a.n_groups * p.n_chunks, p.splits);
     if (a.xcd_q > 1) grid.x = 8 * ((p.n_chunks + a.xcd_q - 1) / a.xcd_q);
     const PlainOrder plain;
     auto go = [&](auto kernel, auto segs) { kernel<<<grid, 256, 0, st>>>(a, segs, plain); };
     const NoSegs none;
-    // more workgroups than compute units (otherwise each has one to itself in any order), rows of unequal key ranges
-    const int items = p.n_chunks * p.splits;
-    if (!sg.n && d.nc >= 64 && a.n_groups <= 8 && a.xcd_q && p.tiled && items <= kMaxOrder &&
-        p.n_chunks < 1024 && items * a.n_groups > 256) {
-        const dim3 line(8 * ((items + a.xcd_q - 1) / a.xcd_q));
-        attn_bf16_kernel<1, true, false, NoSegs, WorkOrder><<<line, 256, 0, st>>>(
-            a, none, make_order(d, a.group, p.n_chunks, p.tiles_per_chunk, p.splits, p.per, imax(0, p.max_keys - d.R), a.xcd_q));
+    if (order.n) {
+        const dim3 line(8 * ((order.n + a.xcd_q - 1) / a.xcd_q));
+        attn_bf16_kernel<1, true, false, NoSegs, WorkOrder><<<line, 256, 0, st>>>(a, none, order);
         return;
     }
     if (fused_rope) go(attn_bf16_kernel<1, false, true, NoSegs, PlainOrder>, none);

@@ -315,6 +315,15 @@ struct AttnPlan {
                          // sequence's current length): a key's split then depends on its position alone
 };
 AttnPlan plan_attention(int B, int n_kv, int group, const RowDesc &d, const Segs &sg, int max_keys);
+// The order in which a launch's (query chunk, key split) items are dealt to its workgroups, split << 10 | chunk.  n == 0: by
+// index.  It depends on the plan and the row structure alone, so a forward works it out once for all its layers (a
+// layer's launch made its own before: 3 us of host time at 64 items, 9 at 288).
+constexpr int kMaxOrder = 512;
+struct WorkOrder {
+    int n;
+    uint32_t item2[kMaxOrder / 2];        // two to a word: a dynamic index into the kernel arguments loads whole words
+};
+WorkOrder attention_order(const AttnPlan &p, int B, int n_kv, int group, const RowDesc &d, const Segs &sg);
 inline size_t attn_partial_floats(int M, int n_q, int hd, int splits) { return (size_t)M * n_q * splits * (hd + 2); }
 
 // The one-token step (R = 1, no mask rows) skips the RoPE launch: the attention workgroups take the new row's Q, K
@@ -335,8 +344,8 @@ struct AttnRope {
 // results to part, which launch_attention_combine folds into out.
 void launch_attention_bf16(const bf16_t *q, KvView kv, const bf16_t *k_scr, const bf16_t *v_scr,
                            const int32_t *prefix_len, const RowDesc &d, const Segs &sg, int B, int M, int n_q,
-                           const AttnPlan &p, float *part, bf16_t *out, int out_af, hipStream_t st,
-                           const AttnRope *rope = nullptr);
+                           const AttnPlan &p, const WorkOrder &order, float *part, bf16_t *out, int out_af,
+                           hipStream_t st, const AttnRope *rope = nullptr);
 // whether launch_attention_bf16 can take the new row from the partial sums for this row structure
 bool attention_rope_ok(RowDesc d, int group, int hd);
 void launch_attention_combine(const float *part, const RowDesc &d, const Segs &sg, int M, int n_q, int n_kv, int hd,

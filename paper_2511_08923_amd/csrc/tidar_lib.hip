@@ -256,16 +256,15 @@ void gemm(tidar_ctx *ctx, const void *a, const void *w, float *out, int M, int N
 // Returns the number of key splits whose partial results wait in the workspace (1: o_out holds the result).  With
 // defer_combine partial results that lie row by row are left for the consumer to fold.
 int attention(tidar_ctx *ctx, const Layout &l, char *ws, KvView kvv, const int32_t *prefix_len, const RowDesc &d,
-              const Segs &sg, int B, int max_keys, void *o_out, hipStream_t st, bool defer_combine = false,
-              const AttnRope *rope = nullptr) {
+              const Segs &sg, int B, const AttnPlan &ap, const WorkOrder &order, void *o_out, hipStream_t st,
+              bool defer_combine = false, const AttnRope *rope = nullptr) {
     const tidar_config &c = ctx->cfg;
     const int M = forward_row_count(B, d, sg);
     if (c.dtype == TIDAR_BF16) {
-        AttnPlan ap = plan_attention(B, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, d, sg, max_keys);
         {
             Prof p(ctx, KC_ATTN, st);
             launch_attention_bf16((const bf16_t *)(ws + l.q), kvv, (const bf16_t *)(ws + l.k_scr),
-                                  (const bf16_t *)(ws + l.v_scr), prefix_len, d, sg, B, M, c.n_q_heads, ap,
+                                  (const bf16_t *)(ws + l.v_scr), prefix_len, d, sg, B, M, c.n_q_heads, ap, order,
                                   (float *)(ws + l.attn_part), (bf16_t *)o_out, 1, st, rope);
         }
         if (ap.splits == 1 || (defer_combine && !ap.tiled)) return ap.splits;
@@ -304,6 +303,13 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
         launch_embed_rows(c.dtype, w->embed, tokens, tok_stride, prefix_len, d, sg, M, c.d_model, c.mask_token_id,
                           c.vocab, layer_view(c, kv, 0), c.rope_base, x, (int32_t *)(ws + l.pos), d.R - head_row0,
                           (float *)(ws + l.rope_cs), st);
+    }
+    // the attention's plan and order are the same in every layer
+    AttnPlan ap = {};
+    WorkOrder order = {};
+    if (c.dtype == TIDAR_BF16) {
+        ap = plan_attention(B, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, d, sg, max_keys);
+        order = attention_order(ap, B, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, d, sg);
     }
     int S_prev = 0;   // split count of the partial sums still waiting to be added to the residual stream
     // A forward of a few rows (the one-token step, very short blocks) is a chain of dependent launches whose kernels
@@ -349,7 +355,7 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
         int S = 1;
         if (fuse32) {
             fused_f32(FUSE_ROPE, w->attn_norm[layer], w->wqkv[layer], M, q_dim + 2 * kv_dim, (float *)(ws + l.q), kvv);
-            attention(ctx, l, ws, kvv, prefix_len, d, sg, B, max_keys, ws + l.o, st);
+            attention(ctx, l, ws, kvv, prefix_len, d, sg, B, ap, order, ws + l.o, st);
             gemm(ctx, ws + l.o, w->wo[layer], g_cur, M, c.d_model, q_dim, false, &S_prev, st);
             fused_f32(FUSE_SWIGLU, w->ffn_norm[layer], w->w_gate_up[layer], M, 2 * c.d_ff, (float *)(ws + l.h), kvv);
             gemm(ctx, ws + l.h, w->w_down[layer], g_cur, M, c.d_model, c.d_ff, false, &S_prev, st);
@@ -385,7 +391,7 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
             launch_rope_kv(c.dtype, g_cur, S, (const float *)(ws + l.rope_cs), prefix_len, d, sg, B, M, c.n_q_heads, kvv,
                            ws + l.q, ws + l.k_scr, ws + l.v_scr, st);
         }
-        const int a_splits = attention(ctx, l, ws, kvv, prefix_len, d, sg, B, max_keys, ws + l.o, st, fuse,
+        const int a_splits = attention(ctx, l, ws, kvv, prefix_len, d, sg, B, ap, order, ws + l.o, st, fuse,
                                        rope.part ? &rope : nullptr);
         if (a_splits > 1) {
             Prof p(ctx, KC_GEMM, st);
@@ -918,6 +924,7 @@ tidar_status tidar_hybrid_attention(tidar_ctx *ctx, const tidar_kv_cache *kv, in
             Prof p(ctx, KC_ATTN, st);
             launch_attention_bf16((const bf16_t *)q, kvv, (const bf16_t *)wsb,
                                   (const bf16_t *)(wsb + scr), prefix_len, d, kUniform, batch, M, c.n_q_heads, ap,
+                                  attention_order(ap, batch, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, d, kUniform),
                                   (float *)(wsb + 2 * scr), (bf16_t *)out, 0, st);
         }
         if (ap.splits == 1) return TIDAR_OK;
