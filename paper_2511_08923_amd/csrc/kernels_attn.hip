@@ -717,17 +717,17 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a, SG sg, OR
 // split keeps an integral reference.  One wave per (row, head): lane = (8-value head-dim chunk, one of 4 split
 // lanes); the split lanes share the splits between them and are folded with two shuffles.  The 16-byte result
 // goes out row-major or in the A-fragment layout of the O projection's input.
-// It is bound by the partial results (2176 rows x 32 heads in 3 splits: 109 MB), so no lane asks for more splits than there
-// are (J: with four at any count 2176 rows took 45 us, 4000 rows x 12 heads in 2 splits 28.7; with J = 1 and the rows
-// of an output line on one XCD 37.3 and 19.7).
-template <int J, class SG>
+// It is bound by the partial results, so no lane asks for more splits than there are (J).  Forwards of up to three query tiles per
+// kv head come here.  LINES, from 481 rows on: the workgroups of the rows that share an output line run on one XCD, us by index ->
+// so: 640 rows x 32 heads in 2 splits 12.5 -> 11.1, 660 x 32 12.6 -> 11.1, 648 x 12 in 4 splits 7.1 -> 6.2.
+template <int J, bool LINES, class SG>
 __global__ __launch_bounds__(64) void attn_combine_kernel(const float *__restrict__ opart,
                                                           const float *__restrict__ mpart,
                                                           const float *__restrict__ lpart, RowDesc d, SG sg, int n_q,
                                                           int n_kv, int splits, int M, bf16_t *__restrict__ out, int out_af,
                                                           ActLayout lay) {
-    const int row = gridDim.x != M ? line_row(blockIdx.x) : blockIdx.x;
-    if (row >= M) return;
+    const int row = LINES ? line_row(blockIdx.x) : blockIdx.x;
+    if (LINES && row >= M) return;
     const int head = blockIdx.y;
     const int b = seq_of_row(d, sg, row);
     int row_base;
@@ -1047,11 +1047,15 @@ void launch_attention_combine(const float *part, const RowDesc &d, const Segs &s
         else by_tiles(NoSegs());
         return;
     }
-    // many rows: the workgroups of the rows that share the output's lines on one XCD
-    const int blocks = out_af && M > 480 ? line_rows(M) : M;
+    const bool lines = out_af && M > 480;
     auto go = [&](auto j, auto segs) {
-        attn_combine_kernel<decltype(j)::value><<<dim3(blocks, n_q), 64, 0, st>>>(
-            part, part + rows * hd, part + rows * hd + rows, d, segs, n_q, n_kv, splits, M, out, out_af, lay);
+        constexpr int J = decltype(j)::value;
+        auto launch = [&](auto kernel, int blocks) {
+            kernel<<<dim3(blocks, n_q), 64, 0, st>>>(part, part + rows * hd, part + rows * hd + rows, d, segs, n_q, n_kv, splits, M,
+                                                     out, out_af, lay);
+        };
+        if (lines) launch(attn_combine_kernel<J, true, decltype(segs)>, line_rows(M));
+        else launch(attn_combine_kernel<J, false, decltype(segs)>, M);
     };
     auto by_splits = [&](auto segs) {
         if (splits <= 4) go(std::integral_constant<int, 1>(), segs);
