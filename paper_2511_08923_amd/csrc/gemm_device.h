@@ -1,9 +1,23 @@
 // Device code shared by the bf16 GEMM kernels: buffer descriptors, the split-K ranges, and the row choice of the fused
 // vocabulary reduction.
 #pragma once
+#include <atomic>
+
 #include "tidar_internal.h"
 
 namespace {
+
+// LDS above 64 KiB has to be granted per kernel, on every device the kernel is launched on; `granted` is the launcher's own
+// (several threads may be the first: the grant is the same).
+constexpr int kLdsDevices = 64;
+inline void grant_lds(const void *kernel, int bytes, std::atomic<bool> (&granted)[kLdsDevices]) {
+    int dev = -1;
+    (void)hipGetDevice(&dev);
+    const bool known = dev >= 0 && dev < kLdsDevices;
+    if (known && granted[dev].load(std::memory_order_relaxed)) return;
+    (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (known) granted[dev].store(true, std::memory_order_relaxed);
+}
 
 constexpr int SPLIT_UNIT = 512;           // k elements
 constexpr int OOB = 0x7ffffff0;           // byte offset beyond any buffer: the load returns zeros

@@ -589,13 +589,8 @@ template <int MT, int CT>
 void launch_few(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi, hipStream_t st,
                 const ChooseArgs &ch) {
     constexpr int SMEM = FEW_CHUNKS * 4 * (CT + 1) * 1024;
-    static bool attr_set[64] = {};           // LDS above 64 KiB has to be granted per kernel and device
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    if (dev < 0 || dev >= 64 || !attr_set[dev]) {
-        (void)hipFuncSetAttribute((const void *)gemm_bf16_few_kernel<MT, CT>, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        if (dev >= 0 && dev < 64) attr_set[dev] = true;
-    }
+    static std::atomic<bool> granted[kLdsDevices];
+    grant_lds((const void *)gemm_bf16_few_kernel<MT, CT>, SMEM, granted);
     gemm_bf16_few_kernel<MT, CT><<<dim3(((N + 31) / 32 + CT - 1) / CT, p.splits), 256, SMEM, st>>>(a, w, out, M, N, K,
                                                                                                  p.splits, epi, ch);
 }
@@ -619,15 +614,8 @@ void launch_large(const bf16_t *a, const bf16_t *w, float *out, int M, int N, in
     // reuse the same memory and need 18 KiB of it
     constexpr size_t PATCH = (size_t)NW * 32 * 36 * 4;
     constexpr size_t SMEM = (size_t)2 * CTL * 8 * 1024 > PATCH ? (size_t)2 * CTL * 8 * 1024 : PATCH;
-    // LDS above 64 KiB has to be granted per kernel, on every device the kernel is launched on
-    static bool attr_set[64] = {};
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    if (dev < 0 || dev >= 64 || !attr_set[dev]) {
-        (void)hipFuncSetAttribute((const void *)gemm_bf16_large_kernel<MTA, WIDE, NT, NW>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)SMEM);
-        if (dev >= 0 && dev < 64) attr_set[dev] = true;
-    }
+    static std::atomic<bool> granted[kLdsDevices];
+    grant_lds((const void *)gemm_bf16_large_kernel<MTA, WIDE, NT, NW>, SMEM, granted);
     gemm_bf16_large_kernel<MTA, WIDE, NT, NW><<<grid, 64 * NW, SMEM, st>>>(a, w, out, M, N, K, p.splits, epi, swz_p, swz_c, n_pass,
                                                                n_colblk, ch);
 }

@@ -142,14 +142,8 @@ template <int RT, int CT, int D, bool SWIGLU>
 void launch_mid(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, hipStream_t st) {
     constexpr int REDUCE_LDS = 4 * phase_of(RT * CT) * 8 * PIECE;
     const int units = ((N + 31) / 32 + CT - 1) / CT * p.splits, n_tall = (M + 31) / 32 - p.m_chunks * (RT - 1);
-    static bool attr_set[64] = {};           // LDS above 64 KiB has to be granted per kernel and device
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    if (dev < 0 || dev >= 64 || !attr_set[dev]) {
-        (void)hipFuncSetAttribute((const void *)gemm_bf16_mid_kernel<RT, CT, D, SWIGLU>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, REDUCE_LDS);
-        if (dev >= 0 && dev < 64) attr_set[dev] = true;
-    }
+    static std::atomic<bool> granted[kLdsDevices];
+    grant_lds((const void *)gemm_bf16_mid_kernel<RT, CT, D, SWIGLU>, REDUCE_LDS, granted);
     gemm_bf16_mid_kernel<RT, CT, D, SWIGLU><<<dim3((units + 7) / 8 * 8 * p.m_chunks), 256, REDUCE_LDS, st>>>(
         a, w, out, M, N, K, p.splits, p.m_chunks, n_tall);
 }

@@ -99,23 +99,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
     // select per load and per tile: 8B step of 8 sequences 38831 us, now 37910; 4096-token prefill 57191, 55564; scoring of
     // 2000 tokens (1.5B) 16168, 15727).
     auto load = [&](int c, int i) __attribute__((always_inline)) {
-        const bool here = c < n_chunks;
-        int4v desc = ld_desc;
-        desc[2] = here ? desc[2] : 0;
-        const unsigned dst = ld_dst + (c & (BUFS - 1)) * CHUNK + (i & ~3) * 1024;
-        const int src = here ? ld_src + c * ld_step + (i & ~3) * 1024 : 0;
-        if ((i & 3) == 0) dma16_at<0>(dst, ld_off[i], desc, src);
-        else if ((i & 3) == 1) dma16_at<1024>(dst, ld_off[i], desc, src);
-        else if ((i & 3) == 2) dma16_at<2048>(dst, ld_off[i], desc, src);
-        else dma16_at<3072>(dst, ld_off[i], desc, src);
-    };
-    // Workgroup barrier for LDS traffic only (loads stay in flight).  The wait is the builtin, not inline assembly: the
-    // compiler then knows that no LDS read is outstanding and counts exactly which of the next ones an MFMA needs.
-    auto barrier = [&]() __attribute__((always_inline)) {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0)
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+        dma16_tile(ld_dst + (c & (BUFS - 1)) * CHUNK, ld_off[i], ld_desc, c < n_chunks, ld_src + c * ld_step, i);
     };
 
     // The wave's row tile i (16 rows) is half mh of the pass's 32-row tile i.
@@ -138,7 +122,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) load(c, i);
     wait_loads<(BUFS - 1) * LOADS>();
-    barrier();
+    lds_barrier_counted();
     // the k loop over RA row tiles
     auto k_loop = [&](auto ra_tag) __attribute__((always_inline)) {
         constexpr int RA = decltype(ra_tag)::value, READS = CT + RA;
@@ -163,7 +147,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
         auto chunk = [&](int s, int c) __attribute__((always_inline)) {
             row(s, 0, 0, [](int) {});
             wait_loads<(BUFS - 2) * LOADS>();
-            barrier();                       // chunk c+1 has landed for everyone, chunk c has been read by everyone
+            lds_barrier_counted();                       // chunk c+1 has landed for everyone, chunk c has been read by everyone
 #pragma unroll
             for (int i = 1; i < RA; ++i) {
                 const int f0 = READS * (i - 1) / (RA - 1), nf = READS * i / (RA - 1) - f0;
@@ -197,7 +181,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
     if (ct_here == RT) k_loop(std::integral_constant<int, RT>());
     else k_loop(std::integral_constant<int, RT - 1>());
     wait_loads<0>();
-    barrier();
+    lds_barrier_counted();
 
     // ---- epilogue
     const int n = lane & 15, g = lane >> 4;
@@ -303,14 +287,8 @@ void launch_rows(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int
                  const ChooseArgs &ch) {
     constexpr int SMEM = BUFS * 4 * (RT > 8 ? RT : 8) * 1024;
     const int n_colblk = (N + 255) / 256, n_tall = (M + 31) / 32 - p.m_chunks * (RT - 1);
-    static bool attr_set[64] = {};           // LDS above 64 KiB has to be granted per kernel and device
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    if (dev < 0 || dev >= 64 || !attr_set[dev]) {
-        (void)hipFuncSetAttribute((const void *)gemm_bf16_rows_kernel<RT, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  SMEM);
-        if (dev >= 0 && dev < 64) attr_set[dev] = true;
-    }
+    static std::atomic<bool> granted[kLdsDevices];
+    grant_lds((const void *)gemm_bf16_rows_kernel<RT, EPI>, SMEM, granted);
     gemm_bf16_rows_kernel<RT, EPI><<<dim3(p.m_chunks * n_colblk, p.splits), 256, SMEM, st>>>(
         a, w, out, M, N, K, p.splits, p.m_chunks, n_tall, n_colblk, ch);
 }

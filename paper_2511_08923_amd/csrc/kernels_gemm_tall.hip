@@ -67,26 +67,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
     int w_off[CT];
 #pragma unroll
     for (int j = 0; j < CT; ++j) w_off[j] = j < w_here ? lane16 : OOB;
-    auto load_tile = [&](unsigned dst, int off, int4v desc, bool here, int src, int i) __attribute__((always_inline)) {
-        desc[2] = here ? desc[2] : 0;
-        dst += (i & ~3) * 1024;
-        src = here ? src + (i & ~3) * 1024 : 0;
-        if ((i & 3) == 0) dma16_at<0>(dst, off, desc, src);
-        else if ((i & 3) == 1) dma16_at<1024>(dst, off, desc, src);
-        else if ((i & 3) == 2) dma16_at<2048>(dst, off, desc, src);
-        else dma16_at<3072>(dst, off, desc, src);
-    };
     auto load_a = [&](int c, int buf, int i) __attribute__((always_inline)) {
-        load_tile(a_dst + buf * A_CHUNK, i < RT - 1 ? lane16 : a_last, da, 4 * c + wave < n_steps, a_src + 4 * c * m_tiles * 1024, i);
+        dma16_tile(a_dst + buf * A_CHUNK, i < RT - 1 ? lane16 : a_last, da, 4 * c + wave < n_steps, a_src + 4 * c * m_tiles * 1024, i);
     };
     auto load_w = [&](int c, int buf, int j) __attribute__((always_inline)) {
-        load_tile(w_dst + buf * W_CHUNK, w_off[j], dw, 4 * c + wave < n_steps, w_src + 4 * c * t32 * 1024, j);
-    };
-    auto barrier = [&]() __attribute__((always_inline)) {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0)
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+        dma16_tile(w_dst + buf * W_CHUNK, w_off[j], dw, 4 * c + wave < n_steps, w_src + 4 * c * t32 * 1024, j);
     };
     auto next = [](int b, int n) { return b + 1 == n ? 0 : b + 1; };
     f32x16 acc[RW][CT];
@@ -112,7 +97,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
 #pragma unroll
         for (int l = 0; l < (c < PA - 1 ? LOADS : LOADS / 4); ++l) load(c - PA, c, c + PW - PA, l);
     wait_loads<CT + (PA - 2) * LOADS + LOADS / 4>();
-    barrier();
+    lds_barrier_counted();
     // the wave's row tiles: wave, wave + 4, ...
     const unsigned char *fa = tall_smem + (wave * 64 + lane) * 16, *fw = tall_smem + PA * A_CHUNK + lane * 16;
     auto k_loop = [&](auto ra_tag) __attribute__((always_inline)) {
@@ -149,7 +134,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
                 };
                 auto sync = [&]() __attribute__((always_inline)) {
                     wait_loads<CT + (PA - 2) * (RT + CT)>();
-                    barrier();               // chunk c+1 has landed for everyone, chunk c has been read by everyone
+                    lds_barrier_counted();               // chunk c+1 has landed for everyone, chunk c has been read by everyone
                 };
                 if constexpr (NM == 0) {
                     if (q == 3) sync();
@@ -185,7 +170,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
     if (mine == RW) k_loop(std::integral_constant<int, RW>());
     else k_loop(std::integral_constant<int, RW - 1>());
     wait_loads<0>();
-    barrier();
+    lds_barrier_counted();
     ChooseArgs none = {};
     large_epilogue<RW, CT, 4>(acc, out, tall_smem, epi, split, M, N, mt_base, ct_here, tile0, wave, 4, wave, lane, none);
 }
@@ -195,14 +180,8 @@ void launch_tall(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int
     constexpr int SMEM = 4 * 1024 * (a_chunks(RT, CT) * RT + w_chunks(RT, CT) * CT);
     static_assert(SMEM >= 4 * 32 * 36 * 4, "the epilogue's patches");
     const int units = ((N + 31) / 32 + CT - 1) / CT * p.splits, n_tall = (M + 31) / 32 - p.m_chunks * (RT - 1);
-    static bool attr_set[64] = {};           // LDS above 64 KiB has to be granted per kernel and device
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    if (dev < 0 || dev >= 64 || !attr_set[dev]) {
-        (void)hipFuncSetAttribute((const void *)gemm_bf16_tall_kernel<RT, CT>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        if (dev >= 0 && dev < 64) attr_set[dev] = true;
-    }
+    static std::atomic<bool> granted[kLdsDevices];
+    grant_lds((const void *)gemm_bf16_tall_kernel<RT, CT>, SMEM, granted);
     gemm_bf16_tall_kernel<RT, CT><<<dim3((units + 7) / 8 * 8 * p.m_chunks), 256, SMEM, st>>>(
         a, w, out, M, N, K, p.splits, epi, p.m_chunks, n_tall);
 }

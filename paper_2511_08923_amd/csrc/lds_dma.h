@@ -33,8 +33,29 @@ __device__ inline void dma16_at(unsigned lds_addr, int voff, int4v desc, int sof
                  : "memory", "m0");
 }
 #pragma clang diagnostic pop
+// Tile i of tiles that lie side by side, 1 KiB each, in memory from soff and in LDS from lds_addr on: four share their base
+// addresses.  Not `here`: out of bounds, through a buffer without records.  (i: a constant of the unrolled code)
+__device__ __attribute__((always_inline)) inline void dma16_tile(unsigned lds_addr, int voff, int4v desc, bool here, int soff,
+                                                                 int i) {
+    desc[2] = here ? desc[2] : 0;
+    lds_addr += (i & ~3) * 1024;
+    soff = here ? soff + (i & ~3) * 1024 : 0;
+    if ((i & 3) == 0) dma16_at<0>(lds_addr, voff, desc, soff);
+    else if ((i & 3) == 1) dma16_at<1024>(lds_addr, voff, desc, soff);
+    else if ((i & 3) == 2) dma16_at<2048>(lds_addr, voff, desc, soff);
+    else dma16_at<3072>(lds_addr, voff, desc, soff);
+}
 __device__ inline void lds_barrier() {       // workgroup barrier for LDS traffic only: global loads stay in flight
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// The same with the wait as the builtin: the compiler then knows that no LDS read is outstanding and counts exactly which of the
+// next ones an MFMA needs.
+__device__ __attribute__((always_inline)) inline void lds_barrier_counted() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }
