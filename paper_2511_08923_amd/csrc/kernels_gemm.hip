@@ -778,11 +778,20 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
         //     11.4, 20.8 -> 17.5, 21.3 -> 18.4; 272 x 1792 x 9216 22.4 -> 18.7.  With fewer splits only up to three row tiles
         //     and from 2048 k on: 72 x 4096 x 12288 26.8 -> 25.9, 72 x 3072 x 8192 17.5 -> 16.4; 272 x 4096 x 4096 17.5 -> 18.0,
         //     272 x 4096 x 12288 37 -> 40, 72 x 4096 x 2048 (512 k) 8.6 -> 9.0.
+        // Where column blocks x splits is a multiple of eight, both row passes of the kernel below run on the same XCD (workgroup i
+        // on XCD i % 8) and the second takes its weights from that XCD's L2: many short shares come here from seven row tiles on
+        // then.  Below -> here at 40 / 96 / 160 / 192 / 224 / 272 rows, weights from HBM: 1536 x 8192 11.2 -> 10.8, 12.0 -> 11.9,
+        // 13.2 -> 14.5, 14.0 -> 15.6, 15.6 -> 16.1, 17.9 -> 18.1; 2560 x 6144 11.4 -> 11.5, 12.4 -> 12.5, 14.4 -> 15.4, 14.8 ->
+        // 16.4, 18.9 -> 16.7, 21.2 -> 19.6 (from the memory-side cache, 40 rows 8.3 -> 10.6); another count, 1536 x 9216: 12.1 ->
+        // 10.9 and 20.6 -> 19.0 at 40 and 272.  The longer shares gain either way (3840 x 10240 21.1 -> 18.4, 23.4 -> 22.1 at 96).
+        // More than 256 workgroups: the second round is ragged and loses, 72 / 272 x 28672 x 4096 49.1 -> 71.5, 73.6 -> 113.0.
         int ct = 0;
         if (!force_single_split) {
             const int share = splits == 1 ? K : (units + splits - 1) / splits * SPLIT_UNIT;
-            const int t_max = splits >= 5 && share <= 1024 ? 10 : splits > 1 && share >= 2048 ? 3 : 0;
-            if (row_split && t <= t_max) ct = 2;
+            const bool short_shares = splits >= 5 && share <= 1024;
+            const int t_min = short_shares && wgs * splits % 8 == 0 ? 7 : 1;
+            const int t_max = short_shares ? 10 : splits > 1 && share >= 2048 ? 3 : 0;
+            if (row_split && t >= t_min && t <= t_max) ct = 2;
             if (splits == 1 && wgs > 128 && (t <= 9 || (N + 255) / 256 * ((t + 4) / 5) > 256)) ct = 3;
             const int n = ct ? (t32 + ct - 1) / ct * splits : 0;
             if (share < 1024 || n < 180 || n > 256) ct = 0;
