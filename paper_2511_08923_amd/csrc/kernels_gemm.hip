@@ -629,8 +629,12 @@ static int fit_splits(int want, int units) {
     return (units + per - 1) / per;
 }
 
-// Products of up to 32 rows that run with two column tiles per workgroup (figures at the launch)
-static bool few_rows_two(int N) { return N < 6144; }
+// Products of up to 32 rows that run with two column tiles per workgroup: those whose 64-column blocks fill the chip with three
+// and more whole splits, or nearly fill it with two (figures at the launch)
+static bool few_rows_two(int N) {
+    const int blocks = (N + 63) / 64;
+    return blocks <= 85 || (blocks >= 116 && blocks <= 128);
+}
 
 bool gemm_fuse_ok(int M, int N, int K) { return M >= 1 && M <= kFuseMaxRows && K <= kFuseMaxK && K % 32 == 0 && N % 16 == 0; }
 
@@ -672,10 +676,13 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
         p.m_chunks = 1;
         // nearest count that brings the grid to about one wave of CUs; from half of that on a single split, which saves
         // the partial sums and, for gate/up, the SwiGLU launch (1.5B shape, 6 rows: 17.1 + 4.0 us in two splits)
-        // (narrow products run in column blocks of 64: as many splits as those need to fill the chip.  A split is a copy of the
-        // output that the next kernel reads, every workgroup of it where that folds the norm in)
-        const int blocks = few_rows_two(N) ? (N + 63) / 64 : wgs;
-        if (!force_single_split && wgs < 128) splits = fit((256 + blocks / 2) / blocks);
+        // Products in column blocks of 64: as many splits as the chip holds workgroups, and none more.  A few workgroups beyond 256
+        // are a second one on some units, which the launch waits for: 6 rows, nearest count -> this, 2176 x 12288 14.7 -> 12.4 us
+        // (8 -> 6 splits), 2944 x 12288 18.4 -> 14.8, 3456 x 12288 20.4 -> 16.9, 4224 x 4096 10.9 -> 9.4, 4480 x 12288 25.7 -> 20.8
+        // (4 -> 3).  (A split is also a copy of the output that the next kernel reads.)
+        const bool two = few_rows_two(N);
+        const int blocks = two ? (N + 63) / 64 : wgs;
+        if (!force_single_split && wgs < 128) splits = fit(two ? 256 / blocks : (256 + blocks / 2) / blocks);
     } else {
         // Partial sums are the expensive part of a split (each one is M x N floats written and read again), so
         // the column blocks are split over K only until about half the CUs are busy; the rest of the chip is
@@ -872,6 +879,8 @@ void launch_gemm_bf16(const bf16_t *a, const bf16_t *w, float *out, int M, int N
         // Two column tiles per workgroup where partial sums of a narrow product leave compute units idle otherwise, four where there
         // are enough of them (and for the epilogues that need gate and up, or a column group, in one wave).  Four / two at 6 rows:
         // 2048 x 1536 5.2 / 4.3 us, 1536 x 8960 7.9 / 7.2, 4096 x 12288 22.3 / 21.2, 4096 x 4096 9.4 / 9.3, 6144 x 4096 11.5 / 12.4.
+        // Wider, where 64-column blocks have room for two splits only: 6016 x 12288 25.8 / 32.6, 5760 x 4096 10.5 / 12.4, 6656 x 8192
+        // 20.3 / 21.2, 7424 x 8192 21.6 / 21.2, 8064 x 4096 14.5 / 14.0, 8192 x 8192 28.2 / 24.2 (20 rows 29.0 / 25.6).
         const bool two = out_row_major == GEMM_EPI_TILED && few_rows_two(N);
         if (p.mt == 1 && two) launch_few<1, 2>(a, w, out, M, N, K, p, out_row_major, st, ch);
         else if (p.mt == 1) launch_few<1, 4>(a, w, out, M, N, K, p, out_row_major, st, ch);
