@@ -161,6 +161,10 @@ tidar_status tidar_workspace_bytes(const tidar_ctx *ctx, int32_t batch, int32_t 
  * K/V and return the first drafts.  Runs in causal chunks through the same
  * kernels as the step; prompts that are no longer than a chunk go through one
  * pass together as far as a chunk's rows and the workspace reach.
+ * The rows that share a pass decide how its sums are grouped, so the bits of a
+ * prompt's results follow its neighbours, prompt_len and ws_bytes, within
+ * rounding of the prompt prefilled alone; with the same arguments they are the
+ * same in every call.
  *   prompt      dev int32 [batch][prompt_stride]
  *   prompt_len  host int32 [batch], each >= 1
  *   prefix_len  dev int32 [batch] out: set to prompt_len

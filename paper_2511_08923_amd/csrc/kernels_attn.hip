@@ -881,7 +881,7 @@ static int xcds_of_group(int n_groups) {
 // The order of a single sequence's causal pass (prefill, scoring; n_groups <= 8, so that a group has 8 / q XCDs to
 // itself).  Its workgroups walk key ranges of very different length, and all of them are resident from the start or
 // nearly so: two to a compute unit, the launch takes as long as the compute unit with the most to do (a workgroup left
-// alone on its SIMDs goes on at close to twice the speed).  The dispatcher deals the first 32 of an XCD's workgroups to
+// alone on its SIMDs goes on at 1.4 times the speed, not at twice, so unequal pairs cost).  The dispatcher deals the first 32 of an XCD's workgroups to
 // its 32 compute units and the next 32 to the same units in the same order, so by index a unit got the same rows of two
 // query heads, twice the longest range or twice the shortest.  Here the item in second place on a unit is the shorter
 // the longer the first one is; what is left after two rounds follows with the longest first.  8B prefill of 4096

@@ -26,9 +26,10 @@
 //     reads per MFMA, which the LDS has room for).  The weight fragment is the MFMA's first operand, so the
 //     accumulators hold the output transposed (lane = row): every epilogue starts from that.
 //   * split-K over blockIdx.y works in units of 512 k, row passes over blockIdx.z; up to 480 rows the split count
-//     and the kernel family depend on (N, K) and the row class (M <= 32 or not) only, so the partial-sum grouping of a
+//     and the order of a row's sum depend on (N, K) and the row class (M <= 4 with the producer folded in, M <= 32, more)
+//     only, so the partial-sum grouping of a
 //     row does not depend on how many rows travel with it (from 481 rows on both also follow the number of 256-row
-//     multiples).  Splits fill about half the CUs, two row passes the other half: a split
+//     multiples; which of the kernels with one order serves a row count is the plan's).  Splits fill about half the CUs, two row passes the other half: a split
 //     costs an M x N partial sum written and read again, a row pass only a second read of W from L2.
 //   * output: [split][32-column tile][row][32] fp32 partial sums (summed in fixed order by the consumer), or
 //     row-major logits, or - fused epilogues - bf16 SwiGLU products in the next GEMM's A-fragment layout, or
@@ -128,7 +129,7 @@ __device__ inline void store_tiles(const f32x4 (&acc)[MTW][NT], float *out, int 
     }
 }
 
-// ------------------------------------------------------------------ M <= 4: the same, its producer folded in
+// ------------------------------------------------------------------ M <= 4: one row tile, the GEMM's producer folded in
 // The A operand is built by the workgroup itself (see FuseArgs) into LDS as plain bf16 rows of its share of K; a
 // lane's fragment is then one 16-byte LDS read (lanes of rows that do not exist take zeros).  W streams through a register
 // ring, whose first loads are in flight while the prologue runs.
