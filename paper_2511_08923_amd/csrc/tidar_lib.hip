@@ -680,9 +680,16 @@ tidar_status tidar_workspace_bytes(const tidar_ctx *ctx, int32_t batch, int32_t 
     const tidar_config &c = ctx->cfg;
     if (batch < 1 || batch > c.max_batch || k < 1 || k > c.max_k || max_prefix_len < 0) return TIDAR_EINVAL;
     const int R = k * (k + 1);
-    Layout a = make_layout(c, batch, step_desc(k), kUniform, batch * R, max_prefix_len + R, true, k);
-    Layout b = make_layout(c, batch, ar_desc(), kUniform, batch, max_prefix_len + 1, true);
-    size_t t = a.total > b.total ? a.total : b.total;
+    // any number of sequences up to batch: the attention takes fewer key splits the more there are, so one more can need less
+    // (the partial sums of the GEMMs grow with the rows: enough for each)
+    size_t t = 0;
+    const size_t g_step = forward_gemm_floats(c, batch * R), g_ar = forward_gemm_floats(c, batch);
+    for (int n = 1; n <= batch; ++n) {
+        Layout a = make_layout(c, n, step_desc(k), kUniform, n * R, max_prefix_len + R, true, k, n * R <= kFuseMaxRows ? 0 : g_step);
+        Layout b = make_layout(c, n, ar_desc(), kUniform, n, max_prefix_len + 1, true, 0, n <= kFuseMaxRows ? 0 : g_ar);
+        if (a.total > t) t = a.total;
+        if (b.total > t) t = b.total;
+    }
     // prefill passes: a full causal chunk, or a last pass of 1..chunk causal rows plus the mask block
     Layout full = make_layout(c, 1, prefill_desc(ctx->prefill_chunk, k, false, 0), kUniform, 0,
                               max_prefix_len + ctx->prefill_chunk, true);
