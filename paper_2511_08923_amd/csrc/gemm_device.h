@@ -30,6 +30,10 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, size_t byte
 __device__ inline bf16x8 buf_load(__amdgpu_buffer_rsrc_t r, int byte_off) {
     return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 0));
 }
+// the same, non-temporal: for weights that one workgroup reads once
+__device__ inline bf16x8 buf_load_once(__amdgpu_buffer_rsrc_t r, int byte_off) {
+    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 2));
+}
 
 struct SplitRange {
     int q0, q1;   // k steps [q0, q1)

@@ -132,7 +132,8 @@ __device__ inline void store_tiles(const f32x4 (&acc)[MTW][NT], float *out, int 
 // ------------------------------------------------------------------ M <= 4: one row tile, the GEMM's producer folded in
 // The A operand is built by the workgroup itself (see FuseArgs) into LDS as plain bf16 rows of its share of K; a
 // lane's fragment is then one 16-byte LDS read (lanes of rows that do not exist take zeros).  W streams through a register
-// ring, whose first loads are in flight while the prologue runs.
+// ring, whose first loads are in flight while the prologue runs; its loads are non-temporal, as nobody reads them again (together
+// with those of gemm_bf16_few_kernel 8B one-token step 3626 -> 3527 us).
 template <int FUSE>
 __global__ __launch_bounds__(256) void gemm_bf16_small_fused_kernel(FuseArgs f, const bf16_t *__restrict__ w,
                                                                     float *__restrict__ out, int M, int N, int K,
@@ -157,7 +158,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_fused_kernel(FuseArgs f, 
                        : OOB;
     const int w_step = 2 * t32 * 1024;
     auto ld_w = [&](int j, int q) {
-        return buf_load(rw, (q < sr.q1 && w_off[j] != OOB) ? w_off[j] + q * w_step : OOB);
+        return buf_load_once(rw, (q < sr.q1 && w_off[j] != OOB) ? w_off[j] + q * w_step : OOB);
     };
     // Loads return in order: the ring's first loads (for a short share of K: all of the workgroup's weights) are
     // issued *behind* the prologue's loads, which come from L2 and the memory-side cache and are back long before
@@ -360,8 +361,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_fused_kernel(FuseArgs f, 
 // (6.1 TB/s; with every wave streaming its own columns and all of A through register rings 35.7 and 42.3), 6 x 2048 x 1536 5.9 ->
 // 4.3, 6 x 17920 x 1536 15.1 -> 13.1, 20 x 17920 x 1536 18.0 -> 14.2, 20 x 151936 x 4096 247 -> 226.  Eight chunks instead of
 // four 34.2 and 225 us (one workgroup per unit), three 36.3 and 229.
-constexpr int FEW_CHUNKS = 4;
-template <int MT, int CT>
+// ONCE: the weights' loads are non-temporal (FEW_ONCE workgroups and more).  A stream of loads alone reaches 7.1 TB/s so, 6.4
+// otherwise: 1 / 20 x 151936 x 4096 210 / 214 -> 186 / 191 us, 6 x 151936 x 1536 83.3 -> 73.5, 1 x 24576 x 4096 32.2 -> 31.4, 20 x
+// 6144 x 4096 11.9 -> 11.4, 20 x 4096 x 12288 21.2 -> 20.8, 20 x 4096 x 4096 9.8 -> 9.3.  With fewer workgroups it is latency that
+// counts, and theirs is longer: 6 and 20 x 17920 x 1536 (140 workgroups) 12.24 and 13.17 -> 12.38 and 13.29.
+constexpr int FEW_CHUNKS = 4, FEW_ONCE = 180;
+template <int MT, int CT, bool ONCE>
 __global__ __launch_bounds__(256) void gemm_bf16_few_kernel(const bf16_t *__restrict__ a, const bf16_t *__restrict__ w,
                                                             float *__restrict__ out, int M, int N, int K, int splits,
                                                             int epi, ChooseArgs ch) {
@@ -388,7 +393,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_kernel(const bf16_t *__rest
         const int src = ((2 * sr.q0 + 4 * c + wave) * t32 + tile0) * 1024;
 #pragma unroll
         for (int j = 0; j < CT; ++j)
-            dma16(dst + (wave * CT + j) * 1024, ok && tile0 + j < t32 ? lane * 16 : OOB, dw, ok ? src + j * 1024 : 0);
+            (ONCE ? dma16_once : dma16)(dst + (wave * CT + j) * 1024, ok && tile0 + j < t32 ? lane * 16 : OOB, dw,
+                                        ok ? src + j * 1024 : 0);
     };
     f32x4 acc[NJ][1][NH];
 #pragma unroll
@@ -590,10 +596,14 @@ template <int MT, int CT>
 void launch_few(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi, hipStream_t st,
                 const ChooseArgs &ch) {
     constexpr int SMEM = FEW_CHUNKS * 4 * (CT + 1) * 1024;
-    static std::atomic<bool> granted[kLdsDevices];
-    grant_lds((const void *)gemm_bf16_few_kernel<MT, CT>, SMEM, granted);
-    gemm_bf16_few_kernel<MT, CT><<<dim3(((N + 31) / 32 + CT - 1) / CT, p.splits), 256, SMEM, st>>>(a, w, out, M, N, K,
-                                                                                                 p.splits, epi, ch);
+    const dim3 grid(((N + 31) / 32 + CT - 1) / CT, p.splits);
+    auto go = [&](auto kernel, std::atomic<bool>(&granted)[kLdsDevices]) {
+        grant_lds((const void *)kernel, SMEM, granted);
+        kernel<<<grid, 256, SMEM, st>>>(a, w, out, M, N, K, p.splits, epi, ch);
+    };
+    static std::atomic<bool> granted[2][kLdsDevices];
+    if (grid.x * grid.y >= FEW_ONCE) go(gemm_bf16_few_kernel<MT, CT, true>, granted[1]);
+    else go(gemm_bf16_few_kernel<MT, CT, false>, granted[0]);
 }
 
 template <int MTA, bool WIDE, int NT = 2, int NW = 4>

@@ -23,6 +23,13 @@ __device__ inline void dma16(unsigned lds_addr, int voff, int4v desc, int soff) 
                  : "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff)
                  : "memory", "m0");
 }
+// The same for data that nobody reads again (weights that one workgroup reads once): non-temporal.
+__device__ inline void dma16_once(unsigned lds_addr, int voff, int4v desc, int soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                 :
+                 : "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff)
+                 : "memory", "m0");
+}
 // The same OFFSET (< 4096) bytes further on, in memory and in LDS alike: tiles that lie side by side in both share lds_addr and
 // soff.
 template <int OFFSET>
