@@ -25,7 +25,7 @@
 //     128 columns for the two-pass launches of 33-480 rows, one column tile per wave (no padded tile slots; twice the LDS fragment
 //     reads per MFMA, which the LDS has room for).  The weight fragment is the MFMA's first operand, so the
 //     accumulators hold the output transposed (lane = row): every epilogue starts from that.
-//   * split-K over blockIdx.y works in units of 512 k, row passes over blockIdx.z; up to 480 rows the split count
+//   * split-K works in units of 512 k, row passes are workgroups of their own; up to 480 rows the split count
 //     and the order of a row's sum depend on (N, K) and the row class (M <= 4 with the producer folded in, M <= 32, more)
 //     only, so the partial-sum grouping of a
 //     row does not depend on how many rows travel with it (from 481 rows on both also follow the number of 256-row
@@ -455,11 +455,16 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
     constexpr int THREADS = 64 * NW;
     constexpr int PFK = 2 * KS;                  // weight ring depth in k steps: two chunks
     constexpr int CTL = WIDE ? MTA : (MTA == 5) ? 9 : 2 * MTA;
-    // Many row passes: the (pass, column block) plane is cut into super-tiles of swz_p x swz_c workgroups, each
-    // handed whole to one XCD (workgroup i of a launch runs on XCD i % 8), passes fastest: the workgroups that
+    // Workgroup i of a launch runs on XCD i % 8.  The row passes of a column block and split follow each other on one XCD
+    // (the second read of its weights is an L2 hit) and the splits are dealt out first: with 2, 4 or 8 of them an XCD sees one
+    // share of K only, so a piece of A that its L2 fetches from afar serves all its workgroups of that share, and not one in
+    // `splits` of them.  Splits over blockIdx.y before: 272 / 216 x 4096 x 12288 41.4 -> 39.0, 37.6 -> 34.4 us inside a step, 4096
+    // x 4096 21.3 -> 20.7, 6144 x 4096 (two splits) the same.
+    // swz_p > 0, many column blocks and one split: the (pass, column block) plane is cut into super-tiles of swz_p x swz_c
+    // workgroups, each handed whole to one XCD, passes fastest: the workgroups that
     // are resident together on an XCD then share their A rows and W columns through its L2 instead of each
     // streaming a private W slice from HBM.
-    int bx = blockIdx.x, bz = blockIdx.z;
+    int bx, bz, split = 0;
     if (swz_p > 0) {
         const int i = blockIdx.x, xcd = i & 7, j = i >> 3;
         const int per = swz_p * swz_c;
@@ -469,6 +474,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
         bz = (st % n_sp) * swz_p + within % swz_p;
         bx = (st / n_sp) * swz_c + within / swz_p;
         if (bz >= n_pass || bx >= n_colblk) return;
+    } else {
+        const int j = blockIdx.x >> 3, unit = (j / n_pass) * 8 + (blockIdx.x & 7);
+        bz = j % n_pass;
+        split = unit % splits;
+        bx = unit / splits;
+        if (bx >= n_colblk) return;
     }
     constexpr int PIECES = CTL * KS * 64;        // 16-byte pieces per chunk
     constexpr int STAGE = (PIECES + THREADS - 1) / THREADS;
@@ -484,7 +495,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
     const int mt_base = bz * CTL;
     const int ct_here = min(CTL, m_tiles - mt_base);
     const int q_total = K >> 4;                                // k steps of 16
-    const SplitRange sr32 = split_range(K, splits, blockIdx.y);
+    const SplitRange sr32 = split_range(K, splits, split);
     const int q0 = sr32.q0 * 2, q1 = min(sr32.q1 * 2, q_total);
     const int c0 = q0 / KS, c1 = (q1 + KS - 1) / KS;
     const int tile0 = (bx * (WIDE ? NW : 2) + ng) * NT;  // first 32-column tile of this wave
@@ -588,7 +599,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
         }
     }
 
-    large_epilogue<MTA, NT, NW>(acc, out, gemm_smem, epi, blockIdx.y, M, N, mt_base, ct_here, tile0, mh * MTA, 1, wave, lane,
+    large_epilogue<MTA, NT, NW>(acc, out, gemm_smem, epi, split, M, N, mt_base, ct_here, tile0, mh * MTA, 1, wave, lane,
                                 ch);
 }
 
@@ -612,14 +623,14 @@ void launch_large(const bf16_t *a, const bf16_t *w, float *out, int M, int N, in
     constexpr int CTL = WIDE ? MTA : (MTA == 5) ? 9 : 2 * MTA;
     constexpr int BN = WIDE ? 32 * NW * NT : 128;
     int m_tiles = (M + 31) / 32;
-    dim3 grid((N + BN - 1) / BN, p.splits, (m_tiles + CTL - 1) / CTL);
-    const int n_colblk = grid.x, n_pass = grid.z;
+    const int n_colblk = (N + BN - 1) / BN, n_pass = (m_tiles + CTL - 1) / CTL;
+    dim3 grid((n_colblk * p.splits + 7) / 8 * 8 * n_pass);
     int swz_p = 0, swz_c = 0;
     if (p.swz > 0 && n_pass >= 2) {          // super-tiles of swz x swz workgroups, dealt to the XCDs in turn
         swz_p = p.swz < n_pass ? p.swz : n_pass;
         swz_c = p.swz;
         const int n_st = ((n_pass + swz_p - 1) / swz_p) * ((n_colblk + swz_c - 1) / swz_c);
-        grid = dim3(8 * ((n_st + 7) / 8) * swz_p * swz_c, p.splits, 1);
+        grid = dim3(8 * ((n_st + 7) / 8) * swz_p * swz_c);
     }
     // two staging buffers of a chunk's A tiles; the epilogue's per-wave transposition patches (4 x 32 x 36 floats)
     // reuse the same memory and need 18 KiB of it
