@@ -77,6 +77,32 @@ __device__ inline RowChoice row_choice(const ChooseArgs &ch, int row, int M) {
     return rc;
 }
 
+// out^T tiles: lane l holds activation row l % 16 and weight columns 4 * (l / 16) .. +3 of each 16 x 16 tile.
+// Two neighbouring column tiles make the 128 bytes a row has in a 32-column tile of the output; half of the lanes
+// trade one tile's values so that eight lanes store one whole row.
+template <bool ROWMAJOR>
+__device__ inline void store_pair(const f32x4 &t0, const f32x4 &t1, float *__restrict__ o, int row0, int col0, int M, int N,
+                                  int lane) {
+    const int n = lane & 15, g = lane >> 4;
+    const bool low = n < 8;
+    f32x4 first, second;                          // rows row0 + n % 8 and row0 + 8 + n % 8
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float give = low ? t1[e] : t0[e];
+        const float got = __builtin_bit_cast(
+            float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, give), 0x128, 0xf, 0xf, true));   // row_ror:8
+        first[e] = low ? t0[e] : got;
+        second[e] = low ? got : t1[e];
+    }
+    const int col = col0 + (low ? 0 : 16) + 4 * g;
+    if (col >= N) return;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int row = row0 + 8 * h + (n & 7);
+        if (row < M) *(f32x4 *)(o + (ROWMAJOR ? (size_t)row * N + col : pt_index(col, row, M))) = h ? second : first;
+    }
+}
+
 // Epilogue of a wave that holds MTA row tiles (row tiles r0, r0 + rs, ... of the workgroup's pass) by NT column tiles
 // (from tile0 on) of 32x32x16 accumulators.  NW waves per workgroup; ct_here: row tiles of the pass that exist; smem: at least NW * 32 * 36
 // floats nobody reads any more (with NT == 1 and GEMM_EPI_ARGMAX all waves of the workgroup have to come here).

@@ -1,18 +1,22 @@
 // bf16 GEMM of 33 to 480 rows: out = A[M][K] x W[N][K]^T, fp32 accumulation, same operand layouts and epilogues as
-// kernels_gemm.hip, and the same 32x32x16 MFMAs in the same order per output tile, so that the results are the same bits.
+// kernels_gemm.hip, and the same products added in the same order per output value (two 32x32x16 MFMAs and one 16x16x32 over the
+// same 32 k give the same bits), so that the results are the same bits.
 //
 // At these row counts the weights come from HBM once and the activations (the step's 272 rows: 2.2 MB at K = 4096) from L2
 // into every workgroup.  What bounds it is how much a compute unit takes in: with weights from HBM among the loads about
-// 57 GB/s whatever the kernel (272 x 24576 x 4096: loads alone 57 us, MFMAs and LDS reads alone 48; activations alone 82
-// GB/s per unit, everything from L2 102), which is why a deeper ring or fewer LDS reads change nothing beyond this:
+// 60 GB/s, whatever the kernel and whichever waves bring which operand (272 x 24576 x 4096: loads alone 52 us, weights alone 33,
+// activations alone 22; MFMAs and LDS reads alone 42), which is why a deeper ring or fewer LDS reads change little beyond this:
 //   * a workgroup owns all row tiles of the pass (up to twelve) and two or three column tiles, one workgroup per compute unit:
-//     no weight is read twice, all of them stream;
+//     no weight is read twice, all of them stream, by non-temporal loads;
 //   * both operands go straight into LDS (buffer_load ... lds), PA chunks of 64 k of A and PW of W: the weights, which
 //     are longer on their way, are asked for up to seven chunks ahead, in front of the activations of nearer chunks;
-//   * four waves over the rows (wave, wave + 4, ...): an A fragment is read from LDS once, a W fragment by every wave; the
-//     fragments of the next k step and the loads are spread between the MFMAs, one barrier per chunk of 64 k.
+//   * 16x16x32 MFMAs, four waves as 2 x 2: a wave owns one half of every row tile and half of the columns, RT x CT tiles of 16 x
+//     16, so that nine row tiles are an even deal (whole 32-row tiles dealt to four waves gave one of them three and the others
+//     two); the fragments of the next half chunk and the loads are spread between the MFMAs, one barrier per chunk of 64 k.
+// With 32x32x16 MFMAs, four waves over whole row tiles and plain loads gate/up read 58.7 us inside a step of 272 rows, now 57.5; 55.3
+// and 52.7 at 216 rows (8B step k = 16 7835 -> 7740 us, 3 x k = 8 6910 -> 6860, 1.5B k = 16 2970 -> 2957).
 // The accumulators are tied to AGPRs by inline assembly: left to the compiler they are copied between the register files
-// around every use (85 instead of 63 us).  The waves sharing K (16x16x32 MFMAs, half the LDS reads) were no faster.
+// around every use (85 instead of 63 us).
 // Measured sizes stand at the rule in plan_gemm_bf16.
 #include <type_traits>
 
@@ -39,12 +43,13 @@ template <int RT, int CT>
 __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__restrict__ a, const bf16_t *__restrict__ w,
                                                              float *__restrict__ out, int M, int N, int K, int splits,
                                                              int epi, int n_pass, int n_tall) {
-    constexpr int PA = a_chunks(RT, CT), PW = w_chunks(RT, CT), RW = (RT + 3) / 4;
+    constexpr int PA = a_chunks(RT, CT), PW = w_chunks(RT, CT);
     constexpr int A_CHUNK = 4 * RT * 1024, W_CHUNK = 4 * CT * 1024;
     static_assert(PA * A_CHUNK + PW * W_CHUNK <= LDS_KB * 1024, "LDS of a compute unit");
     static_assert(PW * CT + PA * RT < 62, "the loads in flight are counted in six bits");
     extern __shared__ __attribute__((aligned(16))) unsigned char tall_smem[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int mh = wave >> 1, ng = wave & 1;
     const int t32 = (N + 31) >> 5, m_tiles = (M + 31) >> 5;
     const int j8 = blockIdx.x >> 3, unit = (j8 / n_pass) * 8 + (blockIdx.x & 7);
     const int bz = j8 % n_pass, split = unit % splits, tile0 = (unit / splits) * CT;
@@ -71,22 +76,22 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
         dma16_tile(a_dst + buf * A_CHUNK, i < RT - 1 ? lane16 : a_last, da, 4 * c + wave < n_steps, a_src + 4 * c * m_tiles * 1024, i);
     };
     auto load_w = [&](int c, int buf, int j) __attribute__((always_inline)) {
-        dma16_tile(w_dst + buf * W_CHUNK, w_off[j], dw, 4 * c + wave < n_steps, w_src + 4 * c * t32 * 1024, j);
+        dma16_tile<true>(w_dst + buf * W_CHUNK, w_off[j], dw, 4 * c + wave < n_steps, w_src + 4 * c * t32 * 1024, j);
     };
     auto next = [](int b, int n) { return b + 1 == n ? 0 : b + 1; };
-    f32x16 acc[RW][CT];
+    // The wave's row tile i (16 rows) is half mh of the pass's tile i.  Its column tiles (16 columns): the halves of column tile
+    // ng and, of three, half ng of the third one.
+    f32x4 acc[RT][CT];
 #pragma unroll
-    for (int i = 0; i < RW; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int j = 0; j < CT; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        for (int j = 0; j < CT; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < PW - PA; ++c)
 #pragma unroll
         for (int j = 0; j < CT; ++j) load_w(c, c, j);
-    // generation g of the loads brings chunks g + PA of A and g + PW of W into the buffers that chunk g leaves; a quarter of it
-    // goes out in step 3 of chunk g, the others in steps 0, 1 and 2 of chunk g + 1
+    // generation g of the loads brings chunks g + PA of A and g + PW of W into the buffers that chunk g leaves; one half of it
+    // goes out in the second half of chunk g, the other in the first half of chunk g + 1
     constexpr int LOADS = RT + CT;
     auto load = [&](int g, int ba, int bw, int l) __attribute__((always_inline)) {
         if (l < RT) load_a(g + PA, ba, l);
@@ -95,70 +100,64 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
 #pragma unroll
     for (int c = 0; c < PA; ++c)
 #pragma unroll
-        for (int l = 0; l < (c < PA - 1 ? LOADS : LOADS / 4); ++l) load(c - PA, c, c + PW - PA, l);
-    wait_loads<CT + (PA - 2) * LOADS + LOADS / 4>();
+        for (int l = 0; l < (c < PA - 1 ? LOADS : LOADS / 2); ++l) load(c - PA, c, c + PW - PA, l);
+    wait_loads<CT + (PA - 2) * LOADS + LOADS / 2>();
     lds_barrier_counted();
-    // the wave's row tiles: wave, wave + 4, ...
-    const unsigned char *fa = tall_smem + (wave * 64 + lane) * 16, *fw = tall_smem + PA * A_CHUNK + lane * 16;
+    // lane (n, g) of a 16x16x32 fragment takes k slots 8g .. 8g+7 of row n: stored k step g/2, stored lane (g%2)*32 + n
+    const int frag = ((lane >> 4) & 1) * 512 + (lane & 15) * 16;
+    const unsigned char *fa = tall_smem + (lane >> 5) * RT * 1024 + frag + mh * 256;
+    const unsigned char *fw = tall_smem + PA * A_CHUNK + (lane >> 5) * CT * 1024 + frag;
+    const unsigned char *fw01 = fw + ng * 1024, *fw2 = fw + 2 * 1024 + ng * 256;
     auto k_loop = [&](auto ra_tag) __attribute__((always_inline)) {
-        constexpr int RA = decltype(ra_tag)::value, NM = RA * CT, READS = RA ? RA + CT : 0;
-        bf16x8 af[2][RA ? RA : 1], wf[2][CT];
-        auto read = [&](int s, int step, const unsigned char *ca, const unsigned char *cw, int f) __attribute__((always_inline)) {
-            // in the order of use: W 0, A 0, the other W, the other A
-            if (f == 0) wf[s][0] = *(const bf16x8 *)(cw + step * CT * 1024);
-            else if (f == 1) af[s][0] = *(const bf16x8 *)(ca + step * RT * 1024);
-            else if (f <= CT) wf[s][f - 1] = *(const bf16x8 *)(cw + (step * CT + f - 1) * 1024);
-            else af[s][f - CT] = *(const bf16x8 *)(ca + (step * RT + 4 * (f - CT)) * 1024);
+        constexpr int RA = decltype(ra_tag)::value, NM = RA * CT, READS = RA + CT;
+        constexpr int B = NM >= 12 ? 3 : 1;           // MFMAs in front of the barrier
+        bf16x8 af[2][RA], wf[2][CT];
+        // fragments of half `half` of a chunk, in the order of use: W 0, A 0, the other W, the other A
+        auto read = [&](int s, int half, int a_buf, int w_buf, int f) __attribute__((always_inline)) {
+            const int ao = a_buf * A_CHUNK + half * 2 * RT * 1024, wo = w_buf * W_CHUNK + half * 2 * CT * 1024;
+            const int j = f == 0 ? 0 : f - 1, i = f == 1 ? 0 : f - CT;
+            if (f == 0 || (f > 1 && f <= CT)) wf[s][j] = *(const bf16x8 *)(j < 2 ? fw01 + wo + j * 256 : fw2 + wo);
+            else af[s][i] = *(const bf16x8 *)(fa + ao + i * 1024);
         };
 #pragma unroll
-        for (int f = 0; f < READS; ++f) read(0, 0, fa, fw, f);
+        for (int f = 0; f < READS; ++f) read(0, 0, 0, 0, f);
         int ba = 0, bw = 0, g = -1, ga = PA - 1, gw = PW - 1;      // buffers of chunk c; generation under way and its buffers
         for (int c = 0; c < n_chunks; ++c) {
             const int na = next(ba, PA), nw = next(bw, PW);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int s = q & 1;
-                const unsigned char *ca = fa + (q == 3 ? na : ba) * A_CHUNK, *cw = fw + (q == 3 ? nw : bw) * W_CHUNK;
-                if (q == 3) {
+            for (int q = 0; q < 2; ++q) {
+                if (q == 1) {
                     ga = ba;
                     gw = bw;
                     g = c;
                 }
-                const int l0 = LOADS * ((q + 1) & 3) / 4, l1 = LOADS * (((q + 1) & 3) + 1) / 4;
-                constexpr int B = NM > 1 ? 1 : 0;         // MFMAs in front of the barrier
+                const int l0 = q ? 0 : LOADS / 2, l1 = q ? LOADS / 2 : LOADS;
                 auto ops = [&](int x, int n) __attribute__((always_inline)) {
-                    const int r0 = READS * x / n, r1 = READS * (x + 1) / n;
-                    for (int f = r0; f < r1; ++f) read(s ^ 1, (q + 1) & 3, ca, cw, f);
-                    const int m0 = l0 + (l1 - l0) * x / n, m1 = l0 + (l1 - l0) * (x + 1) / n;
-                    for (int l = m0; l < m1; ++l) load(g, ga, gw, l);
+                    for (int f = READS * x / n; f < READS * (x + 1) / n; ++f) read(q ^ 1, q ^ 1, q ? na : ba, q ? nw : bw, f);
+                    for (int l = l0 + (l1 - l0) * x / n; l < l0 + (l1 - l0) * (x + 1) / n; ++l) load(g, ga, gw, l);
                 };
-                auto sync = [&]() __attribute__((always_inline)) {
-                    wait_loads<CT + (PA - 2) * (RT + CT)>();
-                    lds_barrier_counted();               // chunk c+1 has landed for everyone, chunk c has been read by everyone
-                };
-                if constexpr (NM == 0) {
-                    if (q == 3) sync();
-                    ops(0, 1);
-                }
 #pragma unroll
                 for (int m = 0; m < NM; ++m) {
-                    if (q == 3 && m == B) sync();
+                    if (q == 1 && m == B) {
+                        wait_loads<CT + (PA - 2) * LOADS>();
+                        lds_barrier_counted();           // chunk c+1 has landed for everyone, chunk c has been read by everyone
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                     // The compiler does not see the MFMAs finish, and where the loop ends it may copy their results at once, so
-                    // the last one of the last chunk brings the wait (32 states; it asks for 12 before its result is read) in
-                    // the same piece of assembly
-                    if (q == 3 && m == NM - 1)
-                        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0\n\t"
+                    // the last one of the last chunk brings the wait (32 states; it asks for fewer than 20 before its result is
+                    // read) in the same piece of assembly
+                    if (q == 1 && m == NM - 1)
+                        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\t"
                                      "s_cmp_lg_i32 %3, %4\n\ts_cbranch_scc1 .Lmore%=\n\ts_nop 15\n\ts_nop 15\n.Lmore%=:"
                                      : "+a"(acc[m / CT][m % CT])
-                                     : "v"(wf[s][m % CT]), "v"(af[s][m / CT]), "s"(c + 1), "s"(n_chunks)
+                                     : "v"(wf[q][m % CT]), "v"(af[q][m / CT]), "s"(c + 1), "s"(n_chunks)
                                      : "scc");
                     else
-                        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
+                        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
                                      : "+a"(acc[m / CT][m % CT])
-                                     : "v"(wf[s][m % CT]), "v"(af[s][m / CT]));
+                                     : "v"(wf[q][m % CT]), "v"(af[q][m / CT]));
                     __builtin_amdgcn_sched_barrier(0);
-                    if (q != 3) ops(m, NM);
+                    if (q == 0) ops(m, NM);
                     else if (m >= B) ops(m - B, NM - B);
                 }
             }
@@ -166,19 +165,65 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
             bw = nw;
         }
     };
-    const int mine = (ct_here - wave + 3) >> 2;              // row tiles of this wave: RW or one less
-    if (mine == RW) k_loop(std::integral_constant<int, RW>());
-    else k_loop(std::integral_constant<int, RW - 1>());
+    const bool last_here = ct_here == RT && (mt_base + RT - 1) * 32 + mh * 16 < M;
+    if (last_here) k_loop(std::integral_constant<int, RT>());
+    else k_loop(std::integral_constant<int, RT - 1>());
     wait_loads<0>();
     lds_barrier_counted();
-    ChooseArgs none = {};
-    large_epilogue<RW, CT, 4>(acc, out, tall_smem, epi, split, M, N, mt_base, ct_here, tile0, wave, 4, wave, lane, none);
+
+    // ---- epilogue: lane (n, g) holds activation row n and weight columns 4g .. 4g+3 of each 16 x 16 tile
+    const int n = lane & 15, g = lane >> 4;
+    auto row_of = [&](int i) { return (mt_base + i) * 32 + mh * 16; };
+    auto exists = [&](int i) { return i < RT - 1 || last_here; };
+    if (epi == GEMM_EPI_SWIGLU) {
+        // The halves of a column tile are gate and up of the same 16 features; a lane's four are half of a 16-byte piece of the
+        // next GEMM's A fragment.  Of the third column tile one wave has the gates, its neighbour the ups: they trade, and each
+        // finishes every other row tile.
+        bf16_t *ho = reinterpret_cast<bf16_t *>(out);
+        auto put = [&](int i, int tile, const f32x4 &gt, const f32x4 &up) __attribute__((always_inline)) {
+            typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+            bf16x4 h;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                h[e] = (bf16_t)(gt[e] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gt[e])) * up[e]);
+            if (tile < t32 && exists(i))
+                *(bf16x4 *)(ho + (((size_t)tile * m_tiles + mt_base + i) * 64 + (g >> 1) * 32 + mh * 16 + n) * 8 + (g & 1) * 4) = h;
+        };
+        f32x4 *trade = reinterpret_cast<f32x4 *>(tall_smem) + mh * RT * 64 + lane;
+        if constexpr (CT == 3) {
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+                if ((i & 1) != ng) trade[i * 64] = acc[i][2];
+            lds_barrier_counted();
+        }
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            put(i, tile0 + ng, acc[i][0], acc[i][1]);
+            if constexpr (CT == 3)
+                if ((i & 1) == ng) {
+                    const f32x4 other = trade[i * 64];
+                    put(i, tile0 + 2, ng ? other : acc[i][2], ng ? acc[i][2] : other);
+                }
+        }
+        return;
+    }
+    float *o = out + (size_t)split * pt_split_stride(M, N);
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        if (!exists(i)) continue;
+        const int col = (tile0 + ng) * 32, col2 = (tile0 + 2) * 32 + ng * 16 + 4 * g, row = row_of(i) + n;
+        if (epi == GEMM_EPI_ROWMAJOR) store_pair<true>(acc[i][0], acc[i][1], o, row_of(i), col, M, N, lane);
+        else store_pair<false>(acc[i][0], acc[i][1], o, row_of(i), col, M, N, lane);
+        if constexpr (CT == 3)
+            if (row < M && col2 < N)
+                *(f32x4 *)(o + (epi == GEMM_EPI_ROWMAJOR ? (size_t)row * N + col2 : pt_index(col2, row, M))) = acc[i][2];
+    }
 }
 
 template <int RT, int CT>
 void launch_tall(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi, hipStream_t st) {
     constexpr int SMEM = 4 * 1024 * (a_chunks(RT, CT) * RT + w_chunks(RT, CT) * CT);
-    static_assert(SMEM >= 4 * 32 * 36 * 4, "the epilogue's patches");
+    static_assert(SMEM >= 2 * RT * 1024, "the epilogue's trade");
     const int units = ((N + 31) / 32 + CT - 1) / CT * p.splits, n_tall = (M + 31) / 32 - p.m_chunks * (RT - 1);
     static std::atomic<bool> granted[kLdsDevices];
     grant_lds((const void *)gemm_bf16_tall_kernel<RT, CT>, SMEM, granted);

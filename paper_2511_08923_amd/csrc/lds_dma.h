@@ -32,25 +32,33 @@ __device__ inline void dma16_once(unsigned lds_addr, int voff, int4v desc, int s
 }
 // The same OFFSET (< 4096) bytes further on, in memory and in LDS alike: tiles that lie side by side in both share lds_addr and
 // soff.
-template <int OFFSET>
+template <int OFFSET, bool ONCE>
 __device__ inline void dma16_at(unsigned lds_addr, int voff, int4v desc, int soff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
-                 :
-                 : "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff), "n"(OFFSET)
-                 : "memory", "m0");
+    if constexpr (ONCE)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%4 nt lds"
+                     :
+                     : "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff), "n"(OFFSET)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
+                     :
+                     : "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff), "n"(OFFSET)
+                     : "memory", "m0");
 }
 #pragma clang diagnostic pop
 // Tile i of tiles that lie side by side, 1 KiB each, in memory from soff and in LDS from lds_addr on: four share their base
-// addresses.  Not `here`: out of bounds, through a buffer without records.  (i: a constant of the unrolled code)
+// addresses.  Not `here`: out of bounds, through a buffer without records.  (i: a constant of the unrolled code; ONCE: as
+// dma16_once)
+template <bool ONCE = false>
 __device__ __attribute__((always_inline)) inline void dma16_tile(unsigned lds_addr, int voff, int4v desc, bool here, int soff,
                                                                  int i) {
     desc[2] = here ? desc[2] : 0;
     lds_addr += (i & ~3) * 1024;
     soff = here ? soff + (i & ~3) * 1024 : 0;
-    if ((i & 3) == 0) dma16_at<0>(lds_addr, voff, desc, soff);
-    else if ((i & 3) == 1) dma16_at<1024>(lds_addr, voff, desc, soff);
-    else if ((i & 3) == 2) dma16_at<2048>(lds_addr, voff, desc, soff);
-    else dma16_at<3072>(lds_addr, voff, desc, soff);
+    if ((i & 3) == 0) dma16_at<0, ONCE>(lds_addr, voff, desc, soff);
+    else if ((i & 3) == 1) dma16_at<1024, ONCE>(lds_addr, voff, desc, soff);
+    else if ((i & 3) == 2) dma16_at<2048, ONCE>(lds_addr, voff, desc, soff);
+    else dma16_at<3072, ONCE>(lds_addr, voff, desc, soff);
 }
 __device__ inline void lds_barrier() {       // workgroup barrier for LDS traffic only: global loads stay in flight
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
