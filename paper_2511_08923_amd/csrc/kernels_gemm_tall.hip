@@ -5,11 +5,12 @@
 // At these row counts the weights come from HBM once and the activations (the step's 272 rows: 2.2 MB at K = 4096) from L2
 // into every workgroup.  What bounds it is how much a compute unit takes in: with weights from HBM among the loads about
 // 60 GB/s, whatever the kernel and whichever waves bring which operand (272 x 24576 x 4096: loads alone 52 us, weights alone 33,
-// activations alone 22; MFMAs and LDS reads alone 42), which is why a deeper ring or fewer LDS reads change little beyond this:
+// activations alone 22; MFMAs and LDS reads alone 42), in the order asked for, which is why a deeper ring or fewer LDS
+// reads change little beyond this:
 //   * a workgroup owns all row tiles of the pass (up to twelve) and two or three column tiles, one workgroup per compute unit:
 //     no weight is read twice, all of them stream, by non-temporal loads;
 //   * both operands go straight into LDS (buffer_load ... lds), PA chunks of 64 k of A and PW of W: the weights, which
-//     are longer on their way, are asked for up to seven chunks ahead, in front of the activations of nearer chunks;
+//     are longer on their way, are asked for up to seven chunks ahead, two chunks at a time;
 //   * 16x16x32 MFMAs, four waves as 2 x 2: a wave owns one half of every row tile and half of the columns, RT x CT tiles of 16 x
 //     16, so that nine row tiles are an even deal (whole 32-row tiles dealt to four waves gave one of them three and the others
 //     two); the fragments of the next half chunk and the loads are spread between the MFMAs, one barrier per chunk of 64 k.
@@ -38,6 +39,16 @@ constexpr int w_chunks(int rt, int ct) {
     return p;
 }
 
+// f(LO), ..., f(HI - 1), each index a constant of the code (left to the unroller, the larger kernels stayed loops, with their
+// fragments in scratch memory)
+template <int LO, int HI, class F>
+__device__ __attribute__((always_inline)) inline void each(F &&f) {
+    if constexpr (LO < HI) {
+        f(std::integral_constant<int, LO>());
+        each<LO + 1, HI>(f);
+    }
+}
+
 // RT: row tiles of the higher passes, CT: column tiles of a workgroup
 template <int RT, int CT>
 __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__restrict__ a, const bf16_t *__restrict__ w,
@@ -56,7 +67,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
     if (tile0 >= t32) return;
     const int mt_base = bz * (RT - 1) + min(bz, n_tall), ct_here = bz < n_tall ? RT : RT - 1;
     const SplitRange sr = split_range(K, splits, split);
-    const int n_steps = 2 * max(sr.q1 - sr.q0, 0), n_chunks = (n_steps + 3) >> 2;      // steps of 16 k
+    const int n_steps = 2 * max(sr.q1 - sr.q0, 0), n_chunks = ((n_steps + 7) >> 3) * 2;      // steps of 16 k; an odd last chunk has one of zeros behind it
 
     // loads: a wave brings one of a chunk's four k steps, of A and of W.  Tiles that do not exist and steps past the last are
     // asked for too, out of bounds: no traffic, zeros in LDS, and the same number of loads in flight everywhere
@@ -86,22 +97,36 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
     for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int j = 0; j < CT; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    // Generation g of the loads goes out when chunk g has been read, one half in the second half of that chunk, the other in the
+    // first half of the next.  It brings chunk g + PA of A and, if g is odd, before that the two chunks g + PW - 1 and g + PW of W:
+    // a compute unit returns loads in the order they were asked for, so activations that lie in its L2 wait behind weights from HBM,
+    // and the fewer times the two alternate the better (both operands' loads of 272 x 24576 x 4096 alone: weights one, two and
+    // three chunks at a time 51.4, 46.6 and 44.4 us; three do not fit).  Weights chunk by chunk -> in pairs: gate/up at 216 rows
+    // 52.4 -> 51.0 us, at 272 57.2 -> 57.0, 1.5B gate/up and down at 272 23.4 -> 22.5 and 18.6 -> 17.8; 3 x k = 8 6820 -> 6750, 1.5B k =
+    // 16 2952 -> 2917, 8B k = 16 7700 -> 7665.
+    constexpr int N_LOADS[2] = {RT, RT + 2 * CT}, FIRST[2] = {N_LOADS[0] / 2, N_LOADS[1] / 2};      // even, odd generations
+    auto load = [&](int g, int odd, int ba, int bw_before, int bw, int l) __attribute__((always_inline)) {
+        if (!odd) load_a(g + PA, ba, l);
+        else if (l < 2 * CT) load_w(g + PW - 1 + l / CT, l < CT ? bw_before : bw, l % CT);
+        else load_a(g + PA, ba, l - 2 * CT);
+    };
+    // loads of the n generations before g: what may be in flight when chunk g + 1 has to be there is the last PA - 2 of them
+    auto in_flight = [](int g, int n) constexpr {
+        int s = 0;
+        for (int i = 1; i <= n; ++i) s += N_LOADS[(g - i) & 1];
+        return s;
+    };
+    constexpr int W_FIRST = PW - 2 * (PA / 2 + (PA & 1));      // chunks of W that generations before -PA have brought
+    static_assert(W_FIRST >= 0, "W is asked for in pairs, PW - 1 and PW chunks ahead");
 #pragma unroll
-    for (int c = 0; c < PW - PA; ++c)
+    for (int c = 0; c < W_FIRST; ++c)
 #pragma unroll
         for (int j = 0; j < CT; ++j) load_w(c, c, j);
-    // generation g of the loads brings chunks g + PA of A and g + PW of W into the buffers that chunk g leaves; one half of it
-    // goes out in the second half of chunk g, the other in the first half of chunk g + 1
-    constexpr int LOADS = RT + CT;
-    auto load = [&](int g, int ba, int bw, int l) __attribute__((always_inline)) {
-        if (l < RT) load_a(g + PA, ba, l);
-        else load_w(g + PW, bw, l - RT);
-    };
 #pragma unroll
-    for (int c = 0; c < PA; ++c)
+    for (int g = -PA; g < 0; ++g)
 #pragma unroll
-        for (int l = 0; l < (c < PA - 1 ? LOADS : LOADS / 2); ++l) load(c - PA, c, c + PW - PA, l);
-    wait_loads<CT + (PA - 2) * LOADS + LOADS / 2>();
+        for (int l = 0; l < (g < -1 ? N_LOADS[g & 1] : FIRST[1]); ++l) load(g, g & 1, g + PA, g + PW - 1, g + PW, l);
+    wait_loads<in_flight(-1, PA - 2) + FIRST[1]>();
     lds_barrier_counted();
     // lane (n, g) of a 16x16x32 fragment takes k slots 8g .. 8g+7 of row n: stored k step g/2, stored lane (g%2)*32 + n
     const int frag = ((lane >> 4) & 1) * 512 + (lane & 15) * 16;
@@ -121,32 +146,30 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
         };
 #pragma unroll
         for (int f = 0; f < READS; ++f) read(0, 0, 0, 0, f);
-        int ba = 0, bw = 0, g = -1, ga = PA - 1, gw = PW - 1;      // buffers of chunk c; generation under way and its buffers
-        for (int c = 0; c < n_chunks; ++c) {
+        // buffers of chunk c; of the generation under way
+        int c = 0, ba = 0, bw = 0, ga = PA - 1, gw = PW - 1, gw_before = PW - 2;
+        auto chunk = [&](auto odd_tag) __attribute__((always_inline)) {
+            constexpr int ODD = decltype(odd_tag)::value;
             const int na = next(ba, PA), nw = next(bw, PW);
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                if (q == 1) {
+            each<0, 2>([&](auto q_tag) __attribute__((always_inline)) {
+                constexpr int q = q_tag;
+                if constexpr (q == 1) {
                     ga = ba;
+                    gw_before = gw;
                     gw = bw;
-                    g = c;
                 }
-                const int l0 = q ? 0 : LOADS / 2, l1 = q ? LOADS / 2 : LOADS;
-                auto ops = [&](int x, int n) __attribute__((always_inline)) {
-                    for (int f = READS * x / n; f < READS * (x + 1) / n; ++f) read(q ^ 1, q ^ 1, q ? na : ba, q ? nw : bw, f);
-                    for (int l = l0 + (l1 - l0) * x / n; l < l0 + (l1 - l0) * (x + 1) / n; ++l) load(g, ga, gw, l);
-                };
-#pragma unroll
-                for (int m = 0; m < NM; ++m) {
-                    if (q == 1 && m == B) {
-                        wait_loads<CT + (PA - 2) * LOADS>();
+                constexpr int odd = q ? ODD : !ODD, l0 = q ? 0 : FIRST[odd], n_l = q ? FIRST[odd] : N_LOADS[odd] - FIRST[odd];
+                each<0, NM>([&](auto m_tag) __attribute__((always_inline)) {
+                    constexpr int m = m_tag;
+                    if constexpr (q == 1 && m == B) {
+                        wait_loads<in_flight(ODD, PA - 2)>();
                         lds_barrier_counted();           // chunk c+1 has landed for everyone, chunk c has been read by everyone
                     }
                     __builtin_amdgcn_sched_barrier(0);
                     // The compiler does not see the MFMAs finish, and where the loop ends it may copy their results at once, so
                     // the last one of the last chunk brings the wait (32 states; it asks for fewer than 20 before its result is
                     // read) in the same piece of assembly
-                    if (q == 1 && m == NM - 1)
+                    if constexpr (ODD && q == 1 && m == NM - 1)
                         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\t"
                                      "s_cmp_lg_i32 %3, %4\n\ts_cbranch_scc1 .Lmore%=\n\ts_nop 15\n\ts_nop 15\n.Lmore%=:"
                                      : "+a"(acc[m / CT][m % CT])
@@ -157,12 +180,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
                                      : "+a"(acc[m / CT][m % CT])
                                      : "v"(wf[q][m % CT]), "v"(af[q][m / CT]));
                     __builtin_amdgcn_sched_barrier(0);
-                    if (q == 0) ops(m, NM);
-                    else if (m >= B) ops(m - B, NM - B);
-                }
-            }
+                    constexpr int x = q ? m - B : m, n = q ? NM - B : NM;        // reads and loads behind this MFMA
+                    if constexpr (x >= 0) {
+                        each<READS * x / n, READS * (x + 1) / n>([&](auto f) __attribute__((always_inline)) {
+                            read(q ^ 1, q ^ 1, q ? na : ba, q ? nw : bw, f);
+                        });
+                        each<l0 + n_l * x / n, l0 + n_l * (x + 1) / n>([&](auto l) __attribute__((always_inline)) {
+                            load(q ? c : c - 1, odd, ga, gw_before, gw, l);
+                        });
+                    }
+                });
+            });
             ba = na;
             bw = nw;
+            ++c;
+        };
+        while (c < n_chunks) {
+            chunk(std::integral_constant<int, 0>());
+            chunk(std::integral_constant<int, 1>());
         }
     };
     const bool last_here = ct_here == RT && (mt_base + RT - 1) * 32 + mh * 16 < M;
