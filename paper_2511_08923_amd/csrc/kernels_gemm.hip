@@ -793,6 +793,24 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
             p.splits = splits;
             return p;
         }
+        // The LM head of up to nine row tiles: the many-row kernel with five column tiles per workgroup, all rows in one pass.  Up to
+        // five row tiles two workgroups share a compute unit, beyond that one: 160-column blocks must then fill their last round
+        // of 256 (151936 columns: 950 blocks, 93 %; 65536: 410, 80 %).  At nine row tiles and long K what a unit takes in decides,
+        // and the two passes below take in less.  Step of one layer with and without logits, kernels below -> this, 151936 x
+        // 4096 at 42 / 72 / 132 / 182 / 210 / 240 / 272 rows: 398 -> 331, 424 -> 346, 483 -> 406, 513 -> 487, 549 -> 534, 580 -> 560, 602 ->
+        // 620 us, with logits 420 -> 377, 448 -> 398, 508 -> 459, 534 -> 508, 569 -> 548, 617 -> 575, 661 -> 656; x 1536 225 -> 160, 245 ->
+        // 170, 271 -> 200, 289 -> 245, 306 -> 261, 307 -> 275, 319 -> 296; 65536 x 4096 254 -> 235, 266 -> 248, 301 -> 288, 331 -> 335, 356 ->
+        // 359, 372 -> 388, 390 -> 423.
+        const int vocab_blocks = (N + 159) / 160, vocab_rounds = (vocab_blocks + 255) / 256;
+        if (force_single_split && wgs >= 512 &&
+            (t <= 5 || (10 * vocab_blocks >= 9 * 256 * vocab_rounds && (t <= 8 || (t == 9 && K <= 2048))))) {
+            p.wide = 3;
+            p.nt = 5;
+            p.mt = t;
+            p.m_chunks = 1;
+            p.splits = 1;
+            return p;
+        }
         const bool row_split = !force_single_split && wgs * splits <= 128;
         const int t32 = (N + 31) / 32;
         // kernels_gemm_tall.hip: all row tiles (up to twelve) in one workgroup, both operands by LDS-DMA.  Same MFMAs in the
@@ -891,6 +909,8 @@ void launch_gemm_bf16(const bf16_t *a, const bf16_t *w, float *out, int M, int N
     if (choose && out_row_major == GEMM_EPI_ARGMAX) ch = *choose;
     if (p.wide == 2) {
         launch_gemm_bf16_tall(a, w, out, M, N, K, p, out_row_major, st);
+    } else if (p.wide == 3) {
+        launch_gemm_bf16_vocab(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.rows) {
         launch_gemm_bf16_rows(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.mid && (out_row_major == GEMM_EPI_TILED || out_row_major == GEMM_EPI_SWIGLU)) {

@@ -29,12 +29,15 @@ namespace {
 constexpr int BUFS = 4;                           // chunks in LDS
 
 // RT: row tiles of the higher passes; the first n_tall of the n_pass passes have RT row tiles, the others RT - 1.
-template <int RT, int EPI>
+// CB: column tiles of 32 of a workgroup.  Eight; or five for the LM head of a few row tiles, in one pass: less of a last round that
+// is nearly empty, weights that nobody else reads (non-temporal), up to five row tiles two workgroups per compute unit (figures at
+// the rule in plan_gemm_bf16).
+template <int RT, int EPI, int CB>
 __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__restrict__ a, const bf16_t *__restrict__ w,
                                                              float *__restrict__ out, int M, int N, int K, int splits,
                                                              int n_pass, int n_tall, int n_colblk, ChooseArgs ch) {
-    constexpr int CT = 8;                              // 16-column tiles of a wave
-    constexpr int LOADS = RT > 8 ? RT : 8;             // loads per wave and chunk
+    constexpr int CT = CB;                             // 16-column tiles of a wave
+    constexpr int LOADS = RT > CB ? RT : CB;           // loads of a wave and chunk, at most
     constexpr int CHUNK = 4 * LOADS * 1024;            // A [k step][row tile], then W [k step][column tile], 1 KiB each
     extern __shared__ __attribute__((aligned(16))) unsigned char rows_smem[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -58,8 +61,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
 
     // loads: waves 0 and 1 bring the W tiles of the chunk's two k steps, waves 2 and 3 the A tiles
     const bool ld_w = wave < 2;
-    const int ld_tiles = ld_w ? t32 : m_tiles, ld_t0 = ld_w ? bx * 8 : mt_base;
-    const int ld_here = ld_w ? min(8, t32 - bx * 8) : ct_here;
+    const int ld_tiles = ld_w ? t32 : m_tiles, ld_t0 = ld_w ? bx * CB : mt_base;
+    const int ld_here = ld_w ? min(CB, t32 - bx * CB) : ct_here;
     const int4v ld_desc = raw_desc(ld_w ? w : a, (size_t)(K >> 4) * ld_tiles * 1024);
     const unsigned ld_dst = lds_address(rows_smem) + ((ld_w ? 2 : 0) + (wave & 1)) * LOADS * 1024;
     const int ld_src = ((sr.q0 * 2 + (wave & 1)) * ld_tiles + ld_t0) * 1024, ld_step = 2 * ld_tiles * 1024;
@@ -73,7 +76,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
     // select per load and per tile: 8B step of 8 sequences 38831 us, now 37910; 4096-token prefill 57191, 55564; scoring of
     // 2000 tokens (1.5B) 16168, 15727).
     auto load = [&](int c, int i) __attribute__((always_inline)) {
-        dma16_tile(ld_dst + (c & (BUFS - 1)) * CHUNK, ld_off[i], ld_desc, c < n_chunks, ld_src + c * ld_step, i);
+        const unsigned dst = ld_dst + (c & (BUFS - 1)) * CHUNK;
+        if constexpr (CB == 8) dma16_tile(dst, ld_off[i], ld_desc, c < n_chunks, ld_src + c * ld_step, i);
+        else if (!ld_w) {                              // a wave asks for its tiles only, and weights are read once
+            if (i < RT) dma16_tile(dst, ld_off[i], ld_desc, c < n_chunks, ld_src + c * ld_step, i);
+        } else if (i < CB) dma16_tile<true>(dst, ld_off[i], ld_desc, c < n_chunks, ld_src + c * ld_step, i);
+    };
+    auto wait_chunks = [&](auto n) __attribute__((always_inline)) {      // until no more than the last n chunks are in flight
+        if constexpr (CB == 8) wait_loads<n * LOADS>();
+        else if (ld_w) wait_loads<n * CB>();
+        else wait_loads<n * RT>();
     };
 
     // The wave's row tile i (16 rows) is half mh of the pass's 32-row tile i.
@@ -85,9 +97,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
     bf16x8 af[2][RT], wf[2][CT];
     // lane (n, g) of a 16x16x32 fragment takes k slots 8g .. 8g+7 of row n: stored k step g/2, stored lane (g%2)*32 + n
     const unsigned char *frag0 = rows_smem + (lane >> 5) * LOADS * 1024 + ((lane >> 4) & 1) * 512 + (lane & 15) * 16;
+    // the wave's even and odd 16-column tiles: CT from ng * CT on
+    const int w_frag[2] = {(ng * CT >> 1) * 1024 + (ng * CT & 1) * 256, ((ng * CT + 1) >> 1) * 1024 + ((ng * CT + 1) & 1) * 256};
     auto read = [&](int s, int c, int f) __attribute__((always_inline)) {      // W fragments first: all of them are
         const unsigned char *b = frag0 + (c & (BUFS - 1)) * CHUNK;             // needed before the second A fragment
-        if (f < CT) wf[s][f] = *(const bf16x8 *)(b + (2 * LOADS + ng * 4 + (f >> 1)) * 1024 + (f & 1) * 256);
+        if (f < CT) wf[s][f] = *(const bf16x8 *)(b + 2 * LOADS * 1024 + w_frag[f & 1] + (f >> 1) * 1024);
         else af[s][f - CT] = *(const bf16x8 *)(b + (f - CT) * 1024 + mh * 256);
     };
 
@@ -95,7 +109,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
     for (int c = 0; c < BUFS; ++c)
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) load(c, i);
-    wait_loads<(BUFS - 1) * LOADS>();
+    wait_chunks(std::integral_constant<int, BUFS - 1>());
     lds_barrier_counted();
     // the k loop over RA row tiles
     auto k_loop = [&](auto ra_tag) __attribute__((always_inline)) {
@@ -108,7 +122,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
                 // The ninth row's accumulators do not fit the 256 AGPRs any more; left to the compiler, which wants
                 // all of them there, they are copied in and out around every use.  (The wait that their reader needs
                 // stands behind the loop and names them.)
-                if (i == 8)
+                if (i == 8 && CT == 8)
                     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[i][j]) : "v"(wf[s][j]), "v"(af[s][i]));
                 else
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][j], af[s][i], acc[i][j], 0, 0, 0);
@@ -120,7 +134,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
         };
         auto chunk = [&](int s, int c) __attribute__((always_inline)) {
             row(s, 0, 0, [](int) {});
-            wait_loads<(BUFS - 2) * LOADS>();
+            wait_chunks(std::integral_constant<int, BUFS - 2>());
             lds_barrier_counted();                       // chunk c+1 has landed for everyone, chunk c has been read by everyone
 #pragma unroll
             for (int i = 1; i < RA; ++i) {
@@ -148,18 +162,19 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
         }
         // The compiler does not see the ninth row's MFMAs finish: the wait (32 states; the longest MFMA asks for
         // fewer than 20 before its result is read) takes their results in and hands them on, so no use comes before it
-        if constexpr (RA == 9)
+        if constexpr (RA == 9 && CT == 8)
             asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc[8][0]), "+v"(acc[8][1]), "+v"(acc[8][2]), "+v"(acc[8][3]),
                          "+v"(acc[8][4]), "+v"(acc[8][5]), "+v"(acc[8][6]), "+v"(acc[8][7]));
     };
-    if (ct_here == RT) k_loop(std::integral_constant<int, RT>());
+    if constexpr (CB < 8) k_loop(std::integral_constant<int, RT>());      // a single pass
+    else if (ct_here == RT) k_loop(std::integral_constant<int, RT>());
     else k_loop(std::integral_constant<int, RT - 1>());
     wait_loads<0>();
     lds_barrier_counted();
 
     // ---- epilogue
     const int n = lane & 15, g = lane >> 4;
-    const int col_w = bx * 256 + ng * 128;                       // the wave's first column
+    const int col_w = bx * 32 * CB + ng * 16 * CT;                       // the wave's first column
     auto row_of = [&](int i) { return (mt_base + i) * 32 + mh * 16; };
     auto exists = [&](int i) { return i < RT - 1 || ct_here == RT; };
     if constexpr (EPI == GEMM_EPI_SWIGLU) {
@@ -185,17 +200,23 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
             }
         }
     } else if constexpr (EPI == GEMM_EPI_ARGMAX) {
-        // per row and 64 columns (four column tiles): a lane walks its columns in rising order (strict > keeps the
-        // lowest column of a tie), then the four lanes of a row are folded
-        const int G = (t32 + 1) >> 1;
+        // per row and group of PG column tiles (64 columns; the 80 of a wave where it has five): a lane walks its columns in
+        // rising order (strict > keeps the lowest column of a tie), then the four lanes of a row are folded
+        constexpr int P = CT == 8 ? 2 : 1, PG = CT / P;
+        const int G = CT == 8 ? (t32 + 1) >> 1 : 2 * n_colblk;
         float *pmax = out;
         int *pidx = (int *)(out + (size_t)G * M);
 #pragma unroll
         for (int i = 0; i < RT; ++i) {
             if (!exists(i)) continue;
             const int row = row_of(i) + n;
-            float best[2] = {-INFINITY, -INFINITY};
-            int bi[2] = {col_w + 4 * g, col_w + 64 + 4 * g};
+            float best[P];
+            int bi[P];
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                best[p] = -INFINITY;
+                bi[p] = col_w + 16 * PG * p + 4 * g;
+            }
             const RowChoice rc = row_choice(ch, row, M);
             if (__any(rc.noisy || rc.sel >= 0)) {            // wave-uniform: rows a token is taken from.  Few of them:
                 // a loop over values the lane parks in LDS (the staging buffers are free) instead of unrolled code
@@ -203,11 +224,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
 #pragma unroll
                 for (int j = 0; j < CT; ++j) park[256 * j] = acc[i][j];
 #pragma unroll
-                for (int p = 0; p < 2; ++p)
+                for (int p = 0; p < P; ++p)
 #pragma unroll 1
-                    for (int t = 0; t < 16; ++t) {
-                        const int col = col_w + 64 * p + 16 * (t >> 2) + 4 * g + (t & 3);
-                        float v = reinterpret_cast<const float *>(park + 256 * (4 * p + (t >> 2)))[t & 3];
+                    for (int t = 0; t < 4 * PG; ++t) {
+                        const int col = col_w + 16 * PG * p + 16 * (t >> 2) + 4 * g + (t & 3);
+                        float v = reinterpret_cast<const float *>(park + 256 * (PG * p + (t >> 2)))[t & 3];
                         if (rc.sel >= 0 && col < N) ch.sel_logits[(size_t)rc.sel * N + col] = v;
                         if (rc.noisy) v = perturbed_logit(v, rc.inv_t, rc.key, (uint32_t)col);
                         if (col < N && v > best[p]) {
@@ -221,14 +242,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int col = col_w + 16 * j + 4 * g + e;
-                        if (col < N && acc[i][j][e] > best[j >> 2]) {
-                            best[j >> 2] = acc[i][j][e];
-                            bi[j >> 2] = col;
+                        if (col < N && acc[i][j][e] > best[j / PG]) {
+                            best[j / PG] = acc[i][j][e];
+                            bi[j / PG] = col;
                         }
                     }
             }
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
+            for (int p = 0; p < P; ++p) {
 #pragma unroll
                 for (int o = 16; o < 64; o <<= 1) {
                     const float ob = __shfl_xor(best[p], o);
@@ -238,9 +259,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
                         bi[p] = oi;
                     }
                 }
-                if (g == 0 && row < M && col_w + 64 * p < 32 * t32) {
-                    pmax[(size_t)((col_w >> 6) + p) * M + row] = best[p];
-                    pidx[(size_t)((col_w >> 6) + p) * M + row] = bi[p];
+                const int group = (bx * 2 + ng) * P + p;
+                if (g == 0 && row < M && group < G) {
+                    pmax[(size_t)group * M + row] = best[p];
+                    pidx[(size_t)group * M + row] = bi[p];
                 }
             }
         }
@@ -250,20 +272,25 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
         for (int i = 0; i < RT; ++i) {
             if (!exists(i)) continue;
 #pragma unroll
-            for (int j = 0; j < CT; j += 2)
+            for (int j = 0; j + 1 < CT; j += 2)
                 store_pair<EPI == GEMM_EPI_ROWMAJOR>(acc[i][j], acc[i][j + 1], o, row_of(i), col_w + 16 * j, M, N, lane);
+            if constexpr (CT & 1) {                    // (logits only)
+                static_assert(EPI == GEMM_EPI_ROWMAJOR, "an odd number of column tiles");
+                const int row = row_of(i) + n, col = col_w + 16 * (CT - 1) + 4 * g;
+                if (row < M && col < N) *(f32x4 *)(o + (size_t)row * N + col) = acc[i][CT - 1];
+            }
         }
     }
 }
 
-template <int RT, int EPI>
+template <int RT, int EPI, int CB = 8>
 void launch_rows(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, hipStream_t st,
                  const ChooseArgs &ch) {
-    constexpr int SMEM = BUFS * 4 * (RT > 8 ? RT : 8) * 1024;
-    const int n_colblk = (N + 255) / 256, n_tall = (M + 31) / 32 - p.m_chunks * (RT - 1);
+    constexpr int SMEM = BUFS * 4 * (RT > CB ? RT : CB) * 1024;
+    const int n_colblk = (N + 32 * CB - 1) / (32 * CB), n_tall = (M + 31) / 32 - p.m_chunks * (RT - 1);
     static std::atomic<bool> granted[kLdsDevices];
-    grant_lds((const void *)gemm_bf16_rows_kernel<RT, EPI>, SMEM, granted);
-    gemm_bf16_rows_kernel<RT, EPI><<<dim3(p.m_chunks * n_colblk, p.splits), 256, SMEM, st>>>(
+    grant_lds((const void *)gemm_bf16_rows_kernel<RT, EPI, CB>, SMEM, granted);
+    gemm_bf16_rows_kernel<RT, EPI, CB><<<dim3(p.m_chunks * n_colblk, p.splits), 256, SMEM, st>>>(
         a, w, out, M, N, K, p.splits, p.m_chunks, n_tall, n_colblk, ch);
 }
 
@@ -276,7 +303,26 @@ void launch_rows_epi(const bf16_t *a, const bf16_t *w, float *out, int M, int N,
     else launch_rows<6, EPI>(a, w, out, M, N, K, p, st, ch);
 }
 
+template <int EPI>
+void launch_vocab(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, hipStream_t st,
+                  const ChooseArgs &ch) {
+    if (p.mt <= 2) launch_rows<2, EPI, 5>(a, w, out, M, N, K, p, st, ch);
+    else if (p.mt == 3) launch_rows<3, EPI, 5>(a, w, out, M, N, K, p, st, ch);
+    else if (p.mt == 4) launch_rows<4, EPI, 5>(a, w, out, M, N, K, p, st, ch);
+    else if (p.mt == 5) launch_rows<5, EPI, 5>(a, w, out, M, N, K, p, st, ch);
+    else if (p.mt == 6) launch_rows<6, EPI, 5>(a, w, out, M, N, K, p, st, ch);
+    else if (p.mt == 7) launch_rows<7, EPI, 5>(a, w, out, M, N, K, p, st, ch);
+    else if (p.mt == 8) launch_rows<8, EPI, 5>(a, w, out, M, N, K, p, st, ch);
+    else launch_rows<9, EPI, 5>(a, w, out, M, N, K, p, st, ch);
+}
+
 }  // namespace
+
+void launch_gemm_bf16_vocab(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi,
+                            hipStream_t st, const ChooseArgs &ch) {
+    if (epi == GEMM_EPI_ARGMAX) launch_vocab<GEMM_EPI_ARGMAX>(a, w, out, M, N, K, p, st, ch);
+    else launch_vocab<GEMM_EPI_ROWMAJOR>(a, w, out, M, N, K, p, st, ch);
+}
 
 void launch_gemm_bf16_rows(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi,
                            hipStream_t st, const ChooseArgs &ch) {

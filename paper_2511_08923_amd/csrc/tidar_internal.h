@@ -204,7 +204,8 @@ struct GemmPlan {
     int bk;        // K elements staged per LDS chunk
     int m_chunks;  // passes over M (grid.z)
     int wide;      // 0: 2 x 2 waves, 1: the waves side by side, each over all row tiles of the pass, 2: the waves over the
-                   // rows, each over all nt column tiles of the workgroup (kernels_gemm_tall.hip)
+                   // rows, each over all nt column tiles of the workgroup (kernels_gemm_tall.hip), 3: the vocabulary's
+                   // form of the many-row kernel, one pass and five column tiles per workgroup
     int nw;        // waves per workgroup: 4, or 8 (side by side, one column tile each: two waves per SIMD)
     int rows;      // the many-row kernel (kernels_gemm_rows.hip): m_chunks passes of mt or mt - 1 row tiles of 32
     int mid;       // kernels_gemm_mid.hip: m_chunks passes of mt or mt - 1 row tiles of 32
@@ -232,11 +233,15 @@ void launch_rmsnorm(int dtype, float *x, const float *part, int S, const void *g
 enum { GEMM_EPI_TILED = 0, GEMM_EPI_ROWMAJOR = 1, GEMM_EPI_SWIGLU = 2, GEMM_EPI_ARGMAX = 3 };
 // GEMM_EPI_ARGMAX (single split): no output matrix; every wave reduces its columns to the largest value of each
 // row and the lowest column that holds it.  out is then [G][M] floats (values) followed by [G][M] ints (columns),
-// G = gemm_argmax_groups(M, N) column groups; launch_argmax_groups folds the groups (ties: lowest column).
-inline int gemm_argmax_groups(int M, int N) { return M <= 32 ? (N + 31) / 32 : (N + 63) / 64; }
+// G = gemm_argmax_groups(M, N, plan) column groups; launch_argmax_groups folds the groups (ties: lowest column).
+inline int gemm_argmax_groups(int M, int N, const GemmPlan &p) {
+    return M <= 32 ? (N + 31) / 32 : p.wide == 3 ? (N + 159) / 160 * 2 : (N + 63) / 64;
+}
 void launch_argmax_groups(const float *part, int M, int G, int32_t *y, hipStream_t st);
 void launch_gemm_bf16(const bf16_t *a, const bf16_t *w_packed, float *out, int M, int N, int K, const GemmPlan &p,
                       int epi, hipStream_t st, const ChooseArgs *choose = nullptr);
+void launch_gemm_bf16_vocab(const bf16_t *a, const bf16_t *w_packed, float *out, int M, int N, int K, const GemmPlan &p,
+                            int epi, hipStream_t st, const ChooseArgs &ch);
 void launch_gemm_bf16_rows(const bf16_t *a, const bf16_t *w_packed, float *out, int M, int N, int K, const GemmPlan &p,
                            int epi, hipStream_t st, const ChooseArgs &ch);
 void launch_gemm_bf16_mid(const bf16_t *a, const bf16_t *w_packed, float *out, int M, int N, int K, const GemmPlan &p,

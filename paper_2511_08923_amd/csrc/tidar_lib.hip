@@ -474,7 +474,8 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
     // rows and of their k mix partners (2k of the k(k+1) rows), which argmax_rows mixes, perturbs and reduces.
     // (The per-group pairs fit the logits area: 8 bytes per row and 32 or 64 columns.)
     if (c.dtype == TIDAR_BF16 && !logits_dst && l.logits_bytes > 0) {
-        const int G = gemm_argmax_groups(Mh, c.vocab);
+        const GemmPlan gp = plan_gemm_bf16(Mh, c.vocab, c.d_model, true);
+        const int G = gemm_argmax_groups(Mh, c.vocab, gp);
         const bool mix = mode->beta != 1.0f && n_choose > 0 && mix_stride > 0;
         ChooseArgs ch = {};
         ch.Rh = Rh;
@@ -490,7 +491,6 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
         ch.mix_stride = mix_stride;
         {
             Prof p(ctx, KC_GEMM, st);
-            GemmPlan gp = plan_gemm_bf16(Mh, c.vocab, c.d_model, true);
             launch_gemm_bf16((const bf16_t *)(ws + l.xh), (const bf16_t *)w->lm_head, logits, Mh, c.vocab, c.d_model,
                              gp, GEMM_EPI_ARGMAX, st, &ch);
         }
