@@ -104,19 +104,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
     // three chunks at a time 51.4, 46.6 and 44.4 us; three do not fit).  Weights chunk by chunk -> in pairs: gate/up at 216 rows
     // 52.4 -> 51.0 us, at 272 57.2 -> 57.0, 1.5B gate/up and down at 272 23.4 -> 22.5 and 18.6 -> 17.8; 3 x k = 8 6820 -> 6750, 1.5B k =
     // 16 2952 -> 2917, 8B k = 16 7700 -> 7665.
-    constexpr int N_LOADS[2] = {RT, RT + 2 * CT}, FIRST[2] = {N_LOADS[0] / 2, N_LOADS[1] / 2};      // even, odd generations
+    // With two chunks of A (eleven and twelve row tiles) the next chunk's barrier waits for all of A: it goes out at once, and one
+    // chunk of weights behind it (8B step of 330 / 364 rows in pairs 8570 / 8860 us, so 7990 / 8375).
+    constexpr bool PAIRS = PA > 2;
+    constexpr int N_LOADS[2] = {RT + (PAIRS ? 0 : CT), RT + (PAIRS ? 2 * CT : CT)};                 // even, odd generations
+    constexpr int FIRST[2] = {N_LOADS[0] / (PAIRS ? 2 : 1), N_LOADS[1] / (PAIRS ? 2 : 1)};
     auto load = [&](int g, int odd, int ba, int bw_before, int bw, int l) __attribute__((always_inline)) {
-        if (!odd) load_a(g + PA, ba, l);
-        else if (l < 2 * CT) load_w(g + PW - 1 + l / CT, l < CT ? bw_before : bw, l % CT);
-        else load_a(g + PA, ba, l - 2 * CT);
+        const int a = PAIRS && odd ? l - 2 * CT : l;           // tile of A
+        if (a < 0) load_w(g + PW - 1 + l / CT, l < CT ? bw_before : bw, l % CT);
+        else if (a < RT) load_a(g + PA, ba, a);
+        else load_w(g + PW, bw, a - RT);
     };
-    // loads of the n generations before g: what may be in flight when chunk g + 1 has to be there is the last PA - 2 of them
+    // what may be in flight when chunk g + 1 has to be there: the n = PA - 2 generations before g, and weights asked for behind A
     auto in_flight = [](int g, int n) constexpr {
-        int s = 0;
+        int s = PAIRS ? 0 : CT;
         for (int i = 1; i <= n; ++i) s += N_LOADS[(g - i) & 1];
         return s;
     };
-    constexpr int W_FIRST = PW - 2 * (PA / 2 + (PA & 1));      // chunks of W that generations before -PA have brought
+    constexpr int W_FIRST = PAIRS ? PW - 2 * (PA / 2 + (PA & 1)) : PW - PA;      // chunks of W that generations before -PA have brought
     static_assert(W_FIRST >= 0, "W is asked for in pairs, PW - 1 and PW chunks ahead");
 #pragma unroll
     for (int c = 0; c < W_FIRST; ++c)
