@@ -2,7 +2,7 @@
 //
 // M is the step's row count (1 .. 272 at batch 1; more rows run as row passes, 481 and more in kernels_gemm_rows.hip,
 // the narrower products of 33 .. 480 - the narrowest to 768 - in kernels_gemm_mid.hip, the widest and those of many short
-// shares of K up to 480 rows in kernels_gemm_tall.hip), N and K are model dimensions: every weight byte is used once
+// shares of K up to 480 rows in kernels_gemm_tall.hip, the LM head of 33 .. 288 in a form of kernels_gemm_rows.hip), N and K are model dimensions: every weight byte is used once
 // per step, so the kernel is a weight streamer with MFMA attached.
 //   * W lives in HBM as the register image of the 32x32x16 MFMA B operand
 //     ([k step of 16][32-column tile][lane][8]); a wave's load of one fragment is one fully coalesced 1 KiB read
@@ -454,6 +454,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
     static_assert(NW == 4 || (NW == 8 && WIDE && NT == 1), "eight waves only side by side with one column tile each");
     constexpr int THREADS = 64 * NW;
     constexpr int PFK = 2 * KS;                  // weight ring depth in k steps: two chunks
+    // k steps whose weights are asked for together.  A compute unit returns loads in the order they were asked for, so activations
+    // from L2 wait behind weights from HBM each time the two alternate: a chunk's weights go out at its end, behind its A pieces,
+    // although that makes the ring one chunk deep.  One k step at a time -> so, inside a step: 216 x 4096 x 12288 36.5 -> 35.7 us, x 4096
+    // 18.9 -> 17.8, 272 rows 39.8 -> 39.0 and 21.2 -> 19.5 (6144 x 4096 26.1 -> 27.1); steps of 42 / 132 rows 1885 -> 1838 and 2247 -> 2202
+    // (1.5B), 132 / 216 / 272 rows 5585 -> 5526, 6735 -> 6704 and 7705 -> 7677 (8B).  Four k steps: in between.  Eight waves lose
+    // (LM head 379 -> 389).
+    constexpr int WG = WIDE && NW == 4 ? KS : 1;
     constexpr int CTL = WIDE ? MTA : (MTA == 5) ? 9 : 2 * MTA;
     // Workgroup i of a launch runs on XCD i % 8.  The row passes of a column block and split follow each other on one XCD
     // (the second read of its weights is an L2 hit) and the splits are dealt out first: with 2, 4 or 8 of them an XCD sees one
@@ -550,9 +557,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
     for (int s = 0; s < STAGE; ++s) store_a1(s, 0);
 #pragma unroll
     for (int f = 0; f < FR; ++f) {
-        if (f % MTA == MTA - 1) {
+        if (f % (MTA * WG) == MTA * WG - 1) {
 #pragma unroll
-            for (int j = 0; j < NT; ++j) wbuf[KS + f / MTA][j] = ld_w(j, q0 + KS + f / MTA);
+            for (int d = WG - 1; d >= 0; --d)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) wbuf[KS + f / MTA - d][j] = ld_w(j, q0 + KS + f / MTA - d);
         }
         if ((f & 1) && (f >> 1) < STAGE) load_a1(f >> 1, c0 + 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -582,9 +591,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
                 for (int j = 0; j < NT; ++j)
                     acc[mt][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wbuf[slot][j], af[f % (AFD + 1)], acc[mt][j],
                                                                          0, 0, 0);   // W first: acc = out^T
-                if (mt == MTA - 1) {              // this k step's ring slot is free again
+                if (mt == MTA - 1 && ks % WG == WG - 1) {              // the ring slots of the last WG k steps are free again
 #pragma unroll
-                    for (int j = 0; j < NT; ++j) wbuf[slot][j] = ld_w(j, c * KS + ks + PFK);
+                    for (int d = WG - 1; d >= 0; --d)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j) wbuf[slot - d][j] = ld_w(j, c * KS + ks - d + PFK);
                 }
                 // the next chunk's A goes to the other LDS buffer one piece at a time between the MFMAs (a
                 // burst of stores would sit in front of the fragment reads in the in-order LDS queue), and
@@ -825,9 +836,9 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
         //     11.4, 20.8 -> 17.5, 21.3 -> 18.4; 272 x 1792 x 9216 22.4 -> 18.7.  With fewer splits only up to three row tiles
         //     and from 2048 k on: 72 x 4096 x 12288 26.8 -> 25.9, 72 x 3072 x 8192 17.5 -> 16.4; 272 x 4096 x 4096 17.5 -> 18.0,
         //     272 x 4096 x 12288 37 -> 40, 72 x 4096 x 2048 (512 k) 8.6 -> 9.0.
-        // Where column blocks x splits is a multiple of eight, both row passes of the kernel below run on the same XCD (workgroup i
-        // on XCD i % 8) and the second takes its weights from that XCD's L2: many short shares come here from seven row tiles on
-        // then.  Below -> here at 40 / 96 / 160 / 192 / 224 / 272 rows, weights from HBM: 1536 x 8192 11.2 -> 10.8, 12.0 -> 11.9,
+        // Where column blocks x splits is a multiple of eight, many short shares come here from seven row tiles on only.  (Measured
+        // when the two row passes below ran on one XCD, and shared the weights in its L2, at those counts alone, and before both
+        // kernels grouped their loads.)  Below -> here at 40 / 96 / 160 / 192 / 224 / 272 rows, weights from HBM: 1536 x 8192 11.2 -> 10.8, 12.0 -> 11.9,
         // 13.2 -> 14.5, 14.0 -> 15.6, 15.6 -> 16.1, 17.9 -> 18.1; 2560 x 6144 11.4 -> 11.5, 12.4 -> 12.5, 14.4 -> 15.4, 14.8 ->
         // 16.4, 18.9 -> 16.7, 21.2 -> 19.6 (from the memory-side cache, 40 rows 8.3 -> 10.6); another count, 1536 x 9216: 12.1 ->
         // 10.9 and 20.6 -> 19.0 at 40 and 272.  The longer shares gain either way (3840 x 10240 21.1 -> 18.4, 23.4 -> 22.1 at 96).
