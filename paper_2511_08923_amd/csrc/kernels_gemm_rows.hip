@@ -97,11 +97,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_rows_kernel(const bf16_t *__res
     bf16x8 af[2][RT], wf[2][CT];
     // lane (n, g) of a 16x16x32 fragment takes k slots 8g .. 8g+7 of row n: stored k step g/2, stored lane (g%2)*32 + n
     const unsigned char *frag0 = rows_smem + (lane >> 5) * LOADS * 1024 + ((lane >> 4) & 1) * 512 + (lane & 15) * 16;
-    // the wave's even and odd 16-column tiles: CT from ng * CT on
+    // the wave's even and odd 16-column tiles, CT from ng * CT on (of eight, halves of the tiles ng * 4 and on)
     const int w_frag[2] = {(ng * CT >> 1) * 1024 + (ng * CT & 1) * 256, ((ng * CT + 1) >> 1) * 1024 + ((ng * CT + 1) & 1) * 256};
     auto read = [&](int s, int c, int f) __attribute__((always_inline)) {      // W fragments first: all of them are
         const unsigned char *b = frag0 + (c & (BUFS - 1)) * CHUNK;             // needed before the second A fragment
-        if (f < CT) wf[s][f] = *(const bf16x8 *)(b + 2 * LOADS * 1024 + w_frag[f & 1] + (f >> 1) * 1024);
+        if (f < CT && CT == 8) wf[s][f] = *(const bf16x8 *)(b + (2 * LOADS + ng * 4 + (f >> 1)) * 1024 + (f & 1) * 256);
+        else if (f < CT) wf[s][f] = *(const bf16x8 *)(b + 2 * LOADS * 1024 + w_frag[f & 1] + (f >> 1) * 1024);
         else af[s][f - CT] = *(const bf16x8 *)(b + (f - CT) * 1024 + mh * 256);
     };
 
