@@ -199,10 +199,11 @@ enum KernelClass {
 
 struct GemmPlan {
     int mt;        // row tiles per wave: of 16 up to 32 rows (narrow kernel), of 32 beyond, there of the higher passes
-    int nt;        // column tiles per wave: two of 16 (narrow kernel), one or two of 32 (kernels_gemm.hip beyond 32 rows)
+    int nt;        // column tiles: two of 16 per wave (narrow kernel), one or two of 32 per wave (kernels_gemm.hip beyond 32
+                   // rows), of 32 per workgroup (wide 2 and 3)
     int splits;    // split-K factor
     int bk;        // K elements staged per LDS chunk
-    int m_chunks;  // passes over M (grid.z)
+    int m_chunks;  // passes over M
     int wide;      // 0: 2 x 2 waves, 1: the waves side by side, each over all row tiles of the pass, 2: the waves over the
                    // rows, each over all nt column tiles of the workgroup (kernels_gemm_tall.hip), 3: the vocabulary's
                    // form of the many-row kernel, one pass and five column tiles per workgroup
