@@ -442,25 +442,21 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_kernel(const bf16_t *__rest
 // MTA: 32-row tiles per wave.  2 x 2 waves (WIDE false): the workgroup pass covers CTL = 2*MTA row tiles (9 when
 // MTA is 5: the second row half then repeats a tile whose results are dropped) of 128 columns.  WIDE: four waves
 // side by side, each over all CTL = MTA row tiles and NT 32-column tiles of the workgroup's 128 * NT columns.
-// Chunk of K = 128 (8 k steps); weight ring 16 k steps.
-template <int MTA, bool WIDE, int NT = 2, int NW = 4>
+// Chunk of K = 128 (8 k steps); weight ring 16 k steps.  WG: k steps whose weights are asked for together.  A compute unit returns
+// loads in the order they were asked for, so activations from L2 wait behind weights from HBM each time the two alternate: with WG = 8
+// a chunk's weights go out at its end, behind its A pieces, although that makes the ring one chunk deep (where: launch_side).
+template <int MTA, bool WIDE, int NT = 2, int NW = 4, int WG = 1>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *__restrict__ a,
                                                               const bf16_t *__restrict__ w, float *__restrict__ out,
                                                               int M, int N, int K, int splits, int epi,
                                                               int swz_p, int swz_c, int n_pass, int n_colblk,
                                                               ChooseArgs ch) {
     constexpr int KS = 8;
+    static_assert(WG == 1 || (WIDE && WG == KS), "weights by the k step or by the chunk");
     static_assert(NT == 2 || (NT == 1 && WIDE), "one column tile per wave only with the waves side by side");
     static_assert(NW == 4 || (NW == 8 && WIDE && NT == 1), "eight waves only side by side with one column tile each");
     constexpr int THREADS = 64 * NW;
     constexpr int PFK = 2 * KS;                  // weight ring depth in k steps: two chunks
-    // k steps whose weights are asked for together.  A compute unit returns loads in the order they were asked for, so activations
-    // from L2 wait behind weights from HBM each time the two alternate: a chunk's weights go out at its end, behind its A pieces,
-    // although that makes the ring one chunk deep.  One k step at a time -> so, inside a step: 216 x 4096 x 12288 36.5 -> 35.7 us, x 4096
-    // 18.9 -> 17.8, 272 rows 39.8 -> 39.0 and 21.2 -> 19.5 (6144 x 4096 26.1 -> 27.1); steps of 42 / 132 rows 1885 -> 1838 and 2247 -> 2202
-    // (1.5B), 132 / 216 / 272 rows 5585 -> 5526, 6735 -> 6704 and 7705 -> 7677 (8B).  Four k steps: in between.  Eight waves lose
-    // (LM head 379 -> 389).
-    constexpr int WG = WIDE && NW == 4 ? KS : 1;
     constexpr int CTL = WIDE ? MTA : (MTA == 5) ? 9 : 2 * MTA;
     // Workgroup i of a launch runs on XCD i % 8.  The row passes of a column block and split follow each other on one XCD
     // (the second read of its weights is an L2 hit) and the splits are dealt out first: with 2, 4 or 8 of them an XCD sees one
@@ -628,7 +624,7 @@ void launch_few(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int 
     else go(gemm_bf16_few_kernel<MT, CT, false>, granted[0]);
 }
 
-template <int MTA, bool WIDE, int NT = 2, int NW = 4>
+template <int MTA, bool WIDE, int NT = 2, int NW = 4, int WG = 1>
 void launch_large(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi,
                   hipStream_t st, const ChooseArgs &ch) {
     constexpr int CTL = WIDE ? MTA : (MTA == 5) ? 9 : 2 * MTA;
@@ -648,9 +644,30 @@ void launch_large(const bf16_t *a, const bf16_t *w, float *out, int M, int N, in
     constexpr size_t PATCH = (size_t)NW * 32 * 36 * 4;
     constexpr size_t SMEM = (size_t)2 * CTL * 8 * 1024 > PATCH ? (size_t)2 * CTL * 8 * 1024 : PATCH;
     static std::atomic<bool> granted[kLdsDevices];
-    grant_lds((const void *)gemm_bf16_large_kernel<MTA, WIDE, NT, NW>, SMEM, granted);
-    gemm_bf16_large_kernel<MTA, WIDE, NT, NW><<<grid, 64 * NW, SMEM, st>>>(a, w, out, M, N, K, p.splits, epi, swz_p, swz_c, n_pass,
+    grant_lds((const void *)gemm_bf16_large_kernel<MTA, WIDE, NT, NW, WG>, SMEM, granted);
+    gemm_bf16_large_kernel<MTA, WIDE, NT, NW, WG><<<grid, 64 * NW, SMEM, st>>>(a, w, out, M, N, K, p.splits, epi, swz_p, swz_c, n_pass,
                                                                n_colblk, ch);
+}
+
+// Four waves side by side, one column tile each.  Which products ask for a chunk's weights together: those cut over K, with shares of
+// up to 1024 k at any height of a pass, with longer ones in passes of up to five row tiles.  A chunk's activations then come one behind
+// the other, and the ring is one chunk deep; where little of a launch is steady state (short shares) or a chunk is short (few row
+// tiles) that pays.  One k step at a time -> together, weights from HBM, activations just written:
+//   * shares of 1024: 216 / 272 / 340 / 384 / 480 x 4096 x 4096 19.0 -> 17.0, 21.4 -> 19.6, 23.0 -> 22.0, 24.2 -> 22.6, 27.3 -> 27.3 us,
+//     216 / 272 / 384 x 8192 x 2048 18.3 -> 17.2, 21.1 -> 19.5, 23.9 -> 22.4 (192 rows 14.9 -> 15.7);
+//   * longer: 132 / 216 / 256 x 4096 x 12288 31.2 -> 31.0, 37.3 -> 36.1, 39.1 -> 38.0, 216 x 5120 x 4096 22.0 -> 20.6, 132 / 216 x 3840 x
+//     10240 26.3 -> 25.4, 30.7 -> 30.2; five row tiles 272 x 6144 x 4096 25.9 -> 26.6, 320 rows 26.8 -> 27.0, 272 x 8192 x 4096 29.8 ->
+//     29.3, 272 x 4096 x 12288 41.1 -> 41.4, 8B step of 16 layers, 272 / 288 rows 3601 / 3575 -> 3586 / 3558; six and more would lose:
+//     340 / 440 x 4096 x 12288 45.7 -> 47.6, 53.1 -> 55.8, 396 x 6144 x 4096 33.1 -> 34.6, 396 x 8192 x 4096 37.4 -> 39.6;
+//   * one split would lose too: 100 x 16384 x 2048 17.9 -> 20.0, 216 x 28672 x 4096 63 -> 68.6, head of 210 rows, 65536 x 4096, 133 ->
+//     147.
+// Eight waves lose (LM head 379 -> 389), four k steps at a time are in between.
+template <int MTA>
+void launch_side(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi,
+                 hipStream_t st, const ChooseArgs &ch) {
+    const int units = (K + SPLIT_UNIT - 1) / SPLIT_UNIT, share = (units + p.splits - 1) / p.splits;
+    if (p.splits > 1 && (share <= 2 || MTA <= 5)) launch_large<MTA, true, 1, 4, 8>(a, w, out, M, N, K, p, epi, st, ch);
+    else launch_large<MTA, true, 1>(a, w, out, M, N, K, p, epi, st, ch);
 }
 
 }  // namespace
@@ -942,21 +959,21 @@ void launch_gemm_bf16(const bf16_t *a, const bf16_t *w, float *out, int M, int N
     } else if (p.wide && p.nt == 1 && p.nw == 8) {     // eight waves side by side, one column tile each
         launch_large<5, true, 1, 8>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1 && p.mt == 1) {
-        launch_large<1, true, 1>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        launch_side<1>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1 && p.mt == 2) {
-        launch_large<2, true, 1>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        launch_side<2>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1 && p.mt == 3) {
-        launch_large<3, true, 1>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        launch_side<3>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1 && p.mt == 4) {
-        launch_large<4, true, 1>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        launch_side<4>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1 && p.mt == 5) {
-        launch_large<5, true, 1>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        launch_side<5>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1 && p.mt == 6) {
-        launch_large<6, true, 1>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        launch_side<6>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1 && p.mt == 7) {
-        launch_large<7, true, 1>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        launch_side<7>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.wide && p.nt == 1) {
-        launch_large<8, true, 1>(a, w, out, M, N, K, p, out_row_major, st, ch);
+        launch_side<8>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.mt == 1) {
         launch_large<1, false>(a, w, out, M, N, K, p, out_row_major, st, ch);
     } else if (p.mt == 2) {

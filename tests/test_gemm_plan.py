@@ -41,9 +41,11 @@ MANY_ROWS = [(481, 24560, 32), (513, 24560, 64), (545, 24592, 96), (576, 24560, 
 K_SPLIT = [(33, 48, 32), (100, 784, 608), (272, 1536, 1536), (300, 1040, 96), (470, 2048, 1536), (480, 528, 288), (481, 272, 32),
            (513, 784, 96), (545, 528, 64), (576, 1040, 1056), (608, 4112, 160), (650, 304, 608), (768, 1552, 288),
            (160, 1536, 1536), (420, 5136, 288), (369, 2064, 1056)]
-# kernels_gemm, two row passes of four waves side by side: 1+1, 2+1, 2+2, 3+2, 4+3, 6+5, 7+6 and 8+7 row tiles, ragged N and K
+# kernels_gemm, two row passes of four waves side by side: 1+1, 2+1, 2+2, 3+2, 4+3, 6+5, 7+6 and 8+7 row tiles, ragged N and K;
+# in the second half passes on both sides of five row tiles with long shares of K, and one split: weights together and one by one
 TWO_PASS = [(33, 2064, 2080), (65, 4096, 2048), (100, 2064, 2080), (160, 4096, 1056), (200, 4096, 2048), (350, 2064, 2080),
-            (416, 2064, 2080), (470, 2064, 2080)]
+            (416, 2064, 2080), (470, 2064, 2080),
+            (100, 6160, 4128), (300, 6160, 4128), (350, 6160, 4128), (400, 6160, 4128), (480, 6160, 4128), (100, 16368, 288)]
 # kernels_gemm, one split of many column blocks: 2 x 2 waves, one pass of six tiles, 256-column workgroups of eight waves
 WIDE = [(97, 16400, 160), (160, 24576, 608), (170, 16400, 96), (300, 16400, 160), (420, 24576, 96), (470, 24560, 512)]
 
