@@ -103,13 +103,13 @@ __device__ inline void store_pair(const f32x4 &t0, const f32x4 &t1, float *__res
     }
 }
 
-// Epilogue of a wave that holds MTA row tiles (row tiles r0, r0 + rs, ... of the workgroup's pass) by NT column tiles
+// Epilogue of a wave that holds MTA row tiles (from row tile r0 of the workgroup's pass on) by NT column tiles
 // (from tile0 on) of 32x32x16 accumulators.  NW waves per workgroup; ct_here: row tiles of the pass that exist; smem: at least NW * 32 * 36
 // floats nobody reads any more (with NT == 1 and GEMM_EPI_ARGMAX all waves of the workgroup have to come here).
 template <int MTA, int NT, int NW>
 __device__ inline void large_epilogue(const f32x16 (&acc)[MTA][NT], float *__restrict__ out, unsigned char *gemm_smem,
                                       int epi, int split, int M, int N, int mt_base, int ct_here, int tile0, int r0,
-                                      int rs, int wave, int lane, const ChooseArgs &ch) {
+                                      int wave, int lane, const ChooseArgs &ch) {
     const int t32 = (N + 31) >> 5, m_tiles = (M + 31) >> 5;
     // The weight fragment is the MFMA's first operand, so the accumulator holds the output tile
     // transposed: lane l owns activation row l%32 of the row tile, and its register e is column
@@ -126,7 +126,7 @@ __device__ inline void large_epilogue(const f32x16 (&acc)[MTA][NT], float *__res
         typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
         for (int mt = 0; mt < MTA; ++mt) {
-            const int tile_r = r0 + rs * mt;
+            const int tile_r = r0 + mt;
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 unsigned pk[4];
@@ -165,7 +165,7 @@ __device__ inline void large_epilogue(const f32x16 (&acc)[MTA][NT], float *__res
         int bis[MTA];
 #pragma unroll
         for (int mt = 0; mt < MTA; ++mt) {
-            const int tile_r = r0 + rs * mt;
+            const int tile_r = r0 + mt;
             float best = -INFINITY;
             int bi = tile0 * 32 + 4 * lh;
             bests[mt] = best;
@@ -233,7 +233,7 @@ __device__ inline void large_epilogue(const f32x16 (&acc)[MTA][NT], float *__res
         }
 #pragma unroll
         for (int mt = 0; mt < MTA; ++mt) {
-            const int tile_r = r0 + rs * mt;
+            const int tile_r = r0 + mt;
             const int row = (mt_base + tile_r) * 32 + lq;
             if (tile_r < ct_here && lh == 0 && row < M && tile0 < t32) {
                 pmax[(size_t)(tile0 >> 1) * M + row] = bests[mt];
@@ -250,7 +250,7 @@ __device__ inline void large_epilogue(const f32x16 (&acc)[MTA][NT], float *__res
     float *o = out + (size_t)split * pt_split_stride(M, N);
 #pragma unroll
     for (int mt = 0; mt < MTA; ++mt) {
-        const int tile_r = r0 + rs * mt;
+        const int tile_r = r0 + mt;
         if (tile_r >= ct_here) continue;          // also drops the repeated tile (wave-uniform)
 #pragma unroll
         for (int j = 0; j < NT; ++j) {

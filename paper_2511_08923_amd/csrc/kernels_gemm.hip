@@ -606,8 +606,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_large_kernel(const bf16_t *
         }
     }
 
-    large_epilogue<MTA, NT, NW>(acc, out, gemm_smem, epi, split, M, N, mt_base, ct_here, tile0, mh * MTA, 1, wave, lane,
-                                ch);
+    large_epilogue<MTA, NT, NW>(acc, out, gemm_smem, epi, split, M, N, mt_base, ct_here, tile0, mh * MTA, wave, lane, ch);
 }
 
 template <int MT, int CT>

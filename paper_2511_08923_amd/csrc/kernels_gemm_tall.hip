@@ -252,11 +252,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_tall_kernel(const bf16_t *__res
     for (int i = 0; i < RT; ++i) {
         if (!exists(i)) continue;
         const int col = (tile0 + ng) * 32, col2 = (tile0 + 2) * 32 + ng * 16 + 4 * g, row = row_of(i) + n;
-        if (epi == GEMM_EPI_ROWMAJOR) store_pair<true>(acc[i][0], acc[i][1], o, row_of(i), col, M, N, lane);
-        else store_pair<false>(acc[i][0], acc[i][1], o, row_of(i), col, M, N, lane);
+        store_pair<false>(acc[i][0], acc[i][1], o, row_of(i), col, M, N, lane);
         if constexpr (CT == 3)
-            if (row < M && col2 < N)
-                *(f32x4 *)(o + (epi == GEMM_EPI_ROWMAJOR ? (size_t)row * N + col2 : pt_index(col2, row, M))) = acc[i][2];
+            if (row < M && col2 < N) *(f32x4 *)(o + pt_index(col2, row, M)) = acc[i][2];
     }
 }
 
@@ -281,13 +279,15 @@ void launch_tall_rows(const bf16_t *a, const bf16_t *w, float *out, int M, int N
     else if (p.mt == 7) launch_tall<7, CT>(a, w, out, M, N, K, p, epi, st);
     else if (p.mt == 8) launch_tall<8, CT>(a, w, out, M, N, K, p, epi, st);
     else if (p.mt == 9) launch_tall<9, CT>(a, w, out, M, N, K, p, epi, st);
-    else if (p.mt == 10) launch_tall<10, CT>(a, w, out, M, N, K, p, epi, st);
-    else if (p.mt == 11) launch_tall<11, CT>(a, w, out, M, N, K, p, epi, st);
+    else if constexpr (CT == 2) launch_tall<10, CT>(a, w, out, M, N, K, p, epi, st);       // the plan has no higher ones there
+    else if (p.mt <= 11) launch_tall<11, CT>(a, w, out, M, N, K, p, epi, st);
     else launch_tall<12, CT>(a, w, out, M, N, K, p, epi, st);
 }
 
 }  // namespace
 
+// Partial sums in the tiled layout, or (three column tiles, one split) SwiGLU of the interleaved gate/up matrix: products with a
+// single split forced, the row-major logits among them, are not planned here.
 void launch_gemm_bf16_tall(const bf16_t *a, const bf16_t *w, float *out, int M, int N, int K, const GemmPlan &p, int epi,
                            hipStream_t st) {
     if (p.nt == 2) launch_tall_rows<2>(a, w, out, M, N, K, p, epi, st);

@@ -51,4 +51,4 @@ def test_no_result_is_read_before_the_wait(tmp_path):
         assert any(x.startswith("v_mfma") for x in ins)
         assert early_reads(ins) == [], name
         seen += 1
-    assert seen == 22            # 2 to 12 row tiles x 2 and 3 column tiles
+    assert seen == 19            # 2 to 10 row tiles x 2 column tiles; 2 to 9, 11 and 12 x 3
