@@ -2,8 +2,9 @@
 //
 // M is the step's row count (1 .. 272 at batch 1; more rows run as row passes, 481 and more in kernels_gemm_rows.hip,
 // the narrower products of 33 .. 480 - the narrowest to 768 - in kernels_gemm_mid.hip, the widest and those of many short
-// shares of K up to 480 rows in kernels_gemm_tall.hip, the LM head of 33 .. 288 in a form of kernels_gemm_rows.hip), N and K are model dimensions: every weight byte is used once
-// per step, so the kernel is a weight streamer with MFMA attached.
+// shares of K up to 480 rows in kernels_gemm_tall.hip, the LM head of 33 .. 160 rows over some 65400 columns and more, where its last
+// round of workgroups is nearly full to 256 or 288, in a form of kernels_gemm_rows.hip), N and K are model dimensions: every weight byte
+// is used once per step, so the kernel is a weight streamer with MFMA attached.
 //   * W lives in HBM as the register image of the 32x32x16 MFMA B operand
 //     ([k step of 16][32-column tile][lane][8]); a wave's load of one fragment is one fully coalesced 1 KiB read
 //     that goes straight to VGPRs through a ring many k steps deep (up to 32 rows: into an LDS ring that the
@@ -133,7 +134,8 @@ __device__ inline void store_tiles(const f32x4 (&acc)[MTW][NT], float *out, int 
 // The A operand is built by the workgroup itself (see FuseArgs) into LDS as plain bf16 rows of its share of K; a
 // lane's fragment is then one 16-byte LDS read (lanes of rows that do not exist take zeros).  W streams through a register
 // ring, whose first loads are in flight while the prologue runs; its loads are non-temporal, as nobody reads them again (together
-// with those of gemm_bf16_few_kernel 8B one-token step 3626 -> 3527 us).
+// with those of gemm_bf16_few_kernel 8B one-token step 3626 -> 3527 us; these alone, one-token step of 1 / 2 / 3 / 4 sequences, 1.5B 1620 ->
+// 1584, 1829 -> 1817, 2076 -> 2045, 2284 -> 2242, 8B with eight layers 977 -> 946 to 1103 -> 1079, in grids of 36 to 192 workgroups).
 template <int FUSE>
 __global__ __launch_bounds__(256) void gemm_bf16_small_fused_kernel(FuseArgs f, const bf16_t *__restrict__ w,
                                                                     float *__restrict__ out, int M, int N, int K,
@@ -827,7 +829,14 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
         // 4096 at 42 / 72 / 132 / 182 / 210 / 240 / 272 rows: 398 -> 331, 424 -> 346, 483 -> 406, 513 -> 487, 549 -> 534, 580 -> 560, 602 ->
         // 620 us, with logits 420 -> 377, 448 -> 398, 508 -> 459, 534 -> 508, 569 -> 548, 617 -> 575, 661 -> 656; x 1536 225 -> 160, 245 ->
         // 170, 271 -> 200, 289 -> 245, 306 -> 261, 307 -> 275, 319 -> 296; 65536 x 4096 254 -> 235, 266 -> 248, 301 -> 288, 331 -> 335, 356 ->
-        // 359, 372 -> 388, 390 -> 423.
+        // 359, 372 -> 388, 390 -> 423.  Where the last round is as empty as it can be, up to five row tiles, in a step of three layers
+        // without / with logits: 82000 x 4096 (513 blocks) at 42 / 72 / 132 / 156 rows 503 -> 488 / 503 -> 492, 534 -> 511 / 547 -> 529, 620 -> 602
+        // / 632 -> 625, 626 -> 609 / 640 -> 635, 128256 x 4096 (802) 561 -> 542 / 565 -> 559 to 695 -> 672 / 725 -> 719, 82000 x 1536 265 ->
+        // 264 / 281 -> 281 to 332 -> 322 / 347 -> 340: still no loss.  65536 x 1536 at 42 rows is 1 to 3 % behind in a model of three
+        // layers, whose weights the memory-side cache keeps in part if they are loaded plainly (with plain loads even); with twelve and 28
+        // layers ahead, 812 -> 792 and 1849 -> 1805 us.
+        // (Asked for over and over with nothing between, 182 rows and more lose, 256 x 151936 x 4096 341 -> 381 us; in the steps around
+        // them, 8B with four layers, they gain: 182 / 210 / 240 rows 967 -> 940, 1051 -> 1039, 1100 -> 1101.)
         const int vocab_blocks = (N + 159) / 160, vocab_rounds = (vocab_blocks + 255) / 256;
         if (force_single_split && wgs >= 512 &&
             (t <= 5 || (10 * vocab_blocks >= 9 * 256 * vocab_rounds && (t <= 8 || (t == 9 && K <= 2048))))) {
@@ -840,25 +849,31 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
         }
         const bool row_split = !force_single_split && wgs * splits <= 128;
         const int t32 = (N + 31) / 32;
-        // kernels_gemm_tall.hip: all row tiles (up to twelve) in one workgroup, both operands by LDS-DMA.  Same MFMAs in the
-        // same order per output tile as the kernels below, bit for bit, so the choice may follow the row count.  It needs
-        // most of the compute units at one workgroup each and a share of K that is long against its ring fill:
-        //   * wide single splits, three column tiles per workgroup (gate/up): the weights are read once, by every unit.  Before
-        //     -> this at 40 / 72 / 132 / 216 / 272 rows: 24576 x 4096 38.8 -> 36.2, 45.5 -> 39.7, 56.0 -> 50.7, 57.8 -> 55.3,
-        //     66.3 -> 63.7 us; 17920 x 1536 17.3 -> 15.0, 20.6 -> 16.4, 25.2 -> 21.4, 26.0 -> 23.6, 29.0 -> 26.4 (ten row tiles
-        //     29.7 -> 32.9: to nine).  From eleven on only where 256-column workgroups do not fit one round any
-        //     more: 340 / 440 x 24576 x 4096 129.5 -> 76.6, 134.5 -> 97.9, but 440 x 17920 x 1536 32.8 -> 43.2.
-        //   * two column tiles where K is cut into many short shares (the small model's down): 72 / 272 / 310 x 1536 x 8960 13.5 ->
-        //     11.4, 20.8 -> 17.5, 21.3 -> 18.4; 272 x 1792 x 9216 22.4 -> 18.7.  With fewer splits only up to three row tiles
-        //     and from 2048 k on: 72 x 4096 x 12288 26.8 -> 25.9, 72 x 3072 x 8192 17.5 -> 16.4; 272 x 4096 x 4096 17.5 -> 18.0,
-        //     272 x 4096 x 12288 37 -> 40, 72 x 4096 x 2048 (512 k) 8.6 -> 9.0.
-        // Where column blocks x splits is a multiple of eight, many short shares come here from seven row tiles on only.  (Measured
-        // when the two row passes below ran on one XCD, and shared the weights in its L2, at those counts alone, and before both
-        // kernels grouped their loads.)  Below -> here at 40 / 96 / 160 / 192 / 224 / 272 rows, weights from HBM: 1536 x 8192 11.2 -> 10.8, 12.0 -> 11.9,
-        // 13.2 -> 14.5, 14.0 -> 15.6, 15.6 -> 16.1, 17.9 -> 18.1; 2560 x 6144 11.4 -> 11.5, 12.4 -> 12.5, 14.4 -> 15.4, 14.8 ->
-        // 16.4, 18.9 -> 16.7, 21.2 -> 19.6 (from the memory-side cache, 40 rows 8.3 -> 10.6); another count, 1536 x 9216: 12.1 ->
-        // 10.9 and 20.6 -> 19.0 at 40 and 272.  The longer shares gain either way (3840 x 10240 21.1 -> 18.4, 23.4 -> 22.1 at 96).
-        // More than 256 workgroups: the second round is ragged and loses, 72 / 272 x 28672 x 4096 49.1 -> 71.5, 73.6 -> 113.0.
+        // kernels_gemm_tall.hip: all row tiles (up to twelve) in one workgroup, both operands by LDS-DMA.  It adds the products of a
+        // row in the same order as the kernels below (one 16x16x32 MFMA for two 32x32x16 of theirs: the same bits,
+        // tests/test_gpu_row_class.py), so the choice may follow the row count.  It needs most of the compute units at one
+        // workgroup each and a share of K that is long against its ring fill.  Kernels below -> it, weights from HBM, activations
+        // just written:
+        //   * wide single splits, three column tiles per workgroup (gate/up): the weights are read once, by every unit.  40 / 72 /
+        //     132 / 216 / 272 rows: 24576 x 4096 37.9 -> 32.6, 46.5 -> 37.0, 54.3 -> 43.0, 56.6 -> 49.9, 64.2 -> 54.7 us; 17920 x 1536
+        //     15.8 -> 12.1, 18.8 -> 13.8, 22.5 -> 16.0, 23.3 -> 18.9, 25.5 -> 20.7 (to nine row tiles; 340 rows 29.1 -> 25.4, but 384
+        //     27.7 -> 28.0 and 440 29.0 -> 36.0).  From eleven on only where 256-column workgroups do not fit one round any more:
+        //     340 / 440 x 24576 x 4096 125.8 -> 62.9, 136.6 -> 87.6.  More than 256 workgroups: the second round is ragged and
+        //     loses, 72 / 272 x 28672 x 4096 46.0 -> 62.6, 69.6 -> 97.4.
+        //   * two column tiles where K is cut into many short shares (the small model's down): 72 / 132 / 216 / 272 / 300 x 1536 x 8960
+        //     10.9 -> 9.8, 12.7 -> 12.5, 15.7 -> 15.6, 18.0 -> 17.5, 18.6 -> 18.7, but 192 13.9 -> 15.1 and 256 16.5 -> 16.9: two passes
+        //     of three and of four row tiles are an even deal.  (With both kernels as they were when the line was drawn 272 rows read 20.8
+        //     -> 17.5.)  With fewer splits up to three row tiles, shares from 2048 k on: 72 x 4096 x 12288 26.0 -> 21.5, 72 x 3072 x
+        //     8192 17.0 -> 14.1, 72 x 6144 x 4096 16.5 -> 14.3.  Higher it is ahead here (272 x 4096 x 12288 38.9 -> 37.5, x 6144 x 4096
+        //     25.5 -> 24.1) but was not inside a step, where QKV, O and down of the 8B shape at 272 and 216 rows read 25.9 -> 29.6,
+        //     18.8 -> 18.6, 37.6 -> 39.3 us.
+        // Where column blocks x splits is a multiple of eight, many short shares come here from seven row tiles on only.  The line is
+        // older than the numbering of the two-pass workgroups: their passes shared weights in an XCD's L2 at those counts alone, and
+        // do now at all of them.  With the kernels as they are it gives away what this one gains up to five row tiles, at 40 / 96 / 160 /
+        // 192 / 216 / 256 / 272 rows 1536 x 8192 9.1 -> 8.0, 10.2 -> 9.2, 12.3 -> 11.2, 12.9 -> 12.5, 15.2 -> 13.6, 15.3 -> 14.7, 17.0 ->
+        // 15.4, and keeps what it loses at six: 2560 x 6144 9.7 -> 8.6, 11.2 -> 10.3, 12.7 -> 12.3, 13.6 -> 14.4, 15.4 -> 15.2, 15.9 ->
+        // 16.4, 17.3 -> 17.1; 3072 x 5120 9.7 -> 8.8, 11.0 -> 10.3, 12.7 -> 12.8, 13.4 -> 15.1, 15.4 -> 15.7, 15.9 -> 16.8, 17.4 -> 17.5.
+        // Another count, 1536 x 9216: 9.7 -> 8.7, 11.2 -> 10.3, 13.1 -> 13.1, 14.0 -> 14.7, 15.7 -> 15.7, 16.7 -> 17.1, 18.1 -> 17.7.
         int ct = 0;
         if (!force_single_split) {
             const int share = splits == 1 ? K : (units + splits - 1) / splits * SPLIT_UNIT;

@@ -5,7 +5,7 @@
 // turn) and each accumulates the whole tile of RT x CT 32 x 32 blocks, taking both operands from memory straight into
 // a register ring of D k steps.  Every fragment is loaded once per workgroup ((RT + CT) KiB per RT * CT MFMAs) and no
 // wave waits for another; the four sums meet in LDS at the end, in wave order, where the epilogue reads them in the
-// order it stores them.  What bounds it is the time a compute unit's loads are under way: about 57 GB/s per unit with
+// order it stores them.  What bounds it is the time a compute unit's loads are under way: about 58 GB/s per unit with
 // weights from HBM (the same loop on weights that stay in L2 takes 60 instead of 81 us at 272 x 24576 x 4096, on
 // activations that stay in L1 no less), so it serves the products that leave compute units idle otherwise;
 // the accumulators, held four times, leave no registers for a deeper ring.

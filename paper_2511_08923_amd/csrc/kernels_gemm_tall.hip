@@ -1,21 +1,25 @@
 // bf16 GEMM of 33 to 480 rows: out = A[M][K] x W[N][K]^T, fp32 accumulation, same operand layouts and epilogues as
 // kernels_gemm.hip, and the same products added in the same order per output value (two 32x32x16 MFMAs and one 16x16x32 over the
-// same 32 k give the same bits), so that the results are the same bits.
+// same 32 k give the same bits: tests/test_gpu_row_class.py), so that the results are the same bits.
 //
 // At these row counts the weights come from HBM once and the activations (the step's 272 rows: 2.2 MB at K = 4096) from L2
 // into every workgroup.  What bounds it is how much a compute unit takes in: with weights from HBM among the loads about
-// 60 GB/s, whatever the kernel and whichever waves bring which operand (272 x 24576 x 4096: loads alone 52 us, weights alone 33,
+// 58 GB/s, whatever the kernel and whichever waves bring which operand (272 x 24576 x 4096: loads alone 52 us, weights alone 33,
 // activations alone 22; MFMAs and LDS reads alone 42), in the order asked for, which is why a deeper ring or fewer LDS
 // reads change little beyond this:
 //   * a workgroup owns all row tiles of the pass (up to twelve) and two or three column tiles, one workgroup per compute unit:
-//     no weight is read twice, all of them stream, by non-temporal loads;
+//     a pass reads no weight twice, all of them stream, by non-temporal loads (from 385 rows on there are two passes, whose
+//     workgroups follow each other on one XCD: plain / non-temporal 396, 440, 480 x 24576 x 4096 89.3 / 90.0, 93.4 / 92.2, 98.1 / 100.2
+//     us, x 22016 83.2 / 82.9, 86.6 / 85.2, 93.7 / 94.8);
 //   * both operands go straight into LDS (buffer_load ... lds), PA chunks of 64 k of A and PW of W: the weights, which
 //     are longer on their way, are asked for up to seven chunks ahead, two chunks at a time;
 //   * 16x16x32 MFMAs, four waves as 2 x 2: a wave owns one half of every row tile and half of the columns, RT x CT tiles of 16 x
 //     16, so that nine row tiles are an even deal (whole 32-row tiles dealt to four waves gave one of them three and the others
 //     two); the fragments of the next half chunk and the loads are spread between the MFMAs, one barrier per chunk of 64 k.
 // With 32x32x16 MFMAs, four waves over whole row tiles and plain loads gate/up read 58.7 us inside a step of 272 rows, now 57.5; 55.3
-// and 52.7 at 216 rows (8B step k = 16 7835 -> 7740 us, 3 x k = 8 6910 -> 6860, 1.5B k = 16 2970 -> 2957).
+// and 52.7 at 216 rows (8B step k = 16 7835 -> 7740 us, 3 x k = 8 6910 -> 6860, 1.5B k = 16 2970 -> 2957).  The non-temporal loads'
+// part, plain -> so, weights from HBM, activations just written: 40 / 132 / 272 x 24576 x 4096 34.9 -> 33.5, 44.1 -> 42.7, 59.8 -> 58.2,
+// 132 / 272 x 17920 x 1536 17.0 -> 16.4, 22.5 -> 22.1, 72 / 272 x 1536 x 8960 10.2 -> 9.8, 18.1 -> 17.7, 72 x 4096 x 12288 23.8 -> 22.0.
 // The accumulators are tied to AGPRs by inline assembly: left to the compiler they are copied between the register files
 // around every use (85 instead of 63 us).
 // Measured sizes stand at the rule in plan_gemm_bf16.

@@ -472,7 +472,7 @@ void forward_rows(tidar_ctx *ctx, const tidar_weights *w, const tidar_kv_cache *
     // values first (same noise, same expression as the reduction over materialised logits).  Beta-mixed
     // verification needs two rows of logits side by side: the epilogue then also writes the logits of the k causal
     // rows and of their k mix partners (2k of the k(k+1) rows), which argmax_rows mixes, perturbs and reduces.
-    // (The per-group pairs fit the logits area: 8 bytes per row and 32 or 64 columns.)
+    // (The per-group pairs fit the logits area: 8 bytes per row and 32, 64 or 80 columns.)
     if (c.dtype == TIDAR_BF16 && !logits_dst && l.logits_bytes > 0) {
         const GemmPlan gp = plan_gemm_bf16(Mh, c.vocab, c.d_model, true);
         const int G = gemm_argmax_groups(Mh, c.vocab, gp);

@@ -64,8 +64,8 @@ def test_sizes_of_the_gpu_tests_reach_the_kernel_they_are_for(sizes, kernel):
 
 @pytest.mark.parametrize("N,K", products())
 def test_grouping_of_a_sum_does_not_follow_the_row_count(N, K):
-    """33-480 rows: one kernel family (one chain of 32x32x16 MFMAs per split, or the K-splitting waves) and one split count
-    per (N, K).  From 481 rows on: one per (N, K) and number of 256-row multiples."""
+    """33-480 rows: one kernel family (one chain of products per split, with either MFMA shape, or the K-splitting waves) and one split
+    count per (N, K).  From 481 rows on: one per (N, K) and number of 256-row multiples."""
     plan = planner()
     classes = [range(33, 481)] + [range(max(481, 256 * n + 1), 256 * n + 257) for n in range(1, 36)]
     for rows in classes:

@@ -1,12 +1,13 @@
-"""Which of the products with many short shares of K go to the kernel that holds all row tiles: not those whose two row passes run
-on one XCD anyway (column blocks of 128 x splits a multiple of eight) before the rows are many."""
+"""Which of the products with many short shares of K go to the kernel that holds all row tiles: where column blocks of 128 x splits
+are a multiple of eight only from seven row tiles on, elsewhere at any row count (what both sides of the line measure stands at the
+rule)."""
 import pytest
 
 from test_gemm_plan import planner
 
 
 @pytest.mark.parametrize("N,K,splits", [(1536, 8192, 8), (2560, 6144, 6), (3072, 5120, 5), (1280, 12288, 12), (2048, 7168, 7)])
-def test_passes_on_one_xcd_stay(N, K, splits):
+def test_a_multiple_of_eight_stays_with_two_passes(N, K, splits):
     plan = planner()
     for M in range(33, 321, 7):
         p = plan(M, N, K, False)
