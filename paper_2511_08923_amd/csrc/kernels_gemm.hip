@@ -744,19 +744,20 @@ GemmPlan plan_gemm_bf16(int M, int N, int K, bool force_single_split) {
         const int t = (M + 31) / 32;             // 32-row tiles
         if (!force_single_split && (t < 16 ? wgs * splits <= 64 : t <= 24 && wgs * splits <= 40)) {
             // kernels_gemm_mid.hip: the waves of a workgroup split K.  It takes the products whose two row passes
-            // below would fill less than half of the compute units.  Measured at 132 / 272 / 430 rows, two passes -> this:
-            // with 24-36 column blocks x splits 7.5 / 11.5 / 15.7 -> 6.4 / 8.4 / 10.5 us (1024 x 2048, 4096 x 512; the small
-            // model's O, 1536 x 1536, in 3 splits either way 7.6 / 11.5 / 16.2 -> 6.6 / 8.8 / 12.8), with 48 (its QKV, 2048 x
-            // 1536; 1536 x 2048, 3072 x 1024) 8.0 / 12.3 / 17.2 -> 8.0 / 11.7 / 15.0, with 64 (2048 x 2048, 4096 x 1024) 8.6 /
-            // 13.7 / 18 -> 8.6 / 13.2 / 16.8; up to 100 rows within 5 % of each other.  Where two passes fill more it
+            // below would fill less than half of the compute units.  Measured at 132 / 272 / 430 rows, weights from HBM, activations
+            // just written, two passes -> this: with 24-36 column blocks x splits 7.1 / 10.5 / 13.9 -> 5.5 / 7.1 / 8.4 us (1024 x
+            // 2048), 6.6 / 9.7 / 13.1 -> 5.6 / 6.9 / 8.3 (4096 x 512), 7.4 / 10.5 / 14.6 -> 5.8 / 7.5 / 10.5 (the small model's O,
+            // 1536 x 1536, in 3 splits either way), with 48 (its QKV, 2048 x 1536; 1536 x 2048, 3072 x 1024) 7.8 / 10.8 / 15.0 -> 7.2 /
+            // 10.5 / 12.4, 7.6 / 10.8 / 15.1 -> 7.0 / 10.2 / 12.1, 7.6 / 10.8 / 15.0 -> 7.0 / 10.2 / 11.9, with 64 (2048 x 2048, 4096 x
+            // 1024) 7.9 / 11.1 / 14.9 -> 7.5 / 10.9 / 12.8, 7.8 / 11.2 / 14.9 -> 7.5 / 10.6 / 12.5.  Where two passes fill more it
             // loses 10 % inside a step, where the activations come from other XCDs.
             // The narrowest keep it up to 768 rows, many-row kernel -> this at 544 / 640 / 768 rows: with 36 (1536 x 1536)
             // 21.0 / 18.9 / 20.3 -> 13.4 / 15.1 / 14.3, with 40 (2560 x 1024) 21.4 / 19.6 / 20.8 -> 13.8 / 15.9 / 17.6, with 48
             // (2048 x 1536) 20.0 / 18.7 / 20.4 -> 18.5 / 19.1 / 20.7, with 64 (2048 x 2048) 20.3 / 19.0 / 20.7 -> 22.0 / 23.0 /
             // 22.9.  The row limits are class borders (480 rows, a 256-row multiple): the four waves sum K in four
-            // interleaved shares, so inside a class the choice has to be one of (N, K) alone.  (It is also faster for
-            // wide single-split products of up to five row tiles, 72 x 24576 x 4096 45.2 -> 40.8 us, but not at nine,
-            // 68.2 -> 81.5: those stay below whatever the row count.)
+            // interleaved shares, so inside a class the choice has to be one of (N, K) alone.  (Against two
+            // passes it is also faster for wide single-split products of up to five row tiles, 72 x 24576 x 4096 45.2 ->
+            // 40.8 us, but not at nine, 68.2 -> 81.5; most of those have kernels_gemm_tall.hip now.)
             // Per workgroup: its fragments at the 27 B per clock that a compute unit takes in from afar, or the
             // matrix cores' rate, plus 4 us of launch, ring fill and reduction; a split also costs the partial
             // sums at 6 TB/s out and 4 TB/s back in.  The split count is the best at nine row tiles in two passes,
