@@ -135,7 +135,8 @@ __device__ inline void store_tiles(const f32x4 (&acc)[MTW][NT], float *out, int 
 // lane's fragment is then one 16-byte LDS read (lanes of rows that do not exist take zeros).  W streams through a register
 // ring, whose first loads are in flight while the prologue runs; its loads are non-temporal, as nobody reads them again (together
 // with those of gemm_bf16_few_kernel 8B one-token step 3626 -> 3527 us; these alone, one-token step of 1 / 2 / 3 / 4 sequences, 1.5B 1620 ->
-// 1584, 1829 -> 1817, 2076 -> 2045, 2284 -> 2242, 8B with eight layers 977 -> 946 to 1103 -> 1079, in grids of 36 to 192 workgroups).
+// 1584, 1829 -> 1817, 2076 -> 2045, 2284 -> 2242, 8B with eight layers 977 -> 946 to 1103 -> 1079, in grids of 36 to 192 workgroups; eight and ten layers of d_model 1024 and d_ff 4096
+// and 2816, grids of 16 to 64, 372 -> 378 and 489 -> 498 at one sequence, 419 -> 420 and 542 -> 552 at two).
 template <int FUSE>
 __global__ __launch_bounds__(256) void gemm_bf16_small_fused_kernel(FuseArgs f, const bf16_t *__restrict__ w,
                                                                     float *__restrict__ out, int M, int N, int K,
